@@ -283,6 +283,37 @@ MsArgs make_args(msc_op op, int lanes, const double* d_b, double* d_x) {
   return a;
 }
 
+// The operator's matrices for one product (vectors, shift and temporary left to fill).
+// The links stand in for the stored matrix when they are SU(3) to rounding (two rows) or
+// through all nine values: the product is M's to rounding either way.
+constexpr double kApplySu3Tol = 1e-14;
+ApplyArgs apply_args(msc_op op, int prec, int lanes) {
+  ApplyArgs a{};
+  a.kind = op->kind;
+  a.prec = prec;
+  a.lanes = lanes;
+  a.n = op->n;
+  a.m64 = Csr<double2>{op->rowptr, op->col, op->val64};
+  a.mh64 = Csr<double2>{op->rowptr_h, op->col_h, op->val64_h};
+  a.m32 = Csr<float2>{op->rowptr, op->col, op->val32};
+  a.mh32 = Csr<float2>{op->rowptr_h, op->col_h, op->val32_h};
+  a.sell = op->sell ? 1 : 0;
+  if (op->sell) {
+    a.nslices = op->sell_m.nslices;
+    a.s64 = sell_view(op->sell_m, op->sell_m.val64, op->sell_m.diag64, true);
+    if (op->kind == MSC_A_MHM)
+      a.sh64 = sell_view(op->sell_mh, op->sell_mh.val64, op->sell_mh.diag64, true);
+  }
+  if (op->stencil) {
+    const bool two = op->two_rows && op->su3_dev <= kApplySu3Tol;
+    a.links = two ? 2 : 3;
+    a.w64 = two ? op->wc64 : op->w64;
+    a.ord = op->order_sites64;
+    a.ord.on = a.ord.s1 > 0 ? 1 : 0;
+  }
+  return a;
+}
+
 // Which FP64 heads on the links form their product by the recurrence: all but the first
 // launch and the launches kTrEvery / 2 mod kTrEvery (off the timing samples' positions,
 // which start at multiples of 128); and how many of the first n launches do.
@@ -1511,6 +1542,7 @@ msc_status refresh_two_rows(msc_op op, const double2* d_links, hipStream_t s) {
   double dev = 0.0;
   std::memcpy(&dev, &bits, sizeof dev);
   op->two_rows = false;
+  op->su3_dev = dev;
   if (!(dev <= kSu3Tol)) return MSC_OK;
   if (!op->wc64.w) {
     double2* w64 = nullptr;
@@ -1763,12 +1795,12 @@ msc_status multi_rhs_impl(msc_op op, const double2* B, double2* X, const msc_par
 
   const int lanes = choose_lanes(op, prm);
   auto apply = [&](const double2* in, double2* out, double shift) {
-    return launch_apply(op->kind, MSC_PREC_FP64, lanes, n,
-                        Csr<double2>{op->rowptr, op->col, op->val64},
-                        Csr<double2>{op->rowptr_h, op->col_h, op->val64_h},
-                        Csr<float2>{op->rowptr, op->col, op->val32},
-                        Csr<float2>{op->rowptr_h, op->col_h, op->val32_h}, in, out, shift,
-                        op->ws.t64, op->ws.u64, s);
+    ApplyArgs a = apply_args(op, MSC_PREC_FP64, lanes);
+    a.in = in;
+    a.out = out;
+    a.shift = shift;
+    a.tmp = op->ws.t64;
+    return launch_apply(a, s);
   };
   // |b_k|^2 in the caller's order
   std::vector<double> bn2(ns + 1, 0.0);
@@ -2091,16 +2123,12 @@ msc_status msc_op_apply(msc_op op, int32_t prec, const double* d_in, double* d_o
   const int ns = std::max<int>(1, int(op->sigma.size()));
   msc_status rc = ensure_workspace(op, prec, ns);
   if (rc != MSC_OK) return rc;
-  // the FP64 path needs two complex128 temporaries: t64 and the first slice of u64
-  void* ta = prec == MSC_PREC_MIXED ? op->ws.r : static_cast<void*>(op->ws.t64);
-  void* tb = prec == MSC_PREC_MIXED ? op->ws.t : static_cast<void*>(op->ws.u64);
-  HIP_TRY(launch_apply(op->kind, prec, choose_lanes(op, prm), op->n,
-                       Csr<double2>{op->rowptr, op->col, op->val64},
-                       Csr<double2>{op->rowptr_h, op->col_h, op->val64_h},
-                       Csr<float2>{op->rowptr, op->col, op->val32},
-                       Csr<float2>{op->rowptr_h, op->col_h, op->val32_h},
-                       reinterpret_cast<const double2*>(d_in), reinterpret_cast<double2*>(d_out),
-                       shift, ta, tb, s));
+  ApplyArgs a = apply_args(op, prec, choose_lanes(op, prm));
+  a.in = reinterpret_cast<const double2*>(d_in);
+  a.out = reinterpret_cast<double2*>(d_out);
+  a.shift = shift;
+  a.tmp = prec == MSC_PREC_MIXED ? op->ws.t : static_cast<void*>(op->ws.t64);
+  HIP_TRY(launch_apply(a, s));
   HIP_TRY(hipStreamSynchronize(s));
   return MSC_OK;
 }
@@ -2130,14 +2158,11 @@ msc_status msc_op_apply_noalloc(msc_op op, int32_t prec, const double* d_in, dou
   HIP_TRY(noalloc_scratch(dev, &base));
   msc_params prm;
   msc_params_default(&prm);
-  HIP_TRY(launch_apply_noalloc(op->kind, prec, choose_lanes(op, prm), op->n,
-                               Csr<double2>{op->rowptr, op->col, op->val64},
-                               Csr<double2>{op->rowptr_h, op->col_h, op->val64_h},
-                               Csr<float2>{op->rowptr, op->col, op->val32},
-                               Csr<float2>{op->rowptr_h, op->col_h, op->val32_h},
-                               reinterpret_cast<const double2*>(d_in),
-                               reinterpret_cast<double2*>(d_out), shift, base,
-                               static_cast<hipStream_t>(stream)));
+  ApplyArgs a = apply_args(op, prec, choose_lanes(op, prm));
+  a.in = reinterpret_cast<const double2*>(d_in);
+  a.out = reinterpret_cast<double2*>(d_out);
+  a.shift = shift;
+  HIP_TRY(launch_apply_noalloc(a, base, static_cast<hipStream_t>(stream)));
   return MSC_OK;
 }
 

@@ -273,6 +273,7 @@ struct msc_op_s {
   bool stencil = false;          // matrix-free staggered operator (links kept below)
   msc::Stencil<double2> w64;     // W_mu(x) = eta_mu(x)/2 U_mu(x), complex128 and
   msc::Stencil<float2> w32;      // complex64 copies (device memory owned by the op)
+  double su3_dev = 1.0;          // largest deviation of a link from SU(3)
   bool two_rows = false;         // every link is in SU(3): the iteration reads wc64 / wc32,
   msc::Stencil<double2> wc64;    // the first two rows of each W_mu(x) (6 values), and
   msc::Stencil<float2> wc32;     // rebuilds the third from them
@@ -378,10 +379,24 @@ hipError_t launch_switch_to_mixed(const MsArgs& a64, const MsArgs& a32, int ns, 
 // FP64 true residual norms^2 of shifts [k0, k0+kc) (kc <= 8) of x into sc.res2[k0..].
 hipError_t launch_verify(const MsArgs& a, const double* sigma_by_caller_index, int k0, int kc,
                          double2* u64, hipStream_t s);
-hipError_t launch_apply(int kind, int prec, int lanes, int64_t n, const Csr<double2>& m64,
-                        const Csr<double2>& mh64, const Csr<float2>& m32,
-                        const Csr<float2>& mh32, const double2* in, double2* out,
-                        double shift, void* tmp_a, void* tmp_b, hipStream_t s);
+// One product out = (A + shift) in (in and out may be the same buffer).
+struct ApplyArgs {
+  int kind, prec, lanes;
+  int64_t n;
+  Csr<double2> m64, mh64;
+  Csr<float2> m32, mh32;
+  int sell;                // FP64 may read the sliced copies below
+  int64_t nslices;
+  Sell<double2> s64, sh64;
+  int links;               // FP64 may read the links w64 (rows per link: 2 or 3; 0: none)
+  Stencil<double2> w64;
+  SweepOrder ord;          // of the links' blocks of 64 sites
+  const double2* in;
+  double2* out;
+  double shift;
+  void* tmp;               // n values of the working precision
+};
+hipError_t launch_apply(const ApplyArgs& a, hipStream_t s);
 
 // No-allocation apply: temporaries in a file-scope device array of this many bytes per GPU
 // (FP64: n <= 2^21 rows for A = M^H M, 2^22 for A given; complex64: n <= 2^22).
@@ -391,13 +406,9 @@ size_t apply_scratch_bytes(int kind, int prec, int64_t n);
 // The array's address on `device`, which must be the current device; looked up with
 // hipGetSymbolAddress on the first call per device and kept.
 hipError_t noalloc_scratch(int device, void** ptr);
-// launch_apply with its temporaries carved from `base` (the address noalloc_scratch
+// launch_apply with its temporary at `base` (the address noalloc_scratch
 // returned); hipErrorInvalidValue when n exceeds the array.
-hipError_t launch_apply_noalloc(int kind, int prec, int lanes, int64_t n,
-                                const Csr<double2>& m64, const Csr<double2>& mh64,
-                                const Csr<float2>& m32, const Csr<float2>& mh32,
-                                const double2* in, double2* out, double shift, void* base,
-                                hipStream_t s);
+hipError_t launch_apply_noalloc(ApplyArgs a, void* base, hipStream_t s);
 
 int default_grid(int64_t n, int lanes);
 

@@ -1770,33 +1770,168 @@ __global__ __launch_bounds__(kBlock) void k_verify_second_s(VerifyArgs v) {
   verify_finish(v, nrm);
 }
 
-// ---- plain SpMV with optional shift epilogue (operator application) -------------------
-template <class R, int L>
-__global__ __launch_bounds__(kBlock) void k_spmv(Csr<cplx<R>> m, const cplx<R>* x, cplx<R>* y,
-                                                 int64_t n) {
+// ---- the operator applied on its own: out = (A + shift) in ----------------------------
+// One kernel per half of A.  The first half reads the caller's vector (converted to the
+// working precision where it is gathered), the last one adds shift * in and writes
+// complex128.  `in` and `out` may be the same buffer: for A = M^H M the last half gathers
+// the product of the first and reads `in` at its own rows only, before it writes them;
+// for a given A the launcher keeps the product apart when the two overlap.
+
+// Sizes from which FP64 products read the links (sites) and the sliced copy (rows) instead
+// of the CSR.  Below, the product is a chain of latencies, and the CSR's eight lanes per
+// row have the most of them in flight: per call, links / CSR 33.4 / 28.2 us at 8^3 x 16,
+// 33.8 / 35.0 at 12^4, 39 / 52 at 16^4, 109 / 320 at 24^4; sliced copy / CSR 28.4 / 27.5 at
+// 8^4, 28.2 / 29.1 at 8^3 x 16, 34.3 / 38.3 at 12^4.
+#ifndef MSC_APPLY_SITES_MIN
+#define MSC_APPLY_SITES_MIN 16384
+#endif
+#ifndef MSC_APPLY_SELL_MIN
+#define MSC_APPLY_SELL_MIN 16384
+#endif
+constexpr int64_t kApplySitesMin = MSC_APPLY_SITES_MIN;
+constexpr int64_t kApplySellMin = MSC_APPLY_SELL_MIN;
+
+// x at a gathered column, in the working precision R.
+template <class R, class V>
+__device__ __forceinline__ cplx<R> in_prec(const V& v) { return from_d<R>(to_d(v)); }
+
+__device__ __forceinline__ double2 with_shift(const double2& q, double shift, const double2& xv) {
+  return double2{q.x + shift * xv.x, q.y + shift * xv.y};
+}
+
+// One CSR row times x, L lanes per row, as row_dot but with x in its own precision.
+template <class R, int L, class V>
+__device__ __forceinline__ cplx<R> row_dot_in(const Csr<cplx<R>>& m, const V* __restrict__ x,
+                                              int64_t row, int lane) {
+  const int32_t beg = m.rowptr[row], end = m.rowptr[row + 1];
+  cplx<R> acc = czero<R>();
+  for (int32_t base = beg; base < end; base += kChunk * L) {
+    int32_t c[kChunk];
+    cplx<R> v[kChunk], xv[kChunk];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const int32_t j = base + lane + u * L;
+      const bool ok = j < end;
+      c[u] = ok ? m.col[j] : 0;
+      v[u] = ok ? m.val[j] : czero<R>();
+    }
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) xv[u] = in_prec<R>(x[c[u]]);
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) cfma<R>(acc, v[u], xv[u]);
+  }
+  return group_sum_c<L, R>(acc);
+}
+
+// y = m x (LAST false), or out = m x + shift in (LAST true), from the CSR.
+template <class R, int L, bool LAST, class V>
+__global__ __launch_bounds__(kBlock) void k_apply_csr(Csr<cplx<R>> m, const V* x, cplx<R>* y,
+                                                      const double2* in, double2* out,
+                                                      double shift, int64_t n) {
   constexpr int GPB = kBlock / L;
   const int lane = threadIdx.x % L, grp = threadIdx.x / L;
   int64_t beg, end;
   block_range(n, GPB, beg, end);
   for (int64_t row = beg + grp; row < end; row += GPB) {
-    const cplx<R> v = row_dot<R, L>(m, x, row, lane);
-    if (lane == 0) y[row] = v;
+    const cplx<R> v = row_dot_in<R, L>(m, x, row, lane);
+    if (lane == 0) {
+      if constexpr (LAST)
+        out[row] = with_shift(to_d(v), shift, in[row]);
+      else
+        y[row] = v;
+    }
+  }
+}
+
+// The same in FP64 from the sliced copy, one row per lane.
+template <bool LAST>
+__global__ __launch_bounds__(kBlock) void k_apply_sell(Sell<double2> m, const double2* x,
+                                                       const double2* in, double2* out,
+                                                       double shift, int64_t n, int64_t nslices) {
+  constexpr int SPB = kBlock / kSlice;
+  const int lane = threadIdx.x % kSlice;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+  int64_t beg, end;
+  block_range(nslices, SPB, beg, end);
+  for (int64_t sl = beg + wv; sl < end; sl += SPB) {
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < n ? row : n - 1;
+    double2 v = sell_row<double>(m, x, sl, lane);
+    cfma<double>(v, m.diag[rr], x[rr]);
+    if (row < n) out[row] = LAST ? with_shift(v, shift, in[row]) : v;
   }
 }
 
 template <class R>
-__global__ void k_shift_out(const cplx<R>* q, const double2* in, double2* out, double shift, int64_t n) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const double2 qd = to_d(q[i]), xv = in[i];
-    out[i] = double2{qd.x + shift * xv.x, qd.y + shift * xv.y};
-  }
+__global__ __launch_bounds__(kBlock) void k_apply_shift(const cplx<R>* q, const double2* in,
+                                                        double2* out, double shift, int64_t n) {
+  for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < n;
+       i += int64_t(gridDim.x) * kBlock)
+    out[i] = with_shift(to_d(q[i]), shift, in[i]);
 }
 
-__global__ void k_to32(const double2* in, float2* out, int64_t n) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n;
-       i += int64_t(gridDim.x) * blockDim.x)
-    out[i] = float2{float(in[i].x), float(in[i].y)};
+// One half of A = M^H M on the links in FP64, one site per lane: t = M in (LAST false), or
+// out = M^H t + shift in (LAST true).  Bound by the links and the gathers, as K2 is; where
+// K2 marches along t (tc >= 2 t-slices per column) so does this, with the same carry.  A
+// call at 32^3 x 64 takes 648 us, 1870 on the CSR (eight lanes per row).
+template <int LR, bool LAST, bool MARCH>
+__global__ __launch_bounds__(kBlock, 2) void k_apply_site(Stencil<double2> w, SweepOrder ord,
+                                                          uint32_t tc, const double2* x,
+                                                          const double2* in, double2* out,
+                                                          double shift) {
+  static_assert(!MARCH || LR == 2, "the march carries two-row links");
+  const uint32_t vol = uint32_t(w.vol);
+  const int64_t nblk = (int64_t(vol) + kSiteBlock - 1) / kSiteBlock;
+  constexpr int WPB = kBlock / kWave;
+  const int lane = threadIdx.x % kWave;
+  auto store = [&](uint32_t site, const double2 (&v)[3]) {
+    const int64_t r0 = 3 * int64_t(site);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      out[r0 + c] = LAST ? with_shift(v[c], shift, in[r0 + c]) : v[c];
+  };
+  auto gather = [&](int64_t i) { return x[i]; };
+  if constexpr (MARCH) {
+    const uint32_t vol3 = vol / uint32_t(w.L[3]);
+    const uint32_t bs = vol3 / uint32_t(kSiteBlock);
+    constexpr int K = 3 * LR;
+    TCarry<double, LR> car;
+    int64_t qb, qe;
+    march_range(nblk, WPB, qb, qe);
+    for (uint32_t q = uint32_t(qb); q < uint32_t(qe); ++q) {
+      const uint32_t col = q / tc, chunk = col / bs;
+      const uint32_t blk = (chunk * tc + (q - col * tc)) * bs + (col - chunk * bs);
+      const uint32_t site = blk * uint32_t(kSiteBlock) + uint32_t(lane);  // below vol
+      if (q == uint32_t(qb) || q % tc == 0) {
+        const uint32_t sb = site >= vol3 ? site - vol3 : site + (vol - vol3);  // periodic
+        const double2* __restrict__ wt = w.w + int64_t(3) * K * vol;
+#pragma unroll
+        for (int k = 0; k < K; ++k) car.u[k] = wt[int64_t(k) * vol + sb];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          car.own[c] = x[3 * int64_t(sb) + c];
+          car.fw[c] = x[3 * int64_t(site) + c];
+        }
+      }
+      double2 own[3], v[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) own[c] = car.fw[c];
+      stencil_site_c<double, LR, true>(w, site, own, LAST ? -1 : 1, gather, v, &car);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) car.own[c] = own[c];
+      store(site, v);
+    }
+  } else {
+    for (Sweep sw = make_sweep(nblk, ord, WPB); sw.more(); sw.next()) {
+      const uint32_t site = uint32_t(sw.slice() * kSiteBlock) + uint32_t(lane);
+      const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
+      double2 own[3], v[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) own[c] = x[3 * int64_t(ss) + c];
+      stencil_site<double, LR>(w, ss, own, LAST ? -1 : 1, gather, v);
+      if (site < vol) store(site, v);
+    }
+  }
 }
 
 // Workgroups for `n` items processed `rows_per_pass` at a time: one pass each when that
@@ -1891,6 +2026,17 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// t-slices per column of the march along t that the two-row links of this lattice allow (1:
+// none): a t-slice holds whole blocks of 64 sites and some power of two up to kK2March
+// divides L_t.
+int march_columns(const Stencil<double2>& w) {
+  const int64_t lt = w.L[3];
+  if (w.rows != 2 || lt <= 0 || (w.vol / lt) % kSiteBlock != 0) return 1;
+  for (int c = kK2March; c >= 2; c /= 2)
+    if (lt % c == 0) return c;
+  return 1;
+}
+
 // One iteration: the head (pending update fused with K1 on the sliced ELLPACK path; a
 // separate update kernel followed by the CSR K1 otherwise), the optional reliable
 // update, then K2.
@@ -1909,11 +2055,8 @@ hipError_t iteration_impl(const MsArgs& args, hipStream_t s, hipEvent_t* ev, boo
   // K2 on two-row links marches along t (k2_site<.., true>) when it runs on the resident
   // grid, a t-slice holds whole blocks of 64 sites, some tc >= 2 (at most kK2March)
   // divides L_t and every wave gets a run of at least 4 blocks
-  const int64_t lt = a.w64.L[3], vol = a.w64.vol;
-  int tc = 1;
-  if (lr == 2 && a.ord.on && lt > 0 && (vol / lt) % kSiteBlock == 0)
-    for (int c = kK2March; c >= 2 && tc == 1; c /= 2)
-      if (lt % c == 0) tc = c;
+  const int64_t vol = a.w64.vol;
+  int tc = lr == 2 && a.ord.on ? march_columns(a.w64) : 1;
   const int tc_lattice = tc;
   auto k2s = lr == 3   ? k2_site<R, 3, false>
              : lr == 2 ? (tc > 1 ? k2_site<R, 2, true> : k2_site<R, 2, false>)
@@ -2054,35 +2197,99 @@ hipError_t launch_verify(const MsArgs& a, const double* sigma_by_caller_index, i
   return hipGetLastError();
 }
 
-hipError_t launch_apply(int kind, int prec, int lanes, int64_t n, const Csr<double2>& m64,
-                        const Csr<double2>& mh64, const Csr<float2>& m32,
-                        const Csr<float2>& mh32, const double2* in, double2* out,
-                        double shift, void* tmp_a, void* tmp_b, hipStream_t s) {
-  const int g1 = grid_rows(n, kBlock / lanes);
-  const int g3 = grid_rows(n, kBlock);
-  if (prec == MSC_PREC_MIXED) {
-    float2* a32 = static_cast<float2*>(tmp_a);
-    float2* b32 = static_cast<float2*>(tmp_b);
-    k_to32<<<g3, kBlock, 0, s>>>(in, a32, n);
-    MSC_LANES_SWITCH(lanes, (k_spmv<float, LL><<<g1, kBlock, 0, s>>>(m32, a32, b32, n)));
-    if (kind == MSC_A_MHM) {
-      MSC_LANES_SWITCH(lanes, (k_spmv<float, LL><<<g1, kBlock, 0, s>>>(mh32, b32, a32, n)));
-      k_shift_out<float><<<g3, kBlock, 0, s>>>(a32, in, out, shift, n);
-    } else {
-      k_shift_out<float><<<g3, kBlock, 0, s>>>(b32, in, out, shift, n);
-    }
-  } else {
-    double2* a64 = static_cast<double2*>(tmp_a);
-    MSC_LANES_SWITCH(lanes, (k_spmv<double, LL><<<g1, kBlock, 0, s>>>(m64, in, a64, n)));
-    if (kind == MSC_A_MHM) {
-      double2* b64 = static_cast<double2*>(tmp_b);
-      MSC_LANES_SWITCH(lanes, (k_spmv<double, LL><<<g1, kBlock, 0, s>>>(mh64, a64, b64, n)));
-      k_shift_out<double><<<g3, kBlock, 0, s>>>(b64, in, out, shift, n);
-    } else {
-      k_shift_out<double><<<g3, kBlock, 0, s>>>(a64, in, out, shift, n);
+namespace {
+template <int LR>
+hipError_t apply_links(const ApplyArgs& a, double2* t, hipStream_t s) {
+  const Stencil<double2>& w = a.w64;
+  const int64_t nblk = (w.vol + kSiteBlock - 1) / kSiteBlock;
+  constexpr int WPB = kBlock / kWave;
+  int g = grid_rows(nblk, WPB);
+  if constexpr (LR == 2) {
+    const int tc = march_columns(w);
+    const int gm = resident_grid(reinterpret_cast<const void*>(k_apply_site<2, true, true>), g);
+    // as K2: runs of at least 4 blocks, or there is little to carry
+    if (tc > 1 && a.ord.on && nblk >= int64_t(gm) * WPB * 4) {
+      k_apply_site<2, false, true><<<gm, kBlock, 0, s>>>(w, a.ord, uint32_t(tc), a.in, a.in, t, 0.0);
+      k_apply_site<2, true, true><<<gm, kBlock, 0, s>>>(w, a.ord, uint32_t(tc), t, a.in, a.out,
+                                                        a.shift);
+      return hipGetLastError();
     }
   }
+  if (a.ord.on) g = resident_grid(reinterpret_cast<const void*>(k_apply_site<LR, true, false>), g);
+  k_apply_site<LR, false, false><<<g, kBlock, 0, s>>>(w, a.ord, 1u, a.in, a.in, t, 0.0);
+  k_apply_site<LR, true, false><<<g, kBlock, 0, s>>>(w, a.ord, 1u, t, a.in, a.out, a.shift);
   return hipGetLastError();
+}
+
+// Stored matrix, FP64: the sliced copy from kApplySellMin rows on (one row per lane: below,
+// too few waves hide its chain of loads), else the CSR.
+hipError_t apply_stored64(const ApplyArgs& a, hipStream_t s) {
+  double2* t = static_cast<double2*>(a.tmp);
+  const int g1 = grid_rows(a.n, kBlock / a.lanes);
+  const bool sell = a.sell && a.n >= kApplySellMin;
+  const int gs = sell ? grid_rows(a.nslices, kBlock / kSlice) : 0;
+  if (a.kind == MSC_A_MHM) {
+    if (sell) {
+      k_apply_sell<false><<<gs, kBlock, 0, s>>>(a.s64, a.in, a.in, t, 0.0, a.n, a.nslices);
+      k_apply_sell<true><<<gs, kBlock, 0, s>>>(a.sh64, t, a.in, a.out, a.shift, a.n, a.nslices);
+      return hipGetLastError();
+    }
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<double, LL, false, double2><<<g1, kBlock, 0, s>>>(
+                                  a.m64, a.in, t, a.in, a.out, 0.0, a.n)));
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<double, LL, true, double2><<<g1, kBlock, 0, s>>>(
+                                  a.mh64, t, t, a.in, a.out, a.shift, a.n)));
+    return hipGetLastError();
+  }
+  // A given: one pass, unless it would gather rows that it has overwritten
+  const bool apart = a.in + a.n <= a.out || a.out + a.n <= a.in;
+  if (sell) {
+    if (apart)
+      k_apply_sell<true><<<gs, kBlock, 0, s>>>(a.s64, a.in, a.in, a.out, a.shift, a.n, a.nslices);
+    else
+      k_apply_sell<false><<<gs, kBlock, 0, s>>>(a.s64, a.in, a.in, t, 0.0, a.n, a.nslices);
+  } else if (apart) {
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<double, LL, true, double2><<<g1, kBlock, 0, s>>>(
+                                  a.m64, a.in, t, a.in, a.out, a.shift, a.n)));
+  } else {
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<double, LL, false, double2><<<g1, kBlock, 0, s>>>(
+                                  a.m64, a.in, t, a.in, a.out, 0.0, a.n)));
+  }
+  if (!apart)
+    k_apply_shift<double><<<grid_rows(a.n, kBlock), kBlock, 0, s>>>(t, a.in, a.out, a.shift, a.n);
+  return hipGetLastError();
+}
+
+// complex64 arithmetic: the CSR, whose products are the same bits at every size.
+hipError_t apply_stored32(const ApplyArgs& a, hipStream_t s) {
+  float2* t = static_cast<float2*>(a.tmp);
+  const int g1 = grid_rows(a.n, kBlock / a.lanes);
+  if (a.kind == MSC_A_MHM) {
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<float, LL, false, double2><<<g1, kBlock, 0, s>>>(
+                                  a.m32, a.in, t, a.in, a.out, 0.0, a.n)));
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<float, LL, true, float2><<<g1, kBlock, 0, s>>>(
+                                  a.mh32, t, t, a.in, a.out, a.shift, a.n)));
+    return hipGetLastError();
+  }
+  if (a.in + a.n <= a.out || a.out + a.n <= a.in) {
+    MSC_LANES_SWITCH(a.lanes, (k_apply_csr<float, LL, true, double2><<<g1, kBlock, 0, s>>>(
+                                  a.m32, a.in, t, a.in, a.out, a.shift, a.n)));
+    return hipGetLastError();
+  }
+  MSC_LANES_SWITCH(a.lanes, (k_apply_csr<float, LL, false, double2><<<g1, kBlock, 0, s>>>(
+                                a.m32, a.in, t, a.in, a.out, 0.0, a.n)));
+  k_apply_shift<float><<<grid_rows(a.n, kBlock), kBlock, 0, s>>>(t, a.in, a.out, a.shift, a.n);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_apply(const ApplyArgs& a, hipStream_t s) {
+  if (a.prec == MSC_PREC_MIXED) return apply_stored32(a, s);
+  if (a.links != 0 && a.w64.vol >= kApplySitesMin) {
+    double2* t = static_cast<double2*>(a.tmp);
+    return a.links == 2 ? apply_links<2>(a, t, s) : apply_links<3>(a, t, s);
+  }
+  return apply_stored64(a, s);
 }
 
 // ---- operator application without allocation ------------------------------------------
@@ -2122,18 +2329,10 @@ hipError_t noalloc_scratch(int device, void** ptr) {
   return hipSuccess;
 }
 
-hipError_t launch_apply_noalloc(int kind, int prec, int lanes, int64_t n,
-                                const Csr<double2>& m64, const Csr<double2>& mh64,
-                                const Csr<float2>& m32, const Csr<float2>& mh32,
-                                const double2* in, double2* out, double shift, void* base,
-                                hipStream_t s) {
-  const size_t need = apply_scratch_bytes(kind, prec, n);
-  if (need > kNoAllocScratchBytes) return hipErrorInvalidValue;
-  const size_t elem = prec == MSC_PREC_MIXED ? sizeof(float2) : sizeof(double2);
-  const size_t one = (elem * size_t(n) + 255) / 256 * 256;
-  unsigned char* b = static_cast<unsigned char*>(base);
-  return launch_apply(kind, prec, lanes, n, m64, mh64, m32, mh32, in, out, shift, b,
-                      b + one, s);
+hipError_t launch_apply_noalloc(ApplyArgs a, void* base, hipStream_t s) {
+  if (apply_scratch_bytes(a.kind, a.prec, a.n) > kNoAllocScratchBytes) return hipErrorInvalidValue;
+  a.tmp = base;
+  return launch_apply(a, s);
 }
 
 }  // namespace msc
