@@ -3,19 +3,29 @@
 //
 // Used for the per-shift refinement after a mixed-precision multishift sequence (each
 // shift's FP64 true residual becomes the right-hand side of a correction solve) and for
-// adjoint solves with unrelated right-hand sides.  Vectors of the batch are interleaved,
-// v[i * MP + j] (MP = padded batch width), so a gather of row i's neighbour c reads the
-// MP values of all systems from one contiguous segment; lane j of a row group owns
-// system j, so no cross-lane reduction is needed inside a row.
+// adjoint solves with unrelated right-hand sides.  The vectors of the batch lie one system
+// after the other, v[j n + i], as the caller's do, so that a wave's gathers for one system
+// read neighbouring rows together.
+//
+// Systems still iterating are kept in a list on the device; the two operator halves take
+// it in groups of a few systems, one group per workgroup.  A wave reads the matrix
+// (or the links) of its rows once for its group and gathers each system's values in turn;
+// the workgroups of the other groups on the same rows follow one another on one XCD, whose
+// L2 then serves the matrix to all but the first.  A system that has converged costs
+// nothing from the next iteration on.  Ten systems at 16^4 in FP64, an iteration's halves:
+// 155 and 162 us with 16 interleaved systems on the CSR (10 padded to 16, all of them to
+// the end); 49 and 53 us on the sliced copy, 30 and 35 us on the links on average here.
 //
 // An outer defect-correction cycle recomputes f_j - (A + sigma_j) x_j in FP64 (the
 // multi-vector kernels below), the inner CG runs in the working precision from e = 0,
 // and x_j += e_j is accumulated in FP64.
+#include <algorithm>
 #include <type_traits>
 
 #include "dev_common.h"
 #include "msc_internal.h"
 #include "sell_load.h"
+#include "stencil.h"
 
 namespace msc {
 
@@ -28,45 +38,106 @@ template <> __device__ __forceinline__ Csr<float2> pick_a<float>(const BssArgs& 
 template <> __device__ __forceinline__ Csr<double2> pick_a<double>(const BssArgs& a, bool second) {
   return second ? a.mh64 : a.m64;
 }
+template <class R> __device__ __forceinline__ Sell<cplx<R>> pick_s(const BssArgs& a, bool second);
+template <> __device__ __forceinline__ Sell<float2> pick_s<float>(const BssArgs& a, bool second) {
+  return second ? a.sh32 : a.s32;
+}
+template <> __device__ __forceinline__ Sell<double2> pick_s<double>(const BssArgs& a, bool second) {
+  return second ? a.sh64 : a.s64;
+}
+template <class R> __device__ __forceinline__ Stencil<cplx<R>> pick_l(const BssArgs& a);
+template <> __device__ __forceinline__ Stencil<float2> pick_l<float>(const BssArgs& a) { return a.w32; }
+template <> __device__ __forceinline__ Stencil<double2> pick_l<double>(const BssArgs& a) { return a.w64; }
 
-// Reduce one double per thread to per-system sums (system = lane % MP) and store the
-// workgroup's MP partials.
-template <int MP>
-__device__ __forceinline__ void store_system_partials(double v, double* partial) {
-  __shared__ double part[kBlock / kWave][kBssMax];
+enum { kCsr = 0, kSell = 1, kLinks3 = 2, kLinks2 = 3 };  // what an operator half reads
+
+// Most systems of one group, and most workgroups, by storage.  A wave of the links' halves
+// holds a direction's two links beside its group's accumulators (252 VGPRs at five
+// systems), and two waves per SIMD with little each beat fewer, longer ones; the sliced
+// rows need few registers, and a larger group reads the matrix less often.  Ten systems at
+// 16^4 in FP64, whole solve: links, groups of 1 / 2 / 3 / 5 / 8: 33.0 / 28.7 / 29.7 / 33.4 /
+// 45.2 ms, and 30.8 ms with 768 workgroups; sliced copy (a gradient), groups of 2 / 3 / 4 /
+// 5 / 8 on 512: 61.1 / 59.6 / 58.4 / 55.9 / 58.2 ms; 5 on 768 and 1024: 51.3 and 53.8 ms.
+template <int ST> constexpr int group_max() { return ST == kCsr || ST == kSell ? 5 : 2; }
+template <int ST> constexpr int half_grid() { return ST == kCsr || ST == kSell ? 768 : 512; }
+
+// This workgroup's share of an operator half: systems list[lo, lo + cnt) and, in units of
+// `step` items (rows, slices or blocks of sites), the contiguous range [beg, end).  The
+// grid is a multiple of the XCD count; XCD x owns an eighth of the items, its workgroups
+// are dealt to the groups in turn and the workgroups of a group split its items evenly.
+struct Share {
+  int groups, group, lo, cnt;
+  int64_t beg, end;
+};
+
+__device__ __forceinline__ int group_lo(int nact, int groups, int g) { return nact * g / groups; }
+
+template <int G> __device__ __forceinline__ Share make_share(int nact, int64_t items, int step) {
+  Share h;
+  const int x = int(blockIdx.x) % kXcds, xb = int(blockIdx.x) / kXcds, nb = int(gridDim.x) / kXcds;
+  h.groups = (nact + G - 1) / G;  // nact >= 1 while the batch runs; at most nb
+  h.group = xb % h.groups;
+  h.lo = group_lo(nact, h.groups, h.group);
+  h.cnt = group_lo(nact, h.groups, h.group + 1) - h.lo;
+  const int mates = (nb - h.group + h.groups - 1) / h.groups, me = xb / h.groups;
+  const int64_t units = (items + step - 1) / step;
+  const int64_t u0 = units * x / kXcds, u1 = units * (x + 1) / kXcds;
+  h.beg = (u0 + (u1 - u0) * me / mates) * step;
+  h.end = min((u0 + (u1 - u0) * (me + 1) / mates) * step, items);
+  return h;
+}
+
+// The workgroup's sums of its group's systems, then (in the last workgroup) the totals of
+// all systems of the list into out[0..nact).
+template <int G>
+__device__ __forceinline__ void store_group_partials(double (&v)[G], double* partial) {
+  block_sum_k<kBlock, G>(v);
+  if (threadIdx.x == 0) {
 #pragma unroll
-  for (int off = MP; off < kWave; off <<= 1) v += __shfl_xor(v, off, kWave);
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  if (lane < MP) part[w][lane] = v;
-  __syncthreads();
-  if (threadIdx.x < MP) {
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < kBlock / kWave; ++q) s += part[q][threadIdx.x];
-    store_agent(&partial[blockIdx.x * kBssMax + threadIdx.x], s);
+    for (int q = 0; q < G; ++q) store_agent(&partial[blockIdx.x * G + q], v[q]);
   }
 }
 
-// In the last workgroup: per-system totals of all workgroups' partials into out[0..15].
-__device__ __forceinline__ void sum_system_partials(const double* partial, int count, double* out) {
-  // thread -> (system j = tid / 16, sub-lane s = tid % 16)
-  const int j = threadIdx.x / 16, s = threadIdx.x % 16;
+template <int G>
+__device__ __forceinline__ void sum_group_partials(const double* partial, int nact, int groups,
+                                                   double* out) {
+  // thread -> (position in the list tid / 16, sub-lane tid % 16)
+  const int li = threadIdx.x / 16, s = threadIdx.x % 16;
   double acc = 0.0;
-  for (int b = s; b < count; b += 16) acc += load_agent(&partial[b * kBssMax + j]);
+  if (li < nact) {
+    int g = 0;
+    while (group_lo(nact, groups, g + 1) <= li) ++g;
+    const int u = li - group_lo(nact, groups, g);
+    const int nb = int(gridDim.x) / kXcds, mates = (nb - g + groups - 1) / groups;
+    const int count = mates * kXcds;  // workgroups of the group, sixteen at a time
+    constexpr int kAhead = 8;
+    for (int b = s; b < count; b += 16 * kAhead) {
+      double w[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const int c = b + 16 * k;
+        const int blk = ((c / kXcds) * groups + g) * kXcds + c % kXcds;
+        w[k] = c < count ? load_agent(&partial[blk * G + u]) : 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) acc += w[k];
+    }
+  }
   acc = group_sum<16>(acc);
-  if (s == 0) out[j] = acc;
+  if (s == 0) out[li] = acc;
   __syncthreads();
 }
 
-// After the partials of IK1 are stored: the last workgroup forms a_j = R_j / P_j.
-__device__ void ik1_finish(const BssArgs& a) {
+// After the partials of half 1 are stored: the last workgroup forms a_j = R_j / P_j.
+template <int G> __device__ void ik1_finish(const BssArgs& a, int groups) {
   BssState* st = a.st;
   if (!arrive_last(a.tickets + 8 * kTicketSite)) return;
   __shared__ double tot[kBssMax];
-  sum_system_partials(a.partial, gridDim.x, tot);
-  const int q = threadIdx.x;
-  if (q < st->m && st->active[q]) {
-    const double P = tot[q];
+  const int nact = st->nlist[a.par];
+  sum_group_partials<G>(a.partial, nact, groups, tot);
+  if (int(threadIdx.x) < nact) {
+    const int q = st->list[a.par][threadIdx.x];
+    const double P = tot[threadIdx.x];
     if (P > 0.0 && isfinite(P)) {
       st->a[q] = st->R[q] / P;
     } else {
@@ -77,37 +148,43 @@ __device__ void ik1_finish(const BssArgs& a) {
   }
 }
 
-// After the partials of IK2 are stored: the last workgroup forms b_j and R_j, retires
-// converged systems and decides whether the batch halts.
-__device__ void ik2_finish(const BssArgs& a) {
+// After the partials of half 2 are stored: the last workgroup forms b_j and R_j, retires
+// converged systems, lists the others for the next iteration and decides whether the
+// batch halts.
+template <int G> __device__ void ik2_finish(const BssArgs& a, int groups) {
   BssState* st = a.st;
   if (!arrive_last(a.tickets + 9 * kTicketSite)) return;
   __shared__ double tot[kBssMax];
-  sum_system_partials(a.partial, gridDim.x, tot);
+  const int nact = st->nlist[a.par];
+  sum_group_partials<G>(a.partial, nact, groups, tot);
   if (threadIdx.x < kWave) {
-    const int qq = threadIdx.x;
-    bool upd = false, act = false;
-    if (qq < st->m && st->active[qq]) {
-      const double Rn = tot[qq];
-      upd = true;
-      if (!isfinite(Rn)) {
-        st->bad[qq] = 1;
-        st->active[qq] = 0;
-        upd = false;
-      } else {
-        st->b[qq] = Rn / st->R[qq];
-        st->R[qq] = Rn;
-        st->iters[qq] += 1;
-        if (Rn <= st->target2[qq]) st->active[qq] = 0;
-        act = st->active[qq] != 0;
+    const int li = threadIdx.x;
+    const int q = li < nact ? st->list[a.par][li] : 0;
+    bool act = false;
+    if (li < nact) {
+      bool upd = false;
+      if (st->active[q]) {
+        const double Rn = tot[li];
+        if (!isfinite(Rn)) {
+          st->bad[q] = 1;
+          st->active[q] = 0;
+        } else {
+          upd = true;
+          st->b[q] = Rn / st->R[q];
+          st->R[q] = Rn;
+          st->iters[q] += 1;
+          act = !(Rn <= st->target2[q]);
+          st->active[q] = act ? 1 : 0;
+        }
       }
+      st->upd[q] = upd ? 1 : 0;
     }
-    if (qq < kBssMax) st->upd[qq] = upd ? 1 : 0;
     const uint64_t am = __ballot(act);
-    if (qq == 0) {
+    if (act) st->list[a.par ^ 1][__popcll(am & ((uint64_t(1) << li) - 1))] = q;
+    if (li == 0) {
+      st->nlist[a.par ^ 1] = __popcll(am);
       st->iter += 1;
-      st->nact = __popcll(am);
-      if (st->nact == 0 || st->iter >= st->max_iter) {
+      if (am == 0 || st->iter >= st->max_iter) {
         st->halt = 1;
         store_host_flag(a.hflag, 1);
       }
@@ -116,248 +193,252 @@ __device__ void ik2_finish(const BssArgs& a) {
   }
 }
 
-// ---- IK1: t_j = A1 p_j and P_j = p_j^H (A + sigma_j) p_j ----------------------------
-template <class R, int MP, bool MHM>
-__global__ __launch_bounds__(kBlock) void ik1(BssArgs a) {
-  BssState* st = a.st;
-  if (st->halt) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) st->k3_enable = 0;
-    return;
+// The group's vectors of one array: system list[lo + u] starts at v + list[lo + u] n (the
+// last one repeated past cnt, so that every pointer is valid).
+template <int G, class T>
+__device__ __forceinline__ void group_ptrs(const BssArgs& a, const Share& h, T* v, T* (&o)[G]) {
+  const int* list = a.st->list[a.par];
+#pragma unroll
+  for (int u = 0; u < G; ++u)
+    o[u] = v + int64_t(list[h.lo + (u < h.cnt ? u : h.cnt - 1)]) * a.n;
+}
+
+// P's term of one row: v = (A1 p)_i of system sig, p its direction there.
+template <class R, bool MHM>
+__device__ __forceinline__ double p_term(const cplx<R>& v, const cplx<R>& p, double sig) {
+  if (MHM) return norm2d<R>(v) + sig * norm2d<R>(p);
+  return double(p.x) * double(v.x) + double(p.y) * double(v.y) + sig * norm2d<R>(p);
+}
+
+// r - a (q + sig p) at one row.
+template <class R>
+__device__ __forceinline__ cplx<R> r_next(const cplx<R>& r, const cplx<R>& q, const cplx<R>& p,
+                                          double step, double sig) {
+  const double2 qd = to_d(q), pd = to_d(p), rd = to_d(r);
+  return from_d<R>(double2{rd.x - step * (qd.x + sig * pd.x), rd.y - step * (qd.y + sig * pd.y)});
+}
+
+// Off-diagonal entries of one sliced row times the group's vectors (KP pairs a round trip).
+template <class R, int G, int KP, bool NARROW>
+__device__ __forceinline__ void sell_row_group(const Sell<cplx<R>>& m,
+                                               const cplx<R>* const (&xs)[G], int cnt,
+                                               int64_t sl, int lane, cplx<R> (&acc)[G]) {
+  int32_t c, c1;
+  if (m.wp > 0) {
+    c = int32_t(sl) * m.wp;
+    c1 = c + m.wp;
+  } else {
+    c = load_uniform(m.cptr, sl);
+    c1 = load_uniform(m.cptr, sl + 1);
   }
-  const Csr<cplx<R>> m = pick_a<R>(a, false);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.p);
-  cplx<R>* __restrict__ t = static_cast<cplx<R>*>(a.t);
-  constexpr int GPB = kBlock / MP;
-  const int j = threadIdx.x % MP, grp = threadIdx.x / MP;
-  const double sig = st->sigma[j];
-  int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
-  double acc = 0.0;
-  for (int64_t row = beg + grp; row < end; row += GPB) {
-    cplx<R> sum = czero<R>();
-    const int32_t e0 = m.rowptr[row], e1 = m.rowptr[row + 1];
-    int32_t e = e0;
-    for (; e + 3 < e1; e += 4) {
-      const int32_t c0 = m.col[e], c1 = m.col[e + 1], c2 = m.col[e + 2], c3 = m.col[e + 3];
-      const cplx<R> v0 = m.val[e], v1 = m.val[e + 1], v2 = m.val[e + 2], v3 = m.val[e + 3];
-      const cplx<R> x0 = p[int64_t(c0) * MP + j], x1 = p[int64_t(c1) * MP + j];
-      const cplx<R> x2 = p[int64_t(c2) * MP + j], x3 = p[int64_t(c3) * MP + j];
-      cfma<R>(sum, v0, x0);
-      cfma<R>(sum, v1, x1);
-      cfma<R>(sum, v2, x2);
-      cfma<R>(sum, v3, x3);
-    }
-    for (; e < e1; ++e) cfma<R>(sum, m.val[e], p[int64_t(m.col[e]) * MP + j]);
-    t[row * MP + j] = sum;
-    const cplx<R> pr = p[row * MP + j];
-    if (MHM)
-      acc += norm2d<R>(sum) + sig * norm2d<R>(pr);
+  for (; c < c1; c += KP) {
+    const int np = c1 - c;
+    int2 cc[KP];
+    cplx<R> v[2 * KP];
+    if (np >= KP)
+      sell_load<R, KP, true, NARROW>(m, c, KP, lane, cc, v);
     else
-      acc += double(pr.x) * double(sum.x) + double(pr.y) * double(sum.y) + sig * norm2d<R>(pr);
-  }
-  store_system_partials<MP>(acc, a.partial);
-  ik1_finish(a);
-}
-
-// ---- IK2: r_j <- r_j - a_j (A2 t_j + sigma_j p_j), R_j = |r_j|^2 ----------------------
-template <class R, int MP, bool MHM>
-__global__ __launch_bounds__(kBlock) void ik2(BssArgs a) {
-  BssState* st = a.st;
-  if (st->halt) return;
-  const cplx<R>* __restrict__ t = static_cast<const cplx<R>*>(a.t);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.p);
-  cplx<R>* __restrict__ r = static_cast<cplx<R>*>(a.r);
-  constexpr int GPB = kBlock / MP;
-  const int j = threadIdx.x % MP, grp = threadIdx.x / MP;
-  const double sig = st->sigma[j];
-  const double step = st->active[j] ? st->a[j] : 0.0;
-  int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
-  double acc = 0.0;
-  for (int64_t row = beg + grp; row < end; row += GPB) {
-    double2 q;
-    if (MHM) {
-      const Csr<cplx<R>> mh = pick_a<R>(a, true);
-      cplx<R> sum = czero<R>();
-      const int32_t e0 = mh.rowptr[row], e1 = mh.rowptr[row + 1];
-      int32_t e = e0;
-      for (; e + 3 < e1; e += 4) {
-        const int32_t c0 = mh.col[e], c1 = mh.col[e + 1], c2 = mh.col[e + 2], c3 = mh.col[e + 3];
-        const cplx<R> v0 = mh.val[e], v1 = mh.val[e + 1], v2 = mh.val[e + 2], v3 = mh.val[e + 3];
-        const cplx<R> x0 = t[int64_t(c0) * MP + j], x1 = t[int64_t(c1) * MP + j];
-        const cplx<R> x2 = t[int64_t(c2) * MP + j], x3 = t[int64_t(c3) * MP + j];
-        cfma<R>(sum, v0, x0);
-        cfma<R>(sum, v1, x1);
-        cfma<R>(sum, v2, x2);
-        cfma<R>(sum, v3, x3);
-      }
-      for (; e < e1; ++e) cfma<R>(sum, mh.val[e], t[int64_t(mh.col[e]) * MP + j]);
-      q = to_d(sum);
-    } else {
-      q = to_d(t[row * MP + j]);
-    }
-    const double2 pr = to_d(p[row * MP + j]);
-    const double2 rr = to_d(r[row * MP + j]);
-    double2 nr;
-    nr.x = rr.x - step * (q.x + sig * pr.x);
-    nr.y = rr.y - step * (q.y + sig * pr.y);
-    const cplx<R> sr = from_d<R>(nr);
-    r[row * MP + j] = sr;
-    acc += norm2d<R>(sr);
-  }
-  store_system_partials<MP>(acc, a.partial);
-  ik2_finish(a);
-}
-
-// ---- IK1 and IK2 on the sliced ELLPACK copies: one row per lane, every system of the
-// batch per lane (one read of the matrix row serves all of them) ----------------------
-// Pairs per round trip: the MP gathered values of 2 KP entries stay within the budget.
-template <class R, int MP> constexpr int kp_bss() {
-  return std::is_same<R, float>::value ? (MP <= 4 ? 4 : (MP == 8 ? 2 : 1))
-                                       : (MP <= 4 ? 2 : 1);
-}
-template <class R> __device__ __forceinline__ Sell<cplx<R>> pick_s(const BssArgs& a, bool second);
-template <> __device__ __forceinline__ Sell<float2> pick_s<float>(const BssArgs& a, bool second) {
-  return second ? a.sh32 : a.s32;
-}
-template <> __device__ __forceinline__ Sell<double2> pick_s<double>(const BssArgs& a, bool second) {
-  return second ? a.sh64 : a.s64;
-}
-
-// Per-system workgroup sums of MP doubles per thread, stored as the workgroup's partials.
-template <int MP>
-__device__ __forceinline__ void store_rr_partials(double (&v)[MP], double* partial) {
-  block_sum_k<kBlock, MP>(v);
-  if (threadIdx.x == 0) {
+      sell_load<R, KP, false, NARROW>(m, c, np, lane, cc, v);
 #pragma unroll
-    for (int q = 0; q < MP; ++q) store_agent(&partial[blockIdx.x * kBssMax + q], v[q]);
+    for (int q = 0; q < G; ++q) {
+      if (q < cnt) {
+        cplx<R> g[2 * KP];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) {  // a missing pair: column 0, values 0
+          g[2 * u] = xs[q][cc[u].x];
+          g[2 * u + 1] = xs[q][cc[u].y];
+        }
+#pragma unroll
+        for (int u = 0; u < 2 * KP; ++u)
+          if (u < 2 * np) cfma<R>(acc[q], v[u], g[u]);
+      }
+    }
   }
 }
 
-template <class R, int MP, bool MHM>
-__global__ __launch_bounds__(kBlock) void ik1s(BssArgs a) {
+// One half of the operator for this workgroup's systems and rows: body(row, out) with the
+// products out[u] of every system u < cnt at `row`; lanes with nothing to do skip it.
+template <class R, int G, int ST, int L, class F>
+__device__ __forceinline__ void half(const BssArgs& a, bool second, const Share& h,
+                                     const cplx<R>* const (&xs)[G], F body) {
+  if constexpr (ST == kCsr) {
+    const Csr<cplx<R>> m = pick_a<R>(a, second);
+    constexpr int GPB = kBlock / L;
+    const int lane = threadIdx.x % L;
+    for (int64_t row = h.beg + threadIdx.x / L; row < h.end; row += GPB) {
+      cplx<R> o[G];
+#pragma unroll
+      for (int q = 0; q < G; ++q) o[q] = czero<R>();
+      const int32_t e1 = m.rowptr[row + 1];
+      for (int32_t e = m.rowptr[row] + lane; e < e1; e += L) {
+        const int32_t c = m.col[e];
+        const cplx<R> v = m.val[e];
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+          if (q < h.cnt) cfma<R>(o[q], v, xs[q][c]);
+      }
+#pragma unroll
+      for (int q = 0; q < G; ++q)
+        if (q < h.cnt) o[q] = group_sum_c<L, R>(o[q]);
+      if (lane == 0) body(row, o);
+    }
+  } else if constexpr (ST == kSell) {
+    const Sell<cplx<R>> m = pick_s<R>(a, second);
+    constexpr int KP = std::is_same<R, float>::value ? 4 : 2;
+    const int lane = threadIdx.x % kSlice;
+    const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+    for (int64_t sl = h.beg + wv; sl < h.end; sl += kBlock / kSlice) {
+      const int64_t row = sl * kSlice + lane;
+      const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
+      cplx<R> o[G];
+      const cplx<R> d = m.diag[rr];
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        o[q] = czero<R>();
+        if (q < h.cnt) cfma<R>(o[q], d, xs[q][rr]);
+      }
+      if (m.col16)
+        sell_row_group<R, G, KP, true>(m, xs, h.cnt, sl, lane, o);
+      else
+        sell_row_group<R, G, KP, false>(m, xs, h.cnt, sl, lane, o);
+      if (row < a.n) body(row, o);
+    }
+  } else {
+    constexpr int LR = ST == kLinks2 ? 2 : 3;
+    const Stencil<cplx<R>> w = pick_l<R>(a);
+    const uint32_t vol = uint32_t(w.vol);
+    const int lane = threadIdx.x % kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
+    for (int64_t blk = h.beg + wv; blk < h.end; blk += kBlock / kWave) {
+      const uint32_t site = uint32_t(blk * kWave) + uint32_t(lane);
+      const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
+      cplx<R> o[G][3];
+      stencil_site_group<R, LR, G>(w, ss, second ? -1 : 1, xs, h.cnt, o);
+      if (site < vol) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          cplx<R> oc[G];
+#pragma unroll
+          for (int q = 0; q < G; ++q) oc[q] = o[q][c];
+          body(3 * int64_t(site) + c, oc);
+        }
+      }
+    }
+  }
+}
+
+template <int ST, int L> __device__ __forceinline__ int64_t half_items(const BssArgs& a) {
+  return ST == kCsr ? a.n : (ST == kSell ? a.nslices : (a.w64.vol + kWave - 1) / kWave);
+}
+template <int ST, int L> constexpr int half_step() {
+  return ST == kCsr ? kBlock / L : kBlock / kWave;
+}
+
+// ---- half 1: t_j = A1 p_j and P_j = p_j^H (A + sigma_j) p_j --------------------------
+template <class R, int ST, int L, bool MHM>
+__global__ __launch_bounds__(kBlock, 2) void ik1(BssArgs a) {
+  constexpr int G = group_max<ST>();
   BssState* st = a.st;
   if (st->halt) {
     if (blockIdx.x == 0 && threadIdx.x == 0) st->k3_enable = 0;
     return;
   }
-  const Sell<cplx<R>> m = pick_s<R>(a, false);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.p);
-  cplx<R>* __restrict__ t = static_cast<cplx<R>*>(a.t);
-  constexpr int SPB = kBlock / kSlice;
-  const int lane = threadIdx.x % kSlice;
-  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
-  double sig[MP], acc[MP];
+  const Share h = make_share<G>(st->nlist[a.par], half_items<ST, L>(a), half_step<ST, L>());
+  const cplx<R>* p[G];
+  cplx<R>* t[G];
+  group_ptrs<G, const cplx<R>>(a, h, static_cast<const cplx<R>*>(a.p), p);
+  group_ptrs<G, cplx<R>>(a, h, static_cast<cplx<R>*>(a.t), t);
+  double sig[G], acc[G];
 #pragma unroll
-  for (int q = 0; q < MP; ++q) {
-    sig[q] = st->sigma[q];
-    acc[q] = 0.0;
+  for (int u = 0; u < G; ++u) {
+    sig[u] = st->sigma[st->list[a.par][h.lo + (u < h.cnt ? u : 0)]];
+    acc[u] = 0.0;
   }
-  int64_t beg, end;
-  block_range(a.nslices, SPB, beg, end);
-  for (int64_t sl = beg + wv; sl < end; sl += SPB) {
-    const int64_t row = sl * kSlice + lane;
-    const bool live = row < a.n;
-    const int64_t rr = live ? row : a.n - 1;  // lanes past n read a valid row, unused
-    cplx<R> v[MP], pr[MP];
-    sell_row_rhs<R, MP, kp_bss<R, MP>()>(m, p, sl, lane, v);
-    load_rhs<R, MP>(p, rr, pr);
-    const cplx<R> d = m.diag[rr];
-    if (live) {
+  half<R, G, ST, L>(a, false, h, p, [&](int64_t row, const cplx<R>(&o)[G]) {
 #pragma unroll
-      for (int q = 0; q < MP; ++q) {
-        cfma<R>(v[q], d, pr[q]);
-        t[row * MP + q] = v[q];
-        if (MHM)
-          acc[q] += norm2d<R>(v[q]) + sig[q] * norm2d<R>(pr[q]);
-        else
-          acc[q] += double(pr[q].x) * double(v[q].x) + double(pr[q].y) * double(v[q].y) +
-                    sig[q] * norm2d<R>(pr[q]);
+    for (int u = 0; u < G; ++u) {
+      if (u < h.cnt) {
+        t[u][row] = o[u];
+        acc[u] += p_term<R, MHM>(o[u], p[u][row], sig[u]);
       }
     }
-  }
-  store_rr_partials<MP>(acc, a.partial);
-  ik1_finish(a);
+  });
+  store_group_partials(acc, a.partial);
+  ik1_finish<G>(a, h.groups);
 }
 
-template <class R, int MP, bool MHM>
-__global__ __launch_bounds__(kBlock) void ik2s(BssArgs a) {
+// ---- half 2: r_j <- r_j - a_j (A2 t_j + sigma_j p_j), R_j = |r_j|^2 --------------------
+template <class R, int ST, int L, bool MHM>
+__global__ __launch_bounds__(kBlock, 2) void ik2(BssArgs a) {
+  constexpr int G = group_max<ST>();
   BssState* st = a.st;
   if (st->halt) return;
-  const cplx<R>* __restrict__ t = static_cast<const cplx<R>*>(a.t);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.p);
-  cplx<R>* __restrict__ r = static_cast<cplx<R>*>(a.r);
-  constexpr int SPB = kBlock / kSlice;
-  const int lane = threadIdx.x % kSlice;
-  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
-  double sig[MP], step[MP], acc[MP];
+  const Share h = make_share<G>(st->nlist[a.par], half_items<ST, L>(a), half_step<ST, L>());
+  const cplx<R>* p[G];
+  const cplx<R>* t[G];
+  cplx<R>* r[G];
+  group_ptrs<G, const cplx<R>>(a, h, static_cast<const cplx<R>*>(a.p), p);
+  group_ptrs<G, const cplx<R>>(a, h, static_cast<const cplx<R>*>(a.t), t);
+  group_ptrs<G, cplx<R>>(a, h, static_cast<cplx<R>*>(a.r), r);
+  double sig[G], step[G], acc[G];
 #pragma unroll
-  for (int q = 0; q < MP; ++q) {
-    sig[q] = st->sigma[q];
-    step[q] = st->active[q] ? st->a[q] : 0.0;
-    acc[q] = 0.0;
+  for (int u = 0; u < G; ++u) {
+    const int j = st->list[a.par][h.lo + (u < h.cnt ? u : 0)];
+    sig[u] = st->sigma[j];
+    step[u] = st->active[j] ? st->a[j] : 0.0;
+    acc[u] = 0.0;
   }
-  int64_t beg, end;
-  block_range(a.nslices, SPB, beg, end);
-  for (int64_t sl = beg + wv; sl < end; sl += SPB) {
-    const int64_t row = sl * kSlice + lane;
-    const bool live = row < a.n;
-    const int64_t rr = live ? row : a.n - 1;
-    cplx<R> v[MP], pr[MP], rv[MP];
-    if (MHM) {
-      const Sell<cplx<R>> mh = pick_s<R>(a, true);
-      cplx<R> tr[MP];
-      sell_row_rhs<R, MP, kp_bss<R, MP>()>(mh, t, sl, lane, v);
-      load_rhs<R, MP>(t, rr, tr);
-      const cplx<R> d = mh.diag[rr];
+  auto row_step = [&](int64_t row, const cplx<R>(&o)[G]) {
 #pragma unroll
-      for (int q = 0; q < MP; ++q) cfma<R>(v[q], d, tr[q]);
-    } else {
-      load_rhs<R, MP>(t, rr, v);
-    }
-    load_rhs<R, MP>(p, rr, pr);
-    load_rhs<R, MP>(r, rr, rv);
-    if (live) {
-#pragma unroll
-      for (int q = 0; q < MP; ++q) {
-        const double2 qd = to_d(v[q]), pd = to_d(pr[q]), rd = to_d(rv[q]);
-        double2 nr;
-        nr.x = rd.x - step[q] * (qd.x + sig[q] * pd.x);
-        nr.y = rd.y - step[q] * (qd.y + sig[q] * pd.y);
-        const cplx<R> sr = from_d<R>(nr);
-        r[row * MP + q] = sr;
-        acc[q] += norm2d<R>(sr);
+    for (int u = 0; u < G; ++u) {
+      if (u < h.cnt) {
+        const cplx<R> nr = r_next<R>(r[u][row], o[u], p[u][row], step[u], sig[u]);
+        r[u][row] = nr;
+        acc[u] += norm2d<R>(nr);
       }
     }
+  };
+  if constexpr (MHM) {
+    half<R, G, ST, L>(a, true, h, t, row_step);
+  } else {  // A given: t is A p already
+    const int64_t rows = ST == kCsr ? 1 : kSlice, end = min(h.end * rows, a.n);
+    for (int64_t row = h.beg * rows + threadIdx.x; row < end; row += kBlock) {
+      cplx<R> o[G];
+#pragma unroll
+      for (int u = 0; u < G; ++u) o[u] = u < h.cnt ? t[u][row] : czero<R>();
+      row_step(row, o);
+    }
   }
-  store_rr_partials<MP>(acc, a.partial);
-  ik2_finish(a);
+  store_group_partials(acc, a.partial);
+  ik2_finish<G>(a, h.groups);
 }
 
-// ---- IK3: e_j += a_j p_j; p_j <- r_j + b_j p_j (elementwise over the batch) --------------
-template <class R, int MP>
+// ---- IK3: e_j += a_j p_j; p_j <- r_j + b_j p_j for the systems of this iteration ---------
+template <class R>
 __global__ __launch_bounds__(kBlock) void ik3(BssArgs a) {
   const BssState* st = a.st;
   if (!st->k3_enable) return;
-  const cplx<R>* __restrict__ r = static_cast<const cplx<R>*>(a.r);
-  cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.p);
-  cplx<R>* __restrict__ ev = static_cast<cplx<R>*>(a.e);
-  const int64_t total = a.n * MP;
   int64_t beg, end;
-  block_range(total, kBlock, beg, end);
-  for (int64_t idx = beg + threadIdx.x; idx < end; idx += kBlock) {
-    const int j = int(idx % MP);
+  block_range(a.n, kBlock, beg, end);
+  const int nact = st->nlist[a.par];
+  for (int li = 0; li < nact; ++li) {
+    const int j = st->list[a.par][li];
     if (!st->upd[j]) continue;
-    const double2 pd = to_d(p[idx]);
-    double2 ed = to_d(ev[idx]);
-    const double aj = st->a[j];
-    ed.x = fma(aj, pd.x, ed.x);
-    ed.y = fma(aj, pd.y, ed.y);
-    ev[idx] = from_d<R>(ed);
-    if (st->active[j]) {
-      const double2 rd = to_d(r[idx]);
-      const double bj = st->b[j];
-      p[idx] = from_d<R>(double2{fma(bj, pd.x, rd.x), fma(bj, pd.y, rd.y)});
+    const cplx<R>* __restrict__ r = static_cast<const cplx<R>*>(a.r) + int64_t(j) * a.n;
+    cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.p) + int64_t(j) * a.n;
+    cplx<R>* __restrict__ ev = static_cast<cplx<R>*>(a.e) + int64_t(j) * a.n;
+    const double aj = st->a[j], bj = st->b[j];
+    const bool more = st->active[j] != 0;
+    for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
+      const double2 pd = to_d(p[i]);
+      double2 ed = to_d(ev[i]);
+      ed.x = fma(aj, pd.x, ed.x);
+      ed.y = fma(aj, pd.y, ed.y);
+      ev[i] = from_d<R>(ed);
+      if (more) {
+        const double2 rd = to_d(r[i]);
+        p[i] = from_d<R>(double2{fma(bj, pd.x, rd.x), fma(bj, pd.y, rd.y)});
+      }
     }
   }
 }
@@ -414,7 +495,7 @@ __device__ void res_finish(const ResArgs& v, double (&nrm)[kResChunk]) {
 }
 
 // Row `row`'s residuals from the products acc_q = (A x_q)[row]: norms, and the
-// interleaved r = p = residual, e = 0 when r is set.
+// system's r = p = residual, e = 0 when r is set.
 template <class R>
 __device__ __forceinline__ void res_row(const ResArgs& v, int64_t row, const double2 (&acc)[kResChunk],
                                         double (&nrm)[kResChunk]) {
@@ -430,7 +511,7 @@ __device__ __forceinline__ void res_row(const ResArgs& v, int64_t row, const dou
       rt.y = fv.y - acc[q].y - v.sig[q] * xv.y;
       nrm[q] += fma(rt.x, rt.x, rt.y * rt.y);
       if (r) {
-        const int64_t idx = row * v.mp + v.j0 + q;
+        const int64_t idx = int64_t(v.j0 + q) * v.n + row;
         const cplx<R> rc = from_d<R>(rt);
         r[idx] = rc;
         p[idx] = rc;
@@ -517,14 +598,14 @@ __global__ __launch_bounds__(kBlock) void k_res_second_s(ResArgs v) {
 }
 
 // x_j += e_j (FP64 accumulation of the correction)
-template <class R, int MP>
+template <class R>
 __global__ __launch_bounds__(kBlock) void k_accum(BssArgs a, XPtrs xp) {
-  const cplx<R>* __restrict__ ev = static_cast<const cplx<R>*>(a.e);
   const int m = a.st->m;
   for (int j = 0; j < m; ++j) {
+    const cplx<R>* __restrict__ ev = static_cast<const cplx<R>*>(a.e) + int64_t(j) * a.n;
     double2* __restrict__ x = xp.x[j];
     for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < a.n; i += int64_t(gridDim.x) * kBlock) {
-      const double2 d = to_d(ev[i * MP + j]);
+      const double2 d = to_d(ev[i]);
       double2 v = x[i];
       v.x += d.x;
       v.y += d.y;
@@ -540,14 +621,6 @@ int grid_for(int64_t items, int per_pass) {
   return int((g + kXcds - 1) / kXcds * kXcds);
 }
 
-#define MSC_MP_SWITCH(MPV, CALL)                         \
-  switch (MPV) {                                         \
-    case 4: { constexpr int MPP = 4; CALL; } break;      \
-    case 8: { constexpr int MPP = 8; CALL; } break;      \
-    case 16: { constexpr int MPP = 16; CALL; } break;    \
-    default: return hipErrorInvalidValue;                \
-  }
-
 #define MSC_L_SWITCH(LANES, CALL)                        \
   switch (LANES) {                                       \
     case 4: { constexpr int LL = 4; CALL; } break;       \
@@ -557,27 +630,34 @@ int grid_for(int64_t items, int per_pass) {
     default: return hipErrorInvalidValue;                \
   }
 
+template <class R, int ST, int L>
+void launch_halves(const BssArgs& a, int64_t items, int step, hipStream_t s) {
+  // at least one workgroup per XCD and group
+  const int groups = (a.m + group_max<ST>() - 1) / group_max<ST>();
+  const int grid = std::max(kXcds * groups, std::min(half_grid<ST>(), grid_for(items * groups, step)));
+  if (a.kind == MSC_A_MHM) {
+    ik1<R, ST, L, true><<<grid, kBlock, 0, s>>>(a);
+    ik2<R, ST, L, true><<<grid, kBlock, 0, s>>>(a);
+  } else if constexpr (ST == kCsr || ST == kSell) {  // links are M's
+    ik1<R, ST, L, false><<<grid, kBlock, 0, s>>>(a);
+    ik2<R, ST, L, false><<<grid, kBlock, 0, s>>>(a);
+  }
+}
+
 template <class R>
 hipError_t bss_iteration_impl(const BssArgs& a, hipStream_t s) {
-  const int g1 = grid_for(a.n, kBlock / a.mp);
-  const int g3 = grid_for(a.n * a.mp, kBlock);
-  if (a.sell) {
-    const int gs = grid_for(a.nslices, kBlock / kSlice);
-    if (a.kind == MSC_A_MHM) {
-      MSC_MP_SWITCH(a.mp, (ik1s<R, MPP, true><<<gs, kBlock, 0, s>>>(a)));
-      MSC_MP_SWITCH(a.mp, (ik2s<R, MPP, true><<<gs, kBlock, 0, s>>>(a)));
-    } else {
-      MSC_MP_SWITCH(a.mp, (ik1s<R, MPP, false><<<gs, kBlock, 0, s>>>(a)));
-      MSC_MP_SWITCH(a.mp, (ik2s<R, MPP, false><<<gs, kBlock, 0, s>>>(a)));
-    }
-  } else if (a.kind == MSC_A_MHM) {
-    MSC_MP_SWITCH(a.mp, (ik1<R, MPP, true><<<g1, kBlock, 0, s>>>(a)));
-    MSC_MP_SWITCH(a.mp, (ik2<R, MPP, true><<<g1, kBlock, 0, s>>>(a)));
+  const int gw = kBlock / kWave;
+  const int64_t blocks = (a.w64.vol + kWave - 1) / kWave;
+  if (a.links == 2) {
+    launch_halves<R, kLinks2, 1>(a, blocks, gw, s);
+  } else if (a.links == 3) {
+    launch_halves<R, kLinks3, 1>(a, blocks, gw, s);
+  } else if (a.sell) {
+    launch_halves<R, kSell, 1>(a, a.nslices, gw, s);
   } else {
-    MSC_MP_SWITCH(a.mp, (ik1<R, MPP, false><<<g1, kBlock, 0, s>>>(a)));
-    MSC_MP_SWITCH(a.mp, (ik2<R, MPP, false><<<g1, kBlock, 0, s>>>(a)));
+    MSC_L_SWITCH(a.lanes, (launch_halves<R, kCsr, LL>(a, a.n, kBlock / LL, s)));
   }
-  MSC_MP_SWITCH(a.mp, (ik3<R, MPP><<<g3, kBlock, 0, s>>>(a)));
+  ik3<R><<<grid_for(a.n, kBlock), kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -610,11 +690,10 @@ hipError_t launch_residual(int prec, int lanes, const ResArgs& v, hipStream_t s)
 
 hipError_t launch_accum(int prec, const BssArgs& a, const XPtrs& xp, hipStream_t s) {
   const int g = grid_for(a.n, kBlock);
-  if (prec == MSC_PREC_MIXED) {
-    MSC_MP_SWITCH(a.mp, (k_accum<float, MPP><<<g, kBlock, 0, s>>>(a, xp)));
-  } else {
-    MSC_MP_SWITCH(a.mp, (k_accum<double, MPP><<<g, kBlock, 0, s>>>(a, xp)));
-  }
+  if (prec == MSC_PREC_MIXED)
+    k_accum<float><<<g, kBlock, 0, s>>>(a, xp);
+  else
+    k_accum<double><<<g, kBlock, 0, s>>>(a, xp);
   return hipGetLastError();
 }
 

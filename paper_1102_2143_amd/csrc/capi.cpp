@@ -694,16 +694,13 @@ void free_bss(BssWorkspace& w) {
   w = BssWorkspace{};
 }
 
-msc_status ensure_bss(msc_op op, int prec, int mp, hipStream_t s) {
+msc_status ensure_bss(msc_op op, int prec, int mp) {
   BssWorkspace& w = op->bws;
   const size_t n = size_t(op->n);
-  if (w.st && w.prec == prec && w.mp == mp && w.n == n) return MSC_OK;
+  if (w.st && w.prec == prec && w.mp >= mp && w.n == n) return MSC_OK;
   free_bss(w);
   const size_t bytes = (prec == MSC_PREC_MIXED ? sizeof(float2) : sizeof(double2)) * n * mp;
-  for (void** q : {&w.p, &w.t, &w.r, &w.e}) {
-    HIP_TRY(hipMalloc(q, bytes));
-    HIP_TRY(hipMemsetAsync(*q, 0, bytes, s));
-  }
+  for (void** q : {&w.p, &w.t, &w.r, &w.e}) HIP_TRY(hipMalloc(q, bytes));
   HIP_TRY(dalloc(&w.st, 1));
   HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&w.h_halt), 2 * sizeof(int),
                         hipHostMallocMapped | hipHostMallocCoherent));
@@ -716,9 +713,9 @@ msc_status ensure_bss(msc_op op, int prec, int mp, hipStream_t s) {
   return MSC_OK;
 }
 
-// FP64 residual norms (and, when write_vectors, the interleaved r = p = residual, e = 0)
+// FP64 residual norms (and, when write_vectors, the batch's r = p = residual, e = 0)
 // of systems j in [0, m): r_j = f_j - (A + sig_j) x_j.  res2 receives |r_j|^2.
-msc_status batch_residual(msc_op op, int prec, int lanes, int m, int mp, const double* sig,
+msc_status batch_residual(msc_op op, int prec, int lanes, int m, const double* sig,
                           const double2* const* f, double2* const* x, bool write_vectors,
                           std::vector<double>& res2, hipStream_t s, double* bytes,
                           const msc_params& prm) {
@@ -738,7 +735,6 @@ msc_status batch_residual(msc_op op, int prec, int lanes, int m, int mp, const d
     }
     v.n = op->n;
     v.kc = std::min(kResChunk, m - q0);
-    v.mp = mp;
     v.j0 = q0;
     for (int q = 0; q < v.kc; ++q) {
       v.x[q] = x[q0 + q];
@@ -786,17 +782,17 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
     set_error("batched CG: 1 <= m <= %d systems", kBssMax);
     return MSC_EINVAL;
   }
-  const int mp = m <= 4 ? 4 : (m <= 8 ? 8 : 16);
   msc_status rc = ensure_scratch(op, s);
   if (rc != MSC_OK) return rc;
   rc = ensure_workspace(op, op->ws.prec >= 0 ? op->ws.prec : prec, std::max<int>(1, int(op->sigma.size())));
   if (rc != MSC_OK) return rc;
-  rc = ensure_bss(op, prec, mp, s);
+  rc = ensure_bss(op, prec, m);
   if (rc != MSC_OK) return rc;
   const int lanes = choose_lanes(op, prm);
   BssArgs a{};
   a.kind = op->kind;
-  a.mp = mp;
+  a.m = m;
+  a.lanes = lanes;
   a.n = op->n;
   a.m64 = Csr<double2>{op->rowptr, op->col, op->val64};
   a.m32 = Csr<float2>{op->rowptr, op->col, op->val32};
@@ -804,9 +800,14 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
     a.mh64 = Csr<double2>{op->rowptr_h, op->col_h, op->val64_h};
     a.mh32 = Csr<float2>{op->rowptr_h, op->col_h, op->val32_h};
   }
-  // the SpMVs read the sliced ELLPACK copies where they exist (as the multishift does),
-  // up to 8 systems (16 gathered FP64 values per entry exceed the register budget)
-  a.sell = op->sell && prm.format != MSC_FORMAT_CSR && mp <= 8 ? 1 : 0;
+  // the operator halves read the links or the sliced ELLPACK copies where they exist, as
+  // the multishift does
+  a.sell = op->sell && prm.format != MSC_FORMAT_CSR ? 1 : 0;
+  if (op->stencil && (prm.format == MSC_FORMAT_AUTO || prm.format == MSC_FORMAT_STENCIL)) {
+    a.links = op->two_rows ? 2 : 3;
+    a.w64 = op->two_rows ? op->wc64 : op->w64;
+    a.w32 = op->two_rows ? op->wc32 : op->w32;
+  }
   if (a.sell) {
     const bool narrow = prm.format != MSC_FORMAT_SELL32;
     const SellStore &sm = op->sell_m, &sh = op->sell_mh;
@@ -830,18 +831,18 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
   for (int j = 0; j < m; ++j) xp.x[j] = x[j];
 
   const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
-  const double mat = double(op->nnz) * (w + index_bytes(a.sell, a.s64)) +
-                     double(op->nnz_h) * (w + index_bytes(a.sell, a.sh64)) +
-                     4.0 * (op->n + 1) * (op->kind == MSC_A_MHM ? 2.0 : 1.0);
+  const double mat = a.links ? 2.0 * 12.0 * a.links * w * double(op->w64.vol)
+                             : double(op->nnz) * (w + index_bytes(a.sell, a.s64)) +
+                                   double(op->nnz_h) * (w + index_bytes(a.sell, a.sh64)) +
+                                   4.0 * (op->n + 1) * (op->kind == MSC_A_MHM ? 2.0 : 1.0);
   const int max_cycles = 12;
   std::vector<double> res2;
   for (int cycle = 0;; ++cycle) {
-    rc = batch_residual(op, prec, lanes, m, mp, sig, f, x, true, res2, s, bytes, prm);
+    rc = batch_residual(op, prec, lanes, m, sig, f, x, true, res2, s, bytes, prm);
     if (rc != MSC_OK) return rc;
     bool all_done = true;
     BssState h{};
     h.m = m;
-    h.mp = mp;
     h.max_iter = prm.refine_max_iter;
     for (int j = 0; j < kBssMax; ++j) h.R[j] = 1.0;
     for (int j = 0; j < m; ++j) {
@@ -853,7 +854,10 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
       h.active[j] = (done || !std::isfinite(rn)) ? 0 : 1;
       const double tgt = std::max(delta * rn, kRefineTarget * tol_abs[j]);
       h.target2[j] = tgt * tgt;
-      if (h.active[j]) all_done = false;
+      if (h.active[j]) {
+        all_done = false;
+        h.list[0][h.nlist[0]++] = j;
+      }
     }
     res_abs.assign(m, 0.0);
     for (int j = 0; j < m; ++j) res_abs[j] = std::sqrt(res2[j]);
@@ -869,6 +873,7 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
     while (!done) {
       const int cg = std::min(G, 2 << std::min(chunk, 20));
       for (int g = 0; g < cg; ++g) {
+        a.par = launched & 1;
         HIP_TRY(launch_bss_iteration(prec, a, s));
         ++launched;
       }
@@ -885,10 +890,13 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
     HIP_TRY(launch_accum(prec, a, xp, s));
     HIP_TRY(hipMemcpyAsync(&h, op->bws.st, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    for (int j = 0; j < m; ++j)
+    int64_t iters_all = 0;
+    for (int j = 0; j < m; ++j) {
       if (h.bad[j]) *breakdown = true;
+      iters_all += h.iters[j];
+    }
     *inner_total += h.iter;
-    *bytes += double(h.iter) * (mat + double(op->n) * mp * w * 11.0) +
+    *bytes += double(h.iter) * mat + double(iters_all) * double(op->n) * w * 11.0 +
               double(op->n) * m * (16.0 * 2.0 + w);
     if (*breakdown) break;
   }

@@ -216,7 +216,7 @@ struct Workspace {
 
 struct BssState;
 
-// Buffers of the batched single-shift CG (interleaved n x mp vectors).
+// Buffers of the batched single-shift CG (mp vectors of n each).
 struct BssWorkspace {
   size_t n = 0;
   int mp = 0;
@@ -505,12 +505,16 @@ struct BssState {
   int upd[kBssMax];         // system j was updated this iteration (e_j += a_j p_j)
   int iters[kBssMax];
   int bad[kBssMax];         // breakdown of system j
-  int m, mp, iter, max_iter, halt, nact, k3_enable, pad_;
+  int list[2][kBssMax];     // systems of an iteration of parity 0 / 1
+  int nlist[2];
+  int m, iter, max_iter, halt, k3_enable, pad_;
 };
 
 struct BssArgs {
   int kind;
-  int mp;
+  int m;                                // systems
+  int lanes;                            // CSR: lanes per row
+  int par;                              // parity of the iteration: it takes st->list[par]
   int64_t n;
   Csr<double2> m64, mh64;
   Csr<float2> m32, mh32;
@@ -518,7 +522,10 @@ struct BssArgs {
   int64_t nslices;
   Sell<double2> s64, sh64;
   Sell<float2> s32, sh32;
-  void* p; void* t; void* r; void* e;   // interleaved n x mp vectors of the working precision
+  int links;                            // rows per link read instead (2 or 3), 0: none
+  Stencil<double2> w64;
+  Stencil<float2> w32;
+  void* p; void* t; void* r; void* e;   // m vectors of n, working precision, one after the other
   BssState* st;
   double* partial;                      // kMaxGrid * kBssMax
   unsigned* tickets;
@@ -530,8 +537,8 @@ struct XPtrs {
 };
 
 // FP64 residual r_q = f_q - (A + sig_q) x_q for q < kc (<= kResChunk) systems; writes
-// |r_q|^2 to out[q] and, when r != nullptr, r (cast) into column j0 + q of the
-// interleaved r and p and zero into e.
+// |r_q|^2 to out[q] and, when r != nullptr, r (cast) into vector j0 + q of r and p and
+// zero into that of e.
 struct ResArgs {
   Csr<double2> m1;          // M (MHM) -- first half
   Csr<double2> m2;          // M^H (MHM) or A (HERM)
@@ -541,7 +548,7 @@ struct ResArgs {
   int mhm;
   int64_t n;
   int kc;
-  int mp, j0;
+  int j0;
   const double2* x[kResChunk];
   const double2* f[kResChunk];
   double sig[kResChunk];

@@ -160,4 +160,74 @@ __device__ __forceinline__ void stencil_site(const Stencil<cplx<R>>& op, uint32_
                                static_cast<TCarry<R, LR>*>(nullptr));
 }
 
+// M (sign 1) or M^H (sign -1) times several vectors at one site: out[q][c] of xs[q], q <
+// cnt <= G.  A direction's two links are read and completed once for all of them.
+template <class R, int LR, int G>
+__device__ __forceinline__ void stencil_site_group(const Stencil<cplx<R>>& op, uint32_t s, int sign,
+                                                   const cplx<R>* const (&xs)[G], int cnt,
+                                                   cplx<R> (&out)[G][3]) {
+  constexpr int K = 3 * LR;
+  const uint32_t vol = uint32_t(op.vol);
+  uint32_t rem = s, par = 0;
+  cplx<R> h[G][3];
+#pragma unroll
+  for (int q = 0; q < G; ++q)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) h[q][c] = czero<R>();
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) {
+    const uint32_t L = uint32_t(op.L[mu]), st = uint32_t(op.stride[mu]);
+    const uint32_t qt = rem / L, xm = rem - qt * L;
+    rem = qt;
+    const R te = (par & 1u) ? R(-2) : R(2);  // 2 eta_mu
+    par += xm;
+    const uint32_t fwd = xm == L - 1 ? s - (L - 1) * st : s + st;
+    const uint32_t bwd = xm == 0 ? s + (L - 1) * st : s - st;
+    const cplx<R>* __restrict__ wm = op.w + int64_t(mu) * K * vol;
+    cplx<R> U[9], B[9];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      U[k] = wm[int64_t(k) * vol + s];
+      B[k] = wm[int64_t(k) * vol + bwd];
+    }
+    if constexpr (LR == 2) {
+      third_row<R>(U, te);
+      third_row<R>(B, te);
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      if (q < cnt) {
+        cplx<R> gf[3], gb[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          gf[j] = xs[q][3 * int64_t(fwd) + j];
+          gb[j] = xs[q][3 * int64_t(bwd) + j];
+          gb[j].x = -gb[j].x;
+          gb[j].y = -gb[j].y;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            cfma<R>(h[q][c], U[3 * c + j], gf[j]);
+            cfma_conj<R>(h[q][c], B[3 * j + c], gb[j]);
+          }
+        }
+      }
+    }
+  }
+  const R m = R(op.mass);
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    if (q < cnt) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const cplx<R> own = xs[q][3 * int64_t(s) + c];
+        out[q][c].x = fma(m, own.x, sign > 0 ? h[q][c].x : -h[q][c].x);
+        out[q][c].y = fma(m, own.y, sign > 0 ? h[q][c].y : -h[q][c].y);
+      }
+    }
+  }
+}
+
 }  // namespace msc
