@@ -2618,9 +2618,10 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
   const int prec = prm.prec;
   const size_t el = prec == MSC_PREC_MIXED ? sizeof(float) : sizeof(double);
   auto align = [](size_t b) { return (b + 255) / 256 * 256; };
-  const size_t vec = align(el * size_t(n));
-  const size_t need = 3 * vec + align(el * size_t(n) * size_t(std::max(ns - 1, 1))) +
-                      align(sizeof(RealState)) + align(sizeof(double) * ns);
+  const size_t vec = align(sizeof(double) * size_t(n));
+  const size_t need = align(el * size_t(n) * kRealRing) + 4 * vec +
+                      align(el * size_t(n) * size_t(ns)) + align(sizeof(RealState)) +
+                      align(sizeof(double) * ns);
   if (op->rws_bytes < need) {
     if (op->rws) (void)hipFree(op->rws);
     op->rws = nullptr;
@@ -2628,28 +2629,36 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
     HIP_TRY(hipMalloc(&op->rws, need));
     op->rws_bytes = need;
   }
+  if (!op->r_halt) {
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&op->r_halt), 2 * sizeof(int),
+                          hipHostMallocMapped | hipHostMallocCoherent));
+    HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&op->d_r_halt), op->r_halt, 0));
+  }
+  for (auto& e : op->r_ev)
+    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   unsigned char* cur = static_cast<unsigned char*>(op->rws);
   RealArgs a{};
   a.n = n;
   a.nslices = sm.nslices;
-  a.ns = ns;
+  a.steps = std::min(std::max(int(prm.update_steps), 1), kMaxSteps);
   a.m64 = SellReal<double>{sm.cptr, sm.col, sm.col16, sm.cbase, sm.wp, op->rval64, op->rdiag64};
   a.m32 = SellReal<float>{sm.cptr, sm.col, sm.col16, sm.cbase, sm.wp, op->rval32, op->rdiag32};
   a.b = d_b;
   a.x = d_x;
   a.r = cur;
-  cur += vec;
-  a.p = cur;
-  cur += vec;
-  a.t = cur;
-  cur += vec;
+  cur += align(el * size_t(n) * kRealRing);
+  for (double** q : {&a.w[0], &a.w[1], &a.s[0], &a.s[1]}) {
+    *q = reinterpret_cast<double*>(cur);
+    cur += vec;
+  }
   a.pk = cur;
-  cur += align(el * size_t(n) * size_t(std::max(ns - 1, 1)));
+  cur += align(el * size_t(n) * size_t(ns));
   a.st = reinterpret_cast<RealState*>(cur);
   cur += align(sizeof(RealState));
   double* d_res2 = reinterpret_cast<double*>(cur);
   a.partial = op->scratch.partial;
   a.tickets = op->scratch.tickets + 13 * kTicketSite;
+  a.hflag = op->d_r_halt;
 
   std::vector<int> order(ns);
   std::iota(order.begin(), order.end(), 0);
@@ -2657,42 +2666,52 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
                    [&](int i, int j) { return op->sigma[i] < op->sigma[j]; });
   RealState h{};
   h.sigma0 = op->sigma[order[0]];
-  h.eps2 = prm.tol * prm.tol;
-  h.a_prev = 1.0;
-  h.b = 0.0;
-  h.max_iter = prm.max_iter;
+  h.tol2 = prm.tol * prm.tol;
+  h.max_iter = std::max(0, int(prm.max_iter));
   h.ns = ns;
   h.freeze = prm.freeze ? 1 : 0;
-  h.upd_launch = -1;
+  h.rot[0].fresh = 1;
   for (int j = 0; j < ns; ++j) {
     h.s[j] = op->sigma[order[j]] - h.sigma0;
-    h.zeta[j] = h.zeta_prev[j] = 1.0;
-    h.active[j] = 1;
+    h.rot[0].zeta[j] = h.rot[0].zeta_prev[j] = 1.0;
+    h.rot[0].active[j] = 1;
     h.freeze_iter[j] = -1;
     h.orig[j] = order[j];
   }
   HIP_TRY(hipMemcpyAsync(a.st, &h, sizeof h, hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_real_init(prec, a, s));
+  HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve writes the halt word now
+  __atomic_store_n(op->r_halt, 0, __ATOMIC_RELEASE);
+  HIP_TRY(launch_real_start(prec, a, s));
+  // chunks of poll_every iterations; the halt word of one chunk is read once the next one
+  // is queued
   const int G = std::max(1, prm.poll_every);
   int launched = 0;
-  bool done = prm.max_iter <= 0;
-  while (!done) {
+  bool done = false;
+  for (int chunk = 0; !done; ++chunk) {
     for (int g = 0; g < G; ++g) {
-      HIP_TRY(launch_real_iteration(prec, a, launched, s));
+      a.par = launched & 1;
+      HIP_TRY(launch_real_iteration(prec, a, s));
       ++launched;
     }
-    int halt = 0;
-    HIP_TRY(hipMemcpyAsync(&halt, &a.st->halt, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (halt || launched >= prm.max_iter + G) done = true;
+    const int slot = chunk & 1;
+    HIP_TRY(hipEventRecord(op->r_ev[slot], s));
+    if (chunk >= 1) {
+      HIP_TRY(hipEventSynchronize(op->r_ev[slot ^ 1]));
+      if (__atomic_load_n(op->r_halt, __ATOMIC_ACQUIRE)) done = true;
+    }
+    if (launched >= h.max_iter + 2 * G) done = true;
   }
   HIP_TRY(hipMemcpyAsync(&h, a.st, sizeof h, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   std::vector<double> rel(ns, 0.0);
   const double bn = std::sqrt(h.bnorm2);
   if (prm.verify && h.status == 0 && bn > 0.0) {
-    for (int k = 0; k < ns; ++k)
-      HIP_TRY(launch_real_verify(a, d_x + int64_t(k) * n, op->sigma[k], d_res2 + k, s));
+    for (int k0 = 0; k0 < ns; k0 += kRealCheck) {
+      RealSigma sg{};
+      const int cnt = std::min(kRealCheck, ns - k0);
+      for (int q = 0; q < cnt; ++q) sg.v[q] = op->sigma[k0 + q];
+      HIP_TRY(launch_real_verify(a, d_x + int64_t(k0) * n, sg, cnt, d_res2 + k0, s));
+    }
     std::vector<double> r2(ns);
     HIP_TRY(hipMemcpyAsync(r2.data(), d_res2, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -2706,18 +2725,12 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
     info->n_refined = 0;
     info->iters_fp64 = prec == MSC_PREC_FP64 ? h.iter : 0;
     const double w = double(el), nn = double(n);
-    // per iteration: matrix (value + index per stored entry, diagonal), p gather and t
-    // write (RK1); r r/w, t, p (RK2); r, p r/w, x_0 r/w (RK3); per live shift x_k r/w
-    // (FP64) and p_k r/w
+    // per iteration: matrix (value + index per stored entry), r, w and s in and out; per
+    // application: x_k r/w (FP64) and p_k r/w of each listed system, the kept residuals
     const double ib = sm.col16 ? 2.0 : 4.0;
     const double mat = double(op->nnz) * (w + ib) + 4.0 * (nn + 1);
-    double upd = 0.0;
-    for (int j = 1; j < ns; ++j) {
-      const int fi = h.freeze_iter[j] < 0 ? h.iter : h.freeze_iter[j];
-      upd += double(fi) * nn * (16.0 + 2 * w);
-    }
-    info->alg_bytes =
-        double(h.iter) * (mat + nn * (2 * w) + nn * (4 * w) + nn * (3 * w + 16.0)) + upd;
+    info->alg_bytes = double(h.iter) * (mat + nn * (2 * w + 32.0)) +
+                      double(h.n_upd) * nn * (16.0 + 2 * w) + double(h.n_kept) * nn * w;
     if (info->true_rel_res)
       for (int k = 0; k < ns; ++k) info->true_rel_res[k] = rel[k];
     if (info->freeze_iter)
@@ -2812,6 +2825,9 @@ void msc_op_destroy(msc_op op) {
   if (op->bcg) (void)hipFree(op->bcg);
   if (op->osb) (void)hipFree(op->osb);
   if (op->rws) (void)hipFree(op->rws);
+  if (op->r_halt) (void)hipHostFree(op->r_halt);
+  for (auto& e : op->r_ev)
+    if (e) (void)hipEventDestroy(e);
   dfree(op->rval64);
   dfree(op->rval32);
   dfree(op->rdiag64);

@@ -262,6 +262,9 @@ struct msc_op_s {
   int real_state = 0;            // 0 not checked, 1 real (copies built), -1 not real
   void* rws = nullptr;           // real solve buffers
   size_t rws_bytes = 0;
+  int* r_halt = nullptr;         // host-coherent halt word of the real solve
+  int* d_r_halt = nullptr;       // its device address
+  hipEvent_t r_ev[2] = {nullptr, nullptr};
   double2* yadj = nullptr;       // adjoint solutions, ns * n complex128
   size_t yadj_count = 0;
   double* adj_small = nullptr;   // 256 doubles: Gram sums and shift factors
@@ -454,31 +457,53 @@ template <class T> struct SellReal {
   const T* val = nullptr;           // real parts of the sliced copy's values
   const T* diag = nullptr;
 };
+constexpr int kRealGrid = 1024;          // most workgroups of its kernels
+constexpr int kRealRing = kMaxSteps + 1;  // residuals kept: r_n in slot n % kRealRing
+constexpr int kRealCheck = 4;            // systems verified by one launch
+struct RealSigma {
+  double v[kRealCheck];
+};
+// State at the start of iteration n's kernel (indexed by n's parity; the kernel's
+// workgroup 0 writes the other one).  Shifts sorted ascending, j = 0 driving.
+struct RealRot {
+  double g, a;             // |r_{n-1}|^2 and a_{n-1}
+  int iter, halt;          // n; 1: nothing left to do
+  int m, fresh;            // steps composed so far; 1: x and p never written
+  double zeta[kMaxShifts], zeta_prev[kMaxShifts];
+  // p_j now is cp[0] p_j + sum_{i<m} cp[i+1] r_i and x_j gained the like with cx, r_i the
+  // residuals of the composed steps
+  double cx[kMaxSteps + 1][kMaxShifts], cp[kMaxSteps + 1][kMaxShifts];
+  int active[kMaxShifts], took[kMaxShifts];  // took: part of a composed step
+};
 struct RealState {
-  double a, a_prev, b, b_new, P, R, sigma0, bnorm2, eps2;
-  int iter, max_iter, ns, halt, status, rotate, upd_launch, freeze;
-  double s[kMaxShifts], zeta[kMaxShifts], zeta_prev[kMaxShifts], zeta_new[kMaxShifts];
-  double ak[kMaxShifts], bk[kMaxShifts];
-  int active[kMaxShifts], active_next[kMaxShifts], freeze_iter[kMaxShifts], orig[kMaxShifts];
+  double sigma0, tol2, bnorm2, R, eps2;
+  int iter, max_iter, ns, status, freeze;
+  int n_upd, n_kept;       // x_j/p_j updates and residuals read by applications
+  double s[kMaxShifts];
+  int freeze_iter[kMaxShifts], orig[kMaxShifts];
+  RealRot rot[2];
 };
 struct RealArgs {
   int64_t n, nslices;
-  int ns;
+  int par, steps;          // parity of the iteration; steps folded into one application
   SellReal<double> m64;
   SellReal<float> m32;
   const double* b;
   double* x;               // caller's x, shift-major, caller order (FP64 always)
-  void *r, *p, *t, *pk;    // double or float by precision
+  void* r;                 // kRealRing residuals; double or float by precision, as pk
+  double *w[2], *s[2];
+  void* pk;                // ns directions, sorted order
   RealState* st;
   double* partial;
   unsigned* tickets;       // one ticket site
+  int* hflag;              // host-coherent word: 1 once halted
 };
 hipError_t launch_real_extract(const double2* v64, double* r64, float* r32, int64_t count,
                                unsigned long long* imax, hipStream_t s);
-hipError_t launch_real_init(int prec, const RealArgs& a, hipStream_t s);
-hipError_t launch_real_iteration(int prec, const RealArgs& a, int launch, hipStream_t s);
-hipError_t launch_real_verify(const RealArgs& a, const double* x, double sigma, double* out,
-                              hipStream_t s);
+hipError_t launch_real_start(int prec, const RealArgs& a, hipStream_t s);
+hipError_t launch_real_iteration(int prec, const RealArgs& a, hipStream_t s);
+hipError_t launch_real_verify(const RealArgs& a, const double* x, const RealSigma& sg, int cnt,
+                              double* out, hipStream_t s);
 
 // osborn.hip -- a right-hand side per shift through common-residual initial guesses
 constexpr int kOsbSlices = 256;  // workgroups per vector of the norm reduction

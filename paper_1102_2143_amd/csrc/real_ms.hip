@@ -3,17 +3,30 @@
 // shifted recurrences as the complex solve (Section 2, Algorithm 1 with the re-derived
 // constants), on real vectors and a real copy of the sliced ELLPACK matrix, so every
 // matrix value and vector element moves half the bytes of the complex path.  T = double
-// (FP64) or float (single-precision storage and arithmetic with FP64 reductions and FP64
-// shift scalars, the paper's "single" column).
+// (FP64) or float (the matrix, the residuals and the shifted directions in single
+// precision, products and scalars in FP64: the paper's "single" column).
 //
-// One iteration is three kernels; each reduction is finished by the last workgroup to
-// arrive, which also derives the scalars:
-//   RK1  t = A p (sliced ELLPACK, one row per lane), P = p.t + sigma0 p.p
-//        -> a = R / P; per shift zeta', a_k
-//   RK2  r <- r - a (t + sigma0 p), R' = r.r
-//        -> b' = R'/R, b_k = b' (zeta'/zeta)^2, freezing, halting
-//   RK3  x_0 += a p; x_k += a_k p_k, p_k <- zeta'_k r + b_k p_k (live shifts); p <- r + b' p
+// One iteration is one kernel.  A is given, so with w_n = A r_n the iteration needs a single
+// reduction point: g_n = r_n.r_n and d_n = r_n.(A + sigma0) r_n give
+//   b_n = g_n / g_{n-1},  a_n = g_n / (d_n - b_n g_n / a_{n-1}),
+//   s_n = w_n + sigma0 r_n + b_n s_{n-1},  r_{n+1} = r_n - a_n s_n,
+// and w_{n+1} = A r_{n+1} follows in the same kernel, r_{n+1} being formed from r, w and s
+// at every gathered column as its owner forms it (Chronopoulos and Gear's arrangement of
+// CG).  Every workgroup sums the previous kernel's partials itself, in one order.  The
+// shifted vectors take
+//   p_k <- zeta_k r_n + b_k p_k,  x_k += a_k p_k
+// (k = 0, the driving system, with zeta = 1); nothing else reads them, so up to eight steps
+// are composed against the first one's p_k and the residuals of the steps, which stay in a
+// ring, and applied in one pass.
+//
+// Bound by memory: a row moves its matrix entries (10 bytes each), r, w and s in and out
+// (w and s in FP64 always: recurred in single precision, s would add an error of its own),
+// and an eighth of 32 bytes per live shift.  1000 x 1000 points, 15 shifts: 63.2 us an
+// iteration in FP64 and 50.4 in single precision with three kernels (t = A p; r; the
+// shifts' step, unfolded), 29.3 and 26.2 here; 60 x 50 points 24.6 and 10.3 us.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "dev_common.h"
 #include "msc_internal.h"
@@ -97,225 +110,389 @@ __device__ double r_sum(const double* partial, int count, int stride, int k) {
   return block_sum<kBlock>(s);
 }
 
-// Store this workgroup's partial; true in the last workgroup, with the grid sum in *tot.
-__device__ bool r_reduce(const RealArgs& a, double v, double* tot) {
-  const double bs = block_sum<kBlock>(v);
-  if (threadIdx.x == 0) store_agent(&a.partial[blockIdx.x], bs);
-  if (!arrive_last(a.tickets)) return false;
-  __shared__ double sh;
-  const double t = r_sum(a.partial, gridDim.x, 1, 0);
-  if (threadIdx.x == 0) sh = t;
-  __syncthreads();
-  *tot = sh;
-  return true;
-}
-
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_r_init(RealArgs a) {
-  RealState* st = a.st;
-  T* __restrict__ r = static_cast<T*>(a.r);
-  T* __restrict__ p = static_cast<T*>(a.p);
-  T* __restrict__ pk = static_cast<T*>(a.pk);
-  int64_t beg, end;
-  block_range(a.n, kBlock, beg, end);
-  double acc = 0.0;
-  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
-    const double bv = a.b[i];
-    const T bt = T(bv);
-    r[i] = bt;
-    p[i] = bt;
-    for (int j = 1; j < a.ns; ++j) pk[int64_t(j - 1) * a.n + i] = bt;
-    for (int j = 0; j < a.ns; ++j) a.x[int64_t(st->orig[j]) * a.n + i] = 0.0;
-    acc = fma(bv, bv, acc);
+// One row of slice `sl` times the vector val(column), off-diagonal part plus diagonal, in FP64.
+template <class T, class F>
+__device__ __forceinline__ double r_row_f(const SellReal<T>& m, F val, T own, int64_t sl, int lane,
+                                     int64_t row) {
+  int32_t c, c1;
+  if (m.wp > 0) {
+    c = int32_t(sl) * m.wp;
+    c1 = c + m.wp;
+  } else {
+    c = ld_uniform(m.cptr, sl);
+    c1 = ld_uniform(m.cptr, sl + 1);
   }
-  double tot;
-  if (!r_reduce(a, acc, &tot)) return;
-  if (threadIdx.x == 0) {
-    st->bnorm2 = tot;
-    st->R = tot;
-    st->eps2 = st->eps2 * tot;  // the host stored tol^2
-    if (!(tot > 0.0) || !isfinite(tot)) {
-      st->halt = 1;
-      st->status = isfinite(tot) ? 0 : 1;
+  double acc = double(m.diag[row]) * double(own);
+  constexpr int KP = 2;
+  for (; c < c1; c += KP) {
+    int2 cc[KP];
+    T v0[KP], v1[KP], g0[KP], g1[KP];
+#pragma unroll
+    for (int u = 0; u < KP; ++u) {
+      if (c + u < c1) {
+        const int64_t q = int64_t(c + u) * kSlice + lane;
+        cc[u] = r_cols(m, c + u, q);
+        v0[u] = m.val[2 * q];
+        v1[u] = m.val[2 * q + 1];
+      } else {
+        cc[u] = int2{int32_t(row), int32_t(row)};
+        v0[u] = v1[u] = T(0);
+      }
     }
+#pragma unroll
+    for (int u = 0; u < KP; ++u) {
+      g0[u] = val(cc[u].x);
+      g1[u] = val(cc[u].y);
+    }
+#pragma unroll
+    for (int u = 0; u < KP; ++u) acc = fma(double(v1[u]), double(g1[u]), fma(double(v0[u]), double(g0[u]), acc));
+  }
+  return acc;
+}
+
+// Partials of g and d of the kernel of parity par (their reader's parity).
+__device__ __forceinline__ double* r_region(const RealArgs& a, int par, int which) {
+  return a.partial + (2 * par + which) * kMaxGrid;
+}
+
+__device__ __forceinline__ void r_store_partials(const RealArgs& a, int par, double g, double d) {
+  double v[2] = {g, d};
+  block_sum_k<kBlock, 2>(v);
+  if (threadIdx.x == 0) {
+    store_agent(&r_region(a, par, 0)[blockIdx.x], v[0]);
+    store_agent(&r_region(a, par, 1)[blockIdx.x], v[1]);
   }
 }
 
-// ---- RK1: t = A p, P = p.t + sigma0 p.p; a, zeta', a_k --------------------------------
+// r_0 = b in ring slot 0, s = 0, w_0 = A r_0 and the partials of g_0 and d_0.
 template <class T>
-__global__ __launch_bounds__(kBlock) void k_r_k1(RealArgs a) {
-  RealState* st = a.st;
-  if (st->halt) return;
+__global__ __launch_bounds__(kBlock) void k_r_start(RealArgs a) {
   const SellReal<T> m = rmat<T>(a);
-  const T* __restrict__ p = static_cast<const T*>(a.p);
-  T* __restrict__ t = static_cast<T*>(a.t);
-  const double sigma0 = st->sigma0;
+  T* __restrict__ r = static_cast<T*>(a.r);
+  double* __restrict__ w = a.w[0];
+  double* __restrict__ s = a.s[0];
+  const double sigma0 = a.st->sigma0;
   constexpr int SPB = kBlock / kSlice;
   const int lane = threadIdx.x % kSlice;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
   int64_t beg, end;
   block_range(a.nslices, SPB, beg, end);
-  double acc = 0.0;
+  double g = 0.0, d = 0.0;
   for (int64_t sl = beg + wv; sl < end; sl += SPB) {
     const int64_t row = sl * kSlice + lane;
-    const int64_t rr = row < a.n ? row : a.n - 1;
-    const T v = r_row<T>(m, p, sl, lane, rr);
+    const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
+    const T own = T(a.b[rr]);
+    const double v = r_row_f<T>(m, [&](int32_t c) { return T(a.b[c]); }, own, sl, lane, rr);
     if (row < a.n) {
-      t[row] = v;
-      const double pr = double(p[row]);
-      acc += pr * double(v) + sigma0 * pr * pr;
+      r[row] = own;
+      w[row] = v;
+      s[row] = 0.0;
+      const double rd = double(own);
+      g = fma(rd, rd, g);
+      d += rd * v + sigma0 * rd * rd;
     }
   }
-  double P;
-  if (!r_reduce(a, acc, &P)) return;
+  r_store_partials(a, 0, g, d);
+}
+
+// What an iteration's kernel does, shared through LDS.
+struct RealPlan {
+  double a, b;         // a_n, b_n (live only)
+  int live;            // 1: this kernel takes step n
+  int apply;           // 1: the composed steps go into x_k and p_k
+  int m;               // composed steps (the last one step n when live)
+  int fresh;           // 1: first application (x_k and p_k start from zero, unread)
+  int nact;            // systems listed
+  double cx[kMaxSteps + 1][kMaxShifts], cp[kMaxSteps + 1][kMaxShifts];
+  int64_t xo[kMaxShifts], po[kMaxShifts];
+};
+
+// Every workgroup derives a_n, b_n and whether step n runs; the shifts' scalars (wave 0,
+// lane j) are needed by workgroup 0, which writes the next state, and by all where the
+// composed steps are applied.
+__device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
+  RealState* st = a.st;
+  const RealRot& rs = st->rot[a.par];
   const int j = threadIdx.x;
-  // rotate the previous iteration's shift state, then this iteration's constants
-  if (j < a.ns && st->rotate) {
-    if (st->active[j]) {
-      st->zeta_prev[j] = st->zeta[j];
-      st->zeta[j] = st->zeta_new[j];
+  if (j >= kWave) return;
+  const bool head = blockIdx.x == 0;
+  const int n = rs.iter, m0 = rs.m;
+  const double bn2 = n == 0 ? g : st->bnorm2, eps2 = st->tol2 * bn2;
+  const double b = n == 0 ? 0.0 : g / rs.g;
+  const double P = n == 0 ? d : d - b * g / rs.a;
+  const bool done = g <= eps2 || n >= st->max_iter;
+  const bool ok = done ? true : (isfinite(g) && P > 0.0 && isfinite(P));
+  const bool live = !done && ok;
+  const double step = live ? g / P : 0.0;
+  const int m = m0 + (live ? 1 : 0);
+  const bool apply = live ? m >= a.steps : (m0 > 0 || rs.fresh != 0);
+  int listed = 0;
+  if (head || apply) {
+    const bool mine = j < st->ns;
+    double z = 1.0, zp = 1.0, cx[kMaxSteps + 1], cp[kMaxSteps + 1];
+    int act = 0, took = 0;
+#pragma unroll
+    for (int i = 0; i <= kMaxSteps; ++i) cx[i] = cp[i] = 0.0;
+    if (mine) {
+      z = rs.zeta[j];
+      zp = rs.zeta_prev[j];
+      act = rs.active[j];
+      if (m0 > 0) {
+        took = rs.took[j];
+#pragma unroll
+        for (int i = 0; i <= kMaxSteps; ++i) {
+          if (i <= m0) {
+            cx[i] = rs.cx[i][j];
+            cp[i] = rs.cp[i][j];
+          }
+        }
+      } else {
+        cp[0] = 1.0;
+      }
     }
-    st->active[j] = st->active_next[j];
-  }
-  __syncthreads();
-  const bool ok = P > 0.0 && isfinite(P);
-  const double step = ok ? st->R / P : 0.0;
-  if (ok && j < a.ns && j >= 1 && st->active[j]) {
-    const double z = st->zeta[j], zp = st->zeta_prev[j], sj = st->s[j];
-    const double ap = st->a_prev, b = st->b;
-    const double zn = z * zp * ap / (step * b * (zp - z) + zp * ap * (1.0 + sj * step));
-    st->zeta_new[j] = zn;
-    st->ak[j] = step * zn / z;
+    const bool freeze = act && j > 0 && st->freeze && z * z * g <= eps2;
+    if (freeze) act = 0;
+    double zn = z;
+    if (live && act) {
+      // step n of system j: zeta^(n+1), a_j, b_j, composed with the pending ones
+      if (j > 0)
+        zn = n == 0 ? z / (1.0 + st->s[j] * step)
+                    : z * zp * rs.a / (step * b * (zp - z) + zp * rs.a * (1.0 + st->s[j] * step));
+      const double ratio = z / zp, aj = step * zn / z, bj = b * ratio * ratio;
+#pragma unroll
+      for (int i = 0; i <= kMaxSteps; ++i)
+        if (i <= m0) cp[i] *= bj;
+#pragma unroll
+      for (int i = 1; i <= kMaxSteps; ++i)
+        if (i == m) cp[i] = z;
+#pragma unroll
+      for (int i = 0; i <= kMaxSteps; ++i)
+        if (i <= m) cx[i] = fma(aj, cp[i], cx[i]);
+      took = 1;
+    }
+    const bool list = apply && mine && (took || rs.fresh);
+    const uint64_t mask = __ballot(list);
+    if (list) {
+      const int pos = __popcll(mask & ((uint64_t(1) << j) - 1));
+#pragma unroll
+      for (int i = 0; i <= kMaxSteps; ++i) {
+        pl.cx[i][pos] = i <= m ? cx[i] : 0.0;
+        pl.cp[i][pos] = i <= m ? cp[i] : 0.0;
+      }
+      pl.xo[pos] = int64_t(st->orig[j]) * a.n;
+      pl.po[pos] = int64_t(j) * a.n;
+    }
+    listed = __popcll(mask);
+    if (head) {
+      RealRot& nx = st->rot[a.par ^ 1];
+      if (mine) {
+        if (freeze) st->freeze_iter[j] = n;
+        nx.zeta_prev[j] = live && act ? z : zp;
+        nx.zeta[j] = zn;
+        nx.active[j] = act;
+        nx.took[j] = apply ? 0 : took;
+        if (!apply) {
+#pragma unroll
+          for (int i = 0; i <= kMaxSteps; ++i) {
+            nx.cx[i][j] = i <= m ? cx[i] : 0.0;
+            nx.cp[i][j] = i <= m ? cp[i] : 0.0;
+          }
+        }
+      }
+      if (j == 0) {
+        nx.g = g;
+        nx.a = step;
+        nx.iter = live ? n + 1 : n;
+        nx.m = apply ? 0 : m;
+        nx.fresh = apply ? 0 : rs.fresh;
+        nx.halt = live ? 0 : 1;
+        if (n == 0) st->bnorm2 = g;
+        if (apply) {
+          st->n_upd += listed;
+          st->n_kept += m;
+        }
+        if (!live) {
+          st->iter = n;
+          st->R = g;
+          st->eps2 = eps2;
+          st->status = ok ? 0 : 1;
+          store_host_flag(a.hflag, 1);
+        }
+      }
+    }
   }
   if (j == 0) {
-    st->rotate = 0;
-    if (!ok) {
-      st->halt = 1;
-      st->status = 1;
-    } else {
-      st->a = step;
-      st->P = P;
-    }
+    pl.a = step;
+    pl.b = b;
+    pl.live = live ? 1 : 0;
+    pl.apply = apply ? 1 : 0;
+    pl.m = m;
+    pl.fresh = rs.fresh;
+    pl.nact = listed;
   }
 }
 
-// ---- RK2: r <- r - a (t + sigma0 p), R' = r.r; b', b_k, freezing, halting -------------
+// The composed steps of one row: the listed systems' x_k and p_k.
 template <class T>
-__global__ __launch_bounds__(kBlock) void k_r_k2(RealArgs a, int launch) {
-  RealState* st = a.st;
-  if (st->halt) return;
-  T* __restrict__ r = static_cast<T*>(a.r);
-  const T* __restrict__ p = static_cast<const T*>(a.p);
-  const T* __restrict__ t = static_cast<const T*>(a.t);
-  const double step = st->a, sigma0 = st->sigma0;
-  int64_t beg, end;
-  block_range(a.n, kBlock, beg, end);
-  double acc = 0.0;
-  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
-    const double nr = double(r[i]) - step * (double(t[i]) + sigma0 * double(p[i]));
-    const T st_r = T(nr);
-    r[i] = st_r;
-    acc += double(st_r) * double(st_r);
-  }
-  double Rn;
-  if (!r_reduce(a, acc, &Rn)) return;
-  const int j = threadIdx.x;
-  const double bn = Rn / st->R;
-  if (j < a.ns) {
-    int nxt = st->active[j];
-    if (j >= 1 && nxt) {
-      const double ratio = st->zeta_new[j] / st->zeta[j];
-      st->bk[j] = bn * ratio * ratio;
-      if (st->freeze && st->zeta_new[j] * st->zeta_new[j] * Rn <= st->eps2) {
-        nxt = 0;
-        st->freeze_iter[j] = st->iter + 1;
-      }
-    }
-    st->active_next[j] = nxt;
-  }
-  __syncthreads();
-  if (j == 0) {
-    st->b_new = bn;
-    st->a_prev = step;
-    st->b = bn;
-    st->R = Rn;
-    st->iter += 1;
-    st->rotate = 1;
-    st->upd_launch = launch;
-    if (!isfinite(Rn)) {
-      st->halt = 1;
-      st->status = 1;
-    } else if (Rn <= st->eps2 || st->iter >= st->max_iter) {
-      st->halt = 1;
-    }
-  }
-}
-
-// ---- RK3: the step of x_0, of every live shift, and the new direction -----------------
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_r_k3(RealArgs a, int launch) {
-  RealState* st = a.st;
-  if (st->upd_launch != launch) return;
-  __shared__ double ak[kMaxShifts], zn[kMaxShifts], bk[kMaxShifts];
-  __shared__ int64_t xo[kMaxShifts], po[kMaxShifts];
-  __shared__ int nlive;
-  if (threadIdx.x == 0) {
-    int c = 0;
-    for (int j = 1; j < a.ns; ++j) {
-      if (st->active[j]) {
-        ak[c] = st->ak[j];
-        zn[c] = st->zeta_new[j];
-        bk[c] = st->active_next[j] ? st->bk[j] : 0.0;
-        xo[c] = int64_t(st->orig[j]) * a.n;
-        po[c] = int64_t(j - 1) * a.n;
-        ++c;
-      }
-    }
-    nlive = c;
-  }
-  __syncthreads();
-  const double step = st->a, bn = st->b_new;
-  const int live = nlive;
-  T* __restrict__ p = static_cast<T*>(a.p);
+__device__ __forceinline__ void r_apply_row(const RealArgs& a, const RealPlan& pl, int n, int64_t i) {
+  const T* __restrict__ ring = static_cast<const T*>(a.r);
   T* __restrict__ pk = static_cast<T*>(a.pk);
-  const T* __restrict__ r = static_cast<const T*>(a.r);
-  double* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
-  int64_t beg, end;
-  block_range(a.n, kBlock, beg, end);
-  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
-    const double rv = double(r[i]), pv = double(p[i]);
-    x0[i] = fma(step, pv, x0[i]);
-    for (int c = 0; c < live; ++c) {
-      const double pj = double(pk[po[c] + i]);
-      a.x[xo[c] + i] = fma(ak[c], pj, a.x[xo[c] + i]);
-      pk[po[c] + i] = T(fma(zn[c], rv, bk[c] * pj));
+  double* __restrict__ x = a.x;
+  const int m = pl.m;
+  // residuals of the m steps, the last one n (live) or n - 1
+  const int last = pl.live ? n : n - 1;
+  double rk[kMaxSteps];
+#pragma unroll
+  for (int k = 0; k < kMaxSteps; ++k)
+    rk[k] = k < m ? double(ring[int64_t((last - m + 1 + k) % kRealRing) * a.n + i]) : 0.0;
+  constexpr int G = 4;  // systems whose loads are issued together
+  auto group = [&](int q, int cnt) {
+    double xv[G], pv[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      xv[u] = pv[u] = 0.0;
+      if (u < cnt && !pl.fresh) {
+        pv[u] = double(__builtin_nontemporal_load(&pk[pl.po[q + u] + i]));
+        xv[u] = __builtin_nontemporal_load(&x[pl.xo[q + u] + i]);
+      }
     }
-    p[i] = T(fma(bn, pv, rv));
-  }
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      if (u < cnt) {
+        double dx = pl.cx[0][q + u] * pv[u], np = pl.cp[0][q + u] * pv[u];
+#pragma unroll
+        for (int k = 0; k < kMaxSteps; ++k) {
+          if (k < m) {
+            dx = fma(pl.cx[k + 1][q + u], rk[k], dx);
+            np = fma(pl.cp[k + 1][q + u], rk[k], np);
+          }
+        }
+        __builtin_nontemporal_store(xv[u] + dx, &x[pl.xo[q + u] + i]);
+        __builtin_nontemporal_store(T(np), &pk[pl.po[q + u] + i]);
+      }
+    }
+  };
+  for (int q = 0; q < pl.nact; q += G) group(q, min(G, pl.nact - q));
 }
 
-// ---- FP64 true residual |b - (A + sigma) x|^2 of one shift ---------------------------
+// ---- one iteration --------------------------------------------------------------------
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_r_iter(RealArgs a) {
+  RealState* st = a.st;
+  const RealRot& rs = st->rot[a.par];
+  if (rs.halt) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->rot[a.par ^ 1].halt = 1;
+    return;
+  }
+  // partials first: their way overlaps the first row's
+  constexpr int kPer = kRealGrid / kBlock;
+  double g = 0.0, d = 0.0, gv[kPer], dv[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int i = threadIdx.x + u * kBlock;
+    const bool in = i < int(gridDim.x);
+    gv[u] = in ? load_agent(&r_region(a, a.par, 0)[i]) : 0.0;
+    dv[u] = in ? load_agent(&r_region(a, a.par, 1)[i]) : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    g += gv[u];
+    d += dv[u];
+  }
+  __shared__ double tot[2];
+  __shared__ RealPlan pl;
+  {
+    double v[2] = {g, d};
+    block_sum_k<kBlock, 2>(v);
+    if (threadIdx.x == 0) {
+      tot[0] = v[0];
+      tot[1] = v[1];
+    }
+  }
+  __syncthreads();
+  const int n = rs.iter;
+  r_plan(a, tot[0], tot[1], pl);
+  __syncthreads();
+  const bool live = pl.live != 0, apply = pl.apply != 0;
+  if (!live && !apply) return;
+  const SellReal<T> m = rmat<T>(a);
+  T* ring = static_cast<T*>(a.r);
+  const T* __restrict__ r = ring + int64_t(n % kRealRing) * a.n;
+  T* __restrict__ rn = ring + int64_t((n + 1) % kRealRing) * a.n;
+  const double* __restrict__ w = a.w[a.par];
+  const double* __restrict__ s = a.s[a.par];
+  double* __restrict__ wn = a.w[a.par ^ 1];
+  double* __restrict__ sn = a.s[a.par ^ 1];
+  const double step = pl.a, b = pl.b, sigma0 = st->sigma0;
+  // s_n and r_{n+1} at a row, rounded once each: the same bits wherever they are formed
+  auto s_of = [&](int64_t c) {
+    return fma(b, s[c], fma(sigma0, double(r[c]), w[c]));
+  };
+  auto r_of = [&](int64_t c) { return T(fma(-step, s_of(c), double(r[c]))); };
+  constexpr int SPB = kBlock / kSlice;
+  const int lane = threadIdx.x % kSlice;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+  int64_t beg, end;
+  block_range(a.nslices, SPB, beg, end);
+  g = d = 0.0;
+  for (int64_t sl = beg + wv; sl < end; sl += SPB) {
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
+    if (live) {
+      const double sv = s_of(rr);
+      const T own = T(fma(-step, sv, double(r[rr])));
+      const double v = r_row_f<T>(m, [&](int32_t c) { return r_of(c); }, own, sl, lane, rr);
+      if (row < a.n) {
+        rn[row] = own;
+        sn[row] = sv;
+        wn[row] = v;
+        const double rd = double(own);
+        g = fma(rd, rd, g);
+        d += rd * v + sigma0 * rd * rd;
+      }
+    }
+    if (apply && row < a.n) r_apply_row<T>(a, pl, n, row);
+  }
+  if (live) r_store_partials(a, a.par ^ 1, g, d);
+}
+
+// ---- FP64 true residuals |b - (A + sigma_k) x_k|^2 of up to kRealCheck systems ----------
 __global__ __launch_bounds__(kBlock) void k_r_verify(RealArgs a, const double* __restrict__ x,
-                                                     double sigma, double* out) {
+                                                     RealSigma sg, int cnt, double* out) {
   const SellReal<double> m = rmat<double>(a);
   constexpr int SPB = kBlock / kSlice;
   const int lane = threadIdx.x % kSlice;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
   int64_t beg, end;
   block_range(a.nslices, SPB, beg, end);
-  double acc = 0.0;
+  double acc[kRealCheck];
+#pragma unroll
+  for (int q = 0; q < kRealCheck; ++q) acc[q] = 0.0;
   for (int64_t sl = beg + wv; sl < end; sl += SPB) {
     const int64_t row = sl * kSlice + lane;
     const int64_t rr = row < a.n ? row : a.n - 1;
-    const double v = r_row<double>(m, x, sl, lane, rr);
-    if (row < a.n) {
-      const double d = a.b[row] - v - sigma * x[row];
-      acc = fma(d, d, acc);
+#pragma unroll
+    for (int q = 0; q < kRealCheck; ++q) {
+      if (q < cnt) {
+        const double* __restrict__ xq = x + int64_t(q) * a.n;
+        const double v = r_row<double>(m, xq, sl, lane, rr);
+        if (row < a.n) {
+          const double e = a.b[row] - v - sg.v[q] * xq[row];
+          acc[q] = fma(e, e, acc[q]);
+        }
+      }
     }
   }
-  double tot;
-  if (!r_reduce(a, acc, &tot)) return;
-  if (threadIdx.x == 0) *out = tot;
+  block_sum_k<kBlock, kRealCheck>(acc);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < kRealCheck; ++q) store_agent(&a.partial[blockIdx.x * kRealCheck + q], acc[q]);
+  }
+  if (!arrive_last(a.tickets)) return;
+  for (int q = 0; q < cnt; ++q) {
+    const double t = r_sum(a.partial, gridDim.x, kRealCheck, q);
+    if (threadIdx.x == 0) out[q] = t;
+  }
 }
 
 // Real parts of the complex sliced copy (values and diagonal) and the largest imaginary
@@ -336,13 +513,9 @@ __global__ void k_r_extract(const double2* __restrict__ v64, double* __restrict_
   if (local) atomicMax(imax, local);
 }
 
-int r_grid(int64_t n, int rows_per_pass) {
-  int64_t g = (n + rows_per_pass - 1) / rows_per_pass;
-  if (g > kMaxGrid) g = kMaxGrid;
-  if (g < kXcds) g = kXcds;
-  g = (g + kXcds - 1) / kXcds * kXcds;
-  if (g > kMaxGrid) g = kMaxGrid;
-  return int(g);
+int r_grid(int64_t nslices) {
+  const int64_t g = (nslices + kBlock / kSlice - 1) / (kBlock / kSlice);
+  return int((std::min<int64_t>(std::max<int64_t>(g, 1), kRealGrid) + kXcds - 1) / kXcds * kXcds);
 }
 
 }  // namespace
@@ -356,34 +529,27 @@ hipError_t launch_real_extract(const double2* v64, double* r64, float* r32, int6
   return hipGetLastError();
 }
 
-hipError_t launch_real_init(int prec, const RealArgs& a, hipStream_t s) {
-  const int g = r_grid(a.n, kBlock);
+hipError_t launch_real_start(int prec, const RealArgs& a, hipStream_t s) {
+  const int g = r_grid(a.nslices);
   if (prec == MSC_PREC_MIXED)
-    k_r_init<float><<<g, kBlock, 0, s>>>(a);
+    k_r_start<float><<<g, kBlock, 0, s>>>(a);
   else
-    k_r_init<double><<<g, kBlock, 0, s>>>(a);
+    k_r_start<double><<<g, kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
-hipError_t launch_real_iteration(int prec, const RealArgs& a, int launch, hipStream_t s) {
-  const int gs = r_grid(a.nslices, kBlock / kSlice);
-  const int g3 = r_grid(a.n, kBlock);
-  if (prec == MSC_PREC_MIXED) {
-    k_r_k1<float><<<gs, kBlock, 0, s>>>(a);
-    k_r_k2<float><<<g3, kBlock, 0, s>>>(a, launch);
-    k_r_k3<float><<<g3, kBlock, 0, s>>>(a, launch);
-  } else {
-    k_r_k1<double><<<gs, kBlock, 0, s>>>(a);
-    k_r_k2<double><<<g3, kBlock, 0, s>>>(a, launch);
-    k_r_k3<double><<<g3, kBlock, 0, s>>>(a, launch);
-  }
+hipError_t launch_real_iteration(int prec, const RealArgs& a, hipStream_t s) {
+  const int g = r_grid(a.nslices);
+  if (prec == MSC_PREC_MIXED)
+    k_r_iter<float><<<g, kBlock, 0, s>>>(a);
+  else
+    k_r_iter<double><<<g, kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
-hipError_t launch_real_verify(const RealArgs& a, const double* x, double sigma, double* out,
-                              hipStream_t s) {
-  const int gs = r_grid(a.nslices, kBlock / kSlice);
-  k_r_verify<<<gs, kBlock, 0, s>>>(a, x, sigma, out);
+hipError_t launch_real_verify(const RealArgs& a, const double* x, const RealSigma& sg, int cnt,
+                              double* out, hipStream_t s) {
+  k_r_verify<<<r_grid(a.nslices), kBlock, 0, s>>>(a, x, sg, cnt, out);
   return hipGetLastError();
 }
 
