@@ -7,21 +7,29 @@
 // of the driving one, r_n(s) = (z_n / tau_n) r_n, so every shift is advanced from r_n,
 // s_n and r_{n+1} with no extra operator product.
 //
-// One iteration is four kernels; each reduction is finished by the last workgroup to
-// arrive (deterministic fixed-order sum), which also derives the scalars:
-//   BV   v = B p,  w^H v          -> al = rho / w^H v; per shift z_{n+1}, al(s)
-//   BT   t = B s with s = r - al v formed at each gathered column (and stored for the
-//        own row),  t^H s, t^H t  -> om; per shift om(s), tau_{n+1}
-//   BR   r' = s - om t,  w^H r', |r'|^2 -> rho', be; per shift be(s), the update
-//        coefficients, freezing; halt once every shift has converged
-//   BU   every live shift: x(s) += al(s) p(s) + om(s) (z'/tau) s,
-//        p(s) <- (z'/tau') r' + be(s) [p(s) - (om(s)/al(s)) ((z/tau) r - (z'/tau) s)];
-//        the driving direction p <- r' + be (p - om v)
+// One iteration is two kernels, one per product.  Each workgroup sums the previous kernel's
+// partials itself, in one order, and derives the scalars; vectors that the other kernel
+// left to be formed are formed at every gathered column as their owner forms them:
+//   BA   om_{n-1} = t^H s / t^H t, rho_n = w^H s - om w^H t, |r_n|^2 = |s|^2 - |t^H s|^2 /
+//        t^H t, be_n;  r_n = s - om t, p_n = r_n + be (p - om v), v_n = B p_n;  w^H v_n
+//   BB   al_n = rho_n / w^H v_n;  s_n = r_n - al v_n, t_n = B s_n;  t^H s, t^H t, w^H s,
+//        w^H t, |s|^2
+// The shifts take, per step,
+//   x(s) += al(s) p(s) + om(s) (z'/tau) s,
+//   p(s) <- (z'/tau') r' + be(s) [p(s) - (om(s)/al(s)) ((z/tau) r - (z'/tau) s)];
+// nothing else reads them, so up to kBcgSteps steps are composed against the first one's
+// p(s) and the r and s of the steps, which stay in rings, and BA applies them in one pass.
 // Complex scalars are FP64 throughout; the shadow vector is b.
+//
+// Bound by memory and, on grids that fit the caches, by latency.  64 x 48 x 50 points, 8
+// shifts, a solve of 42 steps: 3.60 ms with four kernels on the CSR, 1.95 ms here.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "dev_common.h"
 #include "msc_internal.h"
+#include "sell_load.h"
 
 namespace msc {
 
@@ -92,362 +100,489 @@ __device__ __forceinline__ double2 row_f(const Csr<double2>& m, int64_t row, int
   return group_sum_c<L, double>(acc);
 }
 
-// The last workgroup's fixed-order sum of `count` partials (component k of `stride`).
-__device__ __forceinline__ double bcg_sum(const double* partial, int count, int stride, int k) {
-  constexpr int kPer = kMaxGrid / kBlock;
-  double v[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int i = threadIdx.x + u * kBlock;
-    v[u] = i < count ? load_agent(&partial[i * stride + k]) : 0.0;
+// One sliced row of A (off-diagonal part and diagonal) times gather(col), own at the row.
+template <bool NARROW, class G>
+__device__ __forceinline__ double2 sell_f(const Sell<double2>& m, int64_t sl, int lane, int64_t row,
+                                          double2 own, G gather) {
+  int32_t c, c1;
+  if (m.wp > 0) {
+    c = int32_t(sl) * m.wp;
+    c1 = c + m.wp;
+  } else {
+    c = load_uniform(m.cptr, sl);
+    c1 = load_uniform(m.cptr, sl + 1);
   }
-  double s = 0.0;
+  double2 acc{0.0, 0.0};
+  cmad(acc, m.diag[row], own);
+  constexpr int KP = 2;
+  for (; c < c1; c += KP) {
+    const int np = c1 - c;
+    int2 cc[KP];
+    double2 v[2 * KP], xv[2 * KP];
+    if (np >= KP)
+      sell_load<double, KP, true, NARROW>(m, c, KP, lane, cc, v);
+    else
+      sell_load<double, KP, false, NARROW>(m, c, np, lane, cc, v);
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) s += v[u];
-  return block_sum<kBlock>(s);
+    for (int u = 0; u < KP; ++u) {
+      if (u < np) {
+        xv[2 * u] = gather(cc[u].x);
+        xv[2 * u + 1] = gather(cc[u].y);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * KP; ++u)
+      if (u < 2 * np) cmad(acc, v[u], xv[u]);
+  }
+  return acc;
 }
 
-// Store this workgroup's four partial components; returns true in the last workgroup,
-// where tot[0..3] then hold the grid sums (valid in thread 0, broadcast through LDS).
-__device__ bool bcg_reduce(const BcgArgs& a, double c0, double c1, double c2, double c3,
-                           double (&tot)[4]) {
-  const double v[4] = {c0, c1, c2, c3};
-  double bs[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) bs[k] = block_sum<kBlock>(v[k]);
+// Partials: component k of a kernel's workgroup i at reg[k kBcgGrid + i]; BA's two in the
+// first region, BB's eight in the second.
+__device__ __forceinline__ double* bcg_region(const BcgArgs& a, int which) {
+  return a.partial + which * 2 * kBcgGrid;
+}
+
+template <int K> __device__ __forceinline__ void bcg_store(double* reg, double (&v)[K]) {
+  block_sum_k<kBlock, K>(v);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) store_agent(&a.partial[blockIdx.x * 4 + k], bs[k]);
+    for (int k = 0; k < K; ++k) store_agent(&reg[k * kBcgGrid + blockIdx.x], v[k]);
   }
-  if (!arrive_last(a.tickets)) return false;
-  __shared__ double sh[4];
+}
+
+// The sums of all workgroups' K components, in every thread.  The previous kernel wrote
+// them, so plain loads do, and the XCD's L2 serves all but its first workgroup's.
+template <int K> __device__ __forceinline__ void bcg_sums(const double* reg, double (&tot)[K]) {
+  __shared__ double sh[K];
+  constexpr int kPer = kBcgGrid / kBlock;
+  double v[K];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const double t = bcg_sum(a.partial, gridDim.x, 4, k);
-    if (threadIdx.x == 0) sh[k] = t;
+  for (int k = 0; k < K; ++k) {
+    double w[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = threadIdx.x + u * kBlock;
+      w[u] = i < int(gridDim.x) ? reg[k * kBcgGrid + i] : 0.0;
+    }
+    v[k] = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) v[k] += w[u];
+  }
+  block_sum_k<kBlock, K>(v);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[k] = v[k];
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < 4; ++k) tot[k] = sh[k];
-  return true;
+  for (int k = 0; k < K; ++k) tot[k] = sh[k];
 }
 
-__device__ __forceinline__ void bcg_halt(BcgState* st, int status) {
-  st->status = status;
-  st->halt = 1;
+__device__ __forceinline__ double2* ring(double2* v, int64_t n, int i, int slots) {
+  return v + int64_t(i % slots) * n;
 }
 
-// ---- initialisation: r = p = b, p(s) = b, x(s) = 0, rho = |b|^2 ------------------------
-__global__ __launch_bounds__(kBlock) void k_bcg_init(BcgArgs a) {
-  BcgState* st = a.st;
-  const int ns = a.ns;
+// ---- start: what BA turns into r_0 = p_0 = b (om = be = 0); |b|^2 --------------------------
+__global__ __launch_bounds__(kBlock) void k_bcg_start(BcgArgs a) {
+  double2* __restrict__ s = ring(a.s, a.n, kBcgSteps - 1, kBcgSteps);
   int64_t beg, end;
   block_range(a.n, kBlock, beg, end);
-  double acc = 0.0;
+  double v[8] = {};
   for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
     const double2 bv = a.b[i];
-    a.r[0][i] = bv;
-    a.p[i] = bv;
-    for (int j = 0; j < ns; ++j) {
-      a.pk[int64_t(j) * a.n + i] = bv;
-      a.x[int64_t(st->orig[j]) * a.n + i] = double2{0.0, 0.0};
-    }
-    acc += cabs2(bv);
+    s[i] = bv;
+    a.t[i] = a.p[0][i] = a.v[0][i] = double2{0.0, 0.0};
+    v[7] += cabs2(bv);
   }
-  double tot[4];
-  if (!bcg_reduce(a, acc, 0.0, 0.0, 0.0, tot)) return;
-  if (threadIdx.x == 0) {
-    st->bnorm2 = tot[0];
-    st->rho = double2{tot[0], 0.0};
-    st->eps2 = st->eps2 * tot[0];  // the host stored tol^2
-    if (!(tot[0] > 0.0) || !isfinite(tot[0])) bcg_halt(st, isfinite(tot[0]) ? 0 : 1);
+  bcg_store<8>(bcg_region(a, 1), v);
+}
+
+// What BA does, shared through LDS.
+struct BcgPlan {
+  double2 om, be;
+  int live, apply, m, first, fresh, nact;  // composed steps: first .. first + m - 1
+  double2 cx[kBcgTerms][kMaxShifts], cp[kBcgTerms][kMaxShifts];
+  int64_t xo[kMaxShifts], po[kMaxShifts];
+};
+
+// BA's prologue (wave 0, lane j: shift j).  Step n - 1 (s, t, alpha, z', al(s) known)
+// ends here; every workgroup derives the same, workgroup 0 writes the next state.
+__device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) {
+  BcgState* st = a.st;
+  const BcgRot& rs = st->rot[a.par];
+  const int j = threadIdx.x;
+  if (j >= kWave) return;
+  const bool head = blockIdx.x == 0, mine = j < st->ns;
+  const int n = rs.iter, m0 = rs.m;
+  const double2 ts{tot[0], tot[1]}, ws{tot[3], tot[4]}, wt{tot[5], tot[6]};
+  const double tt = tot[2], ss = tot[7];
+  const double bn2 = n == 0 ? ss : st->bnorm2, eps2 = st->tol2 * bn2;
+  int act = mine ? rs.active[j] : 0;
+  double2 om{0.0, 0.0}, be{0.0, 0.0}, rho{ss, 0.0};
+  double R = ss;
+  // 0: go on, 1: halt, 2: breakdown
+  int stop = 0;
+  const bool step = n > 0;      // a step ends here
+  bool took = mine && m0 > 0 ? rs.took[j] != 0 : false;
+  double2 z{1.0, 0.0}, zn{1.0, 0.0}, tau{1.0, 0.0}, taun{1.0, 0.0};
+  double2 cx[kBcgTerms], cp[kBcgTerms];
+#pragma unroll
+  for (int e = 0; e < kBcgTerms; ++e) cx[e] = cp[e] = double2{0.0, 0.0};
+  // p(s) before the first composed step: itself, or r_0 = b where it was never written
+  if (rs.fresh)
+    cp[1].x = 1.0;
+  else
+    cp[0].x = 1.0;
+  if (mine && m0 > 0) {
+#pragma unroll
+    for (int e = 0; e < kBcgTerms; ++e) {
+      cx[e] = rs.cx[e][j];
+      cp[e] = rs.cp[e][j];
+    }
+  }
+  if (mine) {
+    z = zn = rs.z[j];
+    tau = taun = rs.tau[j];
+  }
+  int m = m0;
+  if (step && st->bad) {
+    stop = 2;  // BB found w^H v = 0: no step n - 1
+  } else if (step) {
+    const bool ok = tt > 0.0 && isfinite(tt) && cfinite(ts);
+    if (ok) om = double2{ts.x / tt, ts.y / tt};
+    const double sj = mine ? st->s[j] : 0.0;
+    const double2 g{1.0 + sj * om.x, sj * om.y};
+    const bool bad = !ok || (act && g.x == 0.0 && g.y == 0.0);
+    if (__ballot(bad)) {
+      stop = 2;
+      act = 0;
+    } else {
+      const double2 al = st->alpha;
+      rho = csub(ws, cmul(om, wt));
+      R = fmax(ss - cabs2(ts) / tt, 0.0);
+      const bool rho_ok = rho.x != 0.0 || rho.y != 0.0, om_ok = om.x != 0.0 || om.y != 0.0;
+      // be = (rho' / rho)(al / om); a vanishing rho' or om ends the sequence after this step
+      if (rho_ok && om_ok) be = cmul(cdiv(rho, rs.rho), cdiv(al, om));
+      int next = act;
+      if (act) {
+        zn = st->zn[j];
+        taun = cmul(tau, g);
+        const double2 als = st->als[j], oms = cdiv(om, g);
+        const double2 c1 = cdiv(zn, tau);    // s_n(s) = c1 s_n
+        const double2 c2 = cdiv(zn, taun);   // r_{n+1}(s) = c2 r_{n+1}
+        const double2 c3 = cdiv(z, tau);     // r_n(s) = c3 r_n
+        const double2 ratio = cdiv(zn, z), bes = cmul(be, cmul(ratio, ratio));
+        const double2 q = cmul(bes, cdiv(oms, als)), qc3 = cmul(q, c3);
+        const double2 xs = cmul(oms, c1), ps = cmul(q, c1);
+        // x += als p + xs s;  p <- bes p + c2 r' - q c3 r + q c1 s, composed as step m0
+#pragma unroll
+        for (int e = 0; e < kBcgTerms; ++e) {
+          cmad(cx[e], als, cp[e]);
+          cp[e] = cmul(bes, cp[e]);
+          if (e == 1 + m0) cp[e] = csub(cp[e], qc3);
+          if (e == 2 + m0) cp[e] = cadd(cp[e], c2);
+          if (e == 2 + kBcgSteps + m0) {
+            cx[e] = cadd(cx[e], xs);
+            cp[e] = cadd(cp[e], ps);
+          }
+        }
+        took = true;
+        const double res2 = cabs2(c2) * R;   // this shift's residual after the step
+        if (res2 <= eps2) {
+          next = 0;
+          if (head) st->freeze_iter[j] = n;
+        }
+        if (!isfinite(res2)) next = 0;
+      }
+      act = next;
+      m = m0 + 1;
+      const bool finite = isfinite(R) && cfinite(rho);
+      if (!finite)
+        stop = 2;
+      else if (__ballot(act != 0) == 0 || !rho_ok || !om_ok || n >= st->max_iter)
+        stop = 1;
+    }
+  } else if (!(bn2 > 0.0) || !isfinite(bn2)) {
+    stop = isfinite(bn2) ? 1 : 2;
+  } else if (st->max_iter <= 0) {
+    stop = 1;
+  }
+  const bool live = stop == 0;
+  const bool apply = live ? m >= kBcgSteps : (m > 0 || rs.fresh);
+  const bool list = apply && mine && (took || rs.fresh);
+  const uint64_t mask = __ballot(list);
+  if (list) {
+    const int pos = __popcll(mask & ((uint64_t(1) << j) - 1));
+#pragma unroll
+    for (int e = 0; e < kBcgTerms; ++e) {
+      pl.cx[e][pos] = cx[e];
+      pl.cp[e][pos] = cp[e];
+    }
+    pl.xo[pos] = int64_t(st->orig[j]) * a.n;
+    pl.po[pos] = int64_t(j) * a.n;
+  }
+  if (j == 0) {
+    pl.om = om;
+    pl.be = be;
+    pl.live = live ? 1 : 0;
+    pl.apply = apply ? 1 : 0;
+    pl.m = m;
+    pl.first = (step && m == m0 ? n - 1 : n) - m;
+    pl.fresh = rs.fresh;
+    pl.nact = __popcll(mask);
+  }
+  if (!head) return;
+  BcgRot& nx = st->rot[a.par ^ 1];
+  if (mine) {
+    nx.zo[j] = took && step ? z : rs.zo[j];
+    nx.z[j] = zn;
+    nx.tau[j] = taun;
+    nx.active[j] = act;
+    nx.took[j] = apply ? 0 : (took ? 1 : 0);
+    if (!apply) {
+#pragma unroll
+      for (int e = 0; e < kBcgTerms; ++e) {
+        nx.cx[e][j] = cx[e];
+        nx.cp[e][j] = cp[e];
+      }
+    }
+    if (!live) st->at_end[j] = act;
+  }
+  if (j == 0) {
+    nx.rho = rho;
+    nx.be = be;
+    nx.al = step ? st->alpha : double2{1.0, 0.0};
+    nx.iter = live ? n + 1 : n;
+    nx.m = apply ? 0 : m;
+    nx.fresh = apply ? 0 : rs.fresh;
+    nx.halt = live ? 0 : 1;
+    if (n == 0) st->bnorm2 = ss;
+    if (!live) {
+      // a step that broke down before its end does not count
+      st->iter = stop == 2 && step && m == m0 ? n - 1 : n;
+      st->status = stop == 2 ? 1 : 0;
+      store_host_flag(a.hflag, 1);
+    }
   }
 }
 
-// ---- BV: v = B p and w^H v; al and the shifted BiCG constants --------------------------
-template <int L>
-__global__ __launch_bounds__(kBlock) void k_bcg_v(BcgArgs a) {
+enum { kBcgCsr = 0, kBcgSell = 1 };
+
+// This workgroup's rows [beg, end): whole slices on the sliced copy.
+template <int ST, int L>
+__device__ __forceinline__ void bcg_rows(const BcgArgs& a, int64_t& beg, int64_t& end) {
+  if constexpr (ST == kBcgSell) {
+    block_range(a.nslices, kBlock / kSlice, beg, end);
+    beg *= kSlice;
+    end *= kSlice;
+  } else {
+    block_range(a.n, kBlock / L, beg, end);
+  }
+}
+
+// The product B x (x = gather(col)) at the workgroup's rows: body(row, own, (B x)_row) in
+// the one lane that owns the row.
+template <int ST, int L, class G, class F>
+__device__ __forceinline__ void bcg_product(const BcgArgs& a, int64_t beg, int64_t end,
+                                            double sigma0, G gather, F body) {
+  if constexpr (ST == kBcgSell) {
+    const int lane = threadIdx.x % kSlice;
+    const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+    for (int64_t sl = beg / kSlice + wv; sl * kSlice < end; sl += kBlock / kSlice) {
+      const int64_t row = sl * kSlice + lane;
+      const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
+      const double2 own = gather(int32_t(rr));
+      double2 q = a.sm.col16 ? sell_f<true>(a.sm, sl, lane, rr, own, gather)
+                             : sell_f<false>(a.sm, sl, lane, rr, own, gather);
+      q.x = fma(sigma0, own.x, q.x);
+      q.y = fma(sigma0, own.y, q.y);
+      if (row < a.n) body(row, own, q);
+    }
+  } else {
+    const int lane = threadIdx.x % L;
+    for (int64_t row = beg + threadIdx.x / L; row < end; row += kBlock / L) {
+      double2 q = row_f<L>(a.m, row, lane, gather);
+      const double2 own = gather(int32_t(row));
+      q.x = fma(sigma0, own.x, q.x);
+      q.y = fma(sigma0, own.y, q.y);
+      if (lane == 0) body(row, own, q);
+    }
+  }
+}
+
+// ---- BA: r_n, p_n, v_n = B p_n and w^H v_n; the shifts' composed steps --------------------
+template <int ST, int L>
+__global__ __launch_bounds__(kBlock) void k_bcg_a(BcgArgs a) {
   BcgState* st = a.st;
-  if (st->halt) return;
-  const double sigma0 = st->sigma0;
-  constexpr int GPB = kBlock / L;
-  const int lane = threadIdx.x % L, grp = threadIdx.x / L;
-  int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
-  double2 acc{0.0, 0.0};
-  const double2* __restrict__ p = a.p;
-  for (int64_t row = beg + grp; row < end; row += GPB) {
-    double2 q = row_f<L>(a.m, row, lane, [&](int32_t c) { return p[c]; });
-    const double2 pr = p[row];
-    q.x = fma(sigma0, pr.x, q.x);
-    q.y = fma(sigma0, pr.y, q.y);
-    if (lane == 0) {
-      a.v[row] = q;
-      cdot_acc(acc, a.b[row], q);
-    }
+  const BcgRot& rs = st->rot[a.par];
+  if (rs.halt) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->rot[a.par ^ 1].halt = 1;
+    return;
   }
-  double tot[4];
-  if (!bcg_reduce(a, acc.x, acc.y, 0.0, 0.0, tot)) return;
-  const int j = threadIdx.x;
-  // rotate the shifted state of the previous iteration, then z_{n+1} and al(s)
-  if (j < a.ns) {
-    if (st->rotate && st->active[j]) {
-      st->z_old[j] = st->z[j];
-      st->z[j] = st->z_new[j];
-      st->tau[j] = st->tau_new[j];
-    }
-    if (st->rotate) st->active[j] = st->active_next[j];
-  }
+  double tot[8];
+  bcg_sums<8>(bcg_region(a, 1), tot);
+  __shared__ BcgPlan pl;
+  bcg_plan(a, tot, pl);
   __syncthreads();
-  const double2 wv{tot[0], tot[1]};
-  const bool ok = cfinite(wv) && (wv.x != 0.0 || wv.y != 0.0);
-  const double2 al = ok ? cdiv(st->rho, wv) : double2{0.0, 0.0};
-  if (ok && j < a.ns && st->active[j]) {
-    const double2 z = st->z[j], zo = st->z_old[j];
-    const double2 alp = st->al_prev, bep = st->be_prev;
-    const double s = st->s[j];
-    // z' = z zo alp / (al bep (zo - z) + zo alp (1 + s al))
-    const double2 one_sal{1.0 + s * al.x, s * al.y};
-    const double2 den = cadd(cmul(cmul(al, bep), csub(zo, z)), cmul(cmul(zo, alp), one_sal));
-    const double2 zn = cdiv(cmul(cmul(z, zo), alp), den);
-    st->z_new[j] = zn;
-    st->al_s[j] = cdiv(cmul(al, zn), z);
+  const int n = rs.iter;
+  const bool live = pl.live != 0;
+  if (!live && !pl.apply) return;
+  const double2 om = pl.om, be = pl.be;
+  const double2* __restrict__ s = ring(a.s, a.n, n + kBcgSteps - 1, kBcgSteps);  // s_{n-1}
+  const double2* __restrict__ t = a.t;
+  const double2* __restrict__ p = a.p[a.par];
+  const double2* __restrict__ v = a.v[a.par];
+  double2* __restrict__ pn = a.p[a.par ^ 1];
+  double2* __restrict__ vn = a.v[a.par ^ 1];
+  double2* __restrict__ rn = ring(a.r, a.n, n, kBcgRing);
+  auto r_of = [&](int64_t c) { return s_of(s[c], t[c], om); };
+  auto p_of = [&](int64_t c) {
+    double2 o = r_of(c);
+    cmad(o, be, s_of(p[c], v[c], om));
+    return o;
+  };
+  int64_t beg, end;
+  bcg_rows<ST, L>(a, beg, end);
+  if (live) {
+    double2 wv{0.0, 0.0};
+    bcg_product<ST, L>(a, beg, end, st->sigma0, [&](int32_t c) { return p_of(c); },
+                       [&](int64_t row, const double2& own, const double2& q) {
+                         pn[row] = own;
+                         vn[row] = q;
+                         rn[row] = r_of(row);
+                         cdot_acc(wv, a.b[row], q);
+                       });
+    double c[2] = {wv.x, wv.y};
+    bcg_store<2>(bcg_region(a, 0), c);
   }
-  if (j == 0) {
-    st->rotate = 0;
-    if (!ok) {
-      bcg_halt(st, 1);
-    } else {
+  if (!pl.apply) return;
+  // x(s) and p(s) from p(s) and the r and s of the composed steps; the last r, r_n, goes
+  // into p(s) only, which a sequence that halts here no longer needs
+  const int m = pl.m, first = pl.first, nact = pl.nact, fresh = pl.fresh;
+  const int64_t stop = end < a.n ? end : a.n;
+  for (int64_t i = beg + threadIdx.x; i < stop; i += kBlock) {
+    double2 b[kBcgTerms];  // b[1 + k] = r_{first + k}, b[2 + kBcgSteps + k] = s_{first + k}
+#pragma unroll
+    for (int k = 0; k < kBcgSteps; ++k) {
+      const bool in = k < m;
+      b[1 + k] = in ? ring(a.r, a.n, first + k, kBcgRing)[i] : double2{0.0, 0.0};
+      b[2 + kBcgSteps + k] = in ? ring(a.s, a.n, first + k, kBcgSteps)[i] : double2{0.0, 0.0};
+    }
+    b[1 + kBcgSteps] = double2{0.0, 0.0};
+    const double2 last = live ? r_of(i) : double2{0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k <= kBcgSteps; ++k)
+      if (k == m) b[1 + k] = last;
+    for (int q = 0; q < nact; ++q) {
+      double2* __restrict__ xj = a.x + pl.xo[q];
+      double2* __restrict__ pj = a.pk + pl.po[q];
+      double2 xv{0.0, 0.0}, np{0.0, 0.0};
+      if (!fresh) {
+        xv = ld_stream(&xj[i]);
+        const double2 pv = ld_stream(&pj[i]);
+        cmad(xv, pl.cx[0][q], pv);
+        cmad(np, pl.cp[0][q], pv);
+      }
+#pragma unroll
+      for (int e = 1; e < kBcgTerms; ++e) {
+        cmad(xv, pl.cx[e][q], b[e]);
+        cmad(np, pl.cp[e][q], b[e]);
+      }
+      st_stream(&xj[i], xv);
+      st_stream(&pj[i], np);
+    }
+  }
+}
+
+// ---- BB: al; s_n and t_n = B s_n with their products ---------------------------------------
+template <int ST, int L>
+__global__ __launch_bounds__(kBlock) void k_bcg_b(BcgArgs a) {
+  BcgState* st = a.st;
+  const BcgRot& rs = st->rot[a.par ^ 1];  // written by this iteration's BA
+  if (rs.halt) return;
+  double wv[2];
+  bcg_sums<2>(bcg_region(a, 0), wv);
+  const double2 wvc{wv[0], wv[1]};
+  const bool ok = cfinite(wvc) && (wvc.x != 0.0 || wvc.y != 0.0);
+  const double2 al = ok ? cdiv(rs.rho, wvc) : double2{0.0, 0.0};
+  const int j = threadIdx.x, n = rs.iter - 1;  // this is step n
+  if (blockIdx.x == 0 && j < kWave) {
+    if (ok && j < st->ns && rs.active[j]) {
+      const double2 z = rs.z[j], zo = rs.zo[j], alp = rs.al, bep = rs.be;
+      const double s = st->s[j];
+      // z' = z zo alp / (al bep (zo - z) + zo alp (1 + s al))
+      const double2 one_sal{1.0 + s * al.x, s * al.y};
+      const double2 den = cadd(cmul(cmul(al, bep), csub(zo, z)), cmul(cmul(zo, alp), one_sal));
+      const double2 zn = cdiv(cmul(cmul(z, zo), alp), den);
+      st->zn[j] = zn;
+      st->als[j] = cdiv(cmul(al, zn), z);
+    }
+    if (j == 0) {
       st->alpha = al;
+      st->bad = ok ? 0 : 1;
     }
   }
-}
-
-// ---- BT: t = B s with s = r - al v formed at each gathered column; t^H s, t^H t -------
-template <int L>
-__global__ __launch_bounds__(kBlock) void k_bcg_t(BcgArgs a) {
-  BcgState* st = a.st;
-  if (st->halt) return;
-  const double sigma0 = st->sigma0;
-  const double2 al = st->alpha;
-  const double2* __restrict__ r = a.r[a.par];
-  const double2* __restrict__ v = a.v;
-  constexpr int GPB = kBlock / L;
-  const int lane = threadIdx.x % L, grp = threadIdx.x / L;
+  if (!ok) return;  // every workgroup sees the same sum; the next BA halts
+  const double2* __restrict__ r = ring(a.r, a.n, n, kBcgRing);
+  const double2* __restrict__ v = a.v[a.par ^ 1];
+  double2* __restrict__ s = ring(a.s, a.n, n, kBcgSteps);
   int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
-  double2 ts{0.0, 0.0};
-  double tt = 0.0;
-  for (int64_t row = beg + grp; row < end; row += GPB) {
-    double2 q = row_f<L>(a.m, row, lane, [&](int32_t c) { return s_of(r[c], v[c], al); });
-    const double2 sr = s_of(r[row], v[row], al);
-    q.x = fma(sigma0, sr.x, q.x);
-    q.y = fma(sigma0, sr.y, q.y);
-    if (lane == 0) {
-      a.s[row] = sr;
-      a.t[row] = q;
-      cdot_acc(ts, q, sr);
-      tt += cabs2(q);
-    }
-  }
-  double tot[4];
-  if (!bcg_reduce(a, ts.x, ts.y, tt, 0.0, tot)) return;
-  const int j = threadIdx.x;
-  const double2 tsum{tot[0], tot[1]};
-  const bool ok = tot[2] > 0.0 && isfinite(tot[2]) && cfinite(tsum);
-  const double2 om = ok ? double2{tsum.x / tot[2], tsum.y / tot[2]} : double2{0.0, 0.0};
-  bool bad = !ok;
-  if (ok && j < a.ns && st->active[j]) {
-    const double s = st->s[j];
-    const double2 g{1.0 + s * om.x, s * om.y};
-    if (g.x == 0.0 && g.y == 0.0) {
-      bad = true;
-    } else {
-      st->om_s[j] = cdiv(om, g);
-      st->tau_new[j] = cmul(st->tau[j], g);
-    }
-  }
-  __shared__ int any_bad;
-  if (j == 0) any_bad = 0;
-  __syncthreads();
-  if (bad) atomicOr(&any_bad, 1);
-  __syncthreads();
-  if (j == 0) {
-    if (any_bad)
-      bcg_halt(st, 1);
-    else
-      st->omega = om;
-  }
+  bcg_rows<ST, L>(a, beg, end);
+  double2 ts{0.0, 0.0}, ws{0.0, 0.0}, wt{0.0, 0.0};
+  double tt = 0.0, ss = 0.0;
+  bcg_product<ST, L>(a, beg, end, st->sigma0, [&](int32_t c) { return s_of(r[c], v[c], al); },
+                     [&](int64_t row, const double2& own, const double2& q) {
+                       s[row] = own;
+                       a.t[row] = q;
+                       const double2 w = a.b[row];
+                       cdot_acc(ts, q, own);
+                       cdot_acc(ws, w, own);
+                       cdot_acc(wt, w, q);
+                       tt += cabs2(q);
+                       ss += cabs2(own);
+                     });
+  double c[8] = {ts.x, ts.y, tt, ws.x, ws.y, wt.x, wt.y, ss};
+  bcg_store<8>(bcg_region(a, 1), c);
 }
 
-// ---- BR: r' = s - om t; w^H r', |r'|^2; be, per-shift coefficients, freezing ---------
-__global__ __launch_bounds__(kBlock) void k_bcg_r(BcgArgs a, int launch) {
-  BcgState* st = a.st;
-  if (st->halt) return;
-  const double2 om = st->omega;
-  double2* __restrict__ rn = a.r[a.par ^ 1];
-  int64_t beg, end;
-  block_range(a.n, kBlock, beg, end);
-  double2 wr{0.0, 0.0};
-  double rr = 0.0;
-  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
-    const double2 sv = a.s[i], tv = a.t[i];
-    double2 nv;
-    nv.x = fma(-om.x, tv.x, fma(om.y, tv.y, sv.x));
-    nv.y = fma(-om.x, tv.y, fma(-om.y, tv.x, sv.y));
-    rn[i] = nv;
-    cdot_acc(wr, a.b[i], nv);
-    rr += cabs2(nv);
-  }
-  double tot[4];
-  if (!bcg_reduce(a, wr.x, wr.y, rr, 0.0, tot)) return;
-  const int j = threadIdx.x;
-  const double2 rho_new{tot[0], tot[1]};
-  const double R = tot[2];
-  const double2 al = st->alpha;
-  const bool rho_ok = rho_new.x != 0.0 || rho_new.y != 0.0;
-  const bool om_ok = om.x != 0.0 || om.y != 0.0;
-  // be = (rho' / rho)(al / om); a vanishing rho' or om ends the sequence after this step
-  const double2 be = (rho_ok && om_ok) ? cmul(cdiv(rho_new, st->rho), cdiv(al, om))
-                                       : double2{0.0, 0.0};
-  int still = 0;
-  if (j < a.ns) {
-    const int act = st->active[j];
-    int nxt = act;
-    if (act) {
-      const double2 z = st->z[j], zn = st->z_new[j], tau = st->tau[j], taun = st->tau_new[j];
-      const double2 als = st->al_s[j], oms = st->om_s[j];
-      const double2 c1 = cdiv(zn, tau);              // s_n(s) = c1 s_n
-      const double2 c2 = cdiv(zn, taun);             // r_{n+1}(s) = c2 r_{n+1}
-      const double2 c3 = cdiv(z, tau);               // r_n(s) = c3 r_n
-      const double2 ratio = cdiv(zn, z);
-      const double2 bes = cmul(be, cmul(ratio, ratio));
-      const double2 q = cmul(bes, cdiv(oms, als));
-      BcgCoef& cf = st->cf[j];
-      cf.xp = als;                 // x(s) += xp p(s) + xs s
-      cf.xs = cmul(oms, c1);
-      cf.pr = c2;                  // p(s) <- pr r' + pp p(s) + po r + ps s
-      cf.pp = bes;
-      cf.po = double2{-(q.x * c3.x - q.y * c3.y), -(q.x * c3.y + q.y * c3.x)};
-      cf.ps = cmul(q, c1);
-      // this shift's residual after the step: |c2|^2 |r'|^2
-      const double res2 = cabs2(c2) * R;
-      if (res2 <= st->eps2) {
-        nxt = 0;
-        st->freeze_iter[j] = st->iter + 1;
-      }
-      if (!(isfinite(res2))) nxt = 0;
-    }
-    st->active_next[j] = nxt;
-    still = nxt;
-  }
-  const bool any_live = __syncthreads_or(still);
-  if (j == 0) {
-    const bool finite = isfinite(R) && cfinite(rho_new);
-    st->beta = be;
-    st->al_prev = al;
-    st->be_prev = be;
-    st->rho = rho_new;
-    st->R = R;
-    st->iter += 1;
-    st->rotate = 1;
-    st->upd_launch = launch;  // BU of this launch applies the step
-    if (!finite) {
-      bcg_halt(st, 1);
-    } else if (!any_live || !rho_ok || !om_ok || st->iter >= st->max_iter) {
-      st->halt = 1;
-    }
-  }
+// Workgroups for the rows, a multiple of the XCD count (at most kBcgGrid: the case above
+// takes 2.35 / 2.26 / 1.96 / 1.95 / 2.02 ms with 256 / 512 / 768 / 1024 / 2048).
+int bcg_grid(int64_t items, int per_pass) {
+  const int64_t g = (items + per_pass - 1) / per_pass;
+  return int((std::min<int64_t>(std::max<int64_t>(g, 1), kBcgGrid) + kXcds - 1) / kXcds * kXcds);
 }
 
-// ---- BU: the step of every live shift and the driving direction ----------------------
-__global__ __launch_bounds__(kBlock) void k_bcg_u(BcgArgs a, int launch) {
-  BcgState* st = a.st;
-  if (st->upd_launch != launch) return;
-  __shared__ BcgCoef cf[kMaxShifts];
-  __shared__ int64_t xo[kMaxShifts];
-  __shared__ int64_t po[kMaxShifts];
-  __shared__ int nlive;
-  if (threadIdx.x == 0) {
-    int c = 0;
-    for (int j = 0; j < a.ns; ++j) {
-      if (st->active[j]) {
-        cf[c] = st->cf[j];
-        xo[c] = int64_t(st->orig[j]) * a.n;
-        po[c] = int64_t(j) * a.n;
-        ++c;
-      }
-    }
-    nlive = c;
-  }
-  __syncthreads();
-  const double2 be = st->beta, om = st->omega;
-  const double2* __restrict__ r0 = a.r[a.par];
-  const double2* __restrict__ r1 = a.r[a.par ^ 1];
-  const int live = nlive;
-  int64_t beg, end;
-  block_range(a.n, kBlock, beg, end);
-  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
-    const double2 rv = r0[i], sv = a.s[i], rnv = r1[i];
-    for (int c = 0; c < live; ++c) {
-      double2* __restrict__ xj = a.x + xo[c];
-      double2* __restrict__ pj = a.pk + po[c];
-      const double2 pv = pj[i];
-      double2 xv = xj[i];
-      cmad(xv, cf[c].xp, pv);
-      cmad(xv, cf[c].xs, sv);
-      xj[i] = xv;
-      double2 np{0.0, 0.0};
-      cmad(np, cf[c].pr, rnv);
-      cmad(np, cf[c].pp, pv);
-      cmad(np, cf[c].po, rv);
-      cmad(np, cf[c].ps, sv);
-      pj[i] = np;
-    }
-    // driving direction p <- r' + be (p - om v)
-    const double2 pv = a.p[i], vv = a.v[i];
-    double2 d = pv;
-    d.x = fma(-om.x, vv.x, fma(om.y, vv.y, d.x));
-    d.y = fma(-om.x, vv.y, fma(-om.y, vv.x, d.y));
-    double2 np = rnv;
-    cmad(np, be, d);
-    a.p[i] = np;
-  }
+template <int ST, int L> void bcg_launch(const BcgArgs& a, int g, hipStream_t s) {
+  k_bcg_a<ST, L><<<g, kBlock, 0, s>>>(a);
+  k_bcg_b<ST, L><<<g, kBlock, 0, s>>>(a);
 }
 
-// Workgroups for n items, rows_per_pass at a time: one pass each up to kMaxGrid, a
-// multiple of the XCD count.
-int bcg_grid(int64_t n, int rows_per_pass) {
-  int64_t g = (n + rows_per_pass - 1) / rows_per_pass;
-  if (g > kMaxGrid) g = kMaxGrid;
-  if (g < kXcds) g = kXcds;
-  g = (g + kXcds - 1) / kXcds * kXcds;
-  if (g > kMaxGrid) g = kMaxGrid;
-  return int(g);
+int bcg_grid_of(const BcgArgs& a) {
+  return a.sell ? bcg_grid(a.nslices, kBlock / kSlice) : bcg_grid(a.n, kBlock / a.lanes);
 }
 
 }  // namespace
 
-hipError_t launch_bcg_init(const BcgArgs& a, hipStream_t s) {
-  const int g = bcg_grid(a.n, kBlock);
-  k_bcg_init<<<g, kBlock, 0, s>>>(a);
+hipError_t launch_bcg_start(const BcgArgs& a, hipStream_t s) {
+  // the first BA reads as many partials as it has workgroups
+  k_bcg_start<<<bcg_grid_of(a), kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
-hipError_t launch_bcg_iteration(const BcgArgs& args, int launch, hipStream_t s) {
-  BcgArgs a = args;
-  const int g1 = bcg_grid(a.n, kBlock / a.lanes);
-  const int g3 = bcg_grid(a.n, kBlock);
-  a.par = launch & 1;
-  switch (a.lanes) {
-    case 4: k_bcg_v<4><<<g1, kBlock, 0, s>>>(a); k_bcg_t<4><<<g1, kBlock, 0, s>>>(a); break;
-    case 8: k_bcg_v<8><<<g1, kBlock, 0, s>>>(a); k_bcg_t<8><<<g1, kBlock, 0, s>>>(a); break;
-    case 16: k_bcg_v<16><<<g1, kBlock, 0, s>>>(a); k_bcg_t<16><<<g1, kBlock, 0, s>>>(a); break;
-    case 32: k_bcg_v<32><<<g1, kBlock, 0, s>>>(a); k_bcg_t<32><<<g1, kBlock, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
+hipError_t launch_bcg_iteration(const BcgArgs& a, hipStream_t s) {
+  const int g = bcg_grid_of(a);
+  if (a.sell) {
+    bcg_launch<kBcgSell, 1>(a, g, s);
+  } else {
+    switch (a.lanes) {
+      case 4: bcg_launch<kBcgCsr, 4>(a, g, s); break;
+      case 8: bcg_launch<kBcgCsr, 8>(a, g, s); break;
+      case 16: bcg_launch<kBcgCsr, 16>(a, g, s); break;
+      case 32: bcg_launch<kBcgCsr, 32>(a, g, s); break;
+      default: return hipErrorInvalidValue;
+    }
   }
-  k_bcg_r<<<g3, kBlock, 0, s>>>(a, launch);
-  k_bcg_u<<<g3, kBlock, 0, s>>>(a, launch);
   return hipGetLastError();
 }
 

@@ -127,6 +127,35 @@ msc_status ensure_workspace(msc_op op, int prec, int ns) {
   return MSC_OK;
 }
 
+msc_status ensure_halt(HaltWord& w) {
+  if (!w.host) {
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&w.host), 2 * sizeof(int),
+                          hipHostMallocMapped | hipHostMallocCoherent));
+    HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&w.dev), w.host, 0));
+  }
+  for (auto& e : w.ev)
+    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  return MSC_OK;
+}
+
+// Queue iterations, poll_every at a time, until the halt word is set: that of one chunk is
+// read once the next one is queued.
+template <class F>
+msc_status run_to_halt(HaltWord& w, const msc_params& prm, int max_iter, hipStream_t s, F iteration) {
+  const int G = std::max(1, prm.poll_every);
+  int launched = 0;
+  for (int chunk = 0; launched < max_iter + 2 * G; ++chunk) {
+    for (int g = 0; g < G; ++g) HIP_TRY(iteration(launched++));
+    const int slot = chunk & 1;
+    HIP_TRY(hipEventRecord(w.ev[slot], s));
+    if (chunk >= 1) {
+      HIP_TRY(hipEventSynchronize(w.ev[slot ^ 1]));
+      if (__atomic_load_n(w.host, __ATOMIC_ACQUIRE)) break;
+    }
+  }
+  return MSC_OK;
+}
+
 int choose_lanes(msc_op op, const msc_params& prm) {
   if (prm.lanes == 4 || prm.lanes == 8 || prm.lanes == 16 || prm.lanes == 32) return prm.lanes;
   const double avg = op->n > 0 ? double(op->nnz) / double(op->n) : 1.0;
@@ -2386,9 +2415,12 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
   const int64_t n = op->n;
   msc_status rc = ensure_scratch(op, s);
   if (rc != MSC_OK) return rc;
-  // buffers: r[2], p, v, s, t (n each), ns directions, the state
+  rc = ensure_halt(op->halt);
+  if (rc != MSC_OK) return rc;
+  // buffers: the rings of r and s, p[2], v[2], t (n each), ns directions, the state
   const size_t vec = sizeof(double2) * size_t(n);
-  const size_t need = vec * (6 + size_t(ns)) + sizeof(BcgState) + 256;
+  const size_t vectors = kBcgRing + kBcgSteps + 5 + size_t(ns);
+  const size_t need = vec * vectors + sizeof(BcgState) + 256;
   if (op->bcg_bytes < need) {
     if (op->bcg) (void)hipFree(op->bcg);
     op->bcg = nullptr;
@@ -2396,25 +2428,35 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
     HIP_TRY(hipMalloc(&op->bcg, need));
     op->bcg_bytes = need;
   }
-  unsigned char* base = static_cast<unsigned char*>(op->bcg);
+  double2* cur = static_cast<double2*>(op->bcg);
+  auto carve = [&](int count) {
+    double2* p = cur;
+    cur += int64_t(count) * n;
+    return p;
+  };
   BcgArgs a{};
   a.n = n;
-  a.ns = ns;
   a.lanes = choose_lanes(op, prm);
   a.m = Csr<double2>{op->rowptr, op->col, op->val64};
+  a.sell = op->sell && prm.format != MSC_FORMAT_CSR ? 1 : 0;
+  if (a.sell) {
+    a.nslices = op->sell_m.nslices;
+    a.sm = sell_view(op->sell_m, op->sell_m.val64, op->sell_m.diag64,
+                     prm.format != MSC_FORMAT_SELL32);
+  }
   a.b = reinterpret_cast<const double2*>(d_b);
   a.x = reinterpret_cast<double2*>(d_x);
-  double2* vbase = reinterpret_cast<double2*>(base);
-  a.r[0] = vbase;
-  a.r[1] = vbase + n;
-  a.p = vbase + 2 * n;
-  a.v = vbase + 3 * n;
-  a.s = vbase + 4 * n;
-  a.t = vbase + 5 * n;
-  a.pk = vbase + 6 * n;
-  a.st = reinterpret_cast<BcgState*>(base + vec * (6 + size_t(ns)));
+  a.r = carve(kBcgRing);
+  a.s = carve(kBcgSteps);
+  for (int q = 0; q < 2; ++q) {
+    a.p[q] = carve(1);
+    a.v[q] = carve(1);
+  }
+  a.t = carve(1);
+  a.pk = carve(ns);
+  a.st = reinterpret_cast<BcgState*>(cur);
   a.partial = op->scratch.partial;
-  a.tickets = op->scratch.tickets + 12 * kTicketSite;
+  a.hflag = op->halt.dev;
 
   std::vector<int> order(ns);
   std::iota(order.begin(), order.end(), 0);
@@ -2422,34 +2464,26 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
                    [&](int i, int j) { return op->sigma[i] < op->sigma[j]; });
   BcgState h{};
   h.sigma0 = op->sigma[order[0]];
-  h.eps2 = prm.tol * prm.tol;  // scaled by |b|^2 in the init kernel
-  h.al_prev = double2{1.0, 0.0};
-  h.be_prev = double2{0.0, 0.0};
-  h.max_iter = prm.max_iter;
+  h.tol2 = prm.tol * prm.tol;
+  h.max_iter = std::max(0, int(prm.max_iter));
   h.ns = ns;
-  h.upd_launch = -1;
+  h.rot[0].fresh = 1;
   for (int j = 0; j < ns; ++j) {
     h.s[j] = op->sigma[order[j]] - h.sigma0;
-    h.z[j] = h.z_old[j] = h.tau[j] = double2{1.0, 0.0};
-    h.active[j] = 1;
+    h.rot[0].z[j] = h.rot[0].zo[j] = h.rot[0].tau[j] = double2{1.0, 0.0};
+    h.rot[0].active[j] = 1;
     h.freeze_iter[j] = -1;
     h.orig[j] = order[j];
   }
   HIP_TRY(hipMemcpyAsync(a.st, &h, sizeof h, hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_bcg_init(a, s));
-  const int G = std::max(1, prm.poll_every);
-  int launched = 0;
-  bool done = prm.max_iter <= 0;
-  while (!done) {
-    for (int g = 0; g < G; ++g) {
-      HIP_TRY(launch_bcg_iteration(a, launched, s));
-      ++launched;
-    }
-    int halt = 0;
-    HIP_TRY(hipMemcpyAsync(&halt, &a.st->halt, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (halt || launched >= prm.max_iter + G) done = true;
-  }
+  HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve sets the halt word now
+  __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
+  HIP_TRY(launch_bcg_start(a, s));
+  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int launch) {
+    a.par = launch & 1;
+    return launch_bcg_iteration(a, s);
+  });
+  if (rc != MSC_OK) return rc;
   HIP_TRY(hipMemcpyAsync(&h, a.st, sizeof h, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   std::vector<double> rel(ns, 0.0);
@@ -2467,7 +2501,7 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
   }
   bool all_ok = true;
   for (int j = 0; j < ns; ++j)
-    if (h.iter > 0 && h.active_next[j]) all_ok = false;  // still advanced at the end
+    if (h.iter > 0 && h.at_end[j]) all_ok = false;  // still advanced at the end
   if (prm.verify)
     for (int k = 0; k < ns; ++k)
       if (!(rel[k] <= prm.tol)) all_ok = false;
@@ -2629,13 +2663,8 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
     HIP_TRY(hipMalloc(&op->rws, need));
     op->rws_bytes = need;
   }
-  if (!op->r_halt) {
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&op->r_halt), 2 * sizeof(int),
-                          hipHostMallocMapped | hipHostMallocCoherent));
-    HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&op->d_r_halt), op->r_halt, 0));
-  }
-  for (auto& e : op->r_ev)
-    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  rc = ensure_halt(op->halt);
+  if (rc != MSC_OK) return rc;
   unsigned char* cur = static_cast<unsigned char*>(op->rws);
   RealArgs a{};
   a.n = n;
@@ -2658,7 +2687,7 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
   double* d_res2 = reinterpret_cast<double*>(cur);
   a.partial = op->scratch.partial;
   a.tickets = op->scratch.tickets + 13 * kTicketSite;
-  a.hflag = op->d_r_halt;
+  a.hflag = op->halt.dev;
 
   std::vector<int> order(ns);
   std::iota(order.begin(), order.end(), 0);
@@ -2679,28 +2708,14 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
     h.orig[j] = order[j];
   }
   HIP_TRY(hipMemcpyAsync(a.st, &h, sizeof h, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve writes the halt word now
-  __atomic_store_n(op->r_halt, 0, __ATOMIC_RELEASE);
+  HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve sets the halt word now
+  __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
   HIP_TRY(launch_real_start(prec, a, s));
-  // chunks of poll_every iterations; the halt word of one chunk is read once the next one
-  // is queued
-  const int G = std::max(1, prm.poll_every);
-  int launched = 0;
-  bool done = false;
-  for (int chunk = 0; !done; ++chunk) {
-    for (int g = 0; g < G; ++g) {
-      a.par = launched & 1;
-      HIP_TRY(launch_real_iteration(prec, a, s));
-      ++launched;
-    }
-    const int slot = chunk & 1;
-    HIP_TRY(hipEventRecord(op->r_ev[slot], s));
-    if (chunk >= 1) {
-      HIP_TRY(hipEventSynchronize(op->r_ev[slot ^ 1]));
-      if (__atomic_load_n(op->r_halt, __ATOMIC_ACQUIRE)) done = true;
-    }
-    if (launched >= h.max_iter + 2 * G) done = true;
-  }
+  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int launch) {
+    a.par = launch & 1;
+    return launch_real_iteration(prec, a, s);
+  });
+  if (rc != MSC_OK) return rc;
   HIP_TRY(hipMemcpyAsync(&h, a.st, sizeof h, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   std::vector<double> rel(ns, 0.0);
@@ -2825,8 +2840,8 @@ void msc_op_destroy(msc_op op) {
   if (op->bcg) (void)hipFree(op->bcg);
   if (op->osb) (void)hipFree(op->osb);
   if (op->rws) (void)hipFree(op->rws);
-  if (op->r_halt) (void)hipHostFree(op->r_halt);
-  for (auto& e : op->r_ev)
+  if (op->halt.host) (void)hipHostFree(op->halt.host);
+  for (auto& e : op->halt.ev)
     if (e) (void)hipEventDestroy(e);
   dfree(op->rval64);
   dfree(op->rval32);

@@ -214,6 +214,13 @@ struct Workspace {
   hipEvent_t ev[2] = {nullptr, nullptr};
 };
 
+// A host-coherent word that kernels set and the host reads after an event.
+struct HaltWord {
+  int* host = nullptr;
+  int* dev = nullptr;       // its device address
+  hipEvent_t ev[2] = {nullptr, nullptr};
+};
+
 struct BssState;
 
 // Buffers of the batched single-shift CG (mp vectors of n each).
@@ -262,9 +269,7 @@ struct msc_op_s {
   int real_state = 0;            // 0 not checked, 1 real (copies built), -1 not real
   void* rws = nullptr;           // real solve buffers
   size_t rws_bytes = 0;
-  int* r_halt = nullptr;         // host-coherent halt word of the real solve
-  int* d_r_halt = nullptr;       // its device address
-  hipEvent_t r_ev[2] = {nullptr, nullptr};
+  msc::HaltWord halt;            // of the real and the BiCGStab solve
   double2* yadj = nullptr;       // adjoint solutions, ns * n complex128
   size_t yadj_count = 0;
   double* adj_small = nullptr;   // 256 doubles: Gram sums and shift factors
@@ -416,36 +421,50 @@ hipError_t launch_apply_noalloc(ApplyArgs a, void* base, hipStream_t s);
 int default_grid(int64_t n, int lanes);
 
 // bicgstab.hip -- multishift BiCGStab for a general A (complex FP64 scalars)
-struct BcgCoef {
-  double2 xp, xs;          // x(s) += xp p(s) + xs s
-  double2 pr, pp, po, ps;  // p(s) <- pr r' + pp p(s) + po r + ps s
+constexpr int kBcgGrid = 1024;               // most workgroups of its kernels
+constexpr int kBcgSteps = 4;                 // steps of the shifts folded into one application
+constexpr int kBcgRing = kBcgSteps + 1;      // r_n in slot n % kBcgRing, s_n in n % kBcgSteps
+constexpr int kBcgTerms = 2 * kBcgSteps + 2; // p(s), r_0 .. r_D, s_0 .. s_{D-1}
+// State at the start of iteration n (indexed by n's parity; BA writes the other one, which
+// BB reads).  Shifts sorted ascending, j = 0 driving.
+struct BcgRot {
+  double2 rho, al, be;     // rho_n-1, al_{n-2}, be_{n-1} (in the one BB reads: of n)
+  int iter, halt;          // n; 1: nothing left to do
+  int m, fresh;            // steps composed so far; 1: x(s) and p(s) never written
+  double2 z[kMaxShifts], zo[kMaxShifts], tau[kMaxShifts];
+  // p(s) now is sum_e cp[e] term_e and x(s) gained sum_e cx[e] term_e
+  double2 cx[kBcgTerms][kMaxShifts], cp[kBcgTerms][kMaxShifts];
+  int active[kMaxShifts], took[kMaxShifts];  // took: part of a composed step
 };
 struct BcgState {
-  double sigma0, bnorm2, eps2, R;
-  double2 rho, alpha, omega, beta, al_prev, be_prev;
-  int iter, max_iter, halt, status, rotate, upd_launch, ns, pad_;
-  double s[kMaxShifts];              // sigma_j - sigma0, shifts sorted ascending
-  double2 z[kMaxShifts], z_old[kMaxShifts], z_new[kMaxShifts];
-  double2 tau[kMaxShifts], tau_new[kMaxShifts];
-  double2 al_s[kMaxShifts], om_s[kMaxShifts];
-  BcgCoef cf[kMaxShifts];
-  int active[kMaxShifts], active_next[kMaxShifts], freeze_iter[kMaxShifts], orig[kMaxShifts];
+  double sigma0, tol2, bnorm2;
+  double2 alpha;                     // BB -> the next BA
+  int iter, max_iter, status, ns, bad, pad_;  // bad: BB found w^H v = 0 or not finite
+  double s[kMaxShifts];              // sigma_j - sigma0
+  double2 zn[kMaxShifts], als[kMaxShifts];    // z_{n+1}, al(s): BB -> the next BA
+  int freeze_iter[kMaxShifts], orig[kMaxShifts];
+  int at_end[kMaxShifts];            // still advanced when the sequence halted
+  BcgRot rot[2];
 };
 struct BcgArgs {
   int64_t n;
-  int ns, lanes, par;
+  int lanes, par;
   Csr<double2> m;
+  int sell;                // read the sliced copy
+  int64_t nslices;
+  Sell<double2> sm;
   const double2* b;       // right-hand side, also the shadow vector
   double2* x;             // caller's x, shift-major, caller order
-  double2* r[2];          // r_n and r_{n+1} alternate
-  double2 *p, *v, *s, *t;
+  double2* r;             // kBcgRing residuals
+  double2* s;             // kBcgSteps half-step residuals
+  double2 *p[2], *v[2], *t;
   double2* pk;            // ns directions, sorted order
   BcgState* st;
-  double* partial;        // >= 4 kMaxGrid doubles
-  unsigned* tickets;      // one ticket site
+  double* partial;        // >= 10 kBcgGrid doubles
+  int* hflag;             // host-coherent word: 1 once halted
 };
-hipError_t launch_bcg_init(const BcgArgs& a, hipStream_t s);
-hipError_t launch_bcg_iteration(const BcgArgs& a, int launch, hipStream_t s);
+hipError_t launch_bcg_start(const BcgArgs& a, hipStream_t s);
+hipError_t launch_bcg_iteration(const BcgArgs& a, hipStream_t s);
 
 // real_ms.hip -- multishift CG for a real symmetric positive-definite A
 template <class T> struct SellReal {

@@ -384,15 +384,16 @@ __global__ __launch_bounds__(kBlock) void k_r_iter(RealArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) st->rot[a.par ^ 1].halt = 1;
     return;
   }
-  // partials first: their way overlaps the first row's
+  // the previous kernel's partials: plain loads, which the XCD's L2 serves to all but its
+  // first workgroup
   constexpr int kPer = kRealGrid / kBlock;
   double g = 0.0, d = 0.0, gv[kPer], dv[kPer];
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     const int i = threadIdx.x + u * kBlock;
     const bool in = i < int(gridDim.x);
-    gv[u] = in ? load_agent(&r_region(a, a.par, 0)[i]) : 0.0;
-    dv[u] = in ? load_agent(&r_region(a, a.par, 1)[i]) : 0.0;
+    gv[u] = in ? r_region(a, a.par, 0)[i] : 0.0;
+    dv[u] = in ? r_region(a, a.par, 1)[i] : 0.0;
   }
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
@@ -513,6 +514,9 @@ __global__ void k_r_extract(const double2* __restrict__ v64, double* __restrict_
   if (local) atomicMax(imax, local);
 }
 
+// Workgroups for the rows, a multiple of the XCD count, at most kRealGrid: more of them wait
+// on longer sums of partials (1000 x 1000: 21.5 / 14.8 / 12.5 / 14.6 ms a solve with 256 /
+// 512 / 1024 / 2048).
 int r_grid(int64_t nslices) {
   const int64_t g = (nslices + kBlock / kSlice - 1) / (kBlock / kSlice);
   return int((std::min<int64_t>(std::max<int64_t>(g, 1), kRealGrid) + kXcds - 1) / kXcds * kXcds);
