@@ -107,7 +107,9 @@ __device__ __forceinline__ void stencil_site_c(const Stencil<cplx<R>>& op, uint3
     const bool kept = CAR && mu == 3;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      U[k] = wm[int64_t(k) * vol + s];
+      // a carried t link is read this once: the streaming hint leaves the L2 to the links
+      // and values that the neighbours read again
+      U[k] = kept ? ld_stream(&wm[int64_t(k) * vol + s]) : wm[int64_t(k) * vol + s];
       if (kept)
         B[k] = car->u[k];
       else
