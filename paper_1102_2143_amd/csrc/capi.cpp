@@ -58,13 +58,8 @@ template <class T> void dfree(T*& p) {
 }
 
 void free_workspace(Workspace& w) {
-  for (void* q : {w.r, w.p[0], w.p[1], w.t, w.pk, w.r32, w.p32[0], w.p32[1], w.t32, w.pk32,
-                  w.pkeep0})
+  for (void* q : {w.ring, w.u, w.s, w.pk, w.ring32, w.u32, w.s32, w.pk32})
     if (q) (void)hipFree(q);
-  for (void*& q : w.rkeep) {
-    if (q) (void)hipFree(q);
-    q = nullptr;
-  }
   dfree(w.t64);
   dfree(w.u64);
   dfree(w.st);
@@ -93,18 +88,16 @@ msc_status ensure_scratch(msc_op op, hipStream_t s) {
 msc_status ensure_workspace(msc_op op, int prec, int ns) {
   Workspace& w = op->ws;
   const size_t n = size_t(op->n);
-  const size_t nk = size_t(std::max(ns - 1, 1));
+  // A given alternates two buffers of w and of s
+  const size_t two = op->kind == MSC_A_MHM ? 1 : 2;
   if (!(w.st && w.ns >= ns && w.n == n)) {
     free_workspace(w);
-    HIP_TRY(hipMalloc(&w.r, sizeof(double2) * n));
-    HIP_TRY(hipMalloc(&w.p[0], sizeof(double2) * n));
-    HIP_TRY(hipMalloc(&w.p[1], sizeof(double2) * n));
-    HIP_TRY(hipMalloc(&w.t, sizeof(double2) * n));
-    HIP_TRY(hipMalloc(&w.pk, sizeof(double2) * n * nk));
+    HIP_TRY(hipMalloc(&w.ring, sizeof(double2) * n * kRing));
+    HIP_TRY(hipMalloc(&w.u, sizeof(double2) * n * two));
+    HIP_TRY(hipMalloc(&w.s, sizeof(double2) * n * two));
+    HIP_TRY(hipMalloc(&w.pk, sizeof(double2) * n * size_t(ns)));
     HIP_TRY(dalloc(&w.t64, n));
     HIP_TRY(dalloc(&w.u64, n * 8));
-    for (auto& q : w.rkeep) HIP_TRY(hipMalloc(&q, sizeof(double2) * n));
-    HIP_TRY(hipMalloc(&w.pkeep0, sizeof(double2) * n));
     HIP_TRY(dalloc(&w.st, 1));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&w.h_halt), 4 * sizeof(int),
                           hipHostMallocMapped | hipHostMallocCoherent));
@@ -115,13 +108,11 @@ msc_status ensure_workspace(msc_op op, int prec, int ns) {
     w.ns = ns;
     w.prec = MSC_PREC_FP64;
   }
-  if (prec == MSC_PREC_MIXED && !w.r32) {
-    const size_t wn = std::max<size_t>(size_t(w.ns) - 1, 1);
-    HIP_TRY(hipMalloc(&w.r32, sizeof(float2) * n));
-    HIP_TRY(hipMalloc(&w.p32[0], sizeof(float2) * n));
-    HIP_TRY(hipMalloc(&w.p32[1], sizeof(float2) * n));
-    HIP_TRY(hipMalloc(&w.t32, sizeof(float2) * n));
-    HIP_TRY(hipMalloc(&w.pk32, sizeof(float2) * n * wn));
+  if (prec == MSC_PREC_MIXED && !w.ring32) {
+    HIP_TRY(hipMalloc(&w.ring32, sizeof(float2) * n * kRing));
+    HIP_TRY(hipMalloc(&w.u32, sizeof(float2) * n * two));
+    HIP_TRY(hipMalloc(&w.s32, sizeof(float2) * n * two));
+    HIP_TRY(hipMalloc(&w.pk32, sizeof(float2) * n * size_t(w.ns)));
     w.prec = MSC_PREC_MIXED;
   }
   return MSC_OK;
@@ -264,6 +255,20 @@ SweepOrder detect_order(const int64_t* d_rowptr, const int32_t* d_col, int64_t n
   return lattice_order(nslices, common[common.size() - 2], common.back());
 }
 
+// The Krylov vectors of one precision (V: double2 or float2).
+template <class V>
+void set_vectors(MsArgs& a, msc_op op, void* ring, void* u, void* s, void* pk) {
+  a.ring = ring;
+  a.pk = pk;
+  const bool two = op->kind != MSC_A_MHM && a.sell;
+  V *u0 = static_cast<V*>(u), *s0 = static_cast<V*>(s);
+  a.u = u0;
+  a.w[0] = u0;
+  a.w[1] = two && u0 ? u0 + op->n : nullptr;
+  a.s[0] = s0;
+  a.s[1] = two && s0 ? s0 + op->n : nullptr;
+}
+
 MsArgs make_args(msc_op op, int lanes, const double* d_b, double* d_x) {
   MsArgs a{};
   a.kind = op->kind;
@@ -295,16 +300,8 @@ MsArgs make_args(msc_op op, int lanes, const double* d_b, double* d_x) {
   a.w32 = op->w32;
   a.b = reinterpret_cast<const double2*>(d_b);
   a.x = reinterpret_cast<double2*>(d_x);
-  a.r = op->ws.r;
-  a.pb[0] = op->ws.p[0];
-  a.pb[1] = op->ws.p[1];
-  a.t = op->ws.t;
-  a.pk = op->ws.pk;
-  for (int k = 0; k < kMaxSteps - 1; ++k) a.rkeep[k] = op->ws.rkeep[k];  // complex64 in phase 2
-  a.pkeep0 = op->ws.pkeep0;
+  set_vectors<double2>(a, op, op->ws.ring, op->ws.u, op->ws.s, op->ws.pk);
   a.hflag = op->ws.d_halt;
-  a.steps = 1;
-  a.defer_ok = 0;
   a.sample = -1;
   a.t64 = op->ws.t64;
   a.st = op->ws.st;
@@ -343,75 +340,49 @@ ApplyArgs apply_args(msc_op op, int prec, int lanes) {
   return a;
 }
 
-// Which FP64 heads on the links form their product by the recurrence: all but the first
-// launch and the launches kTrEvery / 2 mod kTrEvery (off the timing samples' positions,
-// which start at multiples of 128); and how many of the first n launches do.
-bool tr_launch(bool eligible, int launch) {
-  return eligible && launch != 0 && launch % kTrEvery != kTrEvery / 2;
-}
-int tr_launches(int n) {
-  return n <= 1 ? 0 : n - 1 - (n + kTrEvery / 2 - 1) / kTrEvery;
-}
-
-// Algorithmic HBM bytes of one multishift iteration (each array touched once, gathers
-// counted once), per row: see the byte model in the design notes of the repository.
-// Algorithmic bytes of one launch: K1 (t = M p), K2 (r <- r - a (M^H t + sigma0 p)), the
-// all-shift update with `act` active shifts, and the head that fuses the update with K1
-// (the old p is read once for both).
-struct KernelBytes {
-  double k1, k2, upd, head;
-};
-// launch with `act` active shifts; ib / ibh: bytes per column index of the copies of the
-// operator's matrix and of M^H that the SpMVs read.
-// `kept`: residual vectors the head's update writes (a deferring head keeps r) or reads
-// back (an applying head after deferred steps).
-// Matrix bytes of one application of M (or A) and of M^H in precision `prec`: the stored
-// copy (value + index per entry, 4-byte row pointers), or for the matrix-free staggered
-// operator the links, each read once: 4 links x 9 values per site = 12 values per row.
+// Algorithmic HBM bytes (each array touched once, gathers counted once; see the byte model
+// in the design notes of the repository).  Matrix bytes of one application of M (or A) and
+// of M^H in precision `prec`: the stored copy (value + index per entry, ib / ibh bytes an
+// index, 4-byte row pointers), or for the matrix-free staggered operator the links, each read
+// once: 4 links x 9 (two rows: 6) values per site = 12 (8) values per row.
 struct MatBytes {
   double m, mh;
 };
 MatBytes mat_bytes(int kind, int prec, double n, double nnz, double nnz_h, double ib, double ibh,
                    int stencil) {
   const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
-  // links: each read once per site and direction, 3 or 2 rows of 3 values: 12 or 8
-  // values per row of the operator
-  if (stencil) return MatBytes{4.0 * stencil * w * n, 4.0 * stencil * w * n};
-  return MatBytes{nnz * (w + ib) + 4.0 * (n + 1),
-                  kind == MSC_A_MHM ? nnz_h * (w + ibh) + 4.0 * (n + 1) : 0.0};
+  if (stencil) {
+    const double b = 4.0 * stencil * w * n;  // 4 links x 3 values per row and link row
+    return {b, b};
+  }
+  return {nnz * (w + ib) + 4.0 * (n + 1), kind == MSC_A_MHM ? nnz_h * (w + ibh) + 4.0 * (n + 1) : 0.0};
 }
 
-// x0b: bytes per row of x_0 and of its kept direction that the update moves (an applying
-// head reads and writes x_0, 32, and reads the kept direction after deferred steps; the
-// first deferring head of a cycle writes it).
-KernelBytes kernel_bytes(int kind, int prec, double n, const MatBytes& mb, double act,
-                         bool pending, int kept, double x0b) {
+// Bytes of one iteration's operator halves: K1 reads r and writes u; K2 reads u and r, reads
+// and writes s and writes the next r; the single kernel of A given (one) reads and writes r,
+// w and s.
+struct HalfBytes {
+  double k1, k2;
+};
+HalfBytes half_bytes(bool one, int prec, double n, const MatBytes& mb) {
   const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
-  KernelBytes b{};
-  b.k1 = mb.m + 2.0 * n * w;
-  b.k2 = (kind == MSC_A_MHM ? mb.mh + n * w : n * w) + 3.0 * n * w;
-  b.upd = pending ? n * (3.0 * w + x0b) + act * n * (32.0 + 2.0 * w) + kept * n * w : 0.0;
-  b.head = b.k1 + (pending ? b.upd - n * w : 0.0);
-  return b;
+  if (one) return {mb.m + 6.0 * w * n, 0.0};
+  return {mb.m + 2.0 * w * n, mb.mh + 5.0 * w * n};
 }
 
-// act_sum: x_j/p_j row-vector updates performed (shifts listed, summed over the heads);
-// kept: heads that kept r for a deferred step or read it back.
-// x0_total: bytes per row of x_0 and its kept direction summed over the heads (negative:
-// x_0 read and written in every iteration, 32 bytes per row each).
-double iter_bytes(int kind, int prec, double n, const MatBytes& mb, double act_sum,
-                  double iters, double kept, double x0_total = -1.0) {
-  const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;   // Krylov vector element
-  const double mat = mb.m + mb.mh;
-  double vec;
-  if (kind == MSC_A_MHM)
-    vec = n * (w + w) + n * (w + w + 2 * w);  // K1: p gather, t write; K2: t gather, p, r r/w
-  else
-    vec = n * (w + w) + n * (w + w + 2 * w);  // K1: p, t; K2: t, p, r r/w
-  vec += n * (w + 2 * w);                      // K3: r, p r/w
-  const double x0 = x0_total < 0.0 ? 32.0 * n * iters : x0_total * n;
-  const double per_shift = n * (32.0 + 2 * w); // x_j r/w (complex128) + p_j r/w
-  return iters * (mat + vec) + x0 + act_sum * per_shift + kept * n * w;
+// Bytes of applying composed steps: x_j (complex128) and p_j in and out, the kept residuals.
+double flush_bytes(int prec, double n, double shifts, double kept) {
+  const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
+  return n * (shifts * (32.0 + 2.0 * w) + kept * w);
+}
+
+// Bytes of `iters` iterations of one right-hand side of a batched solve: p gather and t write,
+// t gather, p and r in and out, then r and p in and out again (the direction's own kernel),
+// act_sum updates of a shift's vectors, x0 bytes a row for x_0, kept residuals.
+double batch_bytes(int prec, double n, const MatBytes& mb, double act_sum, double iters, double kept,
+                   double x0) {
+  const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
+  return iters * (mb.m + mb.mh + 9.0 * w * n) + x0 * n + act_sum * n * (32.0 + 2 * w) + kept * n * w;
 }
 
 // Events for sampled per-kernel timing; destroyed with the pool.
@@ -480,6 +451,7 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
     }
   }
   const double ib = index_bytes(a64.sell, a64.s64), ibh = index_bytes(a64.sell, a64.sh64);
+  set_vectors<double2>(a64, op, op->ws.ring, op->ws.u, op->ws.s, op->ws.pk);
   MsArgs a32 = a64;
   if (a32.stencil != 0) {  // the complex64 kernels' tile span
     a32.ord = op->order_sites;
@@ -493,12 +465,10 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
       a32.stencil = 3;
   }
   const bool mixed = prec == MSC_PREC_MIXED;
+  prepare_iteration(MSC_PREC_FP64, a64);
   if (mixed) {
-    a32.r = op->ws.r32;
-    a32.pb[0] = op->ws.p32[0];
-    a32.pb[1] = op->ws.p32[1];
-    a32.t = op->ws.t32;
-    a32.pk = op->ws.pk32;
+    set_vectors<float2>(a32, op, op->ws.ring32, op->ws.u32, op->ws.s32, op->ws.pk32);
+    prepare_iteration(MSC_PREC_MIXED, a32);
   }
 
   std::vector<int> order(ns);
@@ -507,19 +477,17 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
                    [&](int i, int j) { return op->sigma[i] < op->sigma[j]; });
   SolveState h{};
   h.sigma0 = op->sigma[order[0]];
-  h.eps2 = tol_stop * tol_stop;  // scaled by |b|^2 in the init kernel
+  h.tol2 = tol_stop * tol_stop;
   // a mixed solve runs in FP64 until |r| <= switch_tol |b|, then in complex64
   const double sw = mixed ? std::max(prm.switch_tol, tol_stop) : 0.0;
-  h.sw_eps2 = sw * sw;
-  h.a_prev = 1.0;
-  h.b = 0.0;
-  h.max_iter = prm.max_iter;
+  h.sw2 = sw * sw;
+  h.max_iter = std::max(0, int(prm.max_iter));
   h.ns = ns;
   h.freeze = prm.freeze ? 1 : 0;
+  h.rot[0].fresh = 1;
   for (int j = 0; j < ns; ++j) {
     h.s[j] = op->sigma[order[j]] - h.sigma0;
-    h.rot[0].zeta[j] = 1.0;
-    h.zeta_prev[j] = 1.0;
+    h.rot[0].zeta[j] = h.rot[0].zeta_prev[j] = 1.0;
     h.rot[0].active[j] = 1;
     h.freeze_iter[j] = -1;
     h.orig[j] = order[j];
@@ -527,21 +495,24 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
   HIP_TRY(hipMemcpyAsync(op->ws.st, &h, sizeof h, hipMemcpyHostToDevice, s));
   __atomic_store_n(op->ws.h_halt, 0, __ATOMIC_RELEASE);  // no kernel of this op is in flight
   a64.par = a32.par = 0;
-  HIP_TRY(launch_init(MSC_PREC_FP64, a64, s));
+  HIP_TRY(launch_init(a64, s));
 
   const int G = std::max(1, prm.poll_every);
+  const int steps = std::min(std::max(int(prm.update_steps), 1), kMaxSteps);
   int phase = MSC_PREC_FP64;
   MsArgs* cur = &a64;
   int launched = 0, chunk = 0, launched_at_switch = -1, iter_at_switch = -1;
-  bool done = prm.max_iter <= 0;
+  bool done = false;
+  int pending = 0;  // iterations since the composed steps were last applied
   EventPool pool;
   std::vector<int> sample_launch;
+  std::vector<char> sample_flush;  // the sampled iteration applied composed steps
   while (!done) {
     for (int g = 0; g < G; ++g) {
       hipEvent_t* ev = nullptr;
       cur->sample = -1;
-      // consecutive launches are sampled in runs as long as a folding cycle (heads that
-      // defer and the one that applies the folded steps), in both phases of a mixed solve;
+      // consecutive launches are sampled in runs as long as a folding cycle (the iterations
+      // that compose and the one that applies), in both phases of a mixed solve;
       // the FP64 phase of a mixed solve takes at most half of the records
       const int cap = mixed && phase == MSC_PREC_FP64 ? kMaxSamples / 2 : kMaxSamples;
       if (prm.timing > 0 && launched % prm.timing < std::max(2, prm.update_steps) &&
@@ -553,11 +524,13 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
         }
         cur->sample = int(sample_launch.size());
         sample_launch.push_back(launched);
+        sample_flush.push_back(pending + 1 >= steps ? 1 : 0);
       }
-      // iteration `launched` starts from the state rot[launched & 1]; in the complex64
-      // phase the reliable update (r recomputed in FP64 after the head has brought x_0 up
-      // to date) is launched every kRuCheck-th iteration and on its period: it runs on
-      // the period, or at a check when the recursive residual has fallen fast
+      // launch `launched` takes its iteration's state from rot[launched & 1]; in the complex64
+      // phase the reliable update (r recomputed in FP64, with x_0 brought up to date) is
+      // launched every kRuCheck-th iteration and on its period: it runs on the period, or at
+      // a check when the recursive residual has fallen fast
+      cur->launch = launched;
       cur->par = launched & 1;
       const int since = launched - launched_at_switch;
       const bool ru_period = phase == MSC_PREC_MIXED && prm.reliable_every > 0 && since > 0 &&
@@ -566,12 +539,10 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
                                     since > 0 && since % kRuCheck == 0);
       cur->ru_force = ru_period ? 1 : 0;
       cur->ru_check = ru ? 1 : 0;
-      // links, FP64: the head's product by the recurrence t' = M r + b t; a direct one in
-      // the first launch (no old t yet) and every kTrEvery launches
-      cur->t_rec = tr_launch(phase == MSC_PREC_FP64 && cur->stencil != 0, launched) ? 1 : 0;
-      cur->defer_ok = 1;
-      cur->steps = prm.update_steps;
-      HIP_TRY(launch_iteration(phase, *cur, s, ev, ru));
+      const bool flush = ++pending >= steps;
+      HIP_TRY(launch_iteration(phase, *cur, s, ev, flush));
+      if (flush) pending = 0;
+      cur->flushed = flush ? 1 : 0;
       ++launched;
     }
     const int slot = chunk & 1;
@@ -587,32 +558,34 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
           // end of the FP64 phase: drain, convert the Krylov vectors, continue in complex64
           HIP_TRY(hipStreamSynchronize(s));
           __atomic_store_n(op->ws.h_halt, 0, __ATOMIC_RELEASE);
-          HIP_TRY(hipMemcpy(&iter_at_switch, &op->ws.st->rot[launched & 1].iter, sizeof(int),
-                            hipMemcpyDeviceToHost));
+          HIP_TRY(hipMemcpy(&iter_at_switch, &op->ws.st->iter, sizeof(int), hipMemcpyDeviceToHost));
+          HIP_TRY(launch_final_flush(MSC_PREC_FP64, a64, s));
           a64.par = a32.par = launched & 1;
+          a32.launch = launched;
           HIP_TRY(launch_switch_to_mixed(a64, a32, ns, s));
           phase = MSC_PREC_MIXED;
           cur = &a32;
           launched_at_switch = launched;
           chunk = 0;
+          pending = 0;
         } else {
           done = true;
         }
       }
     }
-    if (launched >= prm.max_iter + 4 * G) done = true;
+    if (launched >= h.max_iter + 4 * G) done = true;
   }
+  HIP_TRY(launch_final_flush(phase, *cur, s));
   HIP_TRY(hipStreamSynchronize(s));
   HIP_TRY(hipMemcpy(&h, op->ws.st, sizeof h, hipMemcpyDeviceToHost));
-  const RotState& fin = h.rot[launched & 1];  // state after the last launched iteration
-  const int iters_fp64 = iter_at_switch >= 0 ? iter_at_switch : fin.iter;
+  const int iters = h.iter;
+  const int iters_fp64 = iter_at_switch >= 0 ? iter_at_switch : iters;
   if (info) {
     clear_timing(*info);
     // only iterations that did work are counted (the loop runs a little past the halt)
     const int first = launched_at_switch >= 0 ? launched_at_switch : 0;
-    const int useful_launches = first + (fin.iter - (iter_at_switch >= 0 ? iter_at_switch : 0));
-    // slot 2 (the separate update kernel) exists on the CSR path only
-    const int slots = a64.sell ? 2 : 3;
+    const int useful_launches = first + (iters - (iter_at_switch >= 0 ? iter_at_switch : 0));
+    const bool one = a64.sell && op->kind != MSC_A_MHM;  // a single kernel an iteration
     const double nn = double(op->n), nz = double(op->nnz), nzh = double(op->nnz_h);
     for (size_t q = 0; q < pool.groups.size(); ++q) {
       const int L = sample_launch[q];
@@ -624,30 +597,20 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
       const bool apart = mixed && !ph32;
       double* kms = apart ? info->fp64_kernel_ms : info->kernel_ms;
       double* kby = apart ? info->fp64_kernel_bytes : info->kernel_bytes;
-      for (int k = 0; k < slots; ++k) {
+      // the application of the composed steps counts with the first half, but apart on the CSR
+      const int applied = a64.sell ? 0 : 2;
+      for (int k = 0; k < 3; ++k) {
+        if ((k == 1 && one) || (k == 2 && !sample_flush[q])) continue;
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, pool.groups[q][2 * k], pool.groups[q][2 * k + 1]));
-        kms[k] += ms;
+        kms[k == 2 ? applied : k] += ms;
       }
-      // the head's update mode and the shifts it listed, as recorded by the head itself
-      const bool pending = !(L == 0 || (ph32 && L == launched_at_switch));
-      const int act = h.smp_nact[q];
-      // an applying head reads the m kept residuals (the deferring ones leave theirs in
-      // the ring)
-      const int kept = h.smp_mode[q] == 1 ? 0 : h.smp_m[q];
       const int phq = ph32 ? MSC_PREC_MIXED : MSC_PREC_FP64;
-      const double wq = ph32 ? 8.0 : 16.0;
-      const double x0b = h.smp_mode[q] == 0 ? 32.0 + (h.smp_m[q] > 0 ? wq : 0.0)
-                                            : (h.smp_m[q] == 0 ? wq : 0.0);
-      const KernelBytes kb =
-          kernel_bytes(op->kind, phq, nn, mat_bytes(op->kind, phq, nn, nz, nzh, ib, ibh,
-                                                   phq == MSC_PREC_FP64 ? a64.stencil : a32.stencil),
-                       double(act), pending, kept, x0b);
-      // a recurrence head also reads the old t (its own row)
-      const bool trq = tr_launch(phq == MSC_PREC_FP64 && a64.stencil != 0, L);
-      kby[0] += (a64.sell ? kb.head : kb.k1) + (trq ? 16.0 * nn : 0.0);
-      kby[1] += kb.k2;
-      if (!a64.sell) kby[2] += kb.upd;
+      const HalfBytes hb = half_bytes(
+          one, phq, nn, mat_bytes(op->kind, phq, nn, nz, nzh, ib, ibh, ph32 ? a32.stencil : a64.stencil));
+      kby[0] += hb.k1;
+      kby[1] += hb.k2;
+      if (sample_flush[q]) kby[applied] += flush_bytes(phq, nn, h.smp_nact[q], h.smp_m[q]);
       (apart ? info->fp64_kernel_samples : info->kernel_samples) += 1;
     }
   }
@@ -656,47 +619,30 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
   if (info && info->freeze_iter) {
     for (int j = 0; j < ns; ++j) {
       int fi = h.freeze_iter[j];
-      if (j == 0 || (fi < 0 && h.s[j] == 0.0)) fi = (fin.R <= h.eps2) ? fin.iter : -1;
+      if (j == 0 || (fi < 0 && h.s[j] == 0.0)) fi = (h.R <= h.eps2) ? iters : -1;
       info->freeze_iter[order[j]] = fi;
     }
   }
-  *iters_out = fin.iter;
-  *status_out = fin.status;
+  *iters_out = iters;
+  *status_out = h.status;
   if (info) info->n_reliable = h.n_reliable;
 
-  // shift-vector updates and kept-r passes counted by the heads, per phase
-  const double act64 = h.n_shift_upd[0], act32 = h.n_shift_upd[1];
-  const double kept64 = h.n_two[0], kept32 = h.n_two[1];
   const double nn = double(op->n), nz = double(op->nnz), nzh = double(op->nnz_h);
-  // x_0 (and its kept direction) per phase: applying heads read and write x_0, and each
-  // cycle with deferred steps writes and reads the kept direction once
-  const double x064 = 32.0 * h.n_apply[0] + 2.0 * 16.0 * h.n_keep0[0];
-  const double x032 = 32.0 * h.n_apply[1] + 2.0 * 8.0 * h.n_keep0[1];
-  *bytes_out = iter_bytes(op->kind, MSC_PREC_FP64, nn,
-                          mat_bytes(op->kind, MSC_PREC_FP64, nn, nz, nzh, ib, ibh, a64.stencil), act64,
-                          double(iters_fp64), kept64, x064) +
-               iter_bytes(op->kind, MSC_PREC_MIXED, nn,
-                          mat_bytes(op->kind, MSC_PREC_MIXED, nn, nz, nzh, ib, ibh, a32.stencil), act32,
-                          double(fin.iter - iters_fp64), kept32, x032) +
-               (a64.stencil != 0 ? 16.0 * nn * double(tr_launches(iters_fp64)) : 0.0) +
-               double(h.n_reliable) *
-                   ((a32.stencil != 0
-                         ? [&] {
-                             // the reliable update reads the FP64 links
-                             const MatBytes rb = mat_bytes(op->kind, MSC_PREC_FP64, nn, nz, nzh, ib,
-                                                           ibh, a32.stencil);
-                             return rb.m + rb.mh;
-                           }()
-                         : nz * (16.0 + ib) + nzh * (16.0 + ibh) +
-                               4.0 * (nn + 1) * (op->kind == MSC_A_MHM ? 2.0 : 1.0)) +
-                    nn * (16.0 * 3 + 8.0));
-  // the fused head reads the old direction once for the update and the product
-  if (a64.sell) *bytes_out -= nn * (16.0 * iters_fp64 + 8.0 * (fin.iter - iters_fp64));
+  auto phase_bytes = [&](int ph, const MsArgs& a, double count, int q) {
+    const HalfBytes hb = half_bytes(a.sell && op->kind != MSC_A_MHM, ph, nn,
+                                    mat_bytes(op->kind, ph, nn, nz, nzh, ib, ibh, a.stencil));
+    return count * (hb.k1 + hb.k2) + flush_bytes(ph, nn, h.n_upd[q], h.n_kept[q]);
+  };
+  // a reliable update reads the FP64 operator, x_0, b and s and writes r
+  const MatBytes rb = mat_bytes(op->kind, MSC_PREC_FP64, nn, nz, nzh, ib, ibh, a32.stencil);
+  *bytes_out = phase_bytes(MSC_PREC_FP64, a64, double(iters_fp64), 0) +
+               phase_bytes(MSC_PREC_MIXED, a32, double(iters - iters_fp64), 1) +
+               double(h.n_reliable) * (rb.m + rb.mh + nn * (16.0 * 3 + 8.0 * 2));
   if (info) info->iters_fp64 = iters_fp64;
 
   rel_out->assign(ns, 0.0);
   *bnorm_out = std::sqrt(h.bnorm2);
-  if (prm.verify && fin.status == 0) {
+  if (prm.verify && h.status == 0) {
     const double bn = std::sqrt(h.bnorm2);
     for (int k0 = 0; k0 < ns; k0 += 8) {
       const int kc = std::min(8, ns - k0);
@@ -1523,10 +1469,10 @@ struct BatchRun {
           const double nn = double(n), nz = double(op->nnz), nzh = double(op->nnz_h);
           const double ib = index_bytes(sys[s].sell, sys[s].s64);
           const double ibh = index_bytes(sys[s].sell, sys[s].sh64);
-          I.alg_bytes = iter_bytes(op->kind, MSC_PREC_FP64, nn,
+          I.alg_bytes = batch_bytes(MSC_PREC_FP64, nn,
                                    mat_bytes(op->kind, MSC_PREC_FP64, nn, nz, nzh, ib, ibh, false),
                                    act64, i64, kept64, x064) +
-                        iter_bytes(op->kind, MSC_PREC_MIXED, nn,
+                        batch_bytes(MSC_PREC_MIXED, nn,
                                    mat_bytes(op->kind, MSC_PREC_MIXED, nn, nz, nzh, ib, ibh, false),
                                    act32, it - i64, kept32, x032) -
                         (double(nrhs[s]) - 1.0) / double(nrhs[s]) *
@@ -2164,7 +2110,7 @@ msc_status msc_op_apply(msc_op op, int32_t prec, const double* d_in, double* d_o
   a.in = reinterpret_cast<const double2*>(d_in);
   a.out = reinterpret_cast<double2*>(d_out);
   a.shift = shift;
-  a.tmp = prec == MSC_PREC_MIXED ? op->ws.t : static_cast<void*>(op->ws.t64);
+  a.tmp = op->ws.t64;
   HIP_TRY(launch_apply(a, s));
   HIP_TRY(hipStreamSynchronize(s));
   return MSC_OK;

@@ -196,18 +196,20 @@ __device__ __forceinline__ bool arrive_last(unsigned* site) {
 // Workgroups are dispatched round-robin over the XCDs.  Renumber them so that the
 // workgroups of one XCD own one contiguous block of rows (its L2 then serves the
 // neighbouring-row gathers of that block).  Requires gridDim.x % 8 == 0 to permute.
-__device__ __forceinline__ int logical_block() {
-  const int g = gridDim.x, b = blockIdx.x;
+// The functions below take the number of workgroups that share the rows; by default all.
+__device__ __forceinline__ int logical_block(int g = gridDim.x) {
+  const int b = blockIdx.x;
   if ((g & (kXcds - 1)) != 0) return b;
   return (b & (kXcds - 1)) * (g / kXcds) + b / kXcds;
 }
 
 // Contiguous [beg, end) slice of `n` items for this workgroup, in units of `step`.
-__device__ __forceinline__ void block_range(int64_t n, int step, int64_t& beg, int64_t& end) {
-  const int64_t g = gridDim.x;
+__device__ __forceinline__ void block_range(int64_t n, int step, int64_t& beg, int64_t& end,
+                                            int workgroups = gridDim.x) {
+  const int64_t g = workgroups;
   const int64_t units = (n + step - 1) / step;
   const int64_t per = (units + g - 1) / g;
-  beg = int64_t(logical_block()) * per * step;
+  beg = int64_t(logical_block(workgroups)) * per * step;
   end = beg + per * step;
   if (end > n) end = n;
   if (beg > n) beg = n;
@@ -245,10 +247,10 @@ struct Sweep {
 };
 
 // wpb: waves per workgroup, each taking one slice at a time.
-__device__ __forceinline__ Sweep make_sweep(int64_t nslices, const SweepOrder& o, int wpb) {
+__device__ __forceinline__ Sweep make_sweep(int64_t nslices, const SweepOrder& o, int wpb,
+                                            int g = gridDim.x) {
   Sweep w{};
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
-  const int g = gridDim.x;
   if (o.on && (g % kXcds) == 0) {
     const int x = int(blockIdx.x % kXcds);
     const int64_t lo = nslices * x / kXcds, hi = nslices * (x + 1) / kXcds;
@@ -265,7 +267,7 @@ __device__ __forceinline__ Sweep make_sweep(int64_t nslices, const SweepOrder& o
     }
   } else {
     int64_t beg, end;
-    block_range(nslices, wpb, beg, end);
+    block_range(nslices, wpb, beg, end, g);
     w.lo = beg;
     w.len = uint32_t(end - beg);
     w.j = uint32_t(wv);

@@ -15,36 +15,9 @@ constexpr int kMaxShifts = 64;
 constexpr int kBlock = 256;          // threads per workgroup for every solver kernel
 constexpr int kMaxGrid = 2048;       // 256 CUs x 8 resident workgroups
 constexpr int kXcds = 8;             // MI355X: 8 accelerator complex dies, one L2 each
-constexpr int kTrEvery = 64;         // launches between two direct products t = M p
 // A "last workgroup" ticket site: eight group counters 128 bytes apart and a final one.
 constexpr int kTicketStride = 32;
 constexpr int kTicketSite = 9 * kTicketStride;
-
-// Scalar state of one multishift solve, resident in device memory.  Shift index j runs
-// over the shifts sorted ascending; j = 0 is the driving shift sigma0.
-//
-// An iteration is a head kernel, which first applies the previous iteration's update
-// (x, p_j, p) and then computes t = M p (K1), followed by K2.  No kernel waits for its
-// own reduction: each workgroup stores a partial sum and the workgroups of the next
-// kernel add the partials up themselves, in one fixed order, so they all obtain the same
-// value.  Workgroup 0 of K2 stores the step constants for the next head; workgroup 0 of
-// the head stores the state the rest of the iteration and the next head start from.
-// What every head workgroup reads while its workgroup 0 writes the successor values is
-// kept twice (RotState): the head of an iteration of parity par reads rot[par] and
-// writes rot[par ^ 1], which K2 and the reliable update then use.
-struct RotState {
-  double R;                    // |r|^2 of the driving recursive residual
-  int iter;                    // iterations completed
-  int halt;                    // 1: the kernels of this iteration do no work
-  int switch_req;              // 1: halted because the FP64 phase of a mixed solve ended
-  int status;                  // 0 running/ok, 1 breakdown
-  int pending;                 // 1: the previous K2's r awaits its update of x, p_j and p
-  int pcur;                    // which of the two direction buffers holds p
-  int ndef;                    // steps of the all-shift update deferred so far (their
-                               // residuals kept; SolveState::dfs)
-  double zeta[kMaxShifts];     // zeta_j^(n)
-  int active[kMaxShifts];      // shift j still updated
-};
 
 // Reliable updates of the complex64 phase: the host launches the update kernels every
 // kRuCheck iterations; they run when the period (msc_params::reliable_every) is due, or
@@ -62,59 +35,56 @@ constexpr int kMaxSamples = 256;
 // residuals of four right-hand sides).
 constexpr int kMaxSteps = 8;
 constexpr int kBatchMaxSteps = 4;
+constexpr int kRing = kMaxSteps + 1;  // residuals kept: launch l's in slot l % kRing
 
-// Deferred steps of shift j composed against the direction p_j at the first of them and
-// the residuals r_0..r_{m-1} the deferring heads kept: so far
-//   x_j gained cx[0] p_j + sum_k cx[k+1] r_k,  and p_j now is cp[0] p_j + sum_k cp[k+1] r_k.
-struct DeferState {
-  double cx[kMaxSteps][kMaxShifts];
-  double cp[kMaxSteps][kMaxShifts];
-  int act[kMaxShifts];          // shift j took part in a deferred step
-  int upd[kMaxShifts];          // a deferred step changed p_j
+// Scalar state of one multishift solve, resident in device memory.  Shift index j runs over
+// the shifts sorted ascending; j = 0 is the driving shift sigma0.  No kernel waits for its
+// own reduction: each workgroup stores a partial sum and the workgroups of the next kernel
+// add the partials up themselves, in one fixed order, so they all obtain the same value.
+//
+// RotState: the state at the start of the iteration n that a launch of parity par runs,
+// rot[par]; one workgroup of its last kernel writes rot[par ^ 1] while the others read.
+struct RotState {
+  double g, a, P;              // |r_{n-1}|^2, a_{n-1} and p_{n-1}^H (A + sigma0) p_{n-1}
+  int iter;                    // n, the steps taken
+  int launch;                  // the launch that takes step n (r_n lies in its ring slot)
+  int halt;                    // 1: the kernels of this iteration do no work
+  int m;                       // steps composed since x_j and p_j were last written
+  int fresh;                   // 1: x_j and p_j were never written
+  double zeta[kMaxShifts];     // zeta_j^(n)
+  double zeta_prev[kMaxShifts];
+  // p_j now is cp[0] p_j + sum_{k<m} cp[k+1] r_{n-m+k}; x_j gained the like with cx
+  double cx[kMaxSteps + 1][kMaxShifts];
+  double cp[kMaxSteps + 1][kMaxShifts];
+  int active[kMaxShifts];      // shift j still updated
+  int took[kMaxShifts];        // shift j took part in a composed step
 };
 
 struct SolveState {
-  double a;          // a_n = R / (p^H (A + sigma0) p)      (K2, workgroup 0)
-  double a_prev;     // a_{n-1} (1 before the first iteration)
-  double b;          // b_{n-1}, last direction coefficient (0 at start)
-  double P;          // p^H (A + sigma0) p                  (K2, workgroup 0)
   double sigma0;
+  double tol2, sw2;  // (mixed_margin tol)^2; switch_tol^2 (0: no switch): times |b|^2
   double bnorm2;
-  double eps2;       // (mixed_margin) tol^2 |b|^2
-  double sw_eps2;    // switch_tol^2 |b|^2: end of the FP64 phase of a mixed solve (0: none)
-  int max_iter;
-  int ns;
-  int freeze;
+  int max_iter, ns, freeze;
   int n_reliable;
-  int kstatus;       // 1: a K2 found p^H (A + sigma0) p <= 0
-  int rslot;         // residual slot a halting head read (where r stays: no K2 follows it)
-  double R_ru;       // |r|^2 right after the last reliable update (or the precision switch)
+  // reliable update of the iteration at hand: whether it runs, the recursive residual's g_n,
+  // Re(r_n^H (A + sigma0) p_{n-1}) of the replaced residual; g right after the last one (or
+  // the precision switch)
+  int ru_flag, pad_;
+  double ru_g, ru_c, R_ru;
   double s[kMaxShifts];         // sigma_j - sigma0
-  double zeta_prev[kMaxShifts]; // zeta_j^(n-1)
-  double zk[kMaxShifts];        // zeta_j^(n+1) of the current iteration (K2 -> head)
-  double ak[kMaxShifts];        // a_j^(n) = a_n zeta^(n+1)/zeta^(n)       (K2 -> head)
   int freeze_iter[kMaxShifts];
   int orig[kMaxShifts];         // caller's index of sorted shift j
-  RotState rot[2];              // rot[par]: state at the start of an iteration of parity par
-  // the deferred steps of the all-shift update, composed (DeferState), indexed by the
-  // parity of the head that writes them
-  DeferState dfs[2];
-  // per sampled head launch (MsArgs::sample): its update mode (Plan), shifts listed and
-  // kept residuals read
-  int smp_mode[kMaxSamples];
+  // the halted sequence: its state's index in rot, steps taken, |r|^2, tol2 |b|^2, 1 on a
+  // breakdown
+  int fin, iter, status, pad2_;
+  double R, eps2;
+  RotState rot[2];
+  // per sampled iteration (MsArgs::sample) that applied its steps: shifts listed and
+  // residuals read; per phase (0: FP64, 1: complex64) the sums over all applications
   int smp_nact[kMaxSamples];
   int smp_m[kMaxSamples];
-  // per phase (0: FP64, 1: complex64): x_j/p_j row updates performed (in units of n
-  // rows), heads that deferred their update, passes over kept residuals (an applying head
-  // reads the ones pending from the ring), heads that applied the
-  // update (x_0 read and written), and heads that kept the direction for x_0's deferred
-  // steps (the applying head of that cycle reads it back)
-  int n_shift_upd[2];
-  int n_defer[2];
-  int n_two[2];
-  int n_apply[2];
-  int n_keep0[2];
-  int pad2_[2];
+  int n_upd[2];
+  int n_kept[2];
 };
 
 // Per-kernel partial-sum scratch, sized for kMaxGrid workgroups x kMaxShifts values.
@@ -195,21 +165,20 @@ struct Workspace {
   size_t n = 0;
   int ns = 0;
   int prec = -1;
-  void* r = nullptr;    // n complex128
-  void* p[2] = {nullptr, nullptr};    // two n complex128 direction buffers
-  void* t = nullptr;    // n complex128
-  void* pk = nullptr;   // (ns-1) * n complex128
-  void* r32 = nullptr;  // complex64 copies for the second phase of a mixed solve
-  void* p32[2] = {nullptr, nullptr};
-  void* t32 = nullptr;
+  // complex128: the residual ring (kRing n), u (A = M^H M: n; A given: its w, two n), s (A =
+  // M^H M: n, A given: two n) and the ns directions
+  void* ring = nullptr;
+  void* u = nullptr;
+  void* s = nullptr;
+  void* pk = nullptr;
+  void* ring32 = nullptr;  // complex64 copies for the second phase of a mixed solve
+  void* u32 = nullptr;
+  void* s32 = nullptr;
   void* pk32 = nullptr;
-  double2* t64 = nullptr;   // n complex128 (reliable updates, verification)
-  void* pkeep0 = nullptr;           // n complex128 (complex64 in phase 2): x_0's first deferred direction
-  void* rkeep[kMaxSteps - 1] = {};  // n complex128 each (complex64
-                            // in the second phase): residuals kept by deferring heads
+  double2* t64 = nullptr;   // n complex128 (reliable updates, products)
   double2* u64 = nullptr;   // 8 * n complex128 (verification SpMM chunk)
   SolveState* st = nullptr;
-  int* h_halt = nullptr;    // host-coherent word the heads write: halt | switch_req << 1
+  int* h_halt = nullptr;    // host-coherent word: halt | switch request << 1
   int* d_halt = nullptr;    // its device address
   hipEvent_t ev[2] = {nullptr, nullptr};
 };
@@ -340,49 +309,44 @@ struct MsArgs {
   int grid;
   Csr<double2> m64, mh64;
   Csr<float2> m32, mh32;
-  int par;               // parity of the iteration: its state is st->rot[par]
-  int gk1, gk2;          // workgroups of this iteration's K1 and K2 (partials to sum)
+  int launch, par;       // the launch, and its parity: its iteration's state is st->rot[par]
+  int gd, gg;            // workgroups that leave partials of d_n (K1) and of g_n (K2)
   int sell;              // K1/K2 read the sliced ELLPACK copies below
   int64_t nslices;
   Sell<double2> s64, sh64;
   Sell<float2> s32, sh32;
   const double2* b;
   double2* x;            // caller's x, shift-major, caller order
-  void* r; void* t; void* pk;
-  void* pb[2];           // the two direction buffers (p of consecutive iterations)
-  // the residual lives in a ring of kMaxSteps slots: slot 0 is r, slot k >= 1 is
-  // rkeep[k - 1]; a head with m steps deferred reads r from slot m, so the m residuals of
-  // the heads that deferred stay in slots 0..m-1 without a copy, and K2 writes the next
-  // residual into the slot of the next head (0 after a head that applied)
-  void* rkeep[kMaxSteps - 1];
-  void* pkeep0;          // the direction p at the first deferred step (x_0's deferred update)
-  int* hflag;            // host-coherent word: halt | switch_req << 1 of the next state
-  int steps;             // steps of the all-shift update folded into one pass (1..kMaxSteps)
-  int defer_ok;          // 1: this launch's head may defer its all-shift update
-  int ru_force;          // reliable-update launch: 1 runs it whatever the residual
-  int ru_check;          // 1: the reliable-update kernels follow this head (x_0 must be
-                         // current when they run)
-  int stencil;           // the head and K2 apply M and M^H from links (kind MHM, sell = 1):
+  void* ring;            // kRing residuals of n
+  void* u;               // u = M r (A = M^H M), A r (A given, CSR)
+  void *w[2], *s[2];     // A given, sliced copy: w and s alternate; else s[0] alone
+  void* pk;              // ns directions, sorted order
+  int* hflag;            // host-coherent word: halt | switch request << 1
+  int flushed;           // 1: the composed steps were applied after the last iteration
+  int ru_force;          // reliable update: 1 runs it whatever the residual
+  int ru_check;          // 1: this iteration begins with a reliable update where one is due
+  int stencil;           // K1 and K2 apply M and M^H from links (kind MHM, sell = 1):
                          // 0 no, 3 full links, 2 two rows per link (w64 / w32 in that form)
   SweepOrder ord;        // slice order of the head and K2 on the sliced path
-  int k2_march;          // links: t-slices per column of K2's march (set per launch; 1: none)
-  int head_march;        // links: the same for the head (1: the sweep order)
-  int t_rec;             // links, FP64: this head forms t' = M r + b t (the old t = M p)
+  int march, m1, m2;     // links: t-slices per column of the march, and whether K1 / K2 march
   Stencil<double2> w64;
   Stencil<float2> w32;
-  int sample;            // slot of SolveState::smp_* for this head, -1: not sampled
+  int sample;            // slot of SolveState::smp_* for this iteration, -1: not sampled
   double2* t64;
   SolveState* st;
   Scratch sc;
 };
-hipError_t launch_init(int prec, const MsArgs& a, hipStream_t s);
-// One iteration of parity a.par; with `reliable`, the FP64 reliable update runs between
-// the head and K2.  ev (optional, 6 events): start/stop pairs attached to the K1 (head),
-// K2 and, on the CSR path, the separate update kernel.
-hipError_t launch_iteration(int prec, const MsArgs& a, hipStream_t s, hipEvent_t* ev = nullptr,
-                            bool reliable = false);
-// Second phase of a mixed solve: copy r, p, p_j of a64 (complex128) into a32's complex64
-// buffers and re-arm the state (halt = switch_req = 0, no further switch).
+// The grids and the march of a phase's iterations (a.gd, a.gg, a.march, a.m1, a.m2).
+void prepare_iteration(int prec, MsArgs& a);
+hipError_t launch_init(const MsArgs& a, hipStream_t s);
+// One iteration of parity a.par, with a.ru_check after the FP64 reliable update where it is
+// due; with `flush` it ends with the application of the composed steps.  ev (optional, 6
+// events): start/stop pairs attached to K1, K2 and the application.
+hipError_t launch_iteration(int prec, const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool flush);
+// The composed steps of a halted sequence.
+hipError_t launch_final_flush(int prec, const MsArgs& a, hipStream_t s);
+// Second phase of a mixed solve: copy r, s, p_j of a64 (complex128) into a32's complex64
+// buffers and re-arm the state at a32.par (after launch_final_flush).
 hipError_t launch_switch_to_mixed(const MsArgs& a64, const MsArgs& a32, int ns, hipStream_t s);
 // FP64 true residual norms^2 of shifts [k0, k0+kc) (kc <= 8) of x into sc.res2[k0..].
 hipError_t launch_verify(const MsArgs& a, const double* sigma_by_caller_index, int k0, int kc,
@@ -417,8 +381,6 @@ hipError_t noalloc_scratch(int device, void** ptr);
 // launch_apply with its temporary at `base` (the address noalloc_scratch
 // returned); hipErrorInvalidValue when n exceeds the array.
 hipError_t launch_apply_noalloc(ApplyArgs a, void* base, hipStream_t s);
-
-int default_grid(int64_t n, int lanes);
 
 // bicgstab.hip -- multishift BiCGStab for a general A (complex FP64 scalars)
 constexpr int kBcgGrid = 1024;               // most workgroups of its kernels

@@ -1,27 +1,31 @@
-// The multishift CG iteration (paper: Section 2, Algorithm 1; Section 3 design rules):
+// The multishift CG iteration (paper: Section 2, Algorithm 1; Section 3 design rules), in
+// Chronopoulos and Gear's arrangement of CG: with w_n = A r_n,
+//   g_n = |r_n|^2,  d_n = r_n^H (A + sigma0) r_n,
+//   b_n = g_n / g_{n-1},  a_n = g_n / (d_n - b_n g_n / a_{n-1}),
+//   s_n = w_n + sigma0 r_n + b_n s_{n-1},  r_{n+1} = r_n - a_n s_n,
+// the steps and residuals of Algorithm 1 without its direction p: the driving system's p
+// and x are updated with the other shifts',
+//   p_j <- zeta_j r_n + b_j p_j,  x_j += a_j p_j     (j = 0, the driving one: zeta = 1).
+// For A = M^H M an iteration is two kernels:
+//   K1  u = M r_n and the partials of |u|^2 (d_n = |u|^2 + sigma0 g_n): it needs no scalar
+//   K2  a_n, b_n; w = M^H u, s_n, r_{n+1} and the partials of g_{n+1}
+// For A given, on the sliced copy, it is one kernel, which forms r_{n+1} at every gathered
+// column and the next w with it; on the CSR, K1 forms w and K2 is elementwise.
 //
-//   K1  t = M p                and  P = |t|^2 + sigma0 |p|^2   (A = M^H M)
-//       t = A p                and  P = Re(p^H t) + sigma0 |p|^2 (A given)
-//   K2  a = R/P and, per shift, zeta^(n+1) and a_j (one lane per shift);
-//       r <- r - a (M^H t + sigma0 p)  and  R' = |r|^2
-//   K3  b = R'/R, b_j, rotation of zeta, freezing, halting;  x_0 += a p;  for every
-//       active shift j: x_j += a_j p_j, p_j <- zeta_j r + b_j p_j;  p <- r + b p  -- one
-//       pass over r and p serves all shifts (Section 3: the shifted updates are the next
-//       most expensive step; register reuse of r and p).
-//
-// On the sliced ELLPACK path an iteration is two kernels: the head (K3 of the previous
-// iteration, then K1 on the new direction, formed at each gathered column) and K2.
-// A head may defer the shifted part of K3; a later one applies up to four composed steps
-// in one pass over x_j and p_j.
+// Nothing reads x_j and p_j but their own update, so K2 only composes each step: the
+// coefficients of x_j's increment and of p_j against the first pending step's p_j and the
+// residuals of the steps, which stay in a ring.  Every update_steps-th iteration (eight), a
+// kernel of its own (k_flush) applies the composed steps of every shift in one pass; so do
+// a reliable update, which reads x_0, the switch to complex64 and the end of the sequence.
 //
 // The shift recurrences are the values forced by the collinearity r_j = zeta_j r:
 //   zeta' = zeta zeta_prev a_prev / (a b (zeta_prev - zeta) + zeta_prev a_prev (1 + s a)),
-//   a_j = a zeta'/zeta,  b_j = b' (zeta'/zeta)^2,  with s = sigma_j - sigma0 >= 0.
+//   a_j = a zeta'/zeta,  b_j = b (zeta/zeta_prev)^2,  with s = sigma_j - sigma0 >= 0.
 // All scalar work stays on the device in FP64 (Section 3: the iteration constants are
 // computed on the GPU to avoid host round trips).  Reductions are deterministic: each
 // workgroup writes one partial, and every workgroup of the consuming kernel sums them in
-// one fixed order (set-up, reliable update and verification: the last workgroup to
-// arrive does).
+// one fixed order (reliable update and verification: the last workgroup to arrive does).
+// The shifts' scalars are the work of one workgroup more than the rows need.
 #include <hip/hip_ext.h>
 
 #include <map>
@@ -66,14 +70,10 @@ template <> __device__ __forceinline__ Sell<double2> pick_shm<double>(const MsAr
 
 // Pairs per round trip of the sliced ELLPACK row product (register budget: complex64
 // keeps a 24-entry staggered row in flight at once, complex128 half of it).
-// Slot k of the residual ring (slot 0: a.r, slot k >= 1: a.rkeep[k - 1]); k is uniform.
-template <class R>
-__device__ __forceinline__ cplx<R>* rslot(const MsArgs& a, int k) {
-  void* q = a.r;
-#pragma unroll
-  for (int j = 1; j < kMaxSteps; ++j)
-    if (k == j) q = a.rkeep[j - 1];
-  return static_cast<cplx<R>*>(q);
+// The residual ring: launch l of the sequence reads its r_n from slot l % kRing (a.launch: a
+// kernel argument, so the first gathers wait for no state) and writes r_{n+1} into the next.
+template <class R> __device__ __forceinline__ cplx<R>* rslot(const MsArgs& a, int l) {
+  return static_cast<cplx<R>*>(a.ring) + int64_t(l % kRing) * a.n;
 }
 
 template <class R> constexpr int sell_kp();
@@ -134,120 +134,8 @@ __device__ __forceinline__ cplx<R> sell_row(const Sell<cplx<R>>& m, const cplx<R
   return m.col16 ? sell_row_cols<R, true>(m, x, sl, lane) : sell_row_cols<R, false>(m, x, sl, lane);
 }
 
-// The next direction r + b p, formed in FP64 and rounded once; a lane that gathers p'
-// at a neighbouring row forms the same bits as the row's owner stores.
-template <class R>
-__device__ __forceinline__ cplx<R> next_dir(double b, const cplx<R>& r, const cplx<R>& p) {
-  const double2 rd = to_d(r), pd = to_d(p);
-  double2 v;
-  v.x = fma(b, pd.x, rd.x);
-  v.y = fma(b, pd.y, rd.y);
-  return from_d<R>(v);
-}
-
-// Minimum waves per SIMD asked of the compiler for the matrix-free head and K2 (1: no
-// constraint).  The FP64 heads need the bound and a scheduling barrier between their
-// update and stencil parts (MSC_SITE_SB): without them the compiler interleaves the two
-// into 256 VGPRs, one wave per SIMD.
-#ifndef MSC_SITE_HEAD_WPE
-#define MSC_SITE_HEAD_WPE 2
-#endif
-#ifndef MSC_SITE_K2_WPE
-#define MSC_SITE_K2_WPE 1
-#endif
-#ifndef MSC_SITE_SB
-#define MSC_SITE_SB 1
-#endif
-// Dynamic LDS of the complex64 site K2 (bytes per workgroup, within the 64 KB a
-// workgroup may hold): three workgroups fit a CU's 160 KB, four do not.
-constexpr size_t kC64K2Lds = size_t(48) << 10;
-// most t-slices per column of K2's march along t
-#ifndef MSC_K2_MARCH
-#define MSC_K2_MARCH 16
-#endif
-constexpr int kK2March = MSC_K2_MARCH;
-#ifndef MSC_HEAD_MARCH
-#define MSC_HEAD_MARCH 1
-#endif
-constexpr bool kHeadMarch = MSC_HEAD_MARCH != 0;
-// waves per SIMD the marching K2 is compiled for (FP64, complex64)
-#ifndef MSC_K2_MARCH_WPE64
-#define MSC_K2_MARCH_WPE64 2
-#endif
-#ifndef MSC_K2_MARCH_WPE32
-#define MSC_K2_MARCH_WPE32 2
-#endif
-
-// Pairs per round trip when each entry gathers two vectors (MSC_SELL_KPN32 / 64).
-#ifndef MSC_SELL_KPN32
-#define MSC_SELL_KPN32 4
-#endif
-#ifndef MSC_SELL_KPN64
-#define MSC_SELL_KPN64 2
-#endif
-template <class R> constexpr int sell_kp_next();
-template <> constexpr int sell_kp_next<float>() { return MSC_SELL_KPN32; }
-template <> constexpr int sell_kp_next<double>() { return MSC_SELL_KPN64; }
-
-template <class R, int KP, bool FULL>
-__device__ __forceinline__ void sell_gather2_fma(const cplx<R>* __restrict__ r,
-                                                 const cplx<R>* __restrict__ p, double b, int np,
-                                                 const int2 (&cc)[KP], const cplx<R> (&v)[2 * KP],
-                                                 cplx<R>& acc) {
-  cplx<R> xr[2 * KP], xp[2 * KP];
-#pragma unroll
-  for (int u = 0; u < KP; ++u) {
-    if (FULL || u < np) {
-      xr[2 * u] = r[cc[u].x];
-      xp[2 * u] = p[cc[u].x];
-      xr[2 * u + 1] = r[cc[u].y];
-      xp[2 * u + 1] = p[cc[u].y];
-    } else {
-      xr[2 * u] = xr[2 * u + 1] = xp[2 * u] = xp[2 * u + 1] = czero<R>();
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < 2 * KP; ++u) cfma<R>(acc, v[u], next_dir<R>(b, xr[u], xp[u]));
-}
-
-// Off-diagonal part of one sliced ELLPACK row per lane times p' = r + b p, with p' formed
-// at each gathered column.
-template <class R, bool NARROW>
-__device__ __forceinline__ cplx<R> sell_row_next_cols(const Sell<cplx<R>>& m,
-                                                      const cplx<R>* __restrict__ r,
-                                                      const cplx<R>* __restrict__ p, double b,
-                                                      int64_t sl, int lane) {
-  constexpr int KP = sell_kp_next<R>();
-  int32_t c, c1;
-  if (m.wp > 0) {
-    c = int32_t(sl) * m.wp;
-    c1 = c + m.wp;
-  } else {
-    c = load_uniform(m.cptr, sl);
-    c1 = load_uniform(m.cptr, sl + 1);
-  }
-  cplx<R> acc = czero<R>();
-  int2 cc[KP];
-  cplx<R> v[2 * KP];
-  for (; c + KP <= c1; c += KP) {
-    sell_load<R, KP, true, NARROW>(m, c, KP, lane, cc, v);
-    sell_gather2_fma<R, KP, true>(r, p, b, KP, cc, v, acc);
-  }
-  if (c < c1) {
-    const int np = c1 - c;
-    sell_load<R, KP, false, NARROW>(m, c, np, lane, cc, v);
-    sell_gather2_fma<R, KP, false>(r, p, b, np, cc, v, acc);
-  }
-  return acc;
-}
-template <class R>
-__device__ __forceinline__ cplx<R> sell_row_next(const Sell<cplx<R>>& m,
-                                                 const cplx<R>* __restrict__ r,
-                                                 const cplx<R>* __restrict__ p, double b,
-                                                 int64_t sl, int lane) {
-  return m.col16 ? sell_row_next_cols<R, true>(m, r, p, b, sl, lane)
-                 : sell_row_next_cols<R, false>(m, r, p, b, sl, lane);
-}
+// most t-slices per column of the march along t
+constexpr int kK2March = 16;
 
 // One CSR row times a vector, L lanes per row; the sum is returned in every lane.
 // Entries of one row handled by a lane per chunk: the column and value loads of a chunk,
@@ -332,8 +220,9 @@ __device__ __forceinline__ double sum_partials(const double* partial, int count,
 }
 
 // ---- the iteration's reductions ------------------------------------------------------
-// K1 stores one partial of P per workgroup in region 0, K2 one partial of R' in region 1;
-// the workgroups of the next kernel each add all of them up in the same order.
+// One partial per workgroup: of g_n in region n % 2, of d_n (|u|^2, or r^H w) in region
+// 2 + n % 2; the reliable update's in 4 and 5.  The consuming kernel's workgroups each add
+// all of them up in the same order; the producer was another kernel, so plain loads do.
 __device__ __forceinline__ double* region(const MsArgs& a, int k) {
   return a.sc.partial + k * kMaxGrid;
 }
@@ -343,658 +232,223 @@ __device__ __forceinline__ void store_partial(double* reg, double acc) {
   if (threadIdx.x == 0) store_agent(&reg[blockIdx.x], tot);
 }
 
-// Partials are loaded early (four per thread, covering grids of up to 1024 workgroups)
-// so their round trip overlaps the caller's own first loads; the sum is identical in
-// every thread of every workgroup that forms it.
+// Partials are loaded early (four per thread and region, covering grids of up to 1024
+// workgroups) so that their round trip overlaps the caller's own first loads.
 constexpr int kEarly = 4;
 struct Early {
-  double v[kEarly];
+  double g[kEarly], d[kEarly];
 };
 
-__device__ __forceinline__ void load_early(const double* reg, int count, Early& e) {
+__device__ __forceinline__ void load_early(const MsArgs& a, Early& e) {
+  const double *rg = region(a, a.par), *rd = region(a, 2 + a.par);
 #pragma unroll
   for (int u = 0; u < kEarly; ++u) {
     const int i = threadIdx.x + u * kBlock;
-    e.v[u] = i < count ? load_agent(&reg[i]) : 0.0;
+    e.g[u] = i < a.gg ? rg[i] : 0.0;
+    e.d[u] = i < a.gd ? rd[i] : 0.0;
   }
 }
 
-__device__ __forceinline__ double all_sum(const double* reg, int count, const Early& e) {
-  __shared__ double total;
-  double s = 0.0;
+// g_n and r_n^H A r_n in every thread.
+__device__ __forceinline__ void both_sums(const MsArgs& a, const Early& e, double& g, double& d) {
+  __shared__ double total[2];
+  const double *rg = region(a, a.par), *rd = region(a, 2 + a.par);
+  double v[2] = {0.0, 0.0};
 #pragma unroll
-  for (int u = 0; u < kEarly; ++u) s += e.v[u];
-  for (int i = threadIdx.x + kEarly * kBlock; i < count; i += kBlock) s += load_agent(&reg[i]);
-  s = block_sum<kBlock>(s);
-  if (threadIdx.x == 0) total = s;
+  for (int u = 0; u < kEarly; ++u) {
+    v[0] += e.g[u];
+    v[1] += e.d[u];
+  }
+  for (int i = threadIdx.x + kEarly * kBlock; i < a.gg; i += kBlock) v[0] += rg[i];
+  for (int i = threadIdx.x + kEarly * kBlock; i < a.gd; i += kBlock) v[1] += rd[i];
+  block_sum_k<kBlock, 2>(v);
+  if (threadIdx.x == 0) {
+    total[0] = v[0];
+    total[1] = v[1];
+  }
   __syncthreads();
-  return total;
+  g = total[0];
+  d = total[1];
 }
 
-// K2 prologue: a = R / P.  Workgroup 0 also stores a, P and, for every active shift j
-// (wave 0, lane j), zeta_j^(n+1) = zeta zeta_- a_- / (a b (zeta_- - zeta) + zeta_- a_-
-// (1 + s_j a)) and a_j = a zeta_j^(n+1) / zeta_j for the next head, and marks the update
-// pending; a breakdown (P <= 0 or not finite) is flagged instead.  Returns false on
-// breakdown.  The iteration's state is the one its head wrote, rot[par ^ 1].
-__device__ bool k2_step(const MsArgs& a, const Early& e, double& step) {
-  SolveState* st = a.st;
-  RotState& rs = st->rot[a.par ^ 1];
-  const int j = threadIdx.x;
-  const bool lead = blockIdx.x == 0 && j < kWave;
-  // workgroup 0, lane j: shift j's state, loaded before the partial sum
-  double z = 1.0, zp = 1.0, sj = 0.0;
-  int act = 0;
-  if (lead && j >= 1 && j < st->ns) {
-    act = rs.active[j];
-    z = rs.zeta[j];
-    zp = st->zeta_prev[j];
-    sj = st->s[j];
-  }
-  const double ap = st->a_prev, b = st->b, R = rs.R;
-  const double P = all_sum(region(a, 0), a.gk1, e);
-  const bool ok = (P > 0.0) && isfinite(P);
-  step = ok ? R / P : 0.0;
-  if (lead) {
-    if (j == 0) rs.pending = 1;
-    if (!ok) {
-      if (j == 0) {
-        st->P = P;
-        st->kstatus = 1;
-      }
-    } else {
-      if (act) {
-        const double zn = z * zp * ap / (step * b * (zp - z) + zp * ap * (1.0 + sj * step));
-        st->zk[j] = zn;
-        st->ak[j] = step * zn / z;
-      }
-      if (j == 0) {
-        st->P = P;
-        st->a = step;
-      }
-    }
-  }
-  return ok;
-}
-
-// Head prologue, shared through LDS.  When the previous K2 left its update pending:
-// R' (from K2's partials) and b = R'/R, and per shift j the coefficients of its update,
-// whether it freezes now (zeta_j^(n+1)^2 R' <= eps2), and the list of shifts to update.
-// Workgroup 0 writes the state the rest of the iteration and the next head start from.
-// Shifts whose x_j and p_j loads the head's update issues together (MSC_UPD_GROUP).
-#ifndef MSC_UPD_GROUP
-#define MSC_UPD_GROUP 4
-#endif
-constexpr int kUpdGroup = MSC_UPD_GROUP;
-
-struct Plan {
-  double bn;                 // b of p <- r + b p (0: p is current, nothing pending)
-  // the shifts this head updates, in list order, with the element offsets of x_j (the
-  // caller's order) and of p_j:  x_j += cx[0] p_j + sum_{k<m} cx[k+1] r_k  and, where pw,
-  // p_j <- cp[0] p_j + sum_{k<m} cp[k+1] r_k + cp[m+1] r  (r_k: the residuals kept by the
-  // m heads that deferred; r: the current one; unused coefficients are 0)
-  double cx[kMaxSteps][kMaxShifts];
-  double cp[kMaxSteps + 1][kMaxShifts];
-  int64_t xo[kMaxShifts];
-  int64_t po[kMaxShifts];
-  int pw[kMaxShifts];
-  // the driving system in the same form (zeta = 1): x_0 += x0c[0] p_1 + sum_{k<m}
-  // x0c[k+1] r_k, p_1 the direction at the first pending step (the current p when m = 0,
-  // else the one the first deferring head kept)
-  double x0c[kMaxSteps];
-  int keep0;                 // 1: this deferring head keeps p for x_0 (first of a cycle)
-  int nact;
-  int mode;                  // 0: apply (the current step and m deferred ones); 1: defer
-  int m;                     // kept residuals read (mode 0)
-  int pending;               // the update runs in this head
-  int ok;                    // 0: breakdown, the head stops
-  int spmv;                  // 1: this head also computes t = M p
+// Step n's scalars, the same in every workgroup.
+struct StepPlan {
+  double a, b;  // a_n, b_n
+  double P;     // p_n^H (A + sigma0) p_n
+  int stop;     // 0: step n runs; 1: converged or at the limit; 2: end of the FP64 phase of
+                // a mixed solve; 3: breakdown (P <= 0 or not finite: A + sigma0 not PD)
 };
 
-// Consecutive steps of shift j compose: with p_j = cp[0] p + sum_k cp[k+1] r_k after the
-// deferred ones, the next step adds a_j p_j to x_j and turns p_j into
-// zeta_j' r + b_j p_j (r: that step's residual), unless j freezes there (p_j stays); a
-// frozen shift takes no further step.  The driving system (lane 0) composes the same way
-// with zeta = 1, a_0 = a and b_0 = b: its x is x_0, its direction p.  A head defers (its r
-// stays in its ring slot; it touches no x_j, p_j and not x_0) while fewer than `steps` - 1
-// steps are pending,
-// its iteration continues and no reliable update (which reads x_0) runs after it;
-// otherwise it applies all of them in one pass.
-template <class T>
-__device__ void head_plan(const MsArgs& a, const Early& e, Plan& pl) {
-  constexpr int ph = sizeof(T) == 4 ? 1 : 0;  // phase: 0 FP64, 1 complex64
+// What the step needs of the state, read before the partials are summed.
+struct StepIn {
+  double g1, a1, P1;           // g_{n-1}, a_{n-1}, P_{n-1}
+  double bn2, tol2, sw2, sigma0;
+  double ru_g, ru_c;
+  int n, halt, max_iter, ru;
+};
+
+__device__ __forceinline__ StepIn step_in(const MsArgs& a) {
+  const SolveState* st = a.st;
+  const RotState& rs = st->rot[a.par];
+  StepIn i;
+  i.halt = rs.halt;
+  i.n = rs.iter;
+  i.g1 = rs.g;
+  i.a1 = rs.a;
+  i.P1 = rs.P;
+  i.bn2 = st->bnorm2;
+  i.tol2 = st->tol2;
+  i.sw2 = st->sw2;
+  i.sigma0 = st->sigma0;
+  i.max_iter = st->max_iter;
+  i.ru = a.ru_check ? st->ru_flag : 0;
+  i.ru_g = st->ru_g;
+  i.ru_c = st->ru_c;
+  return i;
+}
+
+// d: r_n^H A r_n.  After a reliable update has replaced r_n, b_n keeps the recursive
+// residual's g_n (the direction is the sequence's) and P takes r_n^H (A + sigma0) p_{n-1} as
+// measured (ru_c): the shorter form of P supposes a residual orthogonal to the direction
+// before it.
+__device__ __forceinline__ StepPlan step_plan(const StepIn& i, double g, double d) {
+  d += i.sigma0 * g;
+  const double bn2 = i.n == 0 ? g : i.bn2;
+  StepPlan p;
+  p.b = i.n == 0 ? 0.0 : (i.ru ? i.ru_g : g) / i.g1;
+  p.P = i.n == 0 ? d : (i.ru ? d + p.b * (2.0 * i.ru_c + p.b * i.P1) : d - p.b * g / i.a1);
+  p.a = g / p.P;
+  const bool ok = isfinite(g) && p.P > 0.0 && isfinite(p.P);
+  p.stop = g <= i.tol2 * bn2 || i.n >= i.max_iter ? 1
+           : !ok                                  ? 3
+           : g <= i.sw2 * bn2                     ? 2
+                                                  : 0;
+  return p;
+}
+
+// The work of K2's extra workgroup: the shifts' scalars of step n (wave 0, lane j: shift
+// j): freezing, then, when the step runs, zeta^(n+1), a_j and b_j, composed with the
+// pending steps; the state of iteration n + 1, or of the halted sequence.  On small
+// operators it is the longest chain of the iteration: all it reads is read before the sums.
+__device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in, const Early& e) {
   SolveState* st = a.st;
   const RotState& rs = st->rot[a.par];
   RotState& nx = st->rot[a.par ^ 1];
-  const int j = threadIdx.x;
-  const int pending = rs.pending;
-  const int m = rs.ndef;
-  // wave 0, lane j: shift j's state, loaded before the partial sum
-  int act0 = 0, origj = 0, dact = 0, dupd = 0;
-  double z = 1.0, zn = 0.0, akj = 0.0;
-  double cx[kMaxSteps + 1], cp[kMaxSteps + 1];
+  const int j = threadIdx.x, n = in.n;
+  const bool mine = j < st->ns;
+  double z = 1.0, zp = 1.0, s = 0.0, cx[kMaxSteps + 1], cp[kMaxSteps + 1];
+  int act = 0, took = 0;
 #pragma unroll
   for (int i = 0; i <= kMaxSteps; ++i) cx[i] = cp[i] = 0.0;
-  cp[0] = 1.0;
-  const bool drv = j == 0;  // lane 0: the driving system
-  if (j < kWave && j < st->ns) {
-    if (pending) {
-      act0 = drv ? 1 : rs.active[j];
-      z = drv ? 1.0 : rs.zeta[j];
-      zn = drv ? 1.0 : st->zk[j];
-      akj = drv ? st->a : st->ak[j];
-    }
-    if (!drv && (pending || m > 0)) origj = st->orig[j];
-    if (m > 0) {
-      const DeferState& d = st->dfs[a.par];
+  if (mine) {
+    z = rs.zeta[j];
+    zp = rs.zeta_prev[j];
+    act = rs.active[j];
+    took = rs.took[j];
+    s = st->s[j];
 #pragma unroll
-      for (int i = 0; i < kMaxSteps; ++i) {
-        if (i <= m) {
-          cx[i] = d.cx[i][j];
-          cp[i] = d.cp[i][j];
-        }
-      }
-      dact = d.act[j];
-      dupd = d.upd[j];
+    for (int i = 0; i <= kMaxSteps; ++i) {
+      cx[i] = rs.cx[i][j];
+      cp[i] = rs.cp[i][j];
     }
   }
-  const double R = rs.R, eps2 = st->eps2;
-  const int kst = st->kstatus, frz = st->freeze;
-  const double Rn = pending ? all_sum(region(a, 1), a.gk2, e) : R;
-  if (j < kWave) {
-    const bool ok = !pending || (isfinite(Rn) && kst == 0);
-    const double bn = pending ? Rn / R : 0.0;
-    const bool act = pending && ok && act0;
-    const bool freeze_now = act && !drv && frz && zn * zn * Rn <= eps2;
-    const double ratio = act ? zn / z : 0.0;
-    const double bk = bn * ratio * ratio;
-    const int it = pending ? rs.iter + 1 : rs.iter;
-    const bool done = pending && (Rn <= eps2 || it >= st->max_iter);
-    // the FP64 phase of a mixed solve ends here: the update still runs, then the host
-    // converts the Krylov vectors to complex64 and continues
-    const bool sw = pending && !done && Rn <= st->sw_eps2;
-    const bool cont = ok && !done && !sw;
-    // fold the current step into the composition
-    if (act) {
-#pragma unroll
-      for (int i = 0; i < kMaxSteps; ++i)
-        if (i <= m) cx[i] = fma(akj, cp[i], cx[i]);
+  const int m = rs.m, fresh = rs.fresh, freeze = st->freeze;
+  double g, d;
+  both_sums(a, e, g, d);
+  const StepPlan p = step_plan(in, g, d);
+  if (j >= kWave) return;
+  // a flush since the last step leaves nothing pending
+  const bool flushed = a.flushed || in.ru;
+  const int m0 = flushed ? 0 : m;
+  const bool live = p.stop == 0;
+  const double eps2 = in.tol2 * (n == 0 ? g : in.bn2);
+  if (mine) {
+    double zn = z;
+    if (m0 == 0) {
+      took = 0;
+      cp[0] = 1.0;
+      cx[0] = 0.0;
     }
-    if (act && !freeze_now) {
 #pragma unroll
-      for (int i = 0; i < kMaxSteps; ++i)
-        if (i <= m) cp[i] *= bk;
-#pragma unroll
-      for (int i = 1; i <= kMaxSteps; ++i)
-        if (i == m + 1) cp[i] = zn;
+    for (int i = 1; i <= kMaxSteps; ++i)
+      if (i > m0) cx[i] = cp[i] = 0.0;
+    if (act && j > 0 && freeze && z * z * g <= eps2) {
+      act = 0;
+      st->freeze_iter[j] = n;
     }
-    dact = dact || act;
-    dupd = dupd || (act && !freeze_now);
-    // a reliable update after this head reads x_0: the same test as ru_due on the R this
-    // head writes
-    const bool ru_now = a.ru_check && (a.ru_force || Rn < kRuDelta2 * st->R_ru);
-    const int mode = (pending && cont && a.defer_ok && m + 1 < a.steps && !ru_now) ? 1 : 0;
-    const bool listed = mode == 0 && dact && !drv;
-    const uint64_t mask = __ballot(listed);
-    if (listed) {
-      const int pos = __popcll(mask & ((uint64_t(1) << j) - 1));
+    if (live && act) {
+      if (j > 0)
+        zn = n == 0 ? z / (1.0 + s * p.a)
+                    : z * zp * in.a1 / (p.a * p.b * (zp - z) + zp * in.a1 * (1.0 + s * p.a));
+      const double ratio = z / zp, aj = p.a * zn / z, bj = p.b * ratio * ratio;
 #pragma unroll
-      for (int i = 0; i < kMaxSteps; ++i) pl.cx[i][pos] = i <= m ? cx[i] : 0.0;
-#pragma unroll
-      for (int i = 0; i <= kMaxSteps; ++i) pl.cp[i][pos] = i <= m + 1 ? cp[i] : 0.0;
-      pl.xo[pos] = int64_t(origj) * a.n;
-      pl.po[pos] = int64_t(j - 1) * a.n;
-      pl.pw[pos] = dupd ? 1 : 0;
-    }
-    const int nlist = __popcll(mask);
-    if (drv) {
-#pragma unroll
-      for (int i = 0; i < kMaxSteps; ++i) pl.x0c[i] = (mode == 0 && i <= m) ? cx[i] : 0.0;
-      pl.keep0 = (mode == 1 && m == 0) ? 1 : 0;
-      pl.bn = bn;
-      pl.nact = nlist;
-      pl.mode = mode;
-      pl.m = mode == 0 ? m : 0;
-      pl.pending = pending;
-      pl.ok = ok ? 1 : 0;
-      pl.spmv = cont ? 1 : 0;
-    }
-    if (blockIdx.x == 0) {
-      if (j < st->ns) {
-        if (!drv) {
-          nx.zeta[j] = act ? zn : rs.zeta[j];
-          nx.active[j] = act ? (freeze_now ? 0 : 1) : rs.active[j];
-        } else {
-          nx.zeta[0] = rs.zeta[0];
-          nx.active[0] = rs.active[0];
-        }
-        if (mode == 1) {
-          DeferState& d = st->dfs[a.par ^ 1];
-#pragma unroll
-          for (int i = 0; i < kMaxSteps; ++i) {
-            d.cx[i][j] = i <= m ? cx[i] : 0.0;
-            d.cp[i][j] = i <= m + 1 ? cp[i] : 0.0;
-          }
-          d.act[j] = dact ? 1 : 0;
-          d.upd[j] = dupd ? 1 : 0;
-        }
+      for (int i = 0; i <= kMaxSteps; ++i) {
+        if (i <= m0) cp[i] *= bj;
+        if (i == m0 + 1) cp[i] = z;
+        if (i <= m0 + 1) cx[i] = fma(aj, cp[i], cx[i]);
       }
-      if (act && !drv) {
-        st->zeta_prev[j] = z;
-        if (freeze_now) st->freeze_iter[j] = it;
-      }
-      if (drv) {
-        nx.pending = 0;
-        nx.ndef = (ok && mode == 1) ? m + 1 : 0;
-        if (a.sample >= 0 && a.sample < kMaxSamples) {
-          st->smp_mode[a.sample] = mode;
-          st->smp_nact[a.sample] = nlist;
-          st->smp_m[a.sample] = m;
-        }
-        if (pending && ok) {
-          st->n_shift_upd[ph] += nlist;
-          st->n_defer[ph] += mode == 1 ? 1 : 0;
-          st->n_two[ph] += mode == 0 ? m : 0;
-          st->n_apply[ph] += mode == 0 ? 1 : 0;
-          st->n_keep0[ph] += (mode == 1 && m == 0) ? 1 : 0;
-        }
-        if (!ok) {
-          nx.R = R;
-          nx.iter = rs.iter;
-          nx.halt = 1;
-          nx.switch_req = 0;
-          nx.status = 1;
-          nx.pcur = rs.pcur;
-          store_host_flag(a.hflag, 1);
-        } else {
-          nx.R = Rn;
-          nx.iter = it;
-          nx.status = 0;
-          nx.halt = (done || sw) ? 1 : 0;
-          if (done || sw) st->rslot = m;  // no K2 follows: r stays in this head's slot
-          nx.switch_req = sw ? 1 : 0;
-          nx.pcur = pending ? rs.pcur ^ 1 : rs.pcur;
-          store_host_flag(a.hflag, ((done || sw) ? 1 : 0) | (sw ? 2 : 0));
-          if (pending) {
-            st->b = bn;
-            st->a_prev = st->a;
-          }
-        }
-      }
+      took = 1;
     }
-  }
-  __syncthreads();
-}
-
-// A halted iteration carries its state over to the next one (head, workgroup 0).
-__device__ void carry_state(const MsArgs& a) {
-  if (blockIdx.x != 0) return;
-  SolveState* st = a.st;
-  const RotState& rs = st->rot[a.par];
-  RotState& nx = st->rot[a.par ^ 1];
-  const int j = threadIdx.x;
-  if (j < kMaxShifts) {
-    nx.zeta[j] = rs.zeta[j];
-    nx.active[j] = rs.active[j];
+    nx.zeta_prev[j] = live && act ? z : zp;
+    nx.zeta[j] = zn;
+    nx.active[j] = act;
+    nx.took[j] = took;
+#pragma unroll
+    for (int i = 0; i <= kMaxSteps; ++i) {
+      nx.cx[i][j] = cx[i];
+      nx.cp[i][j] = cp[i];
+    }
   }
   if (j == 0) {
-    nx.R = rs.R;
-    nx.iter = rs.iter;
-    nx.halt = 1;
-    nx.switch_req = rs.switch_req;
-    nx.status = rs.status;
-    nx.pending = rs.pending;
-    nx.pcur = rs.pcur;
-    nx.ndef = rs.ndef;
-    store_host_flag(a.hflag, 1 | (rs.switch_req ? 2 : 0));
+    if (n == 0) st->bnorm2 = g;
+    nx.g = live ? g : in.g1;
+    nx.a = live ? p.a : in.a1;
+    nx.P = live ? p.P : in.P1;
+    nx.iter = live ? n + 1 : n;
+    nx.launch = live ? a.launch + 1 : a.launch;
+    nx.m = live ? m0 + 1 : m0;
+    nx.fresh = flushed ? 0 : fresh;
+    nx.halt = live ? 0 : 1;
+    if (!live) {
+      st->fin = a.par ^ 1;
+      st->iter = n;
+      st->R = g;
+      st->eps2 = eps2;
+      st->status = p.stop == 3 ? 1 : 0;
+      store_host_flag(a.hflag, 1 | (p.stop == 2 ? 2 : 0));
+    }
   }
 }
 
-// The pending update of row i: the listed shifts' x_j and p_j and x_0 as the plan
-// composes them (the current step and the m deferred ones, reading the residuals of the
-// m deferring heads from ring slots 0..m-1; a deferring head touches neither x_0 nor any
-// shift, and the first of a cycle keeps p), then the new direction r + b p, which is
-// stored in the other direction buffer and returned.  rr, pp: the row's r and p (already
-// loaded).
-template <class R>
-__device__ __forceinline__ cplx<R> update_row(const MsArgs& a, const Plan& pl, int64_t i,
-                                              const cplx<R>& rr, const cplx<R>& pp,
-                                              double2* __restrict__ x0,
-                                              cplx<R>* __restrict__ pnew) {
-  cplx<R>* __restrict__ pk = static_cast<cplx<R>*>(a.pk);
-  cplx<R>* __restrict__ pkeep0 = static_cast<cplx<R>*>(a.pkeep0);
-  double2* __restrict__ x = a.x;
-  const double2 rd = to_d(rr), pd = to_d(pp);
-  if (pl.keep0) st_stream(&pkeep0[i], pp);
-  // the residuals of the m heads that deferred, in ring slots 0..m-1 (zero beyond m,
-  // where the coefficients are zero too)
-  double2 rk[kMaxSteps - 1];
-#pragma unroll
-  for (int k = 0; k < kMaxSteps - 1; ++k)
-    rk[k] = k < pl.m ? to_d(ld_stream(&rslot<R>(a, k)[i])) : double2{0.0, 0.0};
-  const int m = pl.m;
-  if (pl.mode == 0) {
-    // x_0: with one step (m = 0) the fused multiply-add rounds exactly as x_0 += a p
-    double2 xv = ld_stream(&x0[i]);
-    const double2 p1 = m > 0 ? to_d(ld_stream(&pkeep0[i])) : pd;
-#pragma unroll
-    for (int k = kMaxSteps - 2; k >= 0; --k) {
-      if (k < m) {
-        xv.x = fma(pl.x0c[k + 1], rk[k].x, xv.x);
-        xv.y = fma(pl.x0c[k + 1], rk[k].y, xv.y);
-      }
-    }
-    xv.x = fma(pl.x0c[0], p1.x, xv.x);
-    xv.y = fma(pl.x0c[0], p1.y, xv.y);
-    st_stream(&x0[i], xv);
+// K2's prologue: true in a workgroup that goes on to the rows (with e and in loaded); a
+// halted iteration hands the halt on, the extra workgroup does the plan.
+__device__ __forceinline__ bool k2_begin(const MsArgs& a, Early& e, StepIn& in) {
+  load_early(a, e);
+  in = step_in(a);
+  if (int(blockIdx.x) != a.gg) return true;
+  if (in.halt) {
+    if (threadIdx.x == 0) a.st->rot[a.par ^ 1].halt = 1;
+  } else {
+    plan_workgroup(a, in, e);
   }
-  // shifts in groups of MSC_UPD_GROUP: a group's loads are all issued before its first
-  // store; a last, partial group is masked.  With one step (m = 0) the fused
-  // multiply-adds round exactly as x += a p and p <- zeta r + b p.
-  const int nact = pl.nact;
-  auto group = [&](int q, int cnt, auto full) {
-    cplx<R> pj[kUpdGroup];
-    double2 xj[kUpdGroup];
-#pragma unroll
-    for (int u = 0; u < kUpdGroup; ++u) {
-      if (decltype(full)::value || u < cnt) {
-        pj[u] = ld_stream(&pk[pl.po[q + u] + i]);
-        xj[u] = ld_stream(&x[pl.xo[q + u] + i]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUpdGroup; ++u) {
-      if (decltype(full)::value || u < cnt) {
-        const int c = q + u;
-        const double2 pjd = to_d(pj[u]);
-        double2 xv = xj[u];
-#pragma unroll
-        for (int k = kMaxSteps - 2; k >= 0; --k) {
-          if (k < m) {
-            xv.x = fma(pl.cx[k + 1][c], rk[k].x, xv.x);
-            xv.y = fma(pl.cx[k + 1][c], rk[k].y, xv.y);
-          }
-        }
-        xv.x = fma(pl.cx[0][c], pjd.x, xv.x);
-        xv.y = fma(pl.cx[0][c], pjd.y, xv.y);
-        st_stream(&x[pl.xo[c] + i], xv);
-        if (pl.pw[c]) {
-          const double c0 = pl.cp[0][c];
-          double2 np{c0 * pjd.x, c0 * pjd.y};
-#pragma unroll
-          for (int k = 0; k < kMaxSteps - 1; ++k) {
-            if (k < m) {
-              np.x = fma(pl.cp[k + 1][c], rk[k].x, np.x);
-              np.y = fma(pl.cp[k + 1][c], rk[k].y, np.y);
-            }
-          }
-          const double cr = pl.cp[m + 1][c];
-          np.x = fma(cr, rd.x, np.x);
-          np.y = fma(cr, rd.y, np.y);
-          st_stream(&pk[pl.po[c] + i], from_d<R>(np));
-        }
-      }
-    }
-  };
-  int q = 0;
-  for (; q + kUpdGroup <= nact; q += kUpdGroup) group(q, kUpdGroup, std::true_type{});
-  if (q < nact) group(q, nact - q, std::false_type{});
-  const cplx<R> np = next_dir<R>(pl.bn, rr, pp);
-  st_stream(&pnew[i], np);
-  return np;
+  return false;
 }
 
-// ---- head on the CSR path: the pending update only (K1 follows as its own kernel) -----
-template <class R>
-__global__ __launch_bounds__(kBlock) void k_update(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& rs = st->rot[a.par];
-  if (rs.halt) {
-    carry_state(a);
-    return;
-  }
-  Early e;
-  if (rs.pending) load_early(region(a, 1), a.gk2, e);
-  const int pc = rs.pcur;
-  const int64_t n = a.n;
-  const cplx<R>* __restrict__ rv = rslot<R>(a, rs.ndef);
-  const cplx<R>* __restrict__ pv = static_cast<const cplx<R>*>(a.pb[pc]);
-  cplx<R>* __restrict__ pnew = static_cast<cplx<R>*>(a.pb[pc ^ 1]);
-  double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * n;
-  int64_t beg, end;
-  block_range(n, kBlock, beg, end);
-  // this thread's first row is read while R' is being summed
-  const int64_t i0 = beg + threadIdx.x;
-  const int64_t ic = i0 < end ? i0 : n - 1;
-  const cplx<R> r_first = rv[ic], p_first = pv[ic];
-  __shared__ Plan pl;
-  head_plan<R>(a, e, pl);
-  if (!pl.ok || !pl.pending) return;
-  for (int64_t i = i0; i < end; i += kBlock) {
-    const bool first = i == i0;
-    update_row<R>(a, pl, i, first ? r_first : rv[i], first ? p_first : pv[i], x0, pnew);
-  }
-}
-
-// ---- head on the sliced ELLPACK path: pending update fused with K1 -------------------
-// One row per lane, one slice per wave.  With an update pending, the lane first updates
-// its own row (x, p_j, and p' = r + b p stored in the other buffer), then t = M p' takes
-// p' at the gathered columns from r and the old p, rounded exactly as the owning lane
-// rounds it; P = |t|^2 + sigma0 |p'|^2 (A = M^H M) or Re p'^H t + sigma0 |p'|^2.
-template <class R, bool MHM>
-__global__ __launch_bounds__(kBlock) void k1_fused(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& rs = st->rot[a.par];
-  if (rs.halt) {
-    carry_state(a);
-    return;
-  }
-  const int pending = rs.pending;
-  Early e;
-  if (pending) load_early(region(a, 1), a.gk2, e);
-  const int pc = rs.pcur;
-  const Sell<cplx<R>> m = pick_sm<R>(a);
-  const cplx<R>* __restrict__ rv = rslot<R>(a, rs.ndef);
-  const cplx<R>* __restrict__ pv = static_cast<const cplx<R>*>(a.pb[pc]);
-  cplx<R>* __restrict__ pnew = static_cast<cplx<R>*>(a.pb[pc ^ 1]);
-  cplx<R>* __restrict__ t = static_cast<cplx<R>*>(a.t);
-  double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
-  const double sigma0 = st->sigma0;
-  constexpr int SPB = kBlock / kSlice;
-  const int lane = threadIdx.x % kSlice;
-  Sweep sw = make_sweep(a.nslices, a.ord, SPB);
-  // the first slice's own row is read while R' is being summed
-  const bool has0 = sw.more();
-  const int64_t sl0 = has0 ? sw.slice() : 0;
-  const int64_t row0 = sl0 * kSlice + lane;
-  const int64_t rc = (has0 && row0 < a.n) ? row0 : a.n - 1;
-  const cplx<R> r_first = rv[rc], p_first = pv[rc];
-  __shared__ Plan pl;
-  head_plan<R>(a, e, pl);
-  if (!pl.ok) return;
-  const bool upd = pl.pending != 0;
-  const double bn = pl.bn;
-  double acc = 0.0;
-  for (bool first = true; sw.more(); sw.next(), first = false) {
-    const int64_t sl = first ? sl0 : sw.slice();
-    const int64_t row = sl * kSlice + lane;
-    const bool live = row < a.n;
-    const int64_t rr = live ? row : a.n - 1;  // lanes past n read a valid row, unused
-    const cplx<R> r_i = first ? r_first : rv[rr];
-    const cplx<R> p_i = first ? p_first : pv[rr];
-    cplx<R> p_row = p_i;
-    if (upd) {
-      if (live)
-        p_row = update_row<R>(a, pl, row, r_i, p_i, x0, pnew);
-      else
-        p_row = next_dir<R>(bn, r_i, p_i);
-    }
-    if (!pl.spmv) continue;
-    // without a pending update p' = p: the same product with r := p and b = 0 (exact)
-    const cplx<R> d = m.diag[rr];
-    cplx<R> v = sell_row_next<R>(m, upd ? rv : pv, pv, bn, sl, lane);
-    cfma<R>(v, d, p_row);
-    if (live) {
-      st_stream(&t[row], v);
-      if (MHM)
-        acc += norm2d<R>(v) + sigma0 * norm2d<R>(p_row);
-      else
-        acc += double(p_row.x) * double(v.x) + double(p_row.y) * double(v.y) +
-               sigma0 * norm2d<R>(p_row);
-    }
-  }
-  if (pl.spmv) store_partial(region(a, 0), acc);
-}
-
-// ---- K1 -------------------------------------------------------------------------------
-template <class R, int L, bool MHM>
-__global__ __launch_bounds__(kBlock) void k1_apply(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& ns = st->rot[a.par ^ 1];  // written by this iteration's head
-  if (ns.halt) return;
-  const Csr<cplx<R>> m = pick_m<R>(a);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.pb[ns.pcur]);
-  cplx<R>* __restrict__ t = static_cast<cplx<R>*>(a.t);
-  const double sigma0 = st->sigma0;
-  constexpr int GPB = kBlock / L;
-  const int lane = threadIdx.x % L, grp = threadIdx.x / L;
-  int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
-  double acc = 0.0;
-  auto epilogue = [&](int64_t row, const cplx<R>& v) {
-    t[row] = v;
-    const cplx<R> pr = p[row];
-    if (MHM)
-      acc += norm2d<R>(v) + sigma0 * norm2d<R>(pr);
-    else
-      acc += double(pr.x) * double(v.x) + double(pr.y) * double(v.y) + sigma0 * norm2d<R>(pr);
-  };
-  for (int64_t row = beg + grp; row < end; row += 2 * GPB) {
-    const int64_t row1 = row + GPB;
-    const bool has1 = row1 < end;
-    cplx<R> v0, v1;
-    row_dot2<R, L>(m, p, row, row1, has1, lane, v0, v1);
-    if (lane == 0) {
-      epilogue(row, v0);
-      if (has1) epilogue(row1, v1);
-    }
-  }
-  store_partial(region(a, 0), acc);
-}
-
-// ---- K2 (A = M^H M): r <- r - a (M^H t + sigma0 p), R' = |r|^2 ------------------------
-template <class R, int L>
-__global__ __launch_bounds__(kBlock) void k2_mhm(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& ns = st->rot[a.par ^ 1];  // written by this iteration's head
-  if (ns.halt) return;
-  Early e;
-  load_early(region(a, 0), a.gk1, e);
-  double step;
-  if (!k2_step(a, e, step)) return;  // breakdown: every workgroup sees the same P
-  const Csr<cplx<R>> mh = pick_mh<R>(a);
-  const cplx<R>* __restrict__ t = static_cast<const cplx<R>*>(a.t);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.pb[ns.pcur]);
-  // the residual moves from this head's ring slot to the next one's (in place when equal)
-  const cplx<R>* rin = rslot<R>(a, st->rot[a.par].ndef);
-  cplx<R>* r = rslot<R>(a, ns.ndef);
-  const double sigma0 = st->sigma0;
-  constexpr int GPB = kBlock / L;
-  const int lane = threadIdx.x % L, grp = threadIdx.x / L;
-  int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
-  double acc = 0.0;
-  auto epilogue = [&](int64_t row, const cplx<R>& q) {
-    const double2 pr = to_d(p[row]);
-    const double2 rr = to_d(rin[row]);
-    const double2 qd = to_d(q);
-    double2 nr;
-    nr.x = rr.x - step * (qd.x + sigma0 * pr.x);
-    nr.y = rr.y - step * (qd.y + sigma0 * pr.y);
-    const cplx<R> st_r = from_d<R>(nr);
-    r[row] = st_r;
-    acc += norm2d<R>(st_r);
-  };
-  for (int64_t row = beg + grp; row < end; row += 2 * GPB) {
-    const int64_t row1 = row + GPB;
-    const bool has1 = row1 < end;
-    cplx<R> q0, q1;
-    row_dot2<R, L>(mh, t, row, row1, has1, lane, q0, q1);
-    if (lane == 0) {
-      epilogue(row, q0);
-      if (has1) epilogue(row1, q1);
-    }
-  }
-  store_partial(region(a, 1), acc);
-}
-
-// ---- K2 on the sliced ELLPACK copy of M^H: one row per lane, one slice per wave ------
-template <class R>
-__global__ __launch_bounds__(kBlock) void k2_sell(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& ns = st->rot[a.par ^ 1];  // written by this iteration's head
-  if (ns.halt) return;
-  Early e;
-  load_early(region(a, 0), a.gk1, e);
-  const Sell<cplx<R>> mh = pick_shm<R>(a);
-  const cplx<R>* __restrict__ t = static_cast<const cplx<R>*>(a.t);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.pb[ns.pcur]);
-  // the residual moves from this head's ring slot to the next one's (in place when equal)
-  const cplx<R>* rin = rslot<R>(a, st->rot[a.par].ndef);
-  cplx<R>* r = rslot<R>(a, ns.ndef);
-  const double sigma0 = st->sigma0;
-  constexpr int SPB = kBlock / kSlice;
-  const int lane = threadIdx.x % kSlice;
-  Sweep sw = make_sweep(a.nslices, a.ord, SPB);
-  double acc = 0.0;
-  double step = 0.0;
-  // q = M^H t for one slice, with the row operands of the epilogue
-  struct Row {
-    cplx<R> q, p, r;
-  };
-  auto product = [&](int64_t sl) {
-    const int64_t row = sl * kSlice + lane;
-    const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
-    const cplx<R> tr = t[rr];
-    Row o;
-    o.p = ld_stream(&p[rr]);
-    o.r = ld_stream(&rin[rr]);
-    const cplx<R> d = mh.diag[rr];
-    o.q = sell_row<R>(mh, t, sl, lane);
-    cfma<R>(o.q, d, tr);
-    return o;
-  };
-  auto epilogue = [&](int64_t sl, const Row& o) {
-    const int64_t row = sl * kSlice + lane;
-    if (row >= a.n) return;
-    const double2 pr = to_d(o.p);
-    const double2 rr = to_d(o.r);
-    const double2 qd = to_d(o.q);
-    double2 nr;
-    nr.x = rr.x - step * (qd.x + sigma0 * pr.x);
-    nr.y = rr.y - step * (qd.y + sigma0 * pr.y);
-    const cplx<R> st_r = from_d<R>(nr);
-    st_stream(&r[row], st_r);
-    acc += norm2d<R>(st_r);
-  };
-  // the first slice's product runs while P's partials are on their way
-  const bool has0 = sw.more();
-  const int64_t sl0 = has0 ? sw.slice() : 0;
-  Row first{};
-  if (has0) first = product(sl0);
-  if (!k2_step(a, e, step)) return;  // breakdown: every workgroup sees the same P
-  if (has0) epilogue(sl0, first);
-  for (sw.next(); sw.more(); sw.next()) {
-    const int64_t sl = sw.slice();
-    epilogue(sl, product(sl));
-  }
-  store_partial(region(a, 1), acc);
+// The sums and the step in every other workgroup; false where no step runs.
+__device__ __forceinline__ bool k2_step(const MsArgs& a, const Early& e, const StepIn& in, StepPlan& p) {
+  p.stop = 1;
+  if (in.halt) return false;
+  double g, d;
+  both_sums(a, e, g, d);
+  p = step_plan(in, g, d);
+  return p.stop == 0;
 }
 
 // The march positions [beg, end) of this wave: its XCD's share of [0, n) (workgroups are
 // dealt to the XCDs in turn), split evenly and contiguously over the XCD's waves.
-__device__ __forceinline__ void march_range(int64_t n, int wpb, int64_t& beg, int64_t& end) {
+__device__ __forceinline__ void march_range(int64_t n, int wpb, int64_t& beg, int64_t& end,
+                                            int g = gridDim.x) {
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
-  const int g = gridDim.x;
   int64_t lo = 0, hi = n, nw = int64_t(g) * wpb, w = int64_t(blockIdx.x) * wpb + wv;
   if (g % kXcds == 0) {
     const int x = int(blockIdx.x % kXcds);
@@ -1007,454 +461,684 @@ __device__ __forceinline__ void march_range(int64_t n, int wpb, int64_t& beg, in
   end = lo + (hi - lo) * (w + 1) / nw;
 }
 
-// ---- matrix-free head and K2: one lattice site (three rows) per lane ------------------
-// The waves sweep blocks of 64 sites (192 rows).  The head first applies the pending
-// update to the block's rows, one row per lane in three passes (the same update_row as on
-// the sliced path), then computes t' = M p' for the block's sites, one site per lane,
-// forming p' = r + b p at its own and at every gathered neighbour's rows with next_dir,
-// so that all of them round exactly as the row's owner does; P = |t'|^2 + sigma0 |p'|^2.
-// LR: rows stored per link (3, or 2 for SU(3) links).
-// TR (FP64): t' = M r + b t instead of M (r + b p), the old t being M p from the previous
-// head: one gathered vector instead of two.  The recurrence's rounding stays at the FP64
-// level over the launches between two direct products (the host interleaves a direct
-// one every kTrEvery launches).
-// A lane's own rows (48 or 24 contiguous bytes, read or written by three instructions
-// whose lanes lie 48 or 24 bytes apart) take ordinary loads and stores: with streaming
-// hints a line could leave the cache between the three.
-constexpr int kSiteBlock = kWave;  // sites per wave pass
-
-// MARCH (two-row links; a.head_march = tc >= 2): K2's column order along t, with the t
-// link and the gathered values (p', or r with TR) at the site and at its forward t
-// neighbour carried from one site of a column to the next (TCarry).
-template <class R, int LR, bool TR, bool MARCH = false>
-__global__ __launch_bounds__(kBlock, MSC_SITE_HEAD_WPE) void k1_site(MsArgs a) {
-  static_assert(!MARCH || LR == 2, "the head marches on two-row links");
-  const SolveState* st = a.st;
-  const RotState& rs = st->rot[a.par];
-  if (rs.halt) {
-    carry_state(a);
-    return;
-  }
-  const int pending = rs.pending;
-  Early e;
-  if (pending) load_early(region(a, 1), a.gk2, e);
-  const int pc = rs.pcur;
-  const cplx<R>* __restrict__ rv = rslot<R>(a, rs.ndef);
-  const cplx<R>* __restrict__ pv = static_cast<const cplx<R>*>(a.pb[pc]);
-  cplx<R>* __restrict__ pnew = static_cast<cplx<R>*>(a.pb[pc ^ 1]);
-  cplx<R>* __restrict__ t = static_cast<cplx<R>*>(a.t);
-  double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
-  const Stencil<cplx<R>> w = pick_w<R>(a);
-  const uint32_t vol = uint32_t(w.vol);
-  const int64_t nblk = (int64_t(vol) + kSiteBlock - 1) / kSiteBlock;
-  const double sigma0 = st->sigma0;
-  constexpr int WPB = kBlock / kWave;
-  const int lane = threadIdx.x % kWave;
-  Sweep sw = make_sweep(nblk, a.ord, WPB);
-  __shared__ Plan pl;
-  head_plan<R>(a, e, pl);
-  if (!pl.ok) return;
-  const bool upd = pl.pending != 0;
-  const double bn = pl.bn;
-  double acc = 0.0;
-  if constexpr (MARCH) {
-    const uint32_t tc = uint32_t(a.head_march);
-    const uint32_t vol3 = vol / uint32_t(w.L[3]);  // sites per t-slice
-    const uint32_t bs = vol3 / uint32_t(kSiteBlock);
-    constexpr int K = 3 * LR;
-    const cplx<R>* __restrict__ rg = upd ? rv : pv;
-    // the gathered vector at row i: r with TR (p without a pending update), else p'
-    // (without a pending update bn = 0 and p' = p exactly)
-    auto gv = [&](int64_t i) {
-      if constexpr (TR)
-        return rg[i];
-      else
-        return next_dir<R>(bn, rg[i], pv[i]);
-    };
-    TCarry<R, LR> car;
-    int64_t qb, qe;
-    march_range(nblk, WPB, qb, qe);
-    for (uint32_t q = uint32_t(qb); q < uint32_t(qe); ++q) {
-      const uint32_t col = q / tc, chunk = col / bs;
-      const int64_t blk = int64_t((chunk * tc + (q - col * tc)) * bs + (col - chunk * bs));
-      if (upd) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const int64_t row = (3 * blk + k) * kWave + lane;
-          update_row<R>(a, pl, row, rv[row], pv[row], x0, pnew);  // below n
-        }
-      }
-#if MSC_SITE_SB
-      __builtin_amdgcn_sched_barrier(0);
-#endif
-      if (!pl.spmv) continue;
-      const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);  // below vol
-      if (q == uint32_t(qb) || q % tc == 0) {
-        // a run's first site or a column's: the carry from memory
-        const uint32_t sb = site >= vol3 ? site - vol3 : site + (vol - vol3);  // periodic
-        const cplx<R>* __restrict__ wt = w.w + int64_t(3) * K * vol;
-#pragma unroll
-        for (int k = 0; k < K; ++k) car.u[k] = wt[int64_t(k) * vol + sb];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          car.own[c] = gv(3 * int64_t(sb) + c);
-          car.fw[c] = gv(3 * int64_t(site) + c);
-        }
-      }
-      const int64_t r0 = 3 * int64_t(site);
-      cplx<R> own[3], pr[3], v[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        own[c] = car.fw[c];
-        // p' at the site: with TR own is r (p without a pending update), else p' itself
-        pr[c] = (TR && upd) ? next_dir<R>(bn, own[c], pv[r0 + c]) : own[c];
-      }
-      stencil_site_c<R, LR, true>(w, site, own, 1, gv, v, &car);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        car.own[c] = own[c];
-        if constexpr (TR) {
-          const cplx<R> told = t[r0 + c];
-          v[c].x = fma(bn, told.x, v[c].x);
-          v[c].y = fma(bn, told.y, v[c].y);
-        }
-        t[r0 + c] = v[c];
-        acc += norm2d<R>(v[c]) + sigma0 * norm2d<R>(pr[c]);
-      }
-    }
-    if (pl.spmv) store_partial(region(a, 0), acc);
-    return;
-  }
-  for (; sw.more(); sw.next()) {
-    const int64_t blk = sw.slice();
-    if (upd) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int64_t row = (3 * blk + k) * kWave + lane;
-        if (row < a.n) update_row<R>(a, pl, row, rv[row], pv[row], x0, pnew);
-      }
-    }
-#if MSC_SITE_SB
-    __builtin_amdgcn_sched_barrier(0);
-#endif
-    if (!pl.spmv) continue;
-    const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
-    const bool live = site < vol;
-    const uint32_t ss = live ? site : vol - 1;  // lanes past the volume compute a valid site, unused
-    const int64_t r0 = 3 * int64_t(ss);
-    cplx<R> pr[3], own[3], v[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const cplx<R> ri = rv[r0 + c], pi = pv[r0 + c];
-      pr[c] = upd ? next_dir<R>(bn, ri, pi) : pi;
-      own[c] = TR ? (upd ? ri : pi) : pr[c];
-    }
-    const cplx<R>* __restrict__ rg = upd ? rv : pv;
-    if constexpr (TR) {
-      // without a pending update bn = 0 and the product is M p
-      stencil_site<R, LR>(w, ss, own, 1, [&](int64_t c) { return rg[c]; }, v);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const cplx<R> told = t[r0 + c];
-        v[c].x = fma(bn, told.x, v[c].x);
-        v[c].y = fma(bn, told.y, v[c].y);
-      }
-    } else {
-      // without a pending update p' = p: the same product with r := p and b = 0 (exact)
-      stencil_site<R, LR>(w, ss, own, 1, [&](int64_t c) { return next_dir<R>(bn, rg[c], pv[c]); },
-                          v);
-    }
-    if (live) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        t[r0 + c] = v[c];
-        acc += norm2d<R>(v[c]) + sigma0 * norm2d<R>(pr[c]);
-      }
-    }
-  }
-  if (pl.spmv) store_partial(region(a, 0), acc);
+// s_n = q + sigma0 r + b s, r_{n+1} = r - a s_n at one row (q = (A r_n)_row), formed in FP64
+// and rounded once each.
+template <class R>
+__device__ __forceinline__ void row_step(const StepPlan& p, double sigma0, const cplx<R>& q,
+                                         const cplx<R>& r, const cplx<R>& s, cplx<R>& sn,
+                                         cplx<R>& rn) {
+  const double2 qd = to_d(q), rd = to_d(r), sd = to_d(s);
+  const double2 v{fma(p.b, sd.x, fma(sigma0, rd.x, qd.x)), fma(p.b, sd.y, fma(sigma0, rd.y, qd.y))};
+  sn = from_d<R>(v);
+  rn = from_d<R>(double2{fma(-p.a, v.x, rd.x), fma(-p.a, v.y, rd.y)});
 }
 
-// K2: q = M^H t = m t - D t for the block's sites, then r <- r - a (q + sigma0 p) and
-// R' = |r|^2 on their rows.
-// MARCH (a.k2_march = tc >= 2; the host checks that a t-slice holds whole blocks of 64
-// sites and that tc divides L_t): the blocks are taken in columns of tc consecutive
-// t-slices (march position q: column q / tc, slice q % tc of it; the columns of one
-// chunk of tc slices first), each wave a contiguous run of positions, so that within a
-// column a lane's next site is its last one moved one slice along t: its t link and its
-// values stay in registers (TCarry), and the XCD's waves work through the same few
-// slices together, where the other neighbours lie.
-template <class R, int LR, bool MARCH>
-__global__ __launch_bounds__(kBlock, MARCH ? (sizeof(R) == 8 ? MSC_K2_MARCH_WPE64
-                                                               : MSC_K2_MARCH_WPE32)
-                                            : MSC_SITE_K2_WPE) void k2_site(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& ns = st->rot[a.par ^ 1];  // written by this iteration's head
-  if (ns.halt) return;
-  Early e;
-  load_early(region(a, 0), a.gk1, e);
-  const cplx<R>* __restrict__ t = static_cast<const cplx<R>*>(a.t);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.pb[ns.pcur]);
-  // the residual moves from this head's ring slot to the next one's (in place when equal)
-  const cplx<R>* rin = rslot<R>(a, st->rot[a.par].ndef);
-  cplx<R>* r = rslot<R>(a, ns.ndef);
-  const Stencil<cplx<R>> w = pick_w<R>(a);
-  const uint32_t vol = uint32_t(w.vol);
-  const int64_t nblk = (int64_t(vol) + kSiteBlock - 1) / kSiteBlock;
-  const double sigma0 = st->sigma0;
-  constexpr int WPB = kBlock / kWave;
-  const int lane = threadIdx.x % kWave;
-  Sweep sw = make_sweep(nblk, a.ord, WPB);
+// ---- A = M^H M or the CSR: K1 u = M r_n (A r_n for A given) and d_n's partials -----------
+template <class R, int L, bool MHM>
+__global__ __launch_bounds__(kBlock) void k1_csr(MsArgs a) {
+  const RotState& rs = a.st->rot[a.par];
+  if (rs.halt) return;
+  const Csr<cplx<R>> m = pick_m<R>(a);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
+  constexpr int GPB = kBlock / L;
+  const int lane = threadIdx.x % L, grp = threadIdx.x / L;
+  int64_t beg, end;
+  block_range(a.n, GPB, beg, end);
   double acc = 0.0;
-  double step = 0.0;
-  struct Site {
-    cplx<R> q[3];
+  auto epilogue = [&](int64_t row, const cplx<R>& v) {
+    u[row] = v;
+    if (MHM) {
+      acc += norm2d<R>(v);
+    } else {
+      const cplx<R> rr = r[row];
+      acc += double(rr.x) * double(v.x) + double(rr.y) * double(v.y);
+    }
   };
-  auto product = [&](int64_t blk) {
-    const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
-    const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
-    const int64_t r0 = 3 * int64_t(ss);
-    cplx<R> own[3];
-    Site o;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) own[c] = t[r0 + c];
-    stencil_site<R, LR>(w, ss, own, -1, [&](int64_t c) { return t[c]; }, o.q);
+  for (int64_t row = beg + grp; row < end; row += 2 * GPB) {
+    const int64_t row1 = row + GPB;
+    const bool has1 = row1 < end;
+    cplx<R> v0, v1;
+    row_dot2<R, L>(m, r, row, row1, has1, lane, v0, v1);
+    if (lane == 0) {
+      epilogue(row, v0);
+      if (has1) epilogue(row1, v1);
+    }
+  }
+  store_partial(region(a, 2 + a.par), acc);
+}
+
+// K2: w = M^H u (u itself for A given), s_n, r_{n+1}, g_{n+1}'s partials.
+template <class R, int L, bool MHM>
+__global__ __launch_bounds__(kBlock) void k2_csr(MsArgs a) {
+  Early e;
+  StepIn in;
+  if (!k2_begin(a, e, in)) return;
+  StepPlan p;
+  if (!k2_step(a, e, in, p)) return;
+  const cplx<R>* __restrict__ u = static_cast<const cplx<R>*>(a.u);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
+  cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  const double sigma0 = in.sigma0;
+  int64_t beg, end;
+  double acc = 0.0;
+  auto epilogue = [&](int64_t row, const cplx<R>& q) {
+    cplx<R> sv, nv;
+    row_step<R>(p, sigma0, q, r[row], s[row], sv, nv);
+    s[row] = sv;
+    rn[row] = nv;
+    acc += norm2d<R>(nv);
+  };
+  if constexpr (MHM) {
+    const Csr<cplx<R>> mh = pick_mh<R>(a);
+    constexpr int GPB = kBlock / L;
+    const int lane = threadIdx.x % L, grp = threadIdx.x / L;
+    block_range(a.n, GPB, beg, end, a.gg);
+    for (int64_t row = beg + grp; row < end; row += 2 * GPB) {
+      const int64_t row1 = row + GPB;
+      const bool has1 = row1 < end;
+      cplx<R> q0, q1;
+      row_dot2<R, L>(mh, u, row, row1, has1, lane, q0, q1);
+      if (lane == 0) {
+        epilogue(row, q0);
+        if (has1) epilogue(row1, q1);
+      }
+    }
+  } else {
+    block_range(a.n, kBlock, beg, end, a.gg);
+    for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) epilogue(i, u[i]);
+  }
+  store_partial(region(a, a.par ^ 1), acc);
+}
+
+// ---- the sliced ELLPACK copies: one row per lane, one slice per wave ----------------------
+template <class R>
+__global__ __launch_bounds__(kBlock) void k1_sell(MsArgs a) {
+  const RotState& rs = a.st->rot[a.par];
+  if (rs.halt) return;
+  const Sell<cplx<R>> m = pick_sm<R>(a);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
+  const int lane = threadIdx.x % kSlice;
+  double acc = 0.0;
+  for (Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice); sw.more(); sw.next()) {
+    const int64_t sl = sw.slice();
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
+    const cplx<R> own = r[rr], d = m.diag[rr];
+    cplx<R> v = sell_row<R>(m, r, sl, lane);
+    cfma<R>(v, d, own);
+    if (row < a.n) {
+      u[row] = v;
+      acc += norm2d<R>(v);
+    }
+  }
+  store_partial(region(a, 2 + a.par), acc);
+}
+
+template <class R>
+__global__ __launch_bounds__(kBlock) void k2_sell(MsArgs a) {
+  Early e;
+  StepIn in;
+  if (!k2_begin(a, e, in)) return;
+  const Sell<cplx<R>> mh = pick_shm<R>(a);
+  const cplx<R>* __restrict__ u = static_cast<const cplx<R>*>(a.u);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
+  cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  const double sigma0 = in.sigma0;
+  const int lane = threadIdx.x % kSlice;
+  struct Row {
+    cplx<R> q, r, s;
+  };
+  auto product = [&](int64_t sl) {
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;
+    const cplx<R> ur = u[rr];
+    Row o;
+    o.r = ld_stream(&r[rr]);
+    o.s = ld_stream(&s[rr]);
+    const cplx<R> d = mh.diag[rr];
+    o.q = sell_row<R>(mh, u, sl, lane);
+    cfma<R>(o.q, d, ur);
     return o;
   };
-  auto epilogue = [&](int64_t blk, const Site& o) {
-    const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
-    if (site >= vol) return;
-    const int64_t r0 = 3 * int64_t(site);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const double2 pr = to_d(p[r0 + c]);
-      const double2 rr = to_d(rin[r0 + c]);
-      const double2 qd = to_d(o.q[c]);
-      double2 nr;
-      nr.x = rr.x - step * (qd.x + sigma0 * pr.x);
-      nr.y = rr.y - step * (qd.y + sigma0 * pr.y);
-      const cplx<R> st_r = from_d<R>(nr);
-      r[r0 + c] = st_r;
-      acc += norm2d<R>(st_r);
-    }
+  StepPlan p;
+  double acc = 0.0;
+  auto epilogue = [&](int64_t sl, const Row& o) {
+    const int64_t row = sl * kSlice + lane;
+    if (row >= a.n) return;
+    cplx<R> sv, nv;
+    row_step<R>(p, sigma0, o.q, o.r, o.s, sv, nv);
+    st_stream(&s[row], sv);
+    rn[row] = nv;
+    acc += norm2d<R>(nv);
   };
-  if constexpr (MARCH) {
-    // positions and blocks in 32 bits (the volume is below 2^31)
-    const uint32_t tc = uint32_t(a.k2_march);
-    const uint32_t bs = vol / uint32_t(w.L[3]) / uint32_t(kSiteBlock);  // blocks per t-slice
-    auto block_at = [&](uint32_t q) {
-      const uint32_t col = q / tc, chunk = col / bs;
-      return int64_t((chunk * tc + (q - col * tc)) * bs + (col - chunk * bs));
-    };
-    TCarry<R, LR> car;
-    const uint32_t vol3 = vol / uint32_t(w.L[3]);  // sites per t-slice
-    constexpr int K = 3 * LR;
-    // the carry for a block whose previous site along t this wave did not just take: the
-    // backward t link and the values at the backward t neighbour and at the site
-    auto preload = [&](int64_t blk) {
-      const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
-      const uint32_t sb = site >= vol3 ? site - vol3 : site + (vol - vol3);  // periodic
-      const cplx<R>* __restrict__ wt = w.w + int64_t(3) * K * vol;
-#pragma unroll
-      for (int k = 0; k < K; ++k) car.u[k] = wt[int64_t(k) * vol + sb];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        car.own[c] = t[3 * int64_t(sb) + c];
-        car.fw[c] = t[3 * int64_t(site) + c];
-      }
-    };
-    auto product_c = [&](int64_t blk) {
-      const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);  // below vol
-      cplx<R> own[3];
-      Site o;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) own[c] = car.fw[c];
-      stencil_site_c<R, LR, true>(w, site, own, -1, [&](int64_t c) { return t[c]; }, o.q, &car);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) car.own[c] = own[c];
-      return o;
-    };
-    int64_t qb, qe;
-    march_range(nblk, WPB, qb, qe);
-    uint32_t q = uint32_t(qb);
-    const uint32_t qend = uint32_t(qe);
-    const bool has0 = q < qend;
-    const int64_t b0 = has0 ? block_at(q) : 0;
-    Site first{};
-    if (has0) {
-      preload(b0);
-      first = product_c(b0);
-    }
-    if (!k2_step(a, e, step)) return;  // breakdown: every workgroup sees the same P
-    if (has0) {
-      epilogue(b0, first);
-      // within a column the carry moves on; a new column starts from memory
-#pragma nounroll
-      for (++q; q < qend; ++q) {
-        const int64_t blk = block_at(q);
-        if (q % tc == 0) preload(blk);
-        epilogue(blk, product_c(blk));
-      }
-    }
-    store_partial(region(a, 1), acc);
-    return;
-  }
-  // the first block's product runs while P's partials are on their way
+  // the first slice's product runs while the partials are on their way
+  Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice, a.gg);
   const bool has0 = sw.more();
-  const int64_t b0 = has0 ? sw.slice() : 0;
-  Site first{};
-  if (has0) first = product(b0);
-  if (!k2_step(a, e, step)) return;  // breakdown: every workgroup sees the same P
-  if (has0) epilogue(b0, first);
+  const int64_t sl0 = has0 ? sw.slice() : 0;
+  Row first{};
+  if (has0) first = product(sl0);
+  if (!k2_step(a, e, in, p)) return;
+  if (has0) epilogue(sl0, first);
   for (sw.next(); sw.more(); sw.next()) {
-    const int64_t blk = sw.slice();
-    epilogue(blk, product(blk));
+    const int64_t sl = sw.slice();
+    epilogue(sl, product(sl));
   }
-  store_partial(region(a, 1), acc);
+  store_partial(region(a, a.par ^ 1), acc);
 }
 
-// ---- K2 (A given): elementwise r <- r - a (t + sigma0 p) -------------------------------
-template <class R>
-__global__ __launch_bounds__(kBlock) void k2_herm(MsArgs a) {
-  const SolveState* st = a.st;
-  const RotState& ns = st->rot[a.par ^ 1];  // written by this iteration's head
-  if (ns.halt) return;
+// A given: one kernel.  r_{n+1} is formed at every gathered column from r, w and s, rounded
+// as its owner rounds it, and w_{n+1} = A r_{n+1} with it.
+template <class R, bool NARROW, class F>
+__device__ __forceinline__ cplx<R> sell_row_f(const Sell<cplx<R>>& m, int64_t sl, int lane, F val) {
+  constexpr int KP = std::is_same<R, float>::value ? 4 : 2;
+  int32_t c, c1;
+  if (m.wp > 0) {
+    c = int32_t(sl) * m.wp;
+    c1 = c + m.wp;
+  } else {
+    c = load_uniform(m.cptr, sl);
+    c1 = load_uniform(m.cptr, sl + 1);
+  }
+  cplx<R> acc = czero<R>();
+  for (; c < c1; c += KP) {
+    const int np = c1 - c;
+    int2 cc[KP];
+    cplx<R> v[2 * KP], x[2 * KP];
+    if (np >= KP)
+      sell_load<R, KP, true, NARROW>(m, c, KP, lane, cc, v);
+    else
+      sell_load<R, KP, false, NARROW>(m, c, np, lane, cc, v);
+#pragma unroll
+    for (int u = 0; u < KP; ++u) {
+      if (u < np) {
+        x[2 * u] = val(cc[u].x);
+        x[2 * u + 1] = val(cc[u].y);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * KP; ++u)
+      if (u < 2 * np) cfma<R>(acc, v[u], x[u]);
+  }
+  return acc;
+}
+
+template <class R, class F>
+__device__ __forceinline__ cplx<R> sell_row_any(const Sell<cplx<R>>& m, int64_t sl, int lane, F val) {
+  return m.col16 ? sell_row_f<R, true>(m, sl, lane, val) : sell_row_f<R, false>(m, sl, lane, val);
+}
+
+template <class R> __global__ __launch_bounds__(kBlock) void k_herm(MsArgs a) {
   Early e;
-  load_early(region(a, 0), a.gk1, e);
-  double step;
-  if (!k2_step(a, e, step)) return;  // breakdown: every workgroup sees the same P
-  const cplx<R>* __restrict__ t = static_cast<const cplx<R>*>(a.t);
-  const cplx<R>* __restrict__ p = static_cast<const cplx<R>*>(a.pb[ns.pcur]);
-  // the residual moves from this head's ring slot to the next one's (in place when equal)
-  const cplx<R>* rin = rslot<R>(a, st->rot[a.par].ndef);
-  cplx<R>* r = rslot<R>(a, ns.ndef);
-  const double sigma0 = st->sigma0;
+  StepIn in;
+  if (!k2_begin(a, e, in)) return;
+  StepPlan p;
+  if (!k2_step(a, e, in, p)) return;
+  const Sell<cplx<R>> m = pick_sm<R>(a);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
+  const cplx<R>* __restrict__ w = static_cast<const cplx<R>*>(a.w[a.par]);
+  const cplx<R>* __restrict__ s = static_cast<const cplx<R>*>(a.s[a.par]);
+  cplx<R>* __restrict__ wn = static_cast<cplx<R>*>(a.w[a.par ^ 1]);
+  cplx<R>* __restrict__ sn = static_cast<cplx<R>*>(a.s[a.par ^ 1]);
+  const double sigma0 = in.sigma0;
+  const int lane = threadIdx.x % kSlice;
+  auto next = [&](int32_t c) {
+    cplx<R> sv, nv;
+    row_step<R>(p, sigma0, w[c], r[c], s[c], sv, nv);
+    return nv;
+  };
+  double ag = 0.0, ad = 0.0;
+  for (Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice, a.gg); sw.more(); sw.next()) {
+    const int64_t sl = sw.slice();
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;
+    cplx<R> sv, own;
+    row_step<R>(p, sigma0, w[rr], r[rr], s[rr], sv, own);
+    const cplx<R> dg = m.diag[rr];
+    cplx<R> v = sell_row_any<R>(m, sl, lane, next);
+    cfma<R>(v, dg, own);
+    if (row < a.n) {
+      rn[row] = own;
+      sn[row] = sv;
+      wn[row] = v;
+      ag += norm2d<R>(own);
+      ad += double(own.x) * double(v.x) + double(own.y) * double(v.y);
+    }
+  }
+  double v[2] = {ag, ad};
+  block_sum_k<kBlock, 2>(v);
+  if (threadIdx.x == 0) {
+    store_agent(&region(a, a.par ^ 1)[blockIdx.x], v[0]);
+    store_agent(&region(a, 2 + (a.par ^ 1))[blockIdx.x], v[1]);
+  }
+}
+
+// w_n = A r_n and d_n's partials for the iteration's first k_herm and after a reliable
+// update (only_ru: where it ran).
+template <class R> __global__ __launch_bounds__(kBlock) void k_herm_w(MsArgs a, int only_ru) {
+  const RotState& rs = a.st->rot[a.par];
+  if (rs.halt || (only_ru && !a.st->ru_flag)) return;
+  const Sell<cplx<R>> m = pick_sm<R>(a);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ w = static_cast<cplx<R>*>(a.w[a.par]);
+  const int lane = threadIdx.x % kSlice;
+  double acc = 0.0;
+  for (Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice); sw.more(); sw.next()) {
+    const int64_t sl = sw.slice();
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;
+    const cplx<R> own = r[rr], dg = m.diag[rr];
+    cplx<R> v = sell_row_any<R>(m, sl, lane, [&](int32_t c) { return r[c]; });
+    cfma<R>(v, dg, own);
+    if (row < a.n) {
+      w[row] = v;
+      acc += double(own.x) * double(v.x) + double(own.y) * double(v.y);
+    }
+  }
+  store_partial(region(a, 2 + a.par), acc);
+}
+
+// ---- the links: one lattice site (three rows) per lane --------------------------------------
+// r, u and s lie colour by colour here, v(site, c) at c V + site: a wave's 64 consecutive
+// sites then read and write each colour in one contiguous run, so that streaming hints can
+// be given, and they are: a wave's own rows of r and s, and the t links it carries, are read
+// once per launch, and the L2 is left to the links and values that neighbours read again.
+// MARCH (a.march = tc >= 2 t-slices per column; the host checks that a t-slice holds whole
+// blocks of 64 sites and that tc divides L_t): the blocks are taken in columns of tc
+// consecutive t-slices, and each wave takes a contiguous run of them.  A lane's next site
+// is then its last one moved one slice along t: the site's t link (the next one's backward
+// t link), its values and its forward t neighbour's (the next one's own) stay in registers
+// (TCarry); a run that enters a new column loads them.
+// 32^3 x 64, K1 and K2 of an iteration: FP64 240 and 265 us, complex64 119 and 141 (with rows
+// of three colours together and no hints 322 and 342, 184 and 175, of which the head's r,
+// p and t and the applications, now apart, are a part).
+constexpr int kSiteBlock = kWave;  // sites per wave pass
+
+// The march's block at position q.
+__device__ __forceinline__ uint32_t march_block(uint32_t q, uint32_t tc, uint32_t bs) {
+  const uint32_t col = q / tc, chunk = col / bs;
+  return (chunk * tc + (q - col * tc)) * bs + (col - chunk * bs);
+}
+
+// body(site, out) for this wave's sites, out = (m + sign D) v there; lanes past the volume
+// are left out.  first(): called once by every wave of the workgroup, between its first
+// product (if it has any) and the rest; false ends the work.  g: workgroups that share the
+// sites.
+template <class R, int LR, bool MARCH, class F0, class F>
+__device__ __forceinline__ void for_sites(const MsArgs& a, const Stencil<cplx<R>>& w,
+                                          const cplx<R>* __restrict__ v, int sign, int g, F0 first,
+                                          F body) {
+  const uint32_t vol = uint32_t(w.vol);
+  const int64_t nblk = (int64_t(vol) + kSiteBlock - 1) / kSiteBlock;
+  constexpr int WPB = kBlock / kWave;
+  const int lane = threadIdx.x % kWave;
+  auto at = [&](uint32_t s, int c) { return v[int64_t(c) * vol + s]; };
+  cplx<R> own[3], out[3];
+  if constexpr (MARCH) {
+    const uint32_t tc = uint32_t(a.march);
+    const uint32_t vol3 = vol / uint32_t(w.L[3]);
+    const uint32_t bs = vol3 / uint32_t(kSiteBlock);
+    constexpr int K = 3 * LR;
+    TCarry<R, LR> car;
+    int64_t qb, qe;
+    march_range(nblk, WPB, qb, qe, g);
+#pragma nounroll
+    for (uint32_t q = uint32_t(qb);; ++q) {
+      const bool has = q < uint32_t(qe);
+      uint32_t site = 0;
+      if (has) {
+        site = march_block(q, tc, bs) * uint32_t(kSiteBlock) + uint32_t(lane);  // below vol
+        if (q == uint32_t(qb) || q % tc == 0) {
+          const uint32_t sb = site >= vol3 ? site - vol3 : site + (vol - vol3);  // periodic
+          const cplx<R>* __restrict__ wt = w.w + int64_t(3) * K * vol;
+#pragma unroll
+          for (int k = 0; k < K; ++k) car.u[k] = wt[int64_t(k) * vol + sb];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            car.own[c] = at(sb, c);
+            car.fw[c] = at(site, c);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) own[c] = car.fw[c];
+        stencil_site_c<R, LR, true>(w, site, own, sign, at, out, &car);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) car.own[c] = own[c];
+      }
+      if (q == uint32_t(qb) && !first()) return;
+      if (!has) return;
+      body(site, out);
+    }
+  } else {
+    Sweep sw = make_sweep(nblk, a.ord, WPB, g);
+#pragma nounroll
+    for (bool begin = true;; begin = false, sw.next()) {
+      const bool has = sw.more();
+      uint32_t site = 0;
+      if (has) {
+        site = uint32_t(sw.slice() * kSiteBlock) + uint32_t(lane);
+        const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
+#pragma unroll
+        for (int c = 0; c < 3; ++c) own[c] = at(ss, c);
+        stencil_site<R, LR>(w, ss, own, sign, at, out);
+      }
+      if (begin && !first()) return;
+      if (!has) return;
+      if (site < vol) body(site, out);
+    }
+  }
+}
+
+// STREAM (FP64): u goes out with streaming stores (32^3 x 64: 240 -> 235 us; in complex64
+// they make no difference).
+template <class R, int LR, bool STREAM, bool MARCH>
+__global__ __launch_bounds__(kBlock, 2) void k1_site(MsArgs a) {
+  static_assert(!MARCH || LR == 2, "the march carries two-row links");
+  // looked at after the first block's product: its loads do not wait for the state
+  const int halt = a.st->rot[a.par].halt;
+  const Stencil<cplx<R>> w = pick_w<R>(a);
+  cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
+  double acc = 0.0;
+  for_sites<R, LR, MARCH>(
+      a, w, rslot<R>(a, a.launch), 1, gridDim.x, [&] { return halt == 0; },
+      [&](uint32_t site, const cplx<R>(&out)[3]) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          if constexpr (STREAM)
+            st_stream(&u[c * w.vol + site], out[c]);
+          else
+            u[c * w.vol + site] = out[c];
+          acc += norm2d<R>(out[c]);
+        }
+      });
+  if (!halt) store_partial(region(a, 2 + a.par), acc);
+}
+
+template <class R, int LR, bool MARCH>
+__global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
+  static_assert(!MARCH || LR == 2, "the march carries two-row links");
+  Early e;
+  StepIn in;
+  if (!k2_begin(a, e, in)) return;
+  const Stencil<cplx<R>> w = pick_w<R>(a);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
+  cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  const double sigma0 = in.sigma0;
+  StepPlan p;
+  double acc = 0.0;
+  for_sites<R, LR, MARCH>(
+      a, w, static_cast<const cplx<R>*>(a.u), -1, a.gg,
+      // the first block's product runs while the partials are on their way
+      [&] { return k2_step(a, e, in, p); },
+      [&](uint32_t site, const cplx<R>(&out)[3]) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const int64_t i = c * w.vol + site;
+          cplx<R> sv, nv;
+          row_step<R>(p, sigma0, out[c], ld_stream(&r[i]), ld_stream(&s[i]), sv, nv);
+          st_stream(&s[i], sv);
+          st_stream(&rn[i], nv);
+          acc += norm2d<R>(nv);
+        }
+      });
+  if (p.stop) return;
+  store_partial(region(a, a.par ^ 1), acc);
+}
+
+// ---- the composed steps of every shift: x_j and p_j -------------------------------------------
+// x_j += cx[0] p_j + sum_{k<m} cx[k+1] r_k, p_j <- cp[0] p_j + sum_{k<m} cp[k+1] r_k, the r_k
+// being the m composed steps' residuals; before the first application x_j and p_j are zero
+// and are not read.  One pass for all shifts, one row per lane (x and p_j in the caller's
+// row order).  Bound by memory: 64 bytes a row and shift in FP64, 16 a kept residual.
+// when: 0 always (unless the sequence has halted), 1 for a reliable update that is due
+// (r_n's g has fallen by kRuDelta2 since the last one, or a.ru_force), 2 at the end.
+struct FlushPlan {
+  double cx[kMaxSteps + 1][kMaxShifts], cp[kMaxSteps + 1][kMaxShifts];
+  int64_t xo[kMaxShifts], po[kMaxShifts];
+  int nact, m, first, fresh;
+};
+
+// Shifts whose x_j and p_j loads are issued together.
+constexpr int kUpdGroup = 4;
+
+template <class R, bool COLOURS>
+__global__ __launch_bounds__(kBlock) void k_flush(MsArgs a, int par, int when) {
+  SolveState* st = a.st;
+  const int at = when == 2 ? st->fin : par;
+  const RotState& rs = st->rot[at];
+  if (when != 2 && rs.halt) {
+    if (when == 1 && blockIdx.x == 0 && threadIdx.x == 0) st->ru_flag = 0;
+    return;
+  }
+  int flushed = a.flushed;
+  if (when == 1) {
+    Early e;
+    load_early(a, e);
+    double g, d;
+    both_sums(a, e, g, d);
+    const bool due = a.ru_force || g < kRuDelta2 * st->R_ru;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      st->ru_flag = due ? 1 : 0;
+      st->ru_g = g;
+    }
+    if (!due) return;
+  } else {
+    flushed = 0;
+  }
+  if (flushed || (rs.m == 0 && !rs.fresh)) return;
+  __shared__ FlushPlan pl;
+  const int j = threadIdx.x;
+  if (j < kWave) {
+    const bool list = j < st->ns && ((rs.m > 0 && rs.took[j]) || rs.fresh);
+    const uint64_t mask = __ballot(list);
+    if (list) {
+      const int pos = __popcll(mask & ((uint64_t(1) << j) - 1));
+#pragma unroll
+      for (int i = 0; i <= kMaxSteps; ++i) {
+        pl.cx[i][pos] = rs.cx[i][j];
+        pl.cp[i][pos] = rs.cp[i][j];
+      }
+      pl.xo[pos] = int64_t(st->orig[j]) * a.n;
+      pl.po[pos] = int64_t(j) * a.n;
+    }
+    if (j == 0) {
+      pl.nact = __popcll(mask);
+      pl.m = rs.m;
+      pl.first = rs.launch - rs.m;
+      pl.fresh = rs.fresh;
+      if (blockIdx.x == 0) {
+        constexpr int ph = sizeof(R) == 4 ? 1 : 0;
+        st->n_upd[ph] += pl.nact;
+        st->n_kept[ph] += pl.m;
+        if (a.sample >= 0 && a.sample < kMaxSamples) {
+          st->smp_nact[a.sample] = pl.nact;
+          st->smp_m[a.sample] = pl.m;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int m = pl.m, nact = pl.nact, fresh = pl.fresh;
+  cplx<R>* __restrict__ pk = static_cast<cplx<R>*>(a.pk);
+  double2* __restrict__ x = a.x;
+  const cplx<R>* rk[kMaxSteps];
+#pragma unroll
+  for (int k = 0; k < kMaxSteps; ++k) rk[k] = rslot<R>(a, pl.first + (k < m ? k : 0));
+  const int64_t vol = a.n / 3;
+  int64_t beg, end;
+  block_range(a.n, kBlock, beg, end);
+  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
+    const int64_t ri = COLOURS ? (i % 3) * vol + i / 3 : i;  // the residuals' row
+    double2 rv[kMaxSteps];
+#pragma unroll
+    for (int k = 0; k < kMaxSteps; ++k)
+      rv[k] = k < m ? to_d(ld_stream(&rk[k][ri])) : double2{0.0, 0.0};
+    auto group = [&](int q, int cnt, auto full) {
+      cplx<R> pj[kUpdGroup];
+      double2 xj[kUpdGroup];
+#pragma unroll
+      for (int u = 0; u < kUpdGroup; ++u) {
+        pj[u] = czero<R>();
+        xj[u] = double2{0.0, 0.0};
+        if ((decltype(full)::value || u < cnt) && !fresh) {
+          pj[u] = ld_stream(&pk[pl.po[q + u] + i]);
+          xj[u] = ld_stream(&x[pl.xo[q + u] + i]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kUpdGroup; ++u) {
+        if (decltype(full)::value || u < cnt) {
+          const int c = q + u;
+          const double2 pd = to_d(pj[u]);
+          double2 xv{fma(pl.cx[0][c], pd.x, xj[u].x), fma(pl.cx[0][c], pd.y, xj[u].y)};
+          double2 np{pl.cp[0][c] * pd.x, pl.cp[0][c] * pd.y};
+#pragma unroll
+          for (int k = 0; k < kMaxSteps; ++k) {
+            if (k < m) {
+              const double cx = pl.cx[k + 1][c], cp = pl.cp[k + 1][c];
+              xv.x = fma(cx, rv[k].x, xv.x);
+              xv.y = fma(cx, rv[k].y, xv.y);
+              np.x = fma(cp, rv[k].x, np.x);
+              np.y = fma(cp, rv[k].y, np.y);
+            }
+          }
+          st_stream(&x[pl.xo[c] + i], xv);
+          st_stream(&pk[pl.po[c] + i], from_d<R>(np));
+        }
+      }
+    };
+    int q = 0;
+    for (; q + kUpdGroup <= nact; q += kUpdGroup) group(q, kUpdGroup, std::true_type{});
+    if (q < nact) group(q, nact - q, std::false_type{});
+  }
+}
+
+// ---- start: r_0 = b, s = 0 and g_0's partials (x_j and p_j start unwritten) ----------------
+template <bool COLOURS>
+__global__ __launch_bounds__(kBlock) void k_init(MsArgs a) {
+  double2* __restrict__ r = rslot<double>(a, a.launch);
+  double2* __restrict__ s = static_cast<double2*>(a.s[0]);
+  const int64_t vol = a.n / 3;
   int64_t beg, end;
   block_range(a.n, kBlock, beg, end);
   double acc = 0.0;
   for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
-    const double2 pr = to_d(p[i]), rr = to_d(rin[i]), td = to_d(t[i]);
-    double2 nr;
-    nr.x = rr.x - step * (td.x + sigma0 * pr.x);
-    nr.y = rr.y - step * (td.y + sigma0 * pr.y);
-    const cplx<R> st_r = from_d<R>(nr);
-    r[i] = st_r;
-    acc += norm2d<R>(st_r);
-  }
-  store_partial(region(a, 1), acc);
-}
-
-// ---- initialisation: r = p = p_j = b, x = 0, |b|^2 ------------------------------------
-template <class R>
-__global__ __launch_bounds__(kBlock) void k_init(MsArgs a) {
-  SolveState* st = a.st;
-  const int64_t n = a.n;
-  const int ns = st->ns;
-  cplx<R>* __restrict__ r = static_cast<cplx<R>*>(a.r);
-  cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.pb[0]);  // rot[par].pcur = 0
-  cplx<R>* __restrict__ pk = static_cast<cplx<R>*>(a.pk);
-  int64_t beg, end;
-  block_range(n, kBlock, beg, end);
-  double acc = 0.0;
-  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
     const double2 bv = a.b[i];
-    const cplx<R> br = from_d<R>(bv);
-    r[i] = br;
-    p[i] = br;
-    for (int j = 1; j < ns; ++j) pk[int64_t(j - 1) * n + i] = br;
-    for (int k = 0; k < ns; ++k) a.x[int64_t(k) * n + i] = double2{0.0, 0.0};
+    r[COLOURS ? (i % 3) * vol + i / 3 : i] = bv;
+    s[i] = double2{0.0, 0.0};
     acc += fma(bv.x, bv.x, bv.y * bv.y);
   }
-  const double tot = block_sum<kBlock>(acc);
-  if (threadIdx.x == 0) store_agent(&a.sc.partial[blockIdx.x], tot);
-  if (!arrive_last(a.sc.tickets + 3 * kTicketSite)) return;
-  const double B2 = sum_partials(a.sc.partial, gridDim.x, 1, 0);
-  if (threadIdx.x == 0) {
-    RotState& r0 = st->rot[a.par];
-    st->bnorm2 = B2;
-    r0.R = B2;
-    st->eps2 = st->eps2 * B2;        // host stored tol^2 here
-    st->sw_eps2 = st->sw_eps2 * B2;  // and switch_tol^2 (0 when there is no switch)
-    if (!(B2 > 0.0) || !isfinite(B2)) {
-      r0.halt = 1;
-      if (!isfinite(B2)) r0.status = 1;
-    }
-  }
+  store_partial(region(a, a.par), acc);
 }
 
-// ---- end of the FP64 phase of a mixed solve: Krylov vectors to complex64 -------------
-__global__ __launch_bounds__(kBlock) void k_switch(MsArgs a64, MsArgs a32, int ns) {
+// ---- end of the FP64 phase of a mixed solve: r, s and the p_j to complex64 --------------------
+__global__ __launch_bounds__(kBlock) void k_switch(MsArgs a64, MsArgs a32, int ns, int herm) {
+  SolveState* st = a64.st;
+  const RotState& fin = st->rot[st->fin];
   const int64_t n = a64.n;
-  const int pc = a64.st->rot[a64.par].pcur;  // the direction buffer in use carries over
-  // r stays in the ring slot the halting (switching) head read; slot 0 of complex64
-  const double2* __restrict__ r = rslot<double>(a64, a64.st->rslot);
-  const double2* __restrict__ p = static_cast<const double2*>(a64.pb[pc]);
+  const double2* __restrict__ r = rslot<double>(a64, fin.launch);
+  // the buffer of s the halted iteration would have read: A given alternates two
+  const int from = herm ? st->fin ^ 1 : 0, to = herm ? a64.par : 0;
+  const double2* __restrict__ s = static_cast<const double2*>(a64.s[from]);
   const double2* __restrict__ pk = static_cast<const double2*>(a64.pk);
-  float2* __restrict__ r32 = static_cast<float2*>(a32.r);
-  float2* __restrict__ p32 = static_cast<float2*>(a32.pb[pc]);
+  float2* __restrict__ r32 = rslot<float>(a32, a32.launch);
+  float2* __restrict__ s32 = static_cast<float2*>(a32.s[to]);
   float2* __restrict__ pk32 = static_cast<float2*>(a32.pk);
-  const int64_t total = int64_t(ns) * n;  // r, p, then ns-1 shift directions
+  const int64_t total = int64_t(ns + 1) * n;  // r and s, then ns directions
   for (int64_t idx = blockIdx.x * int64_t(kBlock) + threadIdx.x; idx < total;
        idx += int64_t(gridDim.x) * kBlock) {
     if (idx < n) {
       r32[idx] = from_d<float>(r[idx]);
-      p32[idx] = from_d<float>(p[idx]);
+      s32[idx] = from_d<float>(s[idx]);
     } else {
       pk32[idx - n] = from_d<float>(pk[idx - n]);
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    SolveState* st = a64.st;
-    RotState& rs = st->rot[a64.par];
-    if (rs.status == 0 && rs.switch_req) {
-      rs.halt = 0;
-      rs.switch_req = 0;
-      st->sw_eps2 = 0.0;
-      st->R_ru = rs.R;
-    }
-  }
+  // partials of g: the sum the halted iteration formed
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < kMaxGrid; i += kBlock) region(a64, a64.par)[i] = i ? 0.0 : st->R;
 }
 
-// ---- reliable update: r = b - (A + sigma0) x_0 in FP64, between the head and K2 ----------
-// Launched at check points; runs (in every workgroup alike) when forced by the period or
-// when the recursive residual has dropped by kRuDelta2 in |r|^2 since the last one.
-__device__ __forceinline__ bool ru_due(const MsArgs& a) {
-  const SolveState* st = a.st;
-  const RotState& ns = st->rot[a.par ^ 1];  // written by this iteration's head
-  if (ns.halt) return false;
-  return a.ru_force || ns.R < kRuDelta2 * st->R_ru;
-}
-
-// After each workgroup's share of |r|^2 (acc per thread): the last workgroup replaces R.
-// The update never halts the sequence (K2 decides on the replaced residual), so heads
-// before it may defer their all-shift update; a non-finite residual is a breakdown.
-__device__ void ru_finish(const MsArgs& a, double acc) {
+// The complex64 phase's state at its first iteration, from the halted one's (which may be
+// the same of the two: a lane reads before it writes).
+__global__ __launch_bounds__(kBlock) void k_switch_state(MsArgs a) {
   SolveState* st = a.st;
-  // region 2: the head's partials in region 0 still wait for K2
-  double* reg = region(a, 2);
-  const double tot = block_sum<kBlock>(acc);
-  if (threadIdx.x == 0) store_agent(&reg[blockIdx.x], tot);
-  if (!arrive_last(a.sc.tickets + 2 * kTicketSite)) return;
-  const double Rt = sum_partials(reg, gridDim.x, 1, 0);
-  if (threadIdx.x == 0) {
-    RotState& rs = st->rot[a.par ^ 1];
-    rs.R = Rt;
-    st->R_ru = Rt;
-    st->n_reliable += 1;
-    if (!isfinite(Rt)) {
-      rs.status = 1;
-      rs.halt = 1;
-      store_host_flag(a.hflag, 1);
-    }
+  const RotState& fin = st->rot[st->fin];
+  RotState& rs = st->rot[a.par];
+  const int j = threadIdx.x;
+  if (j < kMaxShifts) {
+    rs.zeta[j] = fin.zeta[j];
+    rs.zeta_prev[j] = fin.zeta_prev[j];
+    rs.active[j] = fin.active[j];
+    rs.took[j] = 0;
+  }
+  if (j == 0) {
+    rs.g = fin.g;
+    rs.a = fin.a;
+    rs.P = fin.P;
+    rs.iter = fin.iter;
+    rs.launch = a.launch;
+    rs.m = 0;
+    rs.fresh = 0;
+    rs.halt = 0;
+    st->sw2 = 0.0;
+    st->R_ru = st->R;
   }
 }
 
-template <int L, bool MHM>
+// ---- reliable update: r_n = b - (A + sigma0) x_0 in FP64, before iteration n ------------------
+// k_flush has brought x_0 up to date and decided whether it runs (st->ru_flag).  The last
+// workgroup replaces g_n's partials and keeps r_n^H s_{n-1}; a non-finite residual ends the
+// sequence in iteration n (breakdown).
+__device__ __forceinline__ bool ru_runs(const MsArgs& a) {
+  return a.st->ru_flag != 0 && !a.st->rot[a.par].halt;
+}
+
+__device__ void ru_finish(const MsArgs& a, double acc, double dot) {
+  SolveState* st = a.st;
+  double v[2] = {acc, dot};
+  block_sum_k<kBlock, 2>(v);
+  if (threadIdx.x == 0) {
+    store_agent(&region(a, 4)[blockIdx.x], v[0]);
+    store_agent(&region(a, 5)[blockIdx.x], v[1]);
+  }
+  if (!arrive_last(a.sc.tickets + 2 * kTicketSite)) return;
+  const double Rt = sum_partials(region(a, 4), gridDim.x, 1, 0);
+  const double ct = sum_partials(region(a, 5), gridDim.x, 1, 0);
+  for (int i = threadIdx.x + 1; i < a.gg; i += kBlock) region(a, a.par)[i] = 0.0;
+  if (threadIdx.x == 0) {
+    region(a, a.par)[0] = Rt;
+    st->R_ru = Rt;
+    st->ru_c = ct;
+    st->n_reliable += 1;
+  }
+}
+
+// One row: r_n from b, (A x_0)_row and x_0; |r_n|^2 and Re(r_n^H s).
+template <class R>
+__device__ __forceinline__ cplx<R> ru_row(const double2& bv, const double2& q, const double2& xv,
+                                          double sigma0, const cplx<R>& s, double& acc, double& dot) {
+  const double2 rt{bv.x - q.x - sigma0 * xv.x, bv.y - q.y - sigma0 * xv.y};
+  const double2 sd = to_d(s);
+  acc += fma(rt.x, rt.x, rt.y * rt.y);
+  dot += rt.x * sd.x + rt.y * sd.y;
+  return from_d<R>(rt);
+}
+
+template <class R> __device__ __forceinline__ const cplx<R>* ru_s(const MsArgs& a) {
+  return static_cast<const cplx<R>*>(a.s[a.s[1] ? a.par : 0]);
+}
+
+template <int L>
 __global__ __launch_bounds__(kBlock) void k_ru_first(MsArgs a) {
   // t64 = M x_0 (A = M^H M) -- first half of the FP64 operator
-  const SolveState* st = a.st;
-  if (!ru_due(a)) return;
-  const double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
+  if (!ru_runs(a)) return;
+  const double2* __restrict__ x0 = a.x + int64_t(a.st->orig[0]) * a.n;
   constexpr int GPB = kBlock / L;
   const int lane = threadIdx.x % L, grp = threadIdx.x / L;
   int64_t beg, end;
@@ -1467,36 +1151,27 @@ __global__ __launch_bounds__(kBlock) void k_ru_first(MsArgs a) {
 
 template <class R, int L, bool MHM>
 __global__ __launch_bounds__(kBlock) void k_ru_second(MsArgs a) {
-  SolveState* st = a.st;
-  if (!ru_due(a)) return;
-  const double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
-  cplx<R>* __restrict__ r = rslot<R>(a, st->rot[a.par].ndef);  // r_i's ring slot
-  const double sigma0 = st->sigma0;
+  if (!ru_runs(a)) return;
+  const double2* __restrict__ x0 = a.x + int64_t(a.st->orig[0]) * a.n;
+  cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const cplx<R>* __restrict__ s = ru_s<R>(a);
   constexpr int GPB = kBlock / L;
   const int lane = threadIdx.x % L, grp = threadIdx.x / L;
   int64_t beg, end;
   block_range(a.n, GPB, beg, end);
-  double acc = 0.0;
+  double acc = 0.0, dot = 0.0;
   for (int64_t row = beg + grp; row < end; row += GPB) {
     const double2 q = MHM ? row_dot<double, L>(a.mh64, a.t64, row, lane)
                           : row_dot<double, L>(a.m64, x0, row, lane);
-    if (lane == 0) {
-      const double2 bv = a.b[row], xv = x0[row];
-      double2 rt;
-      rt.x = bv.x - q.x - sigma0 * xv.x;
-      rt.y = bv.y - q.y - sigma0 * xv.y;
-      r[row] = from_d<R>(rt);
-      acc += fma(rt.x, rt.x, rt.y * rt.y);
-    }
+    if (lane == 0) r[row] = ru_row<R>(a.b[row], q, x0[row], a.st->sigma0, s[row], acc, dot);
   }
-  ru_finish(a, acc);
+  ru_finish(a, acc, dot);
 }
 
 // The same on the sliced ELLPACK copies: one row per lane, one slice per wavefront.
 __global__ __launch_bounds__(kBlock) void k_ru_first_s(MsArgs a) {
-  const SolveState* st = a.st;
-  if (!ru_due(a)) return;
-  const double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
+  if (!ru_runs(a)) return;
+  const double2* __restrict__ x0 = a.x + int64_t(a.st->orig[0]) * a.n;
   constexpr int SPB = kBlock / kSlice;
   const int lane = threadIdx.x % kSlice;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
@@ -1513,45 +1188,32 @@ __global__ __launch_bounds__(kBlock) void k_ru_first_s(MsArgs a) {
 
 template <class R, bool MHM>
 __global__ __launch_bounds__(kBlock) void k_ru_second_s(MsArgs a) {
-  SolveState* st = a.st;
-  if (!ru_due(a)) return;
-  const double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
-  cplx<R>* __restrict__ r = rslot<R>(a, st->rot[a.par].ndef);  // r_i's ring slot
-  const double sigma0 = st->sigma0;
+  if (!ru_runs(a)) return;
+  const double2* __restrict__ x0 = a.x + int64_t(a.st->orig[0]) * a.n;
+  cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const cplx<R>* __restrict__ s = ru_s<R>(a);
+  const Sell<double2> m = MHM ? a.sh64 : a.s64;
+  const double2* __restrict__ in = MHM ? a.t64 : x0;
   constexpr int SPB = kBlock / kSlice;
   const int lane = threadIdx.x % kSlice;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
   int64_t beg, end;
   block_range(a.nslices, SPB, beg, end);
-  double acc = 0.0;
+  double acc = 0.0, dot = 0.0;
   for (int64_t sl = beg + wv; sl < end; sl += SPB) {
     const int64_t row = sl * kSlice + lane;
     const int64_t rr = row < a.n ? row : a.n - 1;
-    const Sell<double2> m = MHM ? a.sh64 : a.s64;
-    const double2* __restrict__ in = MHM ? a.t64 : x0;
     double2 q = sell_row<double>(m, in, sl, lane);
     cfma<double>(q, m.diag[rr], in[rr]);
-    if (row < a.n) {
-      const double2 bv = a.b[row], xv = x0[row];
-      double2 rt;
-      rt.x = bv.x - q.x - sigma0 * xv.x;
-      rt.y = bv.y - q.y - sigma0 * xv.y;
-      r[row] = from_d<R>(rt);
-      acc += fma(rt.x, rt.x, rt.y * rt.y);
-    }
+    if (row < a.n) r[row] = ru_row<R>(a.b[row], q, x0[row], a.st->sigma0, s[row], acc, dot);
   }
-  ru_finish(a, acc);
+  ru_finish(a, acc, dot);
 }
 
-// The same on the links (matrix-free staggered operator, LR rows per link), one site per
-// lane: t64 = M x_0, then r = b - M^H t64 - sigma0 x_0.
-template <int LR>
-__global__ __launch_bounds__(kBlock) void k_ru_first_site(MsArgs a) {
-  const SolveState* st = a.st;
-  if (!ru_due(a)) return;
-  const double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
-  const Stencil<double2> w = a.w64;
-  const uint32_t vol = uint32_t(w.vol);
+// The same on the links (LR rows per link), one site per lane: t64 = M x_0 (in the caller's
+// row order, as x_0 and b), then r_n = b - M^H t64 - sigma0 x_0 (colour by colour).
+template <class F>
+__device__ __forceinline__ void ru_sites(uint32_t vol, F body) {
   constexpr int WPB = kBlock / kWave;
   const int lane = threadIdx.x % kWave;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
@@ -1559,56 +1221,54 @@ __global__ __launch_bounds__(kBlock) void k_ru_first_site(MsArgs a) {
   block_range((int64_t(vol) + kSiteBlock - 1) / kSiteBlock, WPB, beg, end);
   for (int64_t blk = beg + wv; blk < end; blk += WPB) {
     const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
-    const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
-    const int64_t r0 = 3 * int64_t(ss);
+    body(site < vol ? site : vol - 1, site < vol);  // lanes past the volume: unused
+  }
+}
+
+template <int LR>
+__global__ __launch_bounds__(kBlock) void k_ru_first_site(MsArgs a) {
+  if (!ru_runs(a)) return;
+  const double2* __restrict__ x0 = a.x + int64_t(a.st->orig[0]) * a.n;
+  const Stencil<double2> w = a.w64;
+  ru_sites(uint32_t(w.vol), [&](uint32_t site, bool live) {
+    const int64_t r0 = 3 * int64_t(site);
     double2 own[3], v[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) own[c] = x0[r0 + c];
-    stencil_site<double, LR>(w, ss, own, 1, [&](int64_t c) { return x0[c]; }, v);
-    if (site < vol) {
+    stencil_site<double, LR>(w, site, own, 1,
+                             [&](uint32_t t, int c) { return x0[3 * int64_t(t) + c]; }, v);
+    if (live) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) a.t64[r0 + c] = v[c];
     }
-  }
+  });
 }
 
 template <class R, int LR>
 __global__ __launch_bounds__(kBlock) void k_ru_second_site(MsArgs a) {
-  SolveState* st = a.st;
-  if (!ru_due(a)) return;
-  const double2* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
+  if (!ru_runs(a)) return;
+  const double2* __restrict__ x0 = a.x + int64_t(a.st->orig[0]) * a.n;
   const double2* __restrict__ u = a.t64;
-  cplx<R>* __restrict__ r = rslot<R>(a, st->rot[a.par].ndef);  // r_i's ring slot
-  const double sigma0 = st->sigma0;
+  cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const cplx<R>* __restrict__ s = ru_s<R>(a);
   const Stencil<double2> w = a.w64;
-  const uint32_t vol = uint32_t(w.vol);
-  constexpr int WPB = kBlock / kWave;
-  const int lane = threadIdx.x % kWave;
-  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
-  int64_t beg, end;
-  block_range((int64_t(vol) + kSiteBlock - 1) / kSiteBlock, WPB, beg, end);
-  double acc = 0.0;
-  for (int64_t blk = beg + wv; blk < end; blk += WPB) {
-    const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
-    const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
-    const int64_t r0 = 3 * int64_t(ss);
+  double acc = 0.0, dot = 0.0;
+  ru_sites(uint32_t(w.vol), [&](uint32_t site, bool live) {
+    const int64_t r0 = 3 * int64_t(site);
     double2 own[3], q[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) own[c] = u[r0 + c];
-    stencil_site<double, LR>(w, ss, own, -1, [&](int64_t c) { return u[c]; }, q);
-    if (site < vol) {
+    stencil_site<double, LR>(w, site, own, -1,
+                             [&](uint32_t t, int c) { return u[3 * int64_t(t) + c]; }, q);
+    if (live) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const double2 bv = a.b[r0 + c], xv = x0[r0 + c];
-        double2 rt;
-        rt.x = bv.x - q[c].x - sigma0 * xv.x;
-        rt.y = bv.y - q[c].y - sigma0 * xv.y;
-        r[r0 + c] = from_d<R>(rt);
-        acc += fma(rt.x, rt.x, rt.y * rt.y);
+        const int64_t i = c * w.vol + site;
+        r[i] = ru_row<R>(a.b[r0 + c], q[c], x0[r0 + c], a.st->sigma0, s[i], acc, dot);
       }
     }
-  }
-  ru_finish(a, acc);
+  });
+  ru_finish(a, acc, dot);
 }
 
 // ---- verification: FP64 true residual norms of up to 8 solutions ---------------------
@@ -1890,7 +1550,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_site(Stencil<double2> w, Sw
     for (int c = 0; c < 3; ++c)
       out[r0 + c] = LAST ? with_shift(v[c], shift, in[r0 + c]) : v[c];
   };
-  auto gather = [&](int64_t i) { return x[i]; };
+  auto gather = [&](uint32_t t, int c) { return x[3 * int64_t(t) + c]; };
   if constexpr (MARCH) {
     const uint32_t vol3 = vol / uint32_t(w.L[3]);
     const uint32_t bs = vol3 / uint32_t(kSiteBlock);
@@ -1983,17 +1643,93 @@ int resident_grid(const void* kern, int cap, size_t lds = 0) {
 // Launch one kernel of an iteration.  With `ev`, the start/stop events of pair `k` are
 // attached to the dispatch itself (their timestamps are the kernel's own begin and
 // end), so the elapsed time excludes the queue gap between kernels.
-template <class K>
-void launch_timed(K kern, int grid, hipStream_t s, hipEvent_t* ev, int k, const MsArgs& a,
-                  size_t lds = 0) {
+template <class K, class... A>
+void launch_timed(K kern, int grid, hipStream_t s, hipEvent_t* ev, int k, const A&... args) {
   if (ev)
-    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, s, ev[2 * k], ev[2 * k + 1], 0, a);
+    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, ev[2 * k], ev[2 * k + 1], 0, args...);
   else
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, args...);
+}
+
+// t-slices per column of the march along t that the two-row links of this lattice allow (1:
+// none): a t-slice holds whole blocks of 64 sites and some power of two up to kK2March
+// divides L_t.
+int march_columns(const Stencil<double2>& w) {
+  const int64_t lt = w.L[3];
+  if (w.rows != 2 || lt <= 0 || (w.vol / lt) % kSiteBlock != 0) return 1;
+  for (int c = kK2March; c >= 2; c /= 2)
+    if (lt % c == 0) return c;
+  return 1;
+}
+
+// Workgroups of a links' kernel that sweeps or marches in order, at most: two per CU in FP64,
+// four in complex64.  More waves in flight than that outrun the L2 (32^3 x 64: FP64 K1 + applications 355 us, 396 with
+// three workgroups per CU, 447 with one and a half; complex64 180, 187 with five, 186 with
+// three; K2 264 / 261 / 348 and 141 / 141 / 144).
+template <class R> constexpr int site_cap() { return std::is_same<R, double>::value ? 512 : 1024; }
+
+template <class R, int LR, bool MARCH> const void* site_kernel(int half) {
+  constexpr bool STREAM = std::is_same<R, double>::value;
+  return half == 1 ? reinterpret_cast<const void*>(k1_site<R, LR, STREAM, MARCH>)
+                   : reinterpret_cast<const void*>(k2_site<R, LR, MARCH>);
+}
+
+// The grid of a links' half, and whether it marches: it does when every resident wave gets
+// a run of at least 4 blocks.
+template <class R> int site_grid(const MsArgs& a, int half, int& march) {
+  const int64_t nblk = (a.w64.vol + kSiteBlock - 1) / kSiteBlock;
+  constexpr int WPB = kBlock / kWave;
+  const int cap = std::min(a.grid, a.ord.on ? site_cap<R>() : kMaxGrid);
+  const int all = grid_rows(nblk, WPB, cap);
+  march = 0;
+  if (a.stencil == 2 && a.ord.on && a.march > 1) {
+    const int g = resident_grid(site_kernel<R, 2, true>(half), all);
+    if (nblk >= int64_t(g) * WPB * 4) {
+      march = 1;
+      return g;
+    }
+  }
+  if (!a.ord.on) return all;
+  return resident_grid(a.stencil == 2 ? site_kernel<R, 2, false>(half) : site_kernel<R, 3, false>(half),
+                       all);
+}
+
+template <class R> void prepare_impl(MsArgs& a) {
+  const bool mhm = a.kind == MSC_A_MHM;
+  a.m1 = a.m2 = 0;
+  if (a.sell && mhm && a.stencil) {
+    a.march = a.ord.on ? march_columns(a.w64) : 1;
+    a.gd = site_grid<R>(a, 1, a.m1);
+    a.gg = site_grid<R>(a, 2, a.m2);
+  } else if (a.sell) {
+    auto grid = [&](const void* kern) {
+      const int g = grid_rows(a.n, kBlock, a.grid);
+      return a.ord.on ? resident_grid(kern, g) : g;
+    };
+    if (mhm) {
+      a.gd = grid(reinterpret_cast<const void*>(k1_sell<R>));
+      a.gg = grid(reinterpret_cast<const void*>(k2_sell<R>));
+    } else {
+      a.gd = a.gg = grid(reinterpret_cast<const void*>(k_herm<R>));
+    }
+  } else {
+    a.gd = grid_rows(a.n, kBlock / a.lanes, a.grid);
+    a.gg = mhm ? a.gd : grid_rows(a.n, kBlock, a.grid);
+  }
+}
+
+template <class R> hipError_t flush_impl(const MsArgs& a, int par, int when, hipStream_t s, hipEvent_t* ev) {
+  const int g = grid_rows(a.n, kBlock);
+  if (a.sell && a.stencil)
+    launch_timed(k_flush<R, true>, g, s, ev, 2, a, par, when);
+  else
+    launch_timed(k_flush<R, false>, g, s, ev, 2, a, par, when);
+  return hipGetLastError();
 }
 
 template <class R>
 hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
+  if (const hipError_t e = flush_impl<R>(a, a.par, 1, s, nullptr); e != hipSuccess) return e;
   if (a.sell && a.kind == MSC_A_MHM && a.stencil != 0) {
     // the links: the same FP64 operator as the stored copies, a third of their bytes
     const int gs = grid_rows((a.w64.vol + kSiteBlock - 1) / kSiteBlock, kBlock / kWave);
@@ -2013,12 +1749,13 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
       k_ru_second_s<R, true><<<gs, kBlock, 0, s>>>(a);
     } else {
       k_ru_second_s<R, false><<<gs, kBlock, 0, s>>>(a);
+      k_herm_w<R><<<a.gd, kBlock, 0, s>>>(a, 1);
     }
     return hipGetLastError();
   }
   const int g1 = grid_rows(a.n, kBlock / a.lanes);
   if (a.kind == MSC_A_MHM) {
-    MSC_LANES_SWITCH(a.lanes, (k_ru_first<LL, true><<<g1, kBlock, 0, s>>>(a)));
+    MSC_LANES_SWITCH(a.lanes, (k_ru_first<LL><<<g1, kBlock, 0, s>>>(a)));
     MSC_LANES_SWITCH(a.lanes, (k_ru_second<R, LL, true><<<g1, kBlock, 0, s>>>(a)));
   } else {
     MSC_LANES_SWITCH(a.lanes, (k_ru_second<R, LL, false><<<g1, kBlock, 0, s>>>(a)));
@@ -2026,135 +1763,84 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// t-slices per column of the march along t that the two-row links of this lattice allow (1:
-// none): a t-slice holds whole blocks of 64 sites and some power of two up to kK2March
-// divides L_t.
-int march_columns(const Stencil<double2>& w) {
-  const int64_t lt = w.L[3];
-  if (w.rows != 2 || lt <= 0 || (w.vol / lt) % kSiteBlock != 0) return 1;
-  for (int c = kK2March; c >= 2; c /= 2)
-    if (lt % c == 0) return c;
-  return 1;
+template <class R, int LR> void launch_sites(const MsArgs& a, hipStream_t s, hipEvent_t* ev) {
+  constexpr bool STREAM = std::is_same<R, double>::value;
+  if constexpr (LR == 2) {
+    if (a.m1)
+      launch_timed(k1_site<R, 2, STREAM, true>, a.gd, s, ev, 0, a);
+    else
+      launch_timed(k1_site<R, 2, STREAM, false>, a.gd, s, ev, 0, a);
+    if (a.m2)
+      launch_timed(k2_site<R, 2, true>, a.gg + 1, s, ev, 1, a);
+    else
+      launch_timed(k2_site<R, 2, false>, a.gg + 1, s, ev, 1, a);
+  } else {
+    launch_timed(k1_site<R, LR, STREAM, false>, a.gd, s, ev, 0, a);
+    launch_timed(k2_site<R, LR, false>, a.gg + 1, s, ev, 1, a);
+  }
 }
 
-// One iteration: the head (pending update fused with K1 on the sliced ELLPACK path; a
-// separate update kernel followed by the CSR K1 otherwise), the optional reliable
-// update, then K2.
+// One iteration: the reliable update where one is due, the operator halves (K2 has a
+// workgroup more than the rows need), then with `flush` the composed steps.
 template <class R>
-hipError_t iteration_impl(const MsArgs& args, hipStream_t s, hipEvent_t* ev, bool reliable) {
-  const int g1 = grid_rows(args.n, kBlock / args.lanes, args.grid);
-  const int g3 = grid_rows(args.n, kBlock, args.grid);
-  MsArgs a = args;
-  const int lr = (a.sell && a.kind == MSC_A_MHM) ? a.stencil : 0;  // links: rows per link
-  // the head and K2 on the sliced path, and their grids: with a lattice order, the
-  // resident workgroups only (their waves sweep the order in step)
-  const bool tr = a.t_rec && std::is_same<R, double>::value;
-  auto head = lr == 3 ? (tr ? k1_site<R, 3, true> : k1_site<R, 3, false>)
-              : lr == 2 ? (tr ? k1_site<R, 2, true> : k1_site<R, 2, false>)
-                        : (a.kind == MSC_A_MHM ? k1_fused<R, true> : k1_fused<R, false>);
-  // K2 on two-row links marches along t (k2_site<.., true>) when it runs on the resident
-  // grid, a t-slice holds whole blocks of 64 sites, some tc >= 2 (at most kK2March)
-  // divides L_t and every wave gets a run of at least 4 blocks
-  const int64_t vol = a.w64.vol;
-  int tc = lr == 2 && a.ord.on ? march_columns(a.w64) : 1;
-  const int tc_lattice = tc;
-  auto k2s = lr == 3   ? k2_site<R, 3, false>
-             : lr == 2 ? (tc > 1 ? k2_site<R, 2, true> : k2_site<R, 2, false>)
-                       : k2_sell<R>;
-  // the links' kernels take one block of 64 sites per wave pass
-  const int gsite = lr ? grid_rows((vol + kSiteBlock - 1) / kSiteBlock, kBlock / kWave, a.grid)
-                       : g3;
-  int gh = lr ? gsite : g3, gk = gh;
-  // the complex64 K2 on the links takes unused dynamic LDS that leaves room for three of
-  // its workgroups per CU (three waves per SIMD instead of the four its registers allow):
-  // fewer waves in flight keep more of the neighbours in L2
-  const size_t k2lds = (lr && std::is_same<R, float>::value) ? kC64K2Lds : 0;
-  if (a.sell && a.ord.on) {
-    gh = resident_grid(reinterpret_cast<const void*>(head), gh);
-    if (a.kind == MSC_A_MHM) gk = resident_grid(reinterpret_cast<const void*>(k2s), gk, k2lds);
-  }
-  if (tc > 1 && (vol / kSiteBlock) < int64_t(gk) * (kBlock / kWave) * 4) {
-    // runs too short to carry much: the plain order
-    tc = 1;
-    k2s = k2_site<R, 2, false>;
-    gk = resident_grid(reinterpret_cast<const void*>(k2s), gsite, k2lds);
-  }
-  a.k2_march = tc;
-  // the heads on two-row links march with K2's columns (FP64: the recurrence's heads; the
-  // direct products keep the sweep order) when every resident wave gets a run of at
-  // least 4 blocks
-  a.head_march = 1;
-  if (kHeadMarch && lr == 2 && tc_lattice > 1) {
-    decltype(head) hm = nullptr;
-    if constexpr (std::is_same<R, float>::value)
-      hm = k1_site<R, 2, false, true>;
-    else if (tr)
-      hm = k1_site<R, 2, true, true>;
-    if (hm) {
-      const int gm = resident_grid(reinterpret_cast<const void*>(hm), gsite);
-      if (vol / kSiteBlock >= int64_t(gm) * (kBlock / kWave) * 4) {
-        head = hm;
-        gh = gm;
-        a.head_march = tc_lattice;
-      }
-    }
-  }
-  // workgroups of K1 and K2, whose partials K2 and the next head add up
-  if (a.sell) {
-    a.gk1 = gh;
-    a.gk2 = gk;
-  } else {
-    a.gk1 = g1;
-    a.gk2 = a.kind == MSC_A_MHM ? g1 : g3;
-  }
-  if (a.sell) {
-    launch_timed(head, gh, s, ev, 0, a);
-  } else {
-    launch_timed(k_update<R>, g3, s, ev, 2, a);
-    if (a.kind == MSC_A_MHM) {
-      MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_apply<R, LL, true>, g1, s, ev, 0, a)));
-    } else {
-      MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_apply<R, LL, false>, g1, s, ev, 0, a)));
-    }
-  }
-  if (reliable) {
+hipError_t iteration_impl(const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool flush) {
+  if (a.ru_check) {
     const hipError_t e = reliable_impl<R>(a, s);
     if (e != hipSuccess) return e;
   }
-  if (a.kind == MSC_A_MHM) {
-    if (a.sell) {
-      launch_timed(k2s, gk, s, ev, 1, a, k2lds);
-    } else {
-      MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_mhm<R, LL>, g1, s, ev, 1, a)));
-    }
+  const bool mhm = a.kind == MSC_A_MHM;
+  if (a.sell && mhm && a.stencil) {
+    if (a.stencil == 2)
+      launch_sites<R, 2>(a, s, ev);
+    else
+      launch_sites<R, 3>(a, s, ev);
+  } else if (a.sell && mhm) {
+    launch_timed(k1_sell<R>, a.gd, s, ev, 0, a);
+    launch_timed(k2_sell<R>, a.gg + 1, s, ev, 1, a);
+  } else if (a.sell) {
+    launch_timed(k_herm<R>, a.gg + 1, s, ev, 0, a);
+  } else if (mhm) {
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, true>, a.gd, s, ev, 0, a)));
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_csr<R, LL, true>, a.gg + 1, s, ev, 1, a)));
   } else {
-    launch_timed(k2_herm<R>, g3, s, ev, 1, a);
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, false>, a.gd, s, ev, 0, a)));
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_csr<R, LL, false>, a.gg + 1, s, ev, 1, a)));
   }
+  if (flush) return flush_impl<R>(a, a.par ^ 1, 0, s, ev);
   return hipGetLastError();
 }
 
 }  // namespace
 
-int default_grid(int64_t n, int lanes) { return grid_rows(n, kBlock / lanes); }
+void prepare_iteration(int prec, MsArgs& a) {
+  prec == MSC_PREC_MIXED ? prepare_impl<float>(a) : prepare_impl<double>(a);
+}
 
-hipError_t launch_init(int prec, const MsArgs& a, hipStream_t s) {
-  const int g3 = grid_rows(a.n, kBlock);
-  if (prec == MSC_PREC_MIXED)
-    k_init<float><<<g3, kBlock, 0, s>>>(a);
+hipError_t launch_init(const MsArgs& a, hipStream_t s) {
+  if (a.sell && a.stencil)
+    k_init<true><<<a.gg, kBlock, 0, s>>>(a);
   else
-    k_init<double><<<g3, kBlock, 0, s>>>(a);
+    k_init<false><<<a.gg, kBlock, 0, s>>>(a);
+  if (a.sell && a.kind != MSC_A_MHM) k_herm_w<double><<<a.gd, kBlock, 0, s>>>(a, 0);
   return hipGetLastError();
 }
 
-hipError_t launch_iteration(int prec, const MsArgs& a, hipStream_t s, hipEvent_t* ev,
-                            bool reliable) {
-  return prec == MSC_PREC_MIXED ? iteration_impl<float>(a, s, ev, reliable)
-                                : iteration_impl<double>(a, s, ev, reliable);
+hipError_t launch_iteration(int prec, const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool flush) {
+  return prec == MSC_PREC_MIXED ? iteration_impl<float>(a, s, ev, flush)
+                                : iteration_impl<double>(a, s, ev, flush);
+}
+
+hipError_t launch_final_flush(int prec, const MsArgs& a, hipStream_t s) {
+  return prec == MSC_PREC_MIXED ? flush_impl<float>(a, 0, 2, s, nullptr)
+                                : flush_impl<double>(a, 0, 2, s, nullptr);
 }
 
 hipError_t launch_switch_to_mixed(const MsArgs& a64, const MsArgs& a32, int ns, hipStream_t s) {
-  const int g = grid_rows(int64_t(ns) * a64.n, kBlock);
-  k_switch<<<g, kBlock, 0, s>>>(a64, a32, ns);
+  const bool herm = a64.sell && a64.kind != MSC_A_MHM;
+  const int g = grid_rows(int64_t(ns + 1) * a64.n, kBlock);
+  k_switch<<<g, kBlock, 0, s>>>(a64, a32, ns, herm ? 1 : 0);
+  k_switch_state<<<1, kBlock, 0, s>>>(a32);
+  if (herm) k_herm_w<float><<<a32.gd, kBlock, 0, s>>>(a32, 0);
   return hipGetLastError();
 }
 

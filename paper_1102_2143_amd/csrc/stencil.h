@@ -63,10 +63,8 @@ template <class R, int LR> struct TCarry {
   cplx<R> fw[3];
 };
 
-// out[c] = m own[c] + sign (D v)_(3 s + c), c = 0, 1, 2, with v read through gather(row)
-// and own[c] = v at the site's own rows.  LR: link rows stored (3, or 2 for SU(3) links).
-// The sums run over mu = 0..3 and, within a direction, over the neighbour's colours j,
-// forward and backward terms apart, in that order.
+// out[c] = m own[c] + sign (D v)(s, c), c = 0, 1, 2, with v read through gather(site, colour)
+// and own[c] = v(s, c).  LR: link rows stored (3, or 2 for SU(3) links).
 // CAR: car->u and car->own stand in for the backward t link and the backward t
 // neighbour's values, and must hold exactly those (the previous site's t link and values
 // when the site lies one t-slice past it, else loaded for the site); on return car->u
@@ -97,9 +95,9 @@ __device__ __forceinline__ void stencil_site_c(const Stencil<cplx<R>>& op, uint3
     fwd[mu] = xm == L - 1 ? s - (L - 1) * st : s + st;
     bwd[mu] = xm == 0 ? s + (L - 1) * st : s - st;
   }
-  cplx<R> fw[3], bw[3];
+  cplx<R> h[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) fw[c] = bw[c] = czero<R>();
+  for (int c = 0; c < 3; ++c) h[c] = czero<R>();
 #pragma unroll
   for (int mu = 0; mu < 4; ++mu) {
     const cplx<R>* __restrict__ wm = op.w + int64_t(mu) * K * vol;
@@ -117,11 +115,11 @@ __device__ __forceinline__ void stencil_site_c(const Stencil<cplx<R>>& op, uint3
     }
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      gf[j] = gather(3 * int64_t(fwd[mu]) + j);
+      gf[j] = gather(fwd[mu], j);
       if (kept)
         gb[j] = car->own[j];
       else
-        gb[j] = gather(3 * int64_t(bwd[mu]) + j);
+        gb[j] = gather(bwd[mu], j);
     }
     if constexpr (CAR) {
       if (mu == 3) {
@@ -137,20 +135,24 @@ __device__ __forceinline__ void stencil_site_c(const Stencil<cplx<R>>& op, uint3
       third_row<R>(B, te);
     }
 #pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      gb[j].x = -gb[j].x;
+      gb[j].y = -gb[j].y;
+    }
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        cfma<R>(fw[c], U[3 * c + j], gf[j]);
-        cfma_conj<R>(bw[c], B[3 * j + c], gb[j]);
+        cfma<R>(h[c], U[3 * c + j], gf[j]);
+        cfma_conj<R>(h[c], B[3 * j + c], gb[j]);
       }
     }
   }
   const R m = R(op.mass);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const cplx<R> h{fw[c].x - bw[c].x, fw[c].y - bw[c].y};
-    out[c].x = sign > 0 ? fma(m, own[c].x, h.x) : fma(m, own[c].x, -h.x);
-    out[c].y = sign > 0 ? fma(m, own[c].y, h.y) : fma(m, own[c].y, -h.y);
+    out[c].x = fma(m, own[c].x, sign > 0 ? h[c].x : -h[c].x);
+    out[c].y = fma(m, own[c].y, sign > 0 ? h[c].y : -h[c].y);
   }
 }
 
