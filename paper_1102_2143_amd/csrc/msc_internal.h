@@ -329,6 +329,7 @@ struct MsArgs {
                          // 0 no, 3 full links, 2 two rows per link (w64 / w32 in that form)
   SweepOrder ord;        // slice order of the head and K2 on the sliced path
   int march, m1, m2;     // links: t-slices per column of the march, and whether K1 / K2 march
+  int split;             // links: a wave for each direction
   Stencil<double2> w64;
   Stencil<float2> w32;
   int sample;            // slot of SolveState::smp_* for this iteration, -1: not sampled

@@ -890,6 +890,103 @@ __global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
   store_partial(region(a, a.par ^ 1), acc);
 }
 
+// ---- the links of small lattices: one direction per wave --------------------------------------
+// A workgroup takes blocks of 64 sites, its four waves a direction each, so that all loads
+// of a site are in flight at once, over four times the waves; the directions meet in LDS,
+// and each row is then finished by a lane of its own.  Used while every block can have a
+// workgroup (prepare_impl): there an iteration is a chain of latencies.
+// An iteration in FP64, one lane per site and here: 4^4 16.8 and 12.2 us, 12^4 23.4 and 15.1,
+// 16^4 30.2 and 26.9, 18^4 37.9 and 43.0.
+template <class R> using DirParts = cplx<R>[4][3][kWave];
+
+// (m + sign D) v at this thread's row of block `blk` (thread t < 192: colour t / 64 of site t %
+// 64; live: the row exists), after a barrier of its own; the caller's rows are free to use
+// `part` again once every thread has passed the next one.
+template <class R, int LR>
+__device__ __forceinline__ cplx<R> split_row(const Stencil<cplx<R>>& w, const cplx<R>* __restrict__ v,
+                                             int sign, int64_t blk, DirParts<R>& part) {
+  const uint32_t vol = uint32_t(w.vol);
+  const int lane = threadIdx.x % kWave;
+  const int mu = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
+  const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
+  const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
+  const int c = mu < 3 ? mu : 0;
+  const cplx<R> own = v[int64_t(c) * vol + ss];
+  cplx<R> h[3];
+  stencil_dir<R, LR>(w, ss, mu, [&](uint32_t s, int k) { return v[int64_t(k) * vol + s]; }, h);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) part[mu][k][lane] = h[k];
+  __syncthreads();
+  cplx<R> o = czero<R>();
+  if (mu < 3) {
+    const cplx<R> a = part[0][c][lane], b = part[1][c][lane], d = part[2][c][lane], e = part[3][c][lane];
+    const R hx = (a.x + b.x) + (d.x + e.x), hy = (a.y + b.y) + (d.y + e.y), m = R(w.mass);
+    o.x = fma(m, own.x, sign > 0 ? hx : -hx);
+    o.y = fma(m, own.y, sign > 0 ? hy : -hy);
+  }
+  return o;
+}
+
+// This thread's row of a block, or -1.
+__device__ __forceinline__ int64_t split_index(int64_t vol, int64_t blk) {
+  const int64_t site = blk * kSiteBlock + int64_t(threadIdx.x % kWave);
+  return threadIdx.x < 3 * kWave && site < vol ? int64_t(threadIdx.x / kWave) * vol + site : -1;
+}
+
+template <class R, int LR>
+__global__ __launch_bounds__(kBlock) void k1_split(MsArgs a) {
+  const int halt = a.st->rot[a.par].halt;
+  const Stencil<cplx<R>> w = pick_w<R>(a);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
+  const int64_t nblk = (w.vol + kSiteBlock - 1) / kSiteBlock;
+  __shared__ DirParts<R> part;
+  double acc = 0.0;
+  for (int64_t blk = logical_block(); blk < nblk; blk += gridDim.x) {
+    const cplx<R> v = split_row<R, LR>(w, r, 1, blk, part);
+    if (halt) return;
+    const int64_t i = split_index(w.vol, blk);
+    if (i >= 0) {
+      u[i] = v;
+      acc += norm2d<R>(v);
+    }
+    __syncthreads();
+  }
+  store_partial(region(a, 2 + a.par), acc);
+}
+
+template <class R, int LR>
+__global__ __launch_bounds__(kBlock) void k2_split(MsArgs a) {
+  Early e;
+  StepIn in;
+  if (!k2_begin(a, e, in)) return;
+  const Stencil<cplx<R>> w = pick_w<R>(a);
+  const cplx<R>* __restrict__ u = static_cast<const cplx<R>*>(a.u);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
+  cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  const int64_t nblk = (w.vol + kSiteBlock - 1) / kSiteBlock;
+  __shared__ DirParts<R> part;
+  StepPlan p;
+  p.stop = -1;
+  double acc = 0.0;
+  for (int64_t blk = logical_block(a.gg); blk < nblk; blk += a.gg) {
+    const int64_t i = split_index(w.vol, blk);
+    const cplx<R> rv = i >= 0 ? r[i] : czero<R>(), sv = i >= 0 ? s[i] : czero<R>();
+    const cplx<R> q = split_row<R, LR>(w, u, -1, blk, part);
+    if (p.stop < 0 && !k2_step(a, e, in, p)) return;
+    if (i >= 0) {
+      cplx<R> sn, nv;
+      row_step<R>(p, in.sigma0, q, rv, sv, sn, nv);
+      s[i] = sn;
+      rn[i] = nv;
+      acc += norm2d<R>(nv);
+    }
+    __syncthreads();
+  }
+  store_partial(region(a, a.par ^ 1), acc);
+}
+
 // ---- the composed steps of every shift: x_j and p_j -------------------------------------------
 // x_j += cx[0] p_j + sum_{k<m} cx[k+1] r_k, p_j <- cp[0] p_j + sum_{k<m} cp[k+1] r_k, the r_k
 // being the m composed steps' residuals; before the first application x_j and p_j are zero
@@ -1696,8 +1793,15 @@ template <class R> int site_grid(const MsArgs& a, int half, int& march) {
 
 template <class R> void prepare_impl(MsArgs& a) {
   const bool mhm = a.kind == MSC_A_MHM;
-  a.m1 = a.m2 = 0;
+  a.m1 = a.m2 = a.split = 0;
   if (a.sell && mhm && a.stencil) {
+    // a direction per wave while every block of 64 sites gets a workgroup of its own (up to
+    // 65536 sites; k1_split has the times on both sides)
+    a.split = (a.w64.vol + kSiteBlock - 1) / kSiteBlock <= a.grid ? 1 : 0;
+    if (a.split) {
+      a.gd = a.gg = grid_rows(a.w64.vol, kSiteBlock, a.grid);
+      return;
+    }
     a.march = a.ord.on ? march_columns(a.w64) : 1;
     a.gd = site_grid<R>(a, 1, a.m1);
     a.gg = site_grid<R>(a, 2, a.m2);
@@ -1765,6 +1869,11 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
 
 template <class R, int LR> void launch_sites(const MsArgs& a, hipStream_t s, hipEvent_t* ev) {
   constexpr bool STREAM = std::is_same<R, double>::value;
+  if (a.split) {
+    launch_timed(k1_split<R, LR>, a.gd, s, ev, 0, a);
+    launch_timed(k2_split<R, LR>, a.gg + 1, s, ev, 1, a);
+    return;
+  }
   if constexpr (LR == 2) {
     if (a.m1)
       launch_timed(k1_site<R, 2, STREAM, true>, a.gd, s, ev, 0, a);

@@ -164,6 +164,57 @@ __device__ __forceinline__ void stencil_site(const Stencil<cplx<R>>& op, uint32_
                                static_cast<TCarry<R, LR>*>(nullptr));
 }
 
+// Direction mu's share of (D v)(s, .): the forward and the backward term of one direction.
+template <class R, int LR, class G>
+__device__ __forceinline__ void stencil_dir(const Stencil<cplx<R>>& op, uint32_t s, int mu, G gather,
+                                            cplx<R> (&h)[3]) {
+  constexpr int K = 3 * LR;
+  const uint32_t vol = uint32_t(op.vol);
+  uint32_t rem = s, par = 0, fwd = s, bwd = s;
+#pragma unroll
+  for (int nu = 0; nu < 4; ++nu) {
+    if (nu <= mu) {  // mu is uniform
+      const uint32_t L = uint32_t(op.L[nu]), st = uint32_t(op.stride[nu]);
+      const uint32_t q = rem / L, xm = rem - q * L;
+      rem = q;
+      if (nu < mu) {
+        par += xm;
+      } else {
+        fwd = xm == L - 1 ? s - (L - 1) * st : s + st;
+        bwd = xm == 0 ? s + (L - 1) * st : s - st;
+      }
+    }
+  }
+  const cplx<R>* __restrict__ wm = op.w + int64_t(mu) * K * vol;
+  cplx<R> U[9], B[9], gf[3], gb[3];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    U[k] = wm[int64_t(k) * vol + s];
+    B[k] = wm[int64_t(k) * vol + bwd];
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    gf[j] = gather(fwd, j);
+    gb[j] = gather(bwd, j);
+    gb[j].x = -gb[j].x;
+    gb[j].y = -gb[j].y;
+  }
+  if constexpr (LR == 2) {
+    const R te = (par & 1u) ? R(-2) : R(2);
+    third_row<R>(U, te);
+    third_row<R>(B, te);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    h[c] = czero<R>();
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      cfma<R>(h[c], U[3 * c + j], gf[j]);
+      cfma_conj<R>(h[c], B[3 * j + c], gb[j]);
+    }
+  }
+}
+
 // M (sign 1) or M^H (sign -1) times several vectors at one site: out[q][c] of xs[q], q <
 // cnt <= G.  A direction's two links are read and completed once for all of them.
 template <class R, int LR, int G>
