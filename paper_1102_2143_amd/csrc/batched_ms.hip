@@ -3,18 +3,34 @@
 // each iteration kernel covers every row of every unfinished system.
 //
 // Work is split into chunks of rows (each chunk belongs to one system); the kernels are
-// persistent (a bounded grid loops over the chunk list).  The right-hand sides of a
-// system are interleaved, v[i * R + q], so one read of a matrix row serves all of them.
-// Every system has its own scalar state; the last chunk of a system to finish a kernel
-// finalises that system's reductions and recurrences (one lane per (rhs, shift) pair).
-// Each system runs its multishift sequence in FP64 until all its right-hand sides reach
-// switch_tol, then in complex64 with FP64 reliable updates (same scheme as the single
-// solve).
+// persistent (a bounded grid loops over the chunk list), one launch for the systems of each
+// precision.  Every system has its own scalar state.  The sequence is the single solve's
+// (multishift.hip): BK1 u = M r, BS1 the scalars of the step (one workgroup per system, one
+// lane per (rhs, shift)), BK2 the step of s and r, BS2 the stopping rules.  The shifts' steps
+// are composed and applied by a kernel of its own (BF) every few iterations, which also
+// converts a system whose right-hand sides have all reached switch_tol to complex64 (it
+// waits for that BF); reliable updates run between BFs.
+//
+// Operators made from links read them: a wave takes 64 sites of one right-hand side, whose
+// vectors lie apart, colour by colour; the waves of the other right-hand sides on the same
+// sites share its links in the caches.  Stored matrices: the right-hand sides of a system
+// are interleaved, v[i R + q], so that one read of a matrix row serves all of them.
+//
+// The iteration kernels are bound by the round trips of a wave's task (about 28000 tasks of 64
+// sites or rows), so what counts is how many are in flight and how few they are: with each
+// system's last chunk finalising its scalars (a ticket that every chunk waits for), both
+// precisions in one kernel (216 registers) and the descriptors read as vectors, 48 lattices
+// of 4^4 to 12^4 and 16 grids of 32^3, four right-hand sides and ten shifts each, took
+// 122 + 140 us an iteration in complex64; without the tickets 83 + 104; a kernel per
+// precision 66 + 78; descriptors and state through the scalar cache (164 and 98 registers)
+// 53 + 70, FP64 83 + 111 (the vectors and links alone at 5.5 TB/s: 35 + 54 and 70 + 108).
+// The solve in mixed precision: 172 -> 85 ms.
 #include <type_traits>
 
 #include "dev_common.h"
 #include "msc_internal.h"
 #include "sell_load.h"
+#include "stencil.h"
 
 namespace msc {
 
@@ -22,24 +38,57 @@ namespace {
 
 constexpr int kQK = kBatchMaxRhs * kBatchMaxShifts;  // 64 lanes of the finalising wave
 
-template <class R> __device__ __forceinline__ cplx<R>* vec_r(const BatchSys& S);
-template <> __device__ __forceinline__ double2* vec_r<double>(const BatchSys& S) { return S.r64; }
-template <> __device__ __forceinline__ float2* vec_r<float>(const BatchSys& S) { return S.r32; }
-template <class R> __device__ __forceinline__ cplx<R>* vec_p(const BatchSys& S);
-template <> __device__ __forceinline__ double2* vec_p<double>(const BatchSys& S) { return S.p64; }
-template <> __device__ __forceinline__ float2* vec_p<float>(const BatchSys& S) { return S.p32; }
-template <class R> __device__ __forceinline__ cplx<R>* vec_t(const BatchSys& S);
-template <> __device__ __forceinline__ double2* vec_t<double>(const BatchSys& S) { return S.t64; }
-template <> __device__ __forceinline__ float2* vec_t<float>(const BatchSys& S) { return S.t32; }
-template <class R> __device__ __forceinline__ cplx<R>* vec_pk(const BatchSys& S);
-template <> __device__ __forceinline__ double2* vec_pk<double>(const BatchSys& S) { return S.pk64; }
-template <> __device__ __forceinline__ float2* vec_pk<float>(const BatchSys& S) { return S.pk32; }
+// What no kernel of a launch writes (descriptors; the state, in BK1 and BK2), read through the
+// scalar cache: addresses are uniform over the workgroup.
+template <class T> __device__ __forceinline__ T load_const(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "words");
+  using cword = const __attribute__((address_space(4))) uint32_t;
+  uint32_t w[sizeof(T) / 4];
+  cword* c = (cword*)(reinterpret_cast<uintptr_t>(p));
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = c[i];
+  T v;
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
+
+template <class R> struct BVec;  // a system's vectors of one precision
+template <> struct BVec<double> {
+  static __device__ __forceinline__ double2* slot(const BatchSys& S, int k, int64_t len) {
+    return S.ring64 + k * len;
+  }
+  static __device__ __forceinline__ double2* u(const BatchSys& S) { return S.u64; }
+  static __device__ __forceinline__ double2* s(const BatchSys& S) { return S.s64v; }
+  static __device__ __forceinline__ double2* pk(const BatchSys& S) { return S.pk64; }
+  static __device__ __forceinline__ Stencil<double2> w(const BatchSys& S) { return S.w64; }
+};
+template <> struct BVec<float> {
+  static __device__ __forceinline__ float2* slot(const BatchSys& S, int k, int64_t len) {
+    return k == 0 ? S.slot32 : S.ring32 + (k - 1) * len;
+  }
+  static __device__ __forceinline__ float2* u(const BatchSys& S) { return S.u32; }
+  static __device__ __forceinline__ float2* s(const BatchSys& S) { return S.s32v; }
+  static __device__ __forceinline__ float2* pk(const BatchSys& S) { return S.pk32; }
+  static __device__ __forceinline__ Stencil<float2> w(const BatchSys& S) { return S.w32; }
+};
 template <class R> __device__ __forceinline__ Csr<cplx<R>> mat1(const BatchSys& S);
 template <> __device__ __forceinline__ Csr<double2> mat1<double>(const BatchSys& S) { return S.m64; }
 template <> __device__ __forceinline__ Csr<float2> mat1<float>(const BatchSys& S) { return S.m32; }
 template <class R> __device__ __forceinline__ Csr<cplx<R>> mat2(const BatchSys& S);
 template <> __device__ __forceinline__ Csr<double2> mat2<double>(const BatchSys& S) { return S.mh64; }
 template <> __device__ __forceinline__ Csr<float2> mat2<float>(const BatchSys& S) { return S.mh32; }
+
+
+// Slot of the residual ring: step l of a system's phase reads slot l % ring, writes the next.
+template <class R, int RR>
+__device__ __forceinline__ cplx<R>* bslot(const BatchSys& S, int l) {
+  return BVec<R>::slot(S, l % S.ring, S.n * RR);
+}
+
+// Where (row i, rhs q) lies in a system's vectors.
+template <int RR> __device__ __forceinline__ int64_t bidx(const BatchSys& S, int64_t i, int q) {
+  return S.links ? int64_t(q) * S.n + (i % 3) * (S.n / 3) + i / 3 : i * RR + q;
+}
 
 // Row i of a CSR times the RHS-interleaved vector x (RR right-hand sides), L lanes per
 // row; sums returned in every lane of the row group.
@@ -76,58 +125,141 @@ template <class R> __device__ __forceinline__ Sell<cplx<R>> sell2(const BatchSys
 template <> __device__ __forceinline__ Sell<double2> sell2<double>(const BatchSys& S) { return S.sh64; }
 template <> __device__ __forceinline__ Sell<float2> sell2<float>(const BatchSys& S) { return S.sh32; }
 
-// Pairs per round trip of the RR-rhs product (MSC_BATCH_KP32 / MSC_BATCH_KP64 at four
-// right-hand sides, twice that for fewer).
-#ifndef MSC_BATCH_KP32
-#define MSC_BATCH_KP32 4
-#endif
-#ifndef MSC_BATCH_KP64
-#define MSC_BATCH_KP64 2
-#endif
-template <class R, int RR> constexpr int kp_rhs() {
-  return std::is_same<R, float>::value ? (RR >= 4 ? MSC_BATCH_KP32 : 2 * MSC_BATCH_KP32)
-                                       : (RR >= 4 ? MSC_BATCH_KP64 : 2 * MSC_BATCH_KP64);
-}
+// Pairs per round trip of the RR-rhs product (more cost registers, hence waves: 4 rhs with two
+// pairs 93.7 ms, with one 91.9).
+template <int RR> constexpr int kp_rhs() { return RR >= 4 ? 1 : 2; }
 
-// Per-rhs workgroup partials of a chunk: store, take the system's ticket; true in the
-// last chunk of the system, which then holds the per-rhs totals in tot[].
-__device__ __forceinline__ bool chunk_reduce(double (&v)[kBatchMaxRhs], const BatchSys& S, int cidx,
-                                             int ticket, double* tot) {
-  block_sum_k<kBlock, kBatchMaxRhs>(v);
+// Workgroup partials of a chunk (K values): store, take the system's ticket; true in the
+// last chunk of the system, which then holds the totals in tot[].
+template <int K>
+__device__ __forceinline__ bool chunk_reduce(double (&v)[K], const BatchSys& S, int cidx, int ticket,
+                                             double* tot) {
+  block_sum_k<kBlock, K>(v);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int q = 0; q < kBatchMaxRhs; ++q) store_agent(&S.partial[cidx * kBatchMaxRhs + q], v[q]);
+    for (int q = 0; q < K; ++q) store_agent(&S.partial[cidx * K + q], v[q]);
   }
   if (!arrive_last(S.tickets + ticket * kTicketSite, unsigned(S.nchunks), unsigned(cidx))) return false;
-  // thread -> (rhs q = tid / 64, sub-lane) : all loads of a rhs in flight together
-  const int q = threadIdx.x / kWave, s = threadIdx.x % kWave;
+  // thread -> (value q, sub-lane): all loads of a value in flight together
+  constexpr int LN = kBlock / K;
+  const int q = threadIdx.x / LN, s = threadIdx.x % LN;
   double acc = 0.0;
-  for (int c = s; c < S.nchunks; c += kWave) acc += load_agent(&S.partial[c * kBatchMaxRhs + q]);
-  acc = group_sum<kWave>(acc);
+  for (int c = s; c < S.nchunks; c += LN) acc += load_agent(&S.partial[c * K + q]);
+  acc = group_sum<LN>(acc);
   if (s == 0) tot[q] = acc;
   __syncthreads();
   return true;
 }
 
-// ---- BK1: t = A1 p for every rhs; per rhs P = |t|^2 + s0|p|^2 (or Re p^H t + s0|p|^2) ----
+// The iteration kernels' partial sums, one set per wave and chunk, added by the system's
+// workgroup of the next kernel: no wave waits for another.  On links a wave has one
+// right-hand side's (wave % RR), else all of them; either way entry % RR is its q.
+template <int RR>
+__device__ __forceinline__ void wave_partial(const BatchSys& S, const int4& ch, double (&v)[RR]) {
+  const int wv = threadIdx.x / kWave;
+  if (S.links) {
+    const double t = group_sum<kWave>(v[0]);
+    if (threadIdx.x % kWave == 0) S.partial[ch.w * (kBlock / kWave) + wv] = t;
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < RR; ++q) v[q] = group_sum<kWave>(v[q]);
+  if (threadIdx.x % kWave == 0) {
+#pragma unroll
+    for (int q = 0; q < RR; ++q) S.partial[(ch.w * (kBlock / kWave) + wv) * RR + q] = v[q];
+  }
+}
+
+// Their totals per rhs, in every thread's view of tot[] (kBatchMaxRhs).
+template <int RR> __device__ __forceinline__ void system_totals(const BatchSys& S, double* tot) {
+  constexpr int U = 4;
+  const int np = S.nchunks * (kBlock / kWave) * (S.links ? 1 : RR);
+  double a[U] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < np; i += U * kBlock) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u * kBlock < np) a[u] += S.partial[i + u * kBlock];
+  }
+  double v = (a[0] + a[1]) + (a[2] + a[3]);
+  // lanes of one rhs: those equal mod RR
+#pragma unroll
+  for (int o = kWave / 2; o >= RR; o /= 2) v += __shfl_xor(v, o, kWave);
+  __shared__ double part[kBlock / kWave][kBatchMaxRhs];
+  if (int(threadIdx.x % kWave) < RR) part[threadIdx.x / kWave][threadIdx.x % kWave] = v;
+  __syncthreads();
+  if (threadIdx.x < kBatchMaxRhs) {
+    double s = 0.0;
+    if (int(threadIdx.x) < RR)
+      for (int w = 0; w < kBlock / kWave; ++w) s += part[w][threadIdx.x];
+    tot[threadIdx.x] = s;
+  }
+  __syncthreads();
+}
+
+// One wave's share of a links' chunk: 64 sites (from `site`) of right-hand side q.  out = (m +
+// sign D) v there, v and out colour by colour.
+struct SiteTask {
+  int q;
+  uint32_t site;   // this lane's, or the last one of the system where it has none
+  bool live;
+};
+template <int RR> __device__ __forceinline__ SiteTask site_task(const int4& ch) {
+  SiteTask t;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
+  t.q = wv % RR;
+  const uint32_t s0 = uint32_t(ch.y) / 3u, s1 = uint32_t(ch.z) / 3u;
+  const uint32_t s = s0 + uint32_t(wv / RR) * uint32_t(kWave) + threadIdx.x % kWave;
+  t.live = s < s1;
+  t.site = t.live ? s : s1 - 1;
+  return t;
+}
+template <class R>
+__device__ __forceinline__ void site_product(const BatchSys& S, const cplx<R>* __restrict__ v,
+                                             const SiteTask& t, int sign, cplx<R> (&own)[3],
+                                             cplx<R> (&out)[3]) {
+  const Stencil<cplx<R>> w = BVec<R>::w(S);
+  const cplx<R>* __restrict__ vq = v + int64_t(t.q) * S.n;
+  const int64_t vol = w.vol;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) own[c] = vq[c * vol + t.site];
+  auto at = [&](uint32_t s, int c) { return vq[c * vol + s]; };
+  if (S.links == 2)
+    stencil_site<R, 2>(w, t.site, own, sign, at, out);
+  else
+    stencil_site<R, 3>(w, t.site, own, sign, at, out);
+}
+
+// ---- BK1: u = M r (A r for A given) for every rhs and d's share: |u|^2 or Re r^H u --------
 template <class R, int L, int RR>
-__device__ void bk1_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
-  const Csr<cplx<R>> m = mat1<R>(S);
-  const cplx<R>* __restrict__ p = vec_p<R>(S);
-  cplx<R>* __restrict__ t = vec_t<R>(S);
-  const double s0 = st->sigma0;
+__device__ __forceinline__ void bk1_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
+  const cplx<R>* __restrict__ r = bslot<R, RR>(S, load_const(&st->slot));
+  cplx<R>* __restrict__ u = BVec<R>::u(S);
   const bool mhm = S.kind == MSC_A_MHM;
-  double acc[kBatchMaxRhs] = {0.0, 0.0, 0.0, 0.0};
-  auto epilogue = [&](int64_t row, const cplx<R> (&v)[RR], const cplx<R> (&pr)[RR]) {
+  double acc[RR];
+#pragma unroll
+  for (int q = 0; q < RR; ++q) acc[q] = 0.0;
+  auto epilogue = [&](int64_t row, const cplx<R> (&v)[RR], const cplx<R> (&rr)[RR]) {
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
-      t[row * RR + q] = v[q];
-      acc[q] += (mhm ? norm2d<R>(v[q])
-                     : double(pr[q].x) * double(v[q].x) + double(pr[q].y) * double(v[q].y)) +
-                s0 * norm2d<R>(pr[q]);
+      u[row * RR + q] = v[q];
+      acc[q] += mhm ? norm2d<R>(v[q])
+                    : double(rr[q].x) * double(v[q].x) + double(rr[q].y) * double(v[q].y);
     }
   };
-  if (S.sell) {
+  if (S.links) {
+    const SiteTask t = site_task<RR>(ch);
+    cplx<R> own[3], v[3];
+    site_product<R>(S, r, t, 1, own, v);
+    double sum = 0.0;
+    if (t.live) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        u[int64_t(t.q) * S.n + c * S.w64.vol + t.site] = v[c];
+        sum += norm2d<R>(v[c]);
+      }
+    }
+    acc[0] = sum;
+  } else if (S.sell) {
     // one row per lane: the chunk's four slices, one per wave
     const Sell<cplx<R>> ms = sell1<R>(S);
     const int lane = threadIdx.x % kSlice;
@@ -136,9 +268,9 @@ __device__ void bk1_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
       const int64_t row = sl * kSlice + lane;
       const int64_t rr = row < ch.z ? row : ch.z - 1;
       cplx<R> pr[RR], v[RR];
-      load_rhs<R, RR>(p, rr, pr);
+      load_rhs<R, RR>(r, rr, pr);
       const cplx<R> d = ms.diag[rr];
-      sell_row_rhs<R, RR, kp_rhs<R, RR>()>(ms, p, sl, lane, v);
+      sell_row_rhs<R, RR, kp_rhs<RR>()>(ms, r, sl, lane, v);
 #pragma unroll
       for (int q = 0; q < RR; ++q) cfma<R>(v[q], d, pr[q]);
       if (row < ch.z) epilogue(row, v, pr);
@@ -146,414 +278,371 @@ __device__ void bk1_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
   } else {
     constexpr int GPB = kBlock / L;
     const int lane = threadIdx.x % L, grp = threadIdx.x / L;
+    const Csr<cplx<R>> m = mat1<R>(S);
     for (int64_t row = ch.y + grp; row < ch.z; row += GPB) {
       cplx<R> v[RR];
-      row_dot_rhs<R, L, RR>(m, p, row, lane, v);
+      row_dot_rhs<R, L, RR>(m, r, row, lane, v);
       if (lane == 0) {
         cplx<R> pr[RR];
 #pragma unroll
-        for (int q = 0; q < RR; ++q) pr[q] = p[row * RR + q];
+        for (int q = 0; q < RR; ++q) pr[q] = r[row * RR + q];
         epilogue(row, v, pr);
       }
     }
   }
-  __shared__ double tot[kBatchMaxRhs];
-  if (!chunk_reduce(acc, S, ch.w, 0, tot)) return;
-  // finalise: lane = q * 16 + k
-  const int lk = threadIdx.x;
-  if (lk >= kQK) return;
-  if (lk == 0 && st->switch_pending) {
-    // this launch read the complex64 buffers written by the switching update
-    st->switch_pending = 0;
-    st->phase32 = 1;
-  }
-  const int q = lk / kBatchMaxShifts, k = lk % kBatchMaxShifts;
-  if (q >= st->nrhs || st->halt[q]) return;
-  const double P = tot[q];
-  if (!(P > 0.0 && isfinite(P))) {
-    if (k == 0) {
-      st->status[q] = 1;
-      st->halt[q] = 1;
-    }
-    return;
-  }
-  const double a = st->R[q] / P;
-  if (k >= 1 && k < st->ns && st->active[lk]) {
-    const double z = st->zeta[lk], zp = st->zeta_prev[lk], ap = st->a_prev[q], b = st->b[q];
-    const double zn = z * zp * ap / (a * b * (zp - z) + zp * ap * (1.0 + st->s[k] * a));
-    st->zk[lk] = zn;
-    st->ak[lk] = a * zn / z;
-  }
-  if (k == 0) st->a[q] = a;
+  wave_partial<RR>(S, ch, acc);
 }
 
-// ---- BK2: r <- r - a (A2 t + s0 p), R' = |r|^2; recurrences, freezing, halting ------------
-template <class R, int L, int RR>
-__device__ void bk2_chunk(const BatchSys& S, BatchState* st, const int4& ch, int* active_systems,
-                          int defer_ok, int steps) {
-  const cplx<R>* __restrict__ t = vec_t<R>(S);
-  const cplx<R>* __restrict__ p = vec_p<R>(S);
-  cplx<R>* __restrict__ r = vec_r<R>(S);
-  const double s0 = st->sigma0;
-  const bool mhm = S.kind == MSC_A_MHM;
-  double step[RR];
+// The scalars of the step, one workgroup per system.
+__device__ __forceinline__ void bs1_system(BatchState* st, const double* tot) {
+  // lane = q * 16 + k: the scalars of step n of rhs q, and shift k's, composed with
+  // the pending steps; every lane reads the state before any lane writes it
+  const int lk = threadIdx.x;
+  if (lk >= kQK) return;
+  const int q = lk / kBatchMaxShifts, k = lk % kBatchMaxShifts, ns = st->ns;
+  const bool live = q < st->nrhs && !st->halt[q];
+  const int n = live ? st->iter[q] : 0, ru = live ? st->ru[q] : 0, m = live ? st->m[q] : 0;
+  const double g = live ? st->R[q] : 1.0, g1 = live ? st->g1[q] : 1.0, a1 = live ? st->a1[q] : 1.0;
+  const double P1 = live ? st->P1[q] : 1.0, rg = live ? st->ru_g[q] : 0.0, rc = live ? st->ru_c[q] : 0.0;
+  const bool act = live && k < ns && (k == 0 || st->active[lk]);
+  const double z = k ? st->zeta[lk] : 1.0, zp = k ? st->zeta_prev[lk] : 1.0;
+  const bool had = m > 0 && st->took[lk];
+  double cx[kMaxSteps + 1], cp[kMaxSteps + 1];
 #pragma unroll
-  for (int q = 0; q < RR; ++q) step[q] = (q < st->nrhs && !st->halt[q]) ? st->a[q] : 0.0;
-  double acc[kBatchMaxRhs] = {0.0, 0.0, 0.0, 0.0};
-  auto epilogue = [&](int64_t row, const cplx<R> (&qv)[RR]) {
+  for (int i = 0; i <= kMaxSteps; ++i) {
+    cx[i] = m > 0 && i <= m ? st->cx[i][lk] : 0.0;
+    cp[i] = m > 0 && i <= m ? st->cp[i][lk] : 0.0;
+  }
+  if (m == 0) cp[0] = 1.0;
+  const double d = tot[q] + st->sigma0 * g;
+  const double b = n == 0 ? 0.0 : (ru ? rg : g) / g1;
+  const double P = n == 0 ? d : (ru ? d + b * (2.0 * rc + b * P1) : d - b * g / a1);
+  const bool ok = P > 0.0 && isfinite(P);
+  const double a = g / P;
+  if (k == 0 && q < kBatchMaxRhs) st->step[q] = live && ok ? 1 : 0;
+  if (live && !ok && k == 0) {
+    st->status[q] = 1;
+    st->halt[q] = 1;
+  }
+  if (!live || !ok) return;
+  bool took = had;
+  if (act) {
+    const double zn = k == 0   ? 1.0
+                      : n == 0 ? z / (1.0 + st->s[k] * a)
+                               : z * zp * a1 / (a * b * (zp - z) + zp * a1 * (1.0 + st->s[k] * a));
+    const double ratio = z / zp, aj = a * zn / z, bj = b * ratio * ratio;
+#pragma unroll
+    for (int i = 0; i <= kMaxSteps; ++i) {
+      if (i <= m) cp[i] *= bj;
+      if (i == m + 1) cp[i] = z;
+      if (i <= m + 1) cx[i] = fma(aj, cp[i], cx[i]);
+    }
+    st->zeta_prev[lk] = z;
+    st->zeta[lk] = zn;
+    took = true;
+  }
+  st->took[lk] = took ? 1 : 0;
+#pragma unroll
+  for (int i = 0; i <= kMaxSteps; ++i) {
+    st->cx[i][lk] = cx[i];
+    st->cp[i][lk] = cp[i];
+  }
+  if (k == 0) {
+    st->a[q] = st->a1[q] = a;
+    st->b[q] = b;
+    st->P1[q] = P;
+    st->g1[q] = g;
+    st->m[q] = m + 1;
+    st->last[q] = st->slot;  // the newest of the composed steps
+    st->ru[q] = 0;
+  }
+}
+
+// ---- BK2: s <- w + s0 r + b s, r' = r - a s, R' = |r'|^2; freezing, halting, switching -----
+template <class R, int L, int RR>
+__device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
+  const int slot = load_const(&st->slot);
+  const cplx<R>* __restrict__ u = BVec<R>::u(S);
+  const cplx<R>* __restrict__ r = bslot<R, RR>(S, slot);
+  cplx<R>* __restrict__ rn = bslot<R, RR>(S, slot + 1);
+  cplx<R>* __restrict__ sv = BVec<R>::s(S);
+  const double s0 = load_const(&st->sigma0);
+  const bool mhm = S.kind == MSC_A_MHM;
+  double acc[RR];
+#pragma unroll
+  for (int q = 0; q < RR; ++q) acc[q] = 0.0;
+  // one element: the step of rhs q (false: it takes none)
+  auto element = [&](int64_t idx, const cplx<R>& w, double a, double b) {
+    const double2 wd = to_d(w), rd = to_d(r[idx]), sd = to_d(ld_stream(&sv[idx]));
+    const double2 t{fma(b, sd.x, fma(s0, rd.x, wd.x)), fma(b, sd.y, fma(s0, rd.y, wd.y))};
+    const cplx<R> nr = from_d<R>(double2{fma(-a, t.x, rd.x), fma(-a, t.y, rd.y)});
+    st_stream(&sv[idx], from_d<R>(t));
+    rn[idx] = nr;
+    return norm2d<R>(nr);
+  };
+  if (S.links) {
+    const SiteTask t = site_task<RR>(ch);
+    double sum = 0.0;
+    if (t.q < load_const(&st->nrhs) && load_const(&st->step[t.q])) {
+      cplx<R> own[3], w[3];
+      site_product<R>(S, u, t, -1, own, w);
+      const double a = load_const(&st->a[t.q]), b = load_const(&st->b[t.q]);
+      if (t.live) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          sum += element(int64_t(t.q) * S.n + c * S.w64.vol + t.site, w[c], a, b);
+      }
+    }
+    acc[0] = sum;
+  } else {
+    double a[RR], b[RR];
+    bool go[RR];
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
-      const double2 pr = to_d(p[row * RR + q]), rr = to_d(r[row * RR + q]), qd = to_d(qv[q]);
-      const double2 nr{rr.x - step[q] * (qd.x + s0 * pr.x), rr.y - step[q] * (qd.y + s0 * pr.y)};
-      const cplx<R> sr = from_d<R>(nr);
-      r[row * RR + q] = sr;
-      acc[q] += norm2d<R>(sr);
+      go[q] = q < load_const(&st->nrhs) && load_const(&st->step[q]);
+      a[q] = go[q] ? load_const(&st->a[q]) : 0.0;
+      b[q] = go[q] ? load_const(&st->b[q]) : 0.0;
     }
-  };
-  if (S.sell && mhm) {
-    // one row per lane: the chunk's four slices, one per wave
-    const Sell<cplx<R>> ms = sell2<R>(S);
-    const int lane = threadIdx.x % kSlice;
-    const int64_t sl = ch.y / kSlice + __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
-    if (sl * kSlice < ch.z) {
-      const int64_t row = sl * kSlice + lane;
-      const int64_t rr = row < ch.z ? row : ch.z - 1;
-      cplx<R> tr[RR], qv[RR];
-      load_rhs<R, RR>(t, rr, tr);
-      const cplx<R> d = ms.diag[rr];
-      sell_row_rhs<R, RR, kp_rhs<R, RR>()>(ms, t, sl, lane, qv);
+    auto epilogue = [&](int64_t row, const cplx<R> (&w)[RR]) {
 #pragma unroll
-      for (int q = 0; q < RR; ++q) cfma<R>(qv[q], d, tr[q]);
-      if (row < ch.z) epilogue(row, qv);
-    }
-  } else {
-    constexpr int GPB = kBlock / L;
-    const int lane = threadIdx.x % L, grp = threadIdx.x / L;
-    for (int64_t row = ch.y + grp; row < ch.z; row += GPB) {
-      cplx<R> qv[RR];
-      if (mhm) {
-        row_dot_rhs<R, L, RR>(mat2<R>(S), t, row, lane, qv);
-      } else {
+      for (int q = 0; q < RR; ++q)
+        if (go[q]) acc[q] += element(row * RR + q, w[q], a[q], b[q]);
+    };
+    if (S.sell && mhm) {
+      // one row per lane: the chunk's four slices, one per wave
+      const Sell<cplx<R>> ms = sell2<R>(S);
+      const int lane = threadIdx.x % kSlice;
+      const int64_t sl = ch.y / kSlice + __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+      if (sl * kSlice < ch.z) {
+        const int64_t row = sl * kSlice + lane;
+        const int64_t rr = row < ch.z ? row : ch.z - 1;
+        cplx<R> tr[RR], w[RR];
+        load_rhs<R, RR>(u, rr, tr);
+        const cplx<R> d = ms.diag[rr];
+        sell_row_rhs<R, RR, kp_rhs<RR>()>(ms, u, sl, lane, w);
 #pragma unroll
-        for (int q = 0; q < RR; ++q) qv[q] = t[row * RR + q];
+        for (int q = 0; q < RR; ++q) cfma<R>(w[q], d, tr[q]);
+        if (row < ch.z) epilogue(row, w);
       }
-      if (lane == 0) epilogue(row, qv);
+    } else if (mhm) {
+      constexpr int GPB = kBlock / L;
+      const int lane = threadIdx.x % L, grp = threadIdx.x / L;
+      for (int64_t row = ch.y + grp; row < ch.z; row += GPB) {
+        cplx<R> w[RR];
+        row_dot_rhs<R, L, RR>(mat2<R>(S), u, row, lane, w);
+        if (lane == 0) epilogue(row, w);
+      }
+    } else {  // A given: u is A r already
+      const int q = threadIdx.x % RR;  // kBlock is a multiple of RR: this thread's rhs
+      double sum = 0.0, aq = 0.0, bq = 0.0;
+      bool gq = false;
+#pragma unroll
+      for (int k = 0; k < RR; ++k) {
+        if (k == q) {
+          aq = a[k];
+          bq = b[k];
+          gq = go[k];
+        }
+      }
+      const int64_t end = int64_t(ch.z) * RR;
+      if (gq)
+        for (int64_t e = int64_t(ch.y) * RR + threadIdx.x; e < end; e += kBlock)
+          sum += element(e, u[e], aq, bq);
+#pragma unroll
+      for (int k = 0; k < RR; ++k) acc[k] = k == q ? sum : 0.0;
     }
   }
-  __shared__ double tot[kBatchMaxRhs];
-  if (!chunk_reduce(acc, S, ch.w, 1, tot)) return;
-  // one wave finalises: lane = q * 16 + k; every lane reads the state before any lane
+  wave_partial<RR>(S, ch, acc);
+}
+
+__device__ __forceinline__ void bs2_system(BatchState* st, const double* tot, int* active_systems) {
+  // one wave: lane = q * 16 + k; every lane reads the state before any lane
   // writes it, and system-wide decisions travel by ballot, not through memory
   const int lk = threadIdx.x;
   if (lk >= kWave) return;
   const int q = lk / kBatchMaxShifts, k = lk % kBatchMaxShifts;
-  const int nrhs = st->nrhs, ns = st->ns;
-  const bool live = q < nrhs && !st->halt[q];
-  const double Rq = live ? st->R[q] : 1.0;
-  const double aq = live ? st->a[q] : 0.0;
-  const int itq = live ? st->iter[q] : 0;
-  const double eps2q = q < nrhs ? st->eps2[q] : 0.0;
-  const double sw2q = q < nrhs ? st->sw_eps2[q] : 0.0;
-  const int max_iter = st->max_iter;
-  const int phase32 = st->phase32;
-  // lane k = 0 of each rhs composes x_0's steps like a shift with zeta = 1 (step a_q,
-  // direction coefficient b): x_0 then takes them in the BK3 that applies
-  const bool drv = k == 0;
-  const bool act = live && (drv || (k >= 1 && k < ns && st->active[lk]));
-  const double z = (act && !drv) ? st->zeta[lk] : 1.0, zn = (act && !drv) ? st->zk[lk] : 1.0;
-  const double akq = act ? (drv ? aq : st->ak[lk]) : 0.0;
-  // steps this rhs deferred in previous BK3s, composed (read before any lane writes the
-  // state): x_k gained cx[0] p_k + sum_i cx[i+1] r_i, p_k now is cp[0] p_k + sum_i cp[i+1] r_i
-  const int md = q < nrhs ? st->ndef[q] : 0;
-  double cx[kBatchMaxSteps + 1], cp[kBatchMaxSteps + 1];
-#pragma unroll
-  for (int i = 0; i <= kBatchMaxSteps; ++i) cx[i] = cp[i] = 0.0;
-  cp[0] = 1.0;
-  bool dact = false, dupd = false;
-  if (md > 0 && k < ns) {
-#pragma unroll
-    for (int i = 0; i < kBatchMaxSteps; ++i) {
-      if (i <= md) {
-        cx[i] = st->dcx[i][lk];
-        cp[i] = st->dcp[i][lk];
-      }
-    }
-    dact = st->dact[lk] != 0;
-    dupd = st->dupd[lk] != 0;
-  }
+  const bool live = q < st->nrhs && st->step[q] && !st->halt[q];
+  const int it = live ? st->iter[q] + 1 : 0;
+  const double eps2 = live ? st->eps2[q] : 0.0, sw2 = live ? st->sw_eps2[q] : 0.0;
   const double Rn = live ? tot[q] : 0.0;
-  const double bn = Rn / Rq;
-  bool keep_p = false;
-  double bkq = 0.0;
-  if (act && drv) {
-    bkq = bn;
-    keep_p = true;
-  } else if (act) {
-    const double ratio = zn / z;
-    bkq = bn * ratio * ratio;
-    st->bk[lk] = bkq;
-    st->zeta_prev[lk] = z;
-    st->zeta[lk] = zn;
-    keep_p = true;
-    if (zn * zn * Rn <= eps2q) {
-      st->active[lk] = 0;
-      st->freeze_iter[lk] = itq + 1;
-      keep_p = false;
-    }
+  const int phase32 = st->phase32, max_iter = st->max_iter;
+  const bool act = live && k >= 1 && k < st->ns && st->active[lk];
+  const double z = act ? st->zeta[lk] : 0.0;
+  if (act && z * z * Rn <= eps2) {
+    st->active[lk] = 0;
+    st->freeze_iter[lk] = it;
   }
-  // per right-hand side (lanes k == 0)
-  const bool halt_q = live && (!isfinite(Rn) || Rn <= eps2q || itq + 1 >= max_iter);
   bool halted_after = true, below = true;
-  if (k == 0 && q < nrhs) {
-    st->x0_upd[q] = live ? 1 : 0;
-    if (live) {
-      st->b_new[q] = bn;
-      st->a_prev[q] = aq;
-      st->b[q] = bn;
-      st->R[q] = Rn;
-      st->iter[q] = itq + 1;
-      if (!isfinite(Rn)) {
-        st->status[q] = 1;
-        st->halt[q] = 1;
-      } else if (Rn <= eps2q || itq + 1 >= max_iter) {
-        st->halt[q] = 1;
-      } else {
-        halted_after = false;
-        below = Rn <= sw2q;
-      }
+  if (k == 0 && live) {
+    st->R[q] = Rn;
+    st->iter[q] = it;
+    if (!isfinite(Rn)) {
+      st->status[q] = 1;
+      st->halt[q] = 1;
+    } else if (Rn <= eps2 || it >= max_iter) {
+      st->halt[q] = 1;
+    } else {
+      halted_after = false;
+      below = Rn <= sw2;
     }
   }
   const bool all_halted = __ballot(!halted_after) == 0;
   const bool all_below = __ballot(!halted_after && !below) == 0;
-  const bool switching = !all_halted && !phase32 && all_below;
-  // fold this step into the composition (x_k += a_k p_k; p_k <- zeta_k' r + b_k p_k unless
-  // k freezes now); then BK3 either defers it (this rhs continues, the vectors keep their
-  // precision, fewer than `steps` - 1 steps pending) or applies every pending step
-  if (act) {
-#pragma unroll
-    for (int i = 0; i < kBatchMaxSteps; ++i)
-      if (i <= md) cx[i] = fma(akq, cp[i], cx[i]);
-  }
-  if (act && keep_p) {
-#pragma unroll
-    for (int i = 0; i < kBatchMaxSteps; ++i)
-      if (i <= md) cp[i] *= bkq;
-#pragma unroll
-    for (int i = 1; i <= kBatchMaxSteps; ++i)
-      if (i == md + 1) cp[i] = zn;
-  }
-  dact = dact || act;
-  dupd = dupd || (act && keep_p);
-  const bool defer = live && !halt_q && !switching && defer_ok && md + 1 < steps;
-  const bool listed = !defer && dact && !drv;
-  st->upd_x[lk] = listed ? 1 : 0;
-  st->upd_p[lk] = (listed && dupd) ? 1 : 0;
-#pragma unroll
-  for (int i = 0; i < kBatchMaxSteps; ++i) st->cx[i][lk] = i <= md ? cx[i] : 0.0;
-#pragma unroll
-  for (int i = 0; i <= kBatchMaxSteps; ++i) st->cp[i][lk] = i <= md + 1 ? cp[i] : 0.0;
-  if (defer) {
-#pragma unroll
-    for (int i = 0; i < kBatchMaxSteps; ++i) {
-      st->dcx[i][lk] = i <= md ? cx[i] : 0.0;
-      st->dcp[i][lk] = i <= md + 1 ? cp[i] : 0.0;
-    }
-    st->dact[lk] = dact ? 1 : 0;
-    st->dupd[lk] = dupd ? 1 : 0;
-  }
-  const uint64_t lm = __ballot(listed);
-  if (k == 0 && q < nrhs) {
-    st->ndef[q] = defer ? md + 1 : 0;
-    st->m[q] = defer ? 0 : md;
-    st->keep[q] = defer ? md : -1;
-    if (live) {
-      const int ph = phase32 ? 1 : 0;
-      st->n_upd[q][ph] += __popcll((lm >> (q * kBatchMaxShifts)) & 0xffffull);
-      st->n_kept[q][ph] += defer ? 1 : md;
-      st->n_x0[q][ph] += defer ? 0 : 1;
-      st->n_k0[q][ph] += (defer && md == 0) ? 1 : 0;
-    }
-  }
   if (lk == 0) {
-    st->k3_enable = 1;
+    st->slot += 1;
     if (all_halted) {
       st->done = 1;
-      atomicSub(active_systems, 1);
-    } else if (switching) {
+      atomicSub(&active_systems[phase32], 1);
+    } else if (!phase32 && all_below) {
       st->switch_pending = 1;
-      st->iters_fp64 = itq + 1;
+      st->iters_fp64 = it;
     }
   }
 }
 
-// ---- BK3: x_q += a_q p_q, shifted updates, p_q <- r_q + b_q p_q --------------------------
-// The update's per-(rhs, shift) coefficients, staged in LDS once per chunk so the loop
-// over shifts issues its vector loads without first waiting on the scalar state.
-struct K3Coef {
-  double cx[kBatchMaxSteps][kQK], cp[kBatchMaxSteps + 1][kQK];
-  int upd_x[kQK], upd_p[kQK];
-  int orig[kBatchMaxShifts];
-  double bnew[kBatchMaxRhs];
-  int x0_upd[kBatchMaxRhs], m[kBatchMaxRhs], keep[kBatchMaxRhs];
-  int nrhs, ns;
+// ---- BF: the composed steps of every shift; the switch to complex64 ----------------------
+// Bound by the bytes: 8 steps folded, FP64 10 * 64 + 8 * 16 per row and rhs, 940 us at 5.9 M
+// of them = 4.8 TB/s (four steps folded and p read and written besides: 198 us each step).
+// x_k += cx[0] p_k + sum_{i<m} cx[i+1] r_i, p_k likewise with cp (k = 0, the driving system,
+// too); before a system's first BF its x_k and p_k are zero and are not read.  One row per
+// thread, p_k in the caller's row order, [k][q][row].  W != R: r, s and p_k go to complex64.
+struct BFlush {
+  double cx[kMaxSteps + 1][kQK], cp[kMaxSteps + 1][kQK];
+  int took[kQK], orig[kBatchMaxShifts];
+  int m[kBatchMaxRhs], last[kBatchMaxRhs];
+  int nrhs, ns, fresh, slot;
 };
 
 template <class R, class W, int RR>
-__device__ void bk3_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
-  __shared__ K3Coef cf;
+__device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, const int4& ch, BFlush& f, int* active) {
   const int tid = threadIdx.x;
-  __syncthreads();  // the previous chunk of this workgroup is done with cf
+  __syncthreads();  // the previous chunk of this workgroup is done with f
   if (tid < kQK) {
 #pragma unroll
-    for (int i = 0; i < kBatchMaxSteps; ++i) cf.cx[i][tid] = st->cx[i][tid];
-#pragma unroll
-    for (int i = 0; i <= kBatchMaxSteps; ++i) cf.cp[i][tid] = st->cp[i][tid];
-    cf.upd_x[tid] = st->upd_x[tid];
-    cf.upd_p[tid] = st->upd_p[tid];
+    for (int i = 0; i <= kMaxSteps; ++i) {
+      f.cx[i][tid] = st->cx[i][tid];
+      f.cp[i][tid] = st->cp[i][tid];
+    }
+    f.took[tid] = st->took[tid];
   }
-  if (tid < kBatchMaxShifts) cf.orig[tid] = st->orig[tid];
+  if (tid < kBatchMaxShifts) f.orig[tid] = st->orig[tid];
   if (tid < kBatchMaxRhs) {
-    cf.bnew[tid] = st->b_new[tid];
-    cf.x0_upd[tid] = st->x0_upd[tid];
-    cf.m[tid] = st->m[tid];
-    cf.keep[tid] = st->keep[tid];
+    f.m[tid] = st->m[tid];
+    f.last[tid] = st->last[tid];
   }
   if (tid == 0) {
-    cf.nrhs = st->nrhs;
-    cf.ns = st->ns;
+    f.nrhs = st->nrhs;
+    f.ns = st->ns;
+    f.fresh = st->fresh;
+    f.slot = st->slot;
   }
   __syncthreads();
-  const cplx<R>* __restrict__ r = vec_r<R>(S);
-  cplx<R>* __restrict__ p = vec_p<R>(S);
-  cplx<R>* __restrict__ pk = vec_pk<R>(S);
-  // outputs go to the W buffers: W == R except on the switching iteration (FP64 -> FP32)
-  cplx<W>* __restrict__ pw = vec_p<W>(S);
-  cplx<W>* __restrict__ rw = vec_r<W>(S);
-  cplx<W>* __restrict__ pkw = vec_pk<W>(S);
+  constexpr bool same = std::is_same<R, W>::value;
   const int64_t n = S.n;
-  const int ns = cf.ns;
-  const int64_t rows = ch.z - ch.y;
-  for (int64_t e = tid; e < rows * RR; e += kBlock) {
-    const int64_t i = ch.y + e / RR;
-    const int q = int(e % RR);
-    const int64_t idx = i * RR + q;
-    const double2 rd = to_d(r[idx]);
-    const double2 pd = to_d(p[idx]);
-    if (q < cf.nrhs && cf.x0_upd[q]) {
-      // a deferring BK3 keeps r (the first of a cycle p too); the one that applies reads
-      // the m kept residuals and updates x_0 and the shifts (with m = 0 the multiply-adds
-      // round exactly as one step)
-      const int mq = cf.m[q], kq = cf.keep[q];
-      cplx<R>* __restrict__ pkeep0 = static_cast<cplx<R>*>(S.pkeep0);
-      if (kq >= 0) static_cast<cplx<R>*>(S.rkeep[kq])[idx] = r[idx];
-      if (kq == 0) pkeep0[idx] = p[idx];
-      double2 rk[kBatchMaxSteps - 1];
+  const int ns = f.ns, fresh = f.fresh;
+  cplx<R>* __restrict__ pk = BVec<R>::pk(S);
+  cplx<W>* __restrict__ pw = BVec<W>::pk(S);
+  // one (row, rhs) per thread: fewer vectors of the others between two of its loads
+  const int rows = ch.z - ch.y, elems = rows * f.nrhs;
+  for (int e = tid; e < elems; e += kBlock) {
+    const int q = e / rows;
+    const int64_t i = ch.y + e % rows;
+    const int64_t idx = bidx<RR>(S, i, q);
+    if (!same) {
+      bslot<W, RR>(S, 0)[idx] = from_d<W>(to_d(bslot<R, RR>(S, f.slot)[idx]));
+      BVec<W>::s(S)[idx] = from_d<W>(to_d(BVec<R>::s(S)[idx]));
+    }
+    const int m = f.m[q];
+    if (same && m == 0 && !fresh) continue;
+    double2 rv[kMaxSteps];
 #pragma unroll
-      for (int kk = 0; kk < kBatchMaxSteps - 1; ++kk)
-        rk[kk] = kk < mq ? to_d(static_cast<const cplx<R>*>(S.rkeep[kk])[idx]) : double2{0.0, 0.0};
-      if (kq < 0) {
-        double2* x0 = S.x + (int64_t(q) * ns + cf.orig[0]) * n + i;
-        const int l0 = q * kBatchMaxShifts;
-        const double2 p1 = mq > 0 ? to_d(pkeep0[idx]) : pd;
-        double2 xv = *x0;
+    for (int k = 0; k < kMaxSteps; ++k)
+      rv[k] = k < m ? to_d(bslot<R, RR>(S, f.last[q] - m + 1 + k)[idx]) : double2{0.0, 0.0};
+    constexpr int G = 2;  // shifts whose loads are issued together
+    for (int k0 = 0; k0 < ns; k0 += G) {
+      double2 pj[G], xv[G];
+      bool ux[G], ld[G];
 #pragma unroll
-        for (int kk = kBatchMaxSteps - 2; kk >= 0; --kk) {
-          if (kk < mq) {
-            xv.x = fma(cf.cx[kk + 1][l0], rk[kk].x, xv.x);
-            xv.y = fma(cf.cx[kk + 1][l0], rk[kk].y, xv.y);
-          }
-        }
-        xv.x = fma(cf.cx[0][l0], p1.x, xv.x);
-        xv.y = fma(cf.cx[0][l0], p1.y, xv.y);
-        *x0 = xv;
+      for (int u = 0; u < G; ++u) {
+        const int k = k0 + u;
+        ux[u] = k < ns && ((m > 0 && f.took[q * kBatchMaxShifts + k]) || fresh);
+        ld[u] = k < ns && (ux[u] || !same);
+        pj[u] = xv[u] = double2{0.0, 0.0};
+        if (ld[u] && !fresh) pj[u] = to_d(ld_stream(&pk[(int64_t(k) * RR + q) * n + i]));
+        if (ux[u] && !fresh) xv[u] = ld_stream(&S.x[(int64_t(q) * ns + f.orig[k]) * n + i]);
       }
-      constexpr bool same = std::is_same<R, W>::value;
-      // two shifts at a time, their loads issued before either store (x_k and p_k of
-      // different shifts share one array each, so the compiler cannot reorder); frozen
-      // shifts are skipped except on the switching iteration, which copies them
-      for (int k0 = 1; k0 < ns; k0 += 2) {
-        double2 pj[2], xk[2];
-        bool ux[2], ld[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int k = k0 + u;
+      for (int u = 0; u < G; ++u) {
+        const int k = k0 + u;
+        if (!ld[u]) continue;
+        double2 np = pj[u];
+        if (ux[u]) {
           const int lk = q * kBatchMaxShifts + k;
-          ux[u] = k < ns && cf.upd_x[lk];
-          ld[u] = k < ns && (ux[u] || !same);
-          if (ld[u]) pj[u] = to_d(pk[int64_t(k - 1) * n * RR + idx]);
-          if (ux[u]) xk[u] = S.x[(int64_t(q) * ns + cf.orig[k]) * n + i];
-        }
+          const bool some = m > 0 && f.took[lk];
+          double2 xs = xv[u];
+          np = double2{0.0, 0.0};
+          if (some) {
+            xs.x = fma(f.cx[0][lk], pj[u].x, xs.x);
+            xs.y = fma(f.cx[0][lk], pj[u].y, xs.y);
+            np = double2{f.cp[0][lk] * pj[u].x, f.cp[0][lk] * pj[u].y};
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int k = k0 + u;
-          if (!ld[u]) continue;
-          const int lk = q * kBatchMaxShifts + k;
-          const int64_t pidx = int64_t(k - 1) * n * RR + idx;
-          if (ux[u]) {
-            double2 xv = xk[u];
-#pragma unroll
-            for (int kk = kBatchMaxSteps - 2; kk >= 0; --kk) {
-              if (kk < mq) {
-                xv.x = fma(cf.cx[kk + 1][lk], rk[kk].x, xv.x);
-                xv.y = fma(cf.cx[kk + 1][lk], rk[kk].y, xv.y);
+            for (int j = 0; j < kMaxSteps; ++j) {
+              if (j < m) {
+                xs.x = fma(f.cx[j + 1][lk], rv[j].x, xs.x);
+                xs.y = fma(f.cx[j + 1][lk], rv[j].y, xs.y);
+                np.x = fma(f.cp[j + 1][lk], rv[j].x, np.x);
+                np.y = fma(f.cp[j + 1][lk], rv[j].y, np.y);
               }
             }
-            xv.x = fma(cf.cx[0][lk], pj[u].x, xv.x);
-            xv.y = fma(cf.cx[0][lk], pj[u].y, xv.y);
-            S.x[(int64_t(q) * ns + cf.orig[k]) * n + i] = xv;
           }
-          if (cf.upd_p[lk]) {
-            const double c0 = cf.cp[0][lk];
-            double2 np{c0 * pj[u].x, c0 * pj[u].y};
-#pragma unroll
-            for (int kk = 0; kk < kBatchMaxSteps - 1; ++kk) {
-              if (kk < mq) {
-                np.x = fma(cf.cp[kk + 1][lk], rk[kk].x, np.x);
-                np.y = fma(cf.cp[kk + 1][lk], rk[kk].y, np.y);
-              }
-            }
-            const double cr = cf.cp[mq + 1][lk];
-            np.x = fma(cr, rd.x, np.x);
-            np.y = fma(cr, rd.y, np.y);
-            pkw[pidx] = from_d<W>(np);
-          } else if (!same) {
-            pkw[pidx] = from_d<W>(pj[u]);
-          }
+          st_stream(&S.x[(int64_t(q) * ns + f.orig[k]) * n + i], xs);
         }
-      }
-      const double bq = cf.bnew[q];
-      pw[idx] = from_d<W>(double2{fma(bq, pd.x, rd.x), fma(bq, pd.y, rd.y)});
-    } else if (!std::is_same<R, W>::value) {
-      pw[idx] = from_d<W>(pd);
-      for (int k = 1; k < ns; ++k) {
-        const int64_t pidx = int64_t(k - 1) * n * RR + idx;
-        pkw[pidx] = from_d<W>(to_d(pk[pidx]));
+        st_stream(&pw[(int64_t(k) * RR + q) * n + i], from_d<W>(np));
       }
     }
-    if (!std::is_same<R, W>::value) rw[idx] = from_d<W>(rd);
+  }
+  if (!arrive_last(S.tickets + 2 * kTicketSite, unsigned(S.nchunks), unsigned(ch.w))) return;
+  // every chunk has read the state: nothing is pending any more
+  if (tid < kBatchMaxRhs) {
+    const int ph = sizeof(R) == 4 ? 1 : 0, m = f.m[tid];
+    int upd = 0;
+    for (int k = 0; k < ns; ++k)
+      upd += (m > 0 && f.took[tid * kBatchMaxShifts + k]) || fresh ? 1 : 0;
+    if (tid < f.nrhs) {
+      st->n_upd[tid][ph] += upd;
+      st->n_kept[tid][ph] += m;
+    }
+    st->m[tid] = 0;
+  }
+  if (tid == 0) {
+    st->fresh = 0;
+    if (!same) {
+      st->phase32 = 1;
+      st->switch_pending = 0;
+      st->slot = 0;
+      if (!st->done) {
+        atomicSub(&active[0], 1);
+        atomicAdd(&active[1], 1);
+      }
+    }
   }
 }
 
-// ---- init: r = p = p_k = b_q, x = 0, |b_q|^2 ----------------------------------------------
+// ---- init: r = b_q, s = 0, |b_q|^2 ---------------------------------------------------------
 template <int RR>
-__device__ void binit_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
+__device__ __forceinline__ void binit_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
   const int64_t n = S.n;
-  const int ns = st->ns;
-  const int64_t rows = ch.z - ch.y;
   double acc[kBatchMaxRhs] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t e = threadIdx.x; e < rows * RR; e += kBlock) {
-    const int64_t i = ch.y + e / RR;
-    const int q = int(e % RR);
-    const int64_t idx = i * RR + q;
-    const double2 bv = q < st->nrhs ? S.b[int64_t(q) * n + i] : double2{0.0, 0.0};
-    S.r64[idx] = bv;
-    S.p64[idx] = bv;
-    for (int k = 1; k < ns; ++k) S.pk64[int64_t(k - 1) * n * RR + idx] = bv;
-    if (q < st->nrhs)
-      for (int k = 0; k < ns; ++k) S.x[(int64_t(q) * ns + k) * n + i] = double2{0.0, 0.0};
+  double2* __restrict__ r = bslot<double, RR>(S, 0);
+  for (int64_t i = ch.y + threadIdx.x; i < ch.z; i += kBlock) {
 #pragma unroll
-    for (int qq = 0; qq < kBatchMaxRhs; ++qq)
-      if (qq == q) acc[qq] += fma(bv.x, bv.x, bv.y * bv.y);
+    for (int q = 0; q < RR; ++q) {
+      const int64_t idx = bidx<RR>(S, i, q);
+      const double2 bv = q < st->nrhs ? S.b[int64_t(q) * n + i] : double2{0.0, 0.0};
+      r[idx] = bv;
+      S.s64v[idx] = double2{0.0, 0.0};
+      acc[q] += fma(bv.x, bv.x, bv.y * bv.y);
+    }
   }
   __shared__ double tot[kBatchMaxRhs];
   if (!chunk_reduce(acc, S, ch.w, 2, tot)) return;
@@ -571,75 +660,143 @@ __device__ void binit_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
   }
 }
 
-// ---- reliable update of a system in its complex64 phase: r_q = b_q - (A + s0) x_q0 -------
-template <int L, int RR>
-__device__ void bru1_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
-  // u = M x_q0 (FP64), stored interleaved in S.u64
+// ---- FP64 products with several vectors (reliable update, verification) ------------------
+// out(row, v, value) in the lane that owns the row, of vectors in + v step (row order), v <
+// nv <= NV: M in, or M^H in where `second` (A = M^H M's other half; A in for A given).
+template <int L, int NV, class OUT>
+__device__ __forceinline__ void product64(const BatchSys& S, const int4& ch, bool second, int nv,
+                                          const double2* __restrict__ in, int64_t step, OUT out) {
+  const bool mh = second && S.kind == MSC_A_MHM;
+  if (S.vlinks) {
+    // a wave per 64 sites and vector
+    const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
+    const uint32_t s0 = uint32_t(ch.y) / 3u, s1 = uint32_t(ch.z) / 3u;
+    const int blocks = int((s1 - s0 + kWave - 1) / kWave);
+    for (int task = wv; task < blocks * nv; task += kBlock / kWave) {
+      const int v = task % nv;
+      const uint32_t s = s0 + uint32_t(task / nv) * uint32_t(kWave) + threadIdx.x % kWave;
+      const bool live = s < s1;
+      const uint32_t ss = live ? s : s1 - 1;
+      const double2* __restrict__ x = in + v * step;
+      double2 own[3], o[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) own[c] = x[3 * int64_t(ss) + c];
+      auto at = [&](uint32_t t, int c) { return x[3 * int64_t(t) + c]; };
+      if (S.vlinks == 2)
+        stencil_site<double, 2>(S.v64, ss, own, mh ? -1 : 1, at, o);
+      else
+        stencil_site<double, 3>(S.v64, ss, own, mh ? -1 : 1, at, o);
+      if (live) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) out(3 * int64_t(s) + c, v, o[c]);
+      }
+    }
+    return;
+  }
+  if (S.sell) {
+    // a row per lane, KV vectors at a time
+    constexpr int KV = NV < 4 ? NV : 4;
+    const Sell<double2> ms = mh ? S.sh64 : S.s64;
+    const int lane = threadIdx.x % kSlice;
+    const int64_t sl = ch.y / kSlice + __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+    if (sl * kSlice >= ch.z) return;
+    const int64_t row = sl * kSlice + lane;
+    const bool live = row < ch.z;
+    const double2 d = ms.diag[live ? row : ch.z - 1];
+#pragma unroll
+    for (int v0 = 0; v0 < NV; v0 += KV) {
+      if (v0 >= nv) break;
+      const int kc = min(KV, nv - v0);
+      const double2* xs[KV];
+      double2 acc[KV];
+#pragma unroll
+      for (int q = 0; q < KV; ++q) {
+        xs[q] = in + int64_t(min(v0 + q, nv - 1)) * step;
+        acc[q] = double2{0.0, 0.0};
+      }
+      sell_row_multi<double, KV, 1>(ms, xs, kc, sl, lane, acc);
+      if (live) {
+#pragma unroll
+        for (int q = 0; q < KV; ++q) {
+          if (q < kc) {
+            cfma<double>(acc[q], d, xs[q][row]);
+            out(row, v0 + q, acc[q]);
+          }
+        }
+      }
+    }
+    return;
+  }
   constexpr int GPB = kBlock / L;
   const int lane = threadIdx.x % L, grp = threadIdx.x / L;
-  const int64_t n = S.n;
+  const Csr<double2> m = mh ? S.mh64 : S.m64;
   for (int64_t row = ch.y + grp; row < ch.z; row += GPB) {
-    const int32_t beg = S.m64.rowptr[row], end = S.m64.rowptr[row + 1];
-    double2 acc[RR];
+    double2 acc[NV];
 #pragma unroll
-    for (int q = 0; q < RR; ++q) acc[q] = double2{0.0, 0.0};
-    for (int32_t j = beg + lane; j < end; j += L) {
-      const int32_t c = S.m64.col[j];
-      const double2 v = S.m64.val[j];
+    for (int v = 0; v < NV; ++v) acc[v] = double2{0.0, 0.0};
+    const int32_t end = m.rowptr[row + 1];
+    for (int32_t j = m.rowptr[row] + lane; j < end; j += L) {
+      const int32_t c = m.col[j];
+      const double2 a = m.val[j];
 #pragma unroll
-      for (int q = 0; q < RR; ++q)
-        if (q < st->nrhs) cfma<double>(acc[q], v, S.x[(int64_t(q) * st->ns + st->orig[0]) * n + c]);
+      for (int v = 0; v < NV; ++v)
+        if (v < nv) cfma<double>(acc[v], a, in[v * step + c]);
     }
 #pragma unroll
-    for (int q = 0; q < RR; ++q) {
-      acc[q] = group_sum_c<L, double>(acc[q]);
-      if (lane == 0) S.u64[row * RR + q] = acc[q];
+    for (int v = 0; v < NV; ++v) {
+      acc[v] = group_sum_c<L, double>(acc[v]);
+      if (lane == 0 && v < nv) out(row, v, acc[v]);
     }
   }
 }
 
+// ---- reliable update of a system in its complex64 phase: r_q = b_q - (A + s0) x_q0 -------
 template <int L, int RR>
-__device__ void bru2_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
-  constexpr int GPB = kBlock / L;
-  const int lane = threadIdx.x % L, grp = threadIdx.x / L;
+__device__ __forceinline__ void bru1_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
+  // u = M x_q0 (FP64), vector q at ru64 + q n
+  const int64_t n = S.n;
+  const double2* __restrict__ x0 = S.x + int64_t(st->orig[0]) * n;
+  const int64_t step = int64_t(st->ns) * n;
+  product64<L, RR>(S, ch, false, st->nrhs, x0, step,
+                   [&](int64_t i, int v, const double2& o) { S.ru64[v * n + i] = o; });
+}
+
+template <int L, int RR>
+__device__ __forceinline__ void bru2_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
   const int64_t n = S.n;
   const bool mhm = S.kind == MSC_A_MHM;
   const double s0 = st->sigma0;
-  double acc[kBatchMaxRhs] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t row = ch.y + grp; row < ch.z; row += GPB) {
-    const Csr<double2> m2 = mhm ? S.mh64 : S.m64;
-    const int32_t beg = m2.rowptr[row], end = m2.rowptr[row + 1];
-    double2 qv[RR];
+  const double2* __restrict__ x0 = S.x + int64_t(st->orig[0]) * n;
+  const int64_t step = int64_t(st->ns) * n;
+  const double2* __restrict__ in = mhm ? S.ru64 : x0;
+  const int64_t istep = mhm ? n : step;
+  float2* __restrict__ r = bslot<float, RR>(S, st->slot);
+  double acc[2 * kBatchMaxRhs];  // |r_q|^2, then Re r_q^H s_q
 #pragma unroll
-    for (int q = 0; q < RR; ++q) qv[q] = double2{0.0, 0.0};
-    for (int32_t j = beg + lane; j < end; j += L) {
-      const int32_t c = m2.col[j];
-      const double2 v = m2.val[j];
+  for (int q = 0; q < 2 * kBatchMaxRhs; ++q) acc[q] = 0.0;
+  product64<L, RR>(S, ch, true, st->nrhs, in, istep,
+                   [&](int64_t i, int v, const double2& o) {
+                     const double2 bv = S.b[v * n + i], xv = x0[v * step + i];
+                     const double2 rt{bv.x - o.x - s0 * xv.x, bv.y - o.y - s0 * xv.y};
+                     const int64_t idx = bidx<RR>(S, i, v);
+                     const double2 sd = to_d(S.s32v[idx]);
+                     r[idx] = from_d<float>(rt);
 #pragma unroll
-      for (int q = 0; q < RR; ++q) {
-        if (q < st->nrhs) {
-          const double2 in = mhm ? S.u64[int64_t(c) * RR + q] : S.x[(int64_t(q) * st->ns + st->orig[0]) * n + c];
-          cfma<double>(qv[q], v, in);
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < RR; ++q) {
-      qv[q] = group_sum_c<L, double>(qv[q]);
-      if (lane == 0 && q < st->nrhs) {
-        const double2 bv = S.b[int64_t(q) * n + row];
-        const double2 xv = S.x[(int64_t(q) * st->ns + st->orig[0]) * n + row];
-        const double2 rt{bv.x - qv[q].x - s0 * xv.x, bv.y - qv[q].y - s0 * xv.y};
-        S.r32[row * RR + q] = from_d<float>(rt);
-        acc[q] += fma(rt.x, rt.x, rt.y * rt.y);
-      }
-    }
-  }
-  __shared__ double tot[kBatchMaxRhs];
-  if (!chunk_reduce(acc, S, ch.w, 3, tot)) return;
+                     for (int q = 0; q < RR; ++q) {
+                       if (q == v) {
+                         acc[q] += fma(rt.x, rt.x, rt.y * rt.y);
+                         acc[kBatchMaxRhs + q] += rt.x * sd.x + rt.y * sd.y;
+                       }
+                     }
+                   });
+  __shared__ double tot[2 * kBatchMaxRhs];
+  if (!chunk_reduce<2 * kBatchMaxRhs>(acc, S, ch.w, 3, tot)) return;
   if (threadIdx.x < st->nrhs) {
     const int q = threadIdx.x;
     if (!st->halt[q]) {
+      if (!st->ru[q]) st->ru_g[q] = st->R[q];
+      st->ru[q] = 1;
+      st->ru_c[q] = tot[kBatchMaxRhs + q];
       st->R[q] = tot[q];
       if (!isfinite(tot[q])) {
         st->status[q] = 1;
@@ -652,73 +809,130 @@ __device__ void bru2_chunk(const BatchSys& S, BatchState* st, const int4& ch) {
   }
 }
 
+// ---- FP64 true residuals of shifts [k0, k0 + 8) of right-hand side q, every system ----------
+// (a launch for all systems in place of one each: 13 -> 3.5 ms for the 64 systems)
+constexpr int kBvShifts = 8;
+template <int L>
+__device__ __forceinline__ void bv1_chunk(const BatchSys& S, const BatchState* st, const int4& ch, int q, int k0) {
+  const int64_t n = S.n;
+  const int nv = min(kBvShifts, st->ns - k0);
+  const double2* __restrict__ x = S.x + (int64_t(q) * st->ns + k0) * n;
+  double2* __restrict__ u = S.pk64;  // the sequence has ended: its vectors are free
+  product64<L, kBvShifts>(S, ch, false, nv, x, n,
+                          [&](int64_t i, int v, const double2& o) { u[v * n + i] = o; });
+}
+
+template <int L>
+__device__ __forceinline__ void bv2_chunk(const BatchSys& S, const BatchState* st, const int4& ch, int q, int k0,
+                          const double* sig, double* out) {
+  const int64_t n = S.n;
+  const int nv = min(kBvShifts, st->ns - k0);
+  const double2* __restrict__ x = S.x + (int64_t(q) * st->ns + k0) * n;
+  const double2* __restrict__ in = S.kind == MSC_A_MHM ? S.pk64 : x;
+  const double2* __restrict__ b = S.b + int64_t(q) * n;
+  double acc[kBvShifts];
+#pragma unroll
+  for (int v = 0; v < kBvShifts; ++v) acc[v] = 0.0;
+  product64<L, kBvShifts>(S, ch, true, nv, in, n,
+                          [&](int64_t i, int v, const double2& o) {
+                            const double2 bv = b[i], xv = x[v * n + i];
+                            const double ex = bv.x - o.x - sig[k0 + v] * xv.x;
+                            const double ey = bv.y - o.y - sig[k0 + v] * xv.y;
+#pragma unroll
+                            for (int w = 0; w < kBvShifts; ++w)
+                              if (w == v) acc[w] += fma(ex, ex, ey * ey);
+                          });
+  __shared__ double tot[kBvShifts];
+  if (!chunk_reduce<kBvShifts>(acc, S, ch.w, 0, tot)) return;
+  if (threadIdx.x < nv) out[k0 + threadIdx.x] = tot[threadIdx.x];
+}
+
 // ---- persistent drivers over the chunk list ---------------------------------------------
-template <int L, int RR>
-__global__ __launch_bounds__(kBlock) void bk1(BatchArgs a) {
+// Waves per SIMD that the registers are kept to: FP64 3 (at most 168), complex64 4 (128; 5,
+// with 96, is no faster).
+template <class R> constexpr int waves_per_simd() { return sizeof(R) == 4 ? 4 : 3; }
+
+template <class R, int L, int RR>
+__global__ __launch_bounds__(kBlock, waves_per_simd<R>()) void bk1(BatchArgs a) {
   for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-    const int4 ch = a.chunks[c];
-    const BatchSys& S = a.sys[ch.x];
-    BatchState* st = S.st;
-    if (st->done) continue;
-    if (st->phase32 || st->switch_pending)
-      bk1_chunk<float, L, RR>(S, st, ch);
-    else
-      bk1_chunk<double, L, RR>(S, st, ch);
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    const BatchState* st = S.st;
+    if (load_const(&st->phase32) != int(sizeof(R) == 4) || load_const(&st->done) ||
+        load_const(&st->switch_pending))
+      continue;
+    bk1_chunk<R, L, RR>(S, st, ch);
   }
 }
 
-template <int L, int RR>
-__global__ __launch_bounds__(kBlock) void bk2(BatchArgs a) {
+// A system with no step in this launch: finished, waiting for the switch, or in a phase that
+// the launch leaves out.
+__device__ __forceinline__ bool idle(const BatchArgs& a, const BatchState* st) {
+  return st->done || st->switch_pending || !(a.phases & (st->phase32 ? 2 : 1));
+}
+
+template <int RR> __global__ __launch_bounds__(kBlock) void bs1(BatchArgs a) {
+  const BatchSys S = load_const(a.sys + blockIdx.x);
+  if (idle(a, S.st)) return;
+  __shared__ double tot[kBatchMaxRhs];
+  system_totals<RR>(S, tot);
+  bs1_system(S.st, tot);
+}
+
+template <class R, int L, int RR>
+__global__ __launch_bounds__(kBlock, waves_per_simd<R>()) void bk2(BatchArgs a) {
   for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-    const int4 ch = a.chunks[c];
-    const BatchSys& S = a.sys[ch.x];
-    BatchState* st = S.st;
-    if (st->done) continue;
-    if (st->phase32)
-      bk2_chunk<float, L, RR>(S, st, ch, a.active_systems, a.defer_ok, a.steps);
-    else
-      bk2_chunk<double, L, RR>(S, st, ch, a.active_systems, a.defer_ok, a.steps);
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    const BatchState* st = S.st;
+    if (load_const(&st->phase32) != int(sizeof(R) == 4) || load_const(&st->done) ||
+        load_const(&st->switch_pending))
+      continue;
+    bk2_chunk<R, L, RR>(S, st, ch);
   }
+}
+
+template <int RR> __global__ __launch_bounds__(kBlock) void bs2(BatchArgs a) {
+  const BatchSys S = load_const(a.sys + blockIdx.x);
+  if (idle(a, S.st)) return;
+  __shared__ double tot[kBatchMaxRhs];
+  system_totals<RR>(S, tot);  // its barriers come after every thread has looked
+  bs2_system(S.st, tot, a.active_systems);
 }
 
 template <int RR>
-__global__ __launch_bounds__(kBlock, 4) void bk3(BatchArgs a) {
+__global__ __launch_bounds__(kBlock, 4) void bf(BatchArgs a) {
+  __shared__ BFlush f;
   for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-    const int4 ch = a.chunks[c];
-    const BatchSys& S = a.sys[ch.x];
-    const BatchState* st = S.st;
-    if (!st->k3_enable) continue;
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    BatchState* st = S.st;
+    const int any = st->m[0] | st->m[1] | st->m[2] | st->m[3] | st->fresh;
+    if (!any && !st->switch_pending) continue;
     if (st->phase32)
-      bk3_chunk<float, float, RR>(S, st, ch);
+      bf_chunk<float, float, RR>(S, st, ch, f, a.active_systems);
     else if (st->switch_pending)
-      bk3_chunk<double, float, RR>(S, st, ch);
+      bf_chunk<double, float, RR>(S, st, ch, f, a.active_systems);
     else
-      bk3_chunk<double, double, RR>(S, st, ch);
-  }
-}
-
-// k3_enable is consumed by bk3 and cleared for finished systems before the next bk1.
-__global__ void bk_clear(BatchArgs a) {
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < a.nsys; s += gridDim.x * blockDim.x) {
-    BatchState* st = a.sys[s].st;
-    if (st->done) st->k3_enable = 0;
+      bf_chunk<double, double, RR>(S, st, ch, f, a.active_systems);
   }
 }
 
 template <int RR>
 __global__ __launch_bounds__(kBlock) void binit(BatchArgs a) {
   for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-    const int4 ch = a.chunks[c];
-    binit_chunk<RR>(a.sys[ch.x], a.sys[ch.x].st, ch);
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    binit_chunk<RR>(S, S.st, ch);
   }
 }
 
 template <int L, int RR>
 __global__ __launch_bounds__(kBlock) void bru1(BatchArgs a) {
   for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-    const int4 ch = a.chunks[c];
-    const BatchSys& S = a.sys[ch.x];
-    if (S.st->done || !S.st->phase32) continue;
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    if (S.st->done || !S.st->phase32 || S.kind != MSC_A_MHM) continue;
     bru1_chunk<L, RR>(S, S.st, ch);
   }
 }
@@ -726,65 +940,81 @@ __global__ __launch_bounds__(kBlock) void bru1(BatchArgs a) {
 template <int L, int RR>
 __global__ __launch_bounds__(kBlock) void bru2(BatchArgs a) {
   for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-    const int4 ch = a.chunks[c];
-    const BatchSys& S = a.sys[ch.x];
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
     if (S.st->done || !S.st->phase32) continue;
     bru2_chunk<L, RR>(S, S.st, ch);
   }
 }
 
-template <int RP>
-hipError_t iteration_rr(const BatchArgs& a, hipStream_t s) {
-  switch (a.lanes) {
-    case 4: bk1<4, RP><<<a.grid, kBlock, 0, s>>>(a); bk2<4, RP><<<a.grid, kBlock, 0, s>>>(a); break;
-    case 8: bk1<8, RP><<<a.grid, kBlock, 0, s>>>(a); bk2<8, RP><<<a.grid, kBlock, 0, s>>>(a); break;
-    case 16: bk1<16, RP><<<a.grid, kBlock, 0, s>>>(a); bk2<16, RP><<<a.grid, kBlock, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
+// sig and out: kMaxShifts per (system, rhs), in the caller's order; slot of (s, q) = first[s] + q.
+template <int L>
+__global__ __launch_bounds__(kBlock) void bv1(BatchArgs a, int q, int k0) {
+  for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    if (q >= S.st->nrhs || k0 >= S.st->ns || S.kind != MSC_A_MHM) continue;
+    bv1_chunk<L>(S, S.st, ch, q, k0);
   }
-  bk3<RP><<<a.grid, kBlock, 0, s>>>(a);
-  bk_clear<<<1, kBlock, 0, s>>>(a);
-  return hipGetLastError();
 }
 
-template <int RP>
-hipError_t reliable_rr(const BatchArgs& a, hipStream_t s) {
-  switch (a.lanes) {
-    case 4: bru1<4, RP><<<a.grid, kBlock, 0, s>>>(a); bru2<4, RP><<<a.grid, kBlock, 0, s>>>(a); break;
-    case 8: bru1<8, RP><<<a.grid, kBlock, 0, s>>>(a); bru2<8, RP><<<a.grid, kBlock, 0, s>>>(a); break;
-    case 16: bru1<16, RP><<<a.grid, kBlock, 0, s>>>(a); bru2<16, RP><<<a.grid, kBlock, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
+template <int L>
+__global__ __launch_bounds__(kBlock) void bv2(BatchArgs a, int q, int k0) {
+  for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    if (q >= S.st->nrhs || k0 >= S.st->ns) continue;
+    bv2_chunk<L>(S, S.st, ch, q, k0, S.sig, S.res2 + int64_t(q) * kMaxShifts);
   }
-  return hipGetLastError();
 }
+
+#define MSC_BATCH_LANES(CALL)                       \
+  switch (a.lanes) {                                \
+    case 4: { constexpr int LL = 4; CALL; } break;  \
+    case 8: { constexpr int LL = 8; CALL; } break;  \
+    case 16: { constexpr int LL = 16; CALL; } break; \
+    default: return hipErrorInvalidValue;           \
+  }
+#define MSC_BATCH_RHS(CALL)                         \
+  switch (a.rr) {                                   \
+    case 1: { constexpr int RP = 1; CALL; } break;  \
+    case 2: { constexpr int RP = 2; CALL; } break;  \
+    case 4: { constexpr int RP = 4; CALL; } break;  \
+    default: return hipErrorInvalidValue;           \
+  }
 
 }  // namespace
 
 hipError_t launch_batch_init(const BatchArgs& a, hipStream_t s) {
-  switch (a.rr) {
-    case 1: binit<1><<<a.grid, kBlock, 0, s>>>(a); break;
-    case 2: binit<2><<<a.grid, kBlock, 0, s>>>(a); break;
-    case 4: binit<4><<<a.grid, kBlock, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
-  }
+  MSC_BATCH_RHS((binit<RP><<<a.grid, kBlock, 0, s>>>(a)));
   return hipGetLastError();
 }
 
-hipError_t launch_batch_iteration(const BatchArgs& a, hipStream_t s) {
-  switch (a.rr) {
-    case 1: return iteration_rr<1>(a, s);
-    case 2: return iteration_rr<2>(a, s);
-    case 4: return iteration_rr<4>(a, s);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_batch_iteration(const BatchArgs& a, bool flush, hipStream_t s) {
+  if (a.phases & 1) MSC_BATCH_RHS(MSC_BATCH_LANES((bk1<double, LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
+  if (a.phases & 2) MSC_BATCH_RHS(MSC_BATCH_LANES((bk1<float, LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
+  MSC_BATCH_RHS((bs1<RP><<<a.nsys, kBlock, 0, s>>>(a)));
+  if (a.phases & 1) MSC_BATCH_RHS(MSC_BATCH_LANES((bk2<double, LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
+  if (a.phases & 2) MSC_BATCH_RHS(MSC_BATCH_LANES((bk2<float, LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
+  MSC_BATCH_RHS((bs2<RP><<<a.nsys, kBlock, 0, s>>>(a)));
+  if (flush) MSC_BATCH_RHS((bf<RP><<<a.grid, kBlock, 0, s>>>(a)));
+  return hipGetLastError();
 }
 
 hipError_t launch_batch_reliable(const BatchArgs& a, hipStream_t s) {
-  switch (a.rr) {
-    case 1: return reliable_rr<1>(a, s);
-    case 2: return reliable_rr<2>(a, s);
-    case 4: return reliable_rr<4>(a, s);
-    default: return hipErrorInvalidValue;
+  MSC_BATCH_RHS(MSC_BATCH_LANES((bru1<LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
+  MSC_BATCH_RHS(MSC_BATCH_LANES((bru2<LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_verify(const BatchArgs& a, int nrhs, int ns, hipStream_t s) {
+  for (int q = 0; q < nrhs; ++q) {
+    for (int k0 = 0; k0 < ns; k0 += kBvShifts) {
+      MSC_BATCH_LANES((bv1<LL><<<a.grid, kBlock, 0, s>>>(a, q, k0)));
+      MSC_BATCH_LANES((bv2<LL><<<a.grid, kBlock, 0, s>>>(a, q, k0)));
+    }
   }
+  return hipGetLastError();
 }
 
 }  // namespace msc

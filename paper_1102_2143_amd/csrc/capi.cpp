@@ -376,13 +376,11 @@ double flush_bytes(int prec, double n, double shifts, double kept) {
   return n * (shifts * (32.0 + 2.0 * w) + kept * w);
 }
 
-// Bytes of `iters` iterations of one right-hand side of a batched solve: p gather and t write,
-// t gather, p and r in and out, then r and p in and out again (the direction's own kernel),
-// act_sum updates of a shift's vectors, x0 bytes a row for x_0, kept residuals.
-double batch_bytes(int prec, double n, const MatBytes& mb, double act_sum, double iters, double kept,
-                   double x0) {
+// Bytes of `iters` iterations of one right-hand side of a batched solve (the vectors of
+// iteration_bytes' two halves), act_sum updates of a shift's vectors, kept residuals.
+double batch_bytes(int prec, double n, const MatBytes& mb, double act_sum, double iters, double kept) {
   const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
-  return iters * (mb.m + mb.mh + 9.0 * w * n) + x0 * n + act_sum * n * (32.0 + 2 * w) + kept * n * w;
+  return iters * (mb.m + mb.mh + 7.0 * w * n) + flush_bytes(prec, n, act_sum, kept);
 }
 
 // Events for sampled per-kernel timing; destroyed with the pool.
@@ -1027,18 +1025,23 @@ struct BatchRun {
   BatchState* d_st = nullptr;
   unsigned* d_tickets = nullptr;
   int* d_active = nullptr;
+  int active0[2] = {0, 0};
+  double *d_sig = nullptr, *d_res2 = nullptr;
+  std::vector<double> hsig;
   int* h_poll = nullptr;
   hipStream_t sint = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   hipEvent_t ev_sync = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
+  hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};  // by the phases it steps
+  hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
   int replays = 0, n_reliable_launches = 0;
 
   ~BatchRun() {
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
     if (sint) (void)hipStreamSynchronize(sint);
+    for (auto e : gexec)
+      if (e) (void)hipGraphExecDestroy(e);
+    for (auto g : graph)
+      if (g) (void)hipGraphDestroy(g);
     for (auto e : ev)
       if (e) (void)hipEventDestroy(e);
     if (ev_sync) (void)hipEventDestroy(ev_sync);
@@ -1059,17 +1062,38 @@ struct BatchRun {
     auto align = [](size_t v) { return (v + 255) / 256 * 256; };
     size_t bytes = 0;
     std::vector<size_t> off(nsys);
+    const bool mixed = prm.prec == MSC_PREC_MIXED;
+    const bool use_links = prm.format == MSC_FORMAT_AUTO;
+    const size_t ring = size_t(std::min(int(prm.update_steps), kMaxSteps)) + 1;
+    // a links' chunk is one task of 64 sites and one right-hand side per wave
+    auto chunk_rows = [&](int s) {
+      return use_links && ops[s]->stencil ? 3 * kBlock / rr : kBatchChunkRows;
+    };
+    int total_rhs = 0;
     for (int s = 0; s < nsys; ++s) {
-      const size_t n = size_t(ops[s]->n), nk = std::max<size_t>(ops[s]->sigma.size() - 1, 1);
-      const size_t nch = (n + kBatchChunkRows - 1) / kBatchChunkRows;
+      const size_t n = size_t(ops[s]->n), nk = ops[s]->sigma.size(), rows = size_t(chunk_rows(s));
+      const size_t nch = (n + rows - 1) / rows;
+      total_rhs += nrhs[s];
       off[s] = bytes;
-      bytes += (5 + kBatchMaxSteps - 1) * align(sizeof(double2) * n * rr) +
+      bytes += align(sizeof(double2) * n * rr * ring) + 2 * align(sizeof(double2) * n * rr) +
                align(sizeof(double2) * n * rr * nk) +
-               3 * align(sizeof(float2) * n * rr) + align(sizeof(float2) * n * rr * nk) +
-               align(sizeof(double) * nch * kBatchMaxRhs);
-      for (size_t c = 0; c < nch; ++c) {
-        const int64_t r0 = int64_t(c) * kBatchChunkRows;
-        const int64_t r1 = std::min<int64_t>(r0 + kBatchChunkRows, int64_t(n));
+               (mixed ? align(sizeof(float2) * n * rr * nk) : 0) +
+               align(sizeof(double) * nch * kBatchPartial);
+      // Workgroups take the list's entries in turn and lie on the XCDs in turn: each XCD gets
+      // one contiguous part of every system, whose neighbouring rows its L2 then holds, and
+      // an equal share of what is left when systems have finished.
+      const size_t per = (nch + kXcds - 1) / kXcds;
+      std::array<size_t, kXcds> next, end;
+      for (int x = 0; x < kXcds; ++x) {
+        next[x] = std::min(nch, x * per);
+        end[x] = std::min(nch, (x + 1) * per);
+      }
+      for (size_t k = 0; k < nch; ++k) {
+        size_t x = chunks.size() % kXcds;
+        while (next[x] == end[x]) x = (x + 1) % kXcds;
+        const size_t c = next[x]++;
+        const int64_t r0 = int64_t(c) * int64_t(rows);
+        const int64_t r1 = std::min<int64_t>(r0 + int64_t(rows), int64_t(n));
         chunks.push_back(int4{s, int(r0), int(r1), int(c)});
       }
     }
@@ -1084,6 +1108,10 @@ struct BatchRun {
     bytes += align(sizeof(unsigned) * 4 * kTicketSite * nsys);
     const size_t off_act = bytes;
     bytes += 256;
+    const size_t off_sig = bytes;
+    bytes += align(sizeof(double) * kBatchMaxShifts * nsys);
+    const size_t off_res = bytes;
+    bytes += align(sizeof(double) * kMaxShifts * total_rhs);
     HIP_TRY(hipMalloc(&pool, bytes));
     char* base = static_cast<char*>(pool);
     d_sys = reinterpret_cast<BatchSys*>(base + off_sys);
@@ -1091,12 +1119,16 @@ struct BatchRun {
     d_st = reinterpret_cast<BatchState*>(base + off_st);
     d_tickets = reinterpret_cast<unsigned*>(base + off_tk);
     d_active = reinterpret_cast<int*>(base + off_act);
+    d_sig = reinterpret_cast<double*>(base + off_sig);
+    d_res2 = reinterpret_cast<double*>(base + off_res);
+    hsig.assign(size_t(nsys) * kBatchMaxShifts, 0.0);
+    int first = 0;
     sys.resize(nsys);
     hst.assign(nsys, BatchState{});
     const double sw = prm.prec == MSC_PREC_MIXED ? std::max(prm.switch_tol, prm.tol) : 0.0;
     for (int s = 0; s < nsys; ++s) {
       const msc_op op = ops[s];
-      const size_t n = size_t(op->n), nk = std::max<size_t>(op->sigma.size() - 1, 1);
+      const size_t n = size_t(op->n), nk = op->sigma.size(), rows = size_t(chunk_rows(s));
       char* p = base + off[s];
       auto take = [&](size_t b) {
         char* q = p;
@@ -1106,7 +1138,7 @@ struct BatchRun {
       BatchSys& S = sys[s];
       S.kind = op->kind;
       S.n = op->n;
-      S.nchunks = int((n + kBatchChunkRows - 1) / kBatchChunkRows);
+      S.nchunks = int((n + rows - 1) / rows);
       S.m64 = Csr<double2>{op->rowptr, op->col, op->val64};
       S.m32 = Csr<float2>{op->rowptr, op->col, op->val32};
       if (op->kind == MSC_A_MHM) {
@@ -1125,20 +1157,39 @@ struct BatchRun {
           S.sh32 = sell_view(sh, sh.val32, sh.diag32, narrow);
         }
       }
+      if (use_links && op->stencil) {
+        S.links = op->two_rows ? 2 : 3;
+        S.w64 = op->two_rows ? op->wc64 : op->w64;
+        S.w32 = op->two_rows ? op->wc32 : op->w32;
+        const ApplyArgs pa = apply_args(op, MSC_PREC_FP64, lanes);
+        S.vlinks = pa.links;
+        S.v64 = pa.w64;
+      }
       S.b = reinterpret_cast<const double2*>(d_b[s]);
       S.x = reinterpret_cast<double2*>(d_x[s]);
-      S.r64 = reinterpret_cast<double2*>(take(sizeof(double2) * n * rr));
-      S.p64 = reinterpret_cast<double2*>(take(sizeof(double2) * n * rr));
-      S.t64 = reinterpret_cast<double2*>(take(sizeof(double2) * n * rr));
-      S.u64 = reinterpret_cast<double2*>(take(sizeof(double2) * n * rr));
-      for (auto& q : S.rkeep) q = take(sizeof(double2) * n * rr);
-      S.pkeep0 = take(sizeof(double2) * n * rr);
-      S.pk64 = reinterpret_cast<double2*>(take(sizeof(double2) * n * rr * nk));
-      S.r32 = reinterpret_cast<float2*>(take(sizeof(float2) * n * rr));
-      S.p32 = reinterpret_cast<float2*>(take(sizeof(float2) * n * rr));
-      S.t32 = reinterpret_cast<float2*>(take(sizeof(float2) * n * rr));
-      S.pk32 = reinterpret_cast<float2*>(take(sizeof(float2) * n * rr * nk));
-      S.partial = reinterpret_cast<double*>(take(sizeof(double) * S.nchunks * kBatchMaxRhs));
+      const size_t len = n * rr;
+      S.ring = int(ring);
+      S.ring64 = reinterpret_cast<double2*>(take(sizeof(double2) * len * ring));
+      S.u64 = reinterpret_cast<double2*>(take(sizeof(double2) * len));
+      S.s64v = reinterpret_cast<double2*>(take(sizeof(double2) * len));
+      S.pk64 = reinterpret_cast<double2*>(take(sizeof(double2) * len * nk));
+      if (mixed) {
+        // The switch reads r, s and p_k and writes r (slot 0), s and p_k of the complex64
+        // phase: r and s where u lay, which no kernel reads then.  Afterwards the ring of
+        // the FP64 phase is free for the other slots, for u and for the updates' products
+        // (8 (ring - 1) + 8 + 16 <= 16 ring bytes, ring >= 2).
+        S.slot32 = reinterpret_cast<float2*>(S.u64);
+        S.s32v = S.slot32 + len;
+        S.ru64 = S.ring64;
+        S.u32 = reinterpret_cast<float2*>(S.ring64 + len);
+        S.ring32 = S.u32 + len;
+        S.pk32 = reinterpret_cast<float2*>(take(sizeof(float2) * len * nk));
+      }
+      S.partial = reinterpret_cast<double*>(take(sizeof(double) * S.nchunks * kBatchPartial));
+      S.sig = d_sig + size_t(s) * kBatchMaxShifts;
+      S.res2 = d_res2 + size_t(first) * kMaxShifts;
+      first += nrhs[s];
+      std::copy(op->sigma.begin(), op->sigma.end(), hsig.begin() + ptrdiff_t(s) * kBatchMaxShifts);
       S.tickets = d_tickets + 4 * kTicketSite * s;
       S.st = d_st + s;
       // scalar state: shifts sorted ascending, the smallest drives
@@ -1153,6 +1204,7 @@ struct BatchRun {
       h.nrhs = nrhs[s];
       h.max_iter = prm.max_iter;
       h.iters_fp64 = -1;
+      h.fresh = 1;
       for (int k = 0; k < ns; ++k) {
         h.s[k] = op->sigma[order[k]] - h.sigma0;
         h.orig[k] = order[k];
@@ -1161,8 +1213,7 @@ struct BatchRun {
         const double ts = prm.prec == MSC_PREC_MIXED ? prm.tol * prm.mixed_margin : prm.tol;
         h.eps2[q] = ts * ts;
         h.sw_eps2[q] = sw * sw;
-        h.a_prev[q] = 1.0;
-        h.b[q] = 0.0;
+        h.a1[q] = h.g1[q] = h.P1[q] = 1.0;
         h.R[q] = 1.0;
         for (int k = 0; k < kBatchMaxShifts; ++k) {
           const int lk = q * kBatchMaxShifts + k;
@@ -1180,7 +1231,7 @@ struct BatchRun {
     return MSC_OK;
   }
 
-  BatchArgs args() const {
+  BatchArgs args(int phases = 1) const {
     BatchArgs a{};
     a.sys = d_sys;
     a.chunks = d_chunks;
@@ -1190,16 +1241,20 @@ struct BatchRun {
     a.lanes = lanes;
     a.rr = rr;
     a.active_systems = d_active;
+    a.phases = phases;
     return a;
   }
 
-  // upload the descriptors and the initial state, then r = p = p_k = b, x = 0
+  // upload the descriptors and the initial state, then r = b, s = 0
   msc_status reset(hipStream_t s) {
+    active0[0] = nsys;
+    active0[1] = 0;
     HIP_TRY(hipMemcpyAsync(d_sys, sys.data(), sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d_chunks, chunks.data(), sizeof(int4) * nchunks, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d_st, hst.data(), sizeof(BatchState) * nsys, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemsetAsync(d_tickets, 0, sizeof(unsigned) * 4 * kTicketSite * nsys, s));
-    HIP_TRY(hipMemcpyAsync(d_active, &nsys, sizeof(int), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(d_active, active0, sizeof active0, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(d_sig, hsig.data(), sizeof(double) * hsig.size(), hipMemcpyHostToDevice, s));
     HIP_TRY(launch_batch_init(args(), s));
     return MSC_OK;
   }
@@ -1273,9 +1328,10 @@ struct BatchRun {
       apply(c);
       msc_status rc = reset(sint);
       if (rc != MSC_OK) return rc;
-      HIP_TRY(launch_batch_iteration(args(), sint));  // warm-up
+      HIP_TRY(launch_batch_iteration(args(), true, sint));  // warm-up
       HIP_TRY(hipEventRecord(e0, sint));
-      for (int i = 0; i < 4; ++i) HIP_TRY(launch_batch_iteration(args(), sint));
+      for (int i = 1; i <= 4; ++i)
+        HIP_TRY(launch_batch_iteration(args(), i == 4 || i % prm.update_steps == 0, sint));
       HIP_TRY(hipEventRecord(e1, sint));
       HIP_TRY(hipEventSynchronize(e1));
       float ms = 0.f;
@@ -1293,6 +1349,24 @@ struct BatchRun {
     return MSC_OK;
   }
 
+  msc_status capture(const msc_params& prm, int G, int phases) {
+    const int steps = std::min(int(prm.update_steps), kMaxSteps);
+    HIP_TRY(hipStreamBeginCapture(sint, hipStreamCaptureModeThreadLocal));
+    hipError_t e = hipSuccess;
+    // the shifts' steps are applied every update_steps iterations, and by the graph's last
+    // (a reliable update or the end of the solve may follow it)
+    for (int g = 0; g < G && e == hipSuccess; ++g)
+      e = launch_batch_iteration(args(phases), (g + 1) % steps == 0 || g == G - 1, sint);
+    const hipError_t end = hipStreamEndCapture(sint, &graph[phases]);
+    if (e == hipSuccess) e = end;
+    if (e != hipSuccess) {
+      set_error("batched iteration capture failed: %s", hipGetErrorString(e));
+      return MSC_EHIP;
+    }
+    HIP_TRY(hipGraphInstantiate(&gexec[phases], graph[phases], nullptr, nullptr, 0));
+    return MSC_OK;
+  }
+
   msc_status solve(const msc_params& prm, hipStream_t user) {
     grid = std::max(8, std::min(nchunks, kMaxGrid));
     if (prm.max_grid > 0) grid = std::max(8, std::min(grid, prm.max_grid));
@@ -1303,46 +1377,35 @@ struct BatchRun {
     if (rc != MSC_OK) return rc;
     rc = reset(sint);
     if (rc != MSC_OK) return rc;
-    // G iterations captured once, replayed until every system has finished
+    // G iterations captured once for the phases they step, replayed until every system has
+    // finished.  A replay steps the phases that the last poll saw, one replay back: a system
+    // that switched since then waits for the next.
     const int G = std::max(1, prm.poll_every);
-    HIP_TRY(hipStreamBeginCapture(sint, hipStreamCaptureModeThreadLocal));
-    for (int g = 0; g < G; ++g) {
-      // BK3 may defer its shifted update except in the graph's last iteration (a reliable
-      // update or the end of the solve may follow it)
-      BatchArgs ga = args();
-      const int steps = std::min(prm.update_steps, kBatchMaxSteps);
-      ga.defer_ok = (steps > 1 && g < G - 1) ? 1 : 0;
-      ga.steps = steps;
-      hipError_t e = launch_batch_iteration(ga, sint);
-      if (e != hipSuccess) {
-        hipGraph_t tmp = nullptr;
-        (void)hipStreamEndCapture(sint, &tmp);
-        if (tmp) (void)hipGraphDestroy(tmp);
-        set_error("batched iteration capture failed: %s", hipGetErrorString(e));
-        return MSC_EHIP;
-      }
-    }
-    HIP_TRY(hipStreamEndCapture(sint, &graph));
-    HIP_TRY(hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0));
     const int ru_every = (prm.prec == MSC_PREC_MIXED && prm.reliable_every > 0)
                              ? std::max(1, prm.reliable_every / G) : 0;
-    const int max_replays = (prm.max_iter + G - 1) / G + 4;
-    int chunk = 0;
+    const int max_replays = (prm.max_iter + G - 1) / G + 6;
+    int chunk = 0, phases = 1;
     bool done = false;
     while (!done) {
-      HIP_TRY(hipGraphLaunch(gexec, sint));
+      if (!gexec[phases]) {
+        rc = capture(prm, G, phases);
+        if (rc != MSC_OK) return rc;
+      }
+      HIP_TRY(hipGraphLaunch(gexec[phases], sint));
       ++replays;
       if (ru_every > 0 && replays % ru_every == 0) {
         HIP_TRY(launch_batch_reliable(args(), sint));
         ++n_reliable_launches;
       }
       const int slot = chunk & 1;
-      HIP_TRY(hipMemcpyAsync(&h_poll[slot], d_active, sizeof(int), hipMemcpyDeviceToHost, sint));
+      HIP_TRY(hipMemcpyAsync(&h_poll[2 * slot], d_active, 2 * sizeof(int), hipMemcpyDeviceToHost, sint));
       HIP_TRY(hipEventRecord(ev[slot], sint));
       ++chunk;
       if (chunk >= 2) {
         HIP_TRY(hipEventSynchronize(ev[slot ^ 1]));
-        if (h_poll[slot ^ 1] <= 0) done = true;
+        const int* seen = &h_poll[2 * (slot ^ 1)];
+        phases = (seen[0] > 0 ? 1 : 0) | (seen[1] > 0 ? 2 : 0);
+        if (phases == 0) done = true;
       }
       if (replays >= max_replays) done = true;
     }
@@ -1354,36 +1417,20 @@ struct BatchRun {
   msc_status finish(const msc_params& prm, msc_info* info, hipStream_t user,
                     std::chrono::steady_clock::time_point t0) {
     msc_status result = MSC_OK;
-    // every (system, rhs) verification is queued first, each writing its own slot, and
-    // read back with one copy
-    int total = 0;
-    for (int s = 0; s < nsys; ++s) total += nrhs[s];
-    double* d_res2 = nullptr;
+    // every system's residuals in launches of eight shifts of one right-hand side each
+    int total = 0, max_rhs = 0, max_ns = 0;
+    for (int s = 0; s < nsys; ++s) {
+      total += nrhs[s];
+      max_rhs = std::max(max_rhs, int(nrhs[s]));
+      max_ns = std::max(max_ns, int(ops[s]->sigma.size()));
+    }
     std::vector<double> r2all(size_t(total) * kMaxShifts, 0.0);
-    struct Res2Guard {
-      double*& p;
-      ~Res2Guard() { dfree(p); }
-    } res2_guard{d_res2};
     if (prm.verify) {
-      HIP_TRY(dalloc(&d_res2, size_t(total) * kMaxShifts));
-      int t = 0;
       for (int s = 0; s < nsys; ++s) {
-        const msc_op op = ops[s];
-        const int ns = int(op->sigma.size());
-        const int64_t n = op->n;
-        msc_status rc = ensure_scratch(op, sint);
+        msc_status rc = ensure_scratch(ops[s], sint);
         if (rc != MSC_OK) return rc;
-        rc = ensure_workspace(op, MSC_PREC_FP64, ns);
-        if (rc != MSC_OK) return rc;
-        for (int q = 0; q < nrhs[s]; ++q, ++t) {
-          if (hst[s].status[q] != 0) continue;
-          MsArgs a = make_args(op, choose_lanes(op, prm), d_b[s] + 2 * int64_t(q) * n,
-                               d_x[s] + 2 * int64_t(q) * ns * n);
-          a.sc.res2 = d_res2 + size_t(t) * kMaxShifts;
-          for (int k0 = 0; k0 < ns; k0 += 8)
-            HIP_TRY(launch_verify(a, op->sigma.data(), k0, std::min(8, ns - k0), op->ws.u64, sint));
-        }
       }
+      HIP_TRY(launch_batch_verify(args(), max_rhs, max_ns, sint));
       HIP_TRY(hipMemcpyAsync(r2all.data(), d_res2, sizeof(double) * r2all.size(),
                              hipMemcpyDeviceToHost, sint));
       HIP_TRY(hipStreamSynchronize(sint));
@@ -1458,26 +1505,20 @@ struct BatchRun {
             }
           clear_timing(I);
           // algorithmic bytes: this system's share, matrix read once for all its rhs; the
-          // shift-vector updates and kept-r passes as counted by BK2 per phase
+          // shift-vector updates and residuals read by them as counted per phase
           const int it = h.iter[q], i64 = std::min(I.iters_fp64, it);
-          const double act64 = h.n_upd[q][0], act32 = h.n_upd[q][1];
-          const double kept64 = h.n_kept[q][0], kept32 = h.n_kept[q][1];
-          // x_0 read and written by the BK3s that applied, p kept and read back once per
-          // cycle of deferred steps
-          const double x064 = 32.0 * h.n_x0[q][0] + 2.0 * 16.0 * h.n_k0[q][0];
-          const double x032 = 32.0 * h.n_x0[q][1] + 2.0 * 8.0 * h.n_k0[q][1];
           const double nn = double(n), nz = double(op->nnz), nzh = double(op->nnz_h);
           const double ib = index_bytes(sys[s].sell, sys[s].s64);
           const double ibh = index_bytes(sys[s].sell, sys[s].sh64);
-          I.alg_bytes = batch_bytes(MSC_PREC_FP64, nn,
-                                   mat_bytes(op->kind, MSC_PREC_FP64, nn, nz, nzh, ib, ibh, false),
-                                   act64, i64, kept64, x064) +
-                        batch_bytes(MSC_PREC_MIXED, nn,
-                                   mat_bytes(op->kind, MSC_PREC_MIXED, nn, nz, nzh, ib, ibh, false),
-                                   act32, it - i64, kept32, x032) -
-                        (double(nrhs[s]) - 1.0) / double(nrhs[s]) *
-                            ((nz * (16.0 + ib) + nzh * (16.0 + ibh)) * i64 +
-                             (nz * (8.0 + ib) + nzh * (8.0 + ibh)) * (it - i64));
+          double bytes = 0.0;
+          for (int ph = 0; ph < 2; ++ph) {
+            const int prec = ph ? MSC_PREC_MIXED : MSC_PREC_FP64;
+            MatBytes mb = mat_bytes(op->kind, prec, nn, nz, nzh, ib, ibh, sys[s].links);
+            mb.m /= double(nrhs[s]);
+            mb.mh /= double(nrhs[s]);
+            bytes += batch_bytes(prec, nn, mb, h.n_upd[q][ph], ph ? it - i64 : i64, h.n_kept[q][ph]);
+          }
+          I.alg_bytes = bytes;
           I.seconds = 0.0;
         }
       }

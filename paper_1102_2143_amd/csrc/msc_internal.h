@@ -30,11 +30,8 @@ constexpr double kRuDelta2 = 1e-2;
 // Head launches whose update mode is recorded for the byte model of sampled timings.
 constexpr int kMaxSamples = 256;
 
-// Steps of the all-shift update one pass over x_j and p_j may fold together: up to 8 in
-// the single solve, up to 4 in the batched one (whose update kernel holds the kept
-// residuals of four right-hand sides).
+// Steps of the all-shift update one pass over x_j and p_j may fold together.
 constexpr int kMaxSteps = 8;
-constexpr int kBatchMaxSteps = 4;
 constexpr int kRing = kMaxSteps + 1;  // residuals kept: launch l's in slot l % kRing
 
 // Scalar state of one multishift solve, resident in device memory.  Shift index j runs over
@@ -570,60 +567,61 @@ struct ResArgs {
 constexpr int kBatchMaxRhs = 4;
 constexpr int kBatchMaxShifts = 16;
 constexpr int kBatchChunkRows = 256;
+constexpr int kBatchPartial = 4 * kBatchMaxRhs;  // partial sums of a chunk: one set per wave
 
 struct BatchState {
-  // per right-hand side q
-  double R[kBatchMaxRhs], a[kBatchMaxRhs], a_prev[kBatchMaxRhs], b[kBatchMaxRhs];
-  double b_new[kBatchMaxRhs], bnorm2[kBatchMaxRhs], eps2[kBatchMaxRhs], sw_eps2[kBatchMaxRhs];
-  int iter[kBatchMaxRhs], halt[kBatchMaxRhs], status[kBatchMaxRhs], x0_upd[kBatchMaxRhs];
-  // per (q, sorted shift k), index q * 16 + k
+  // per right-hand side q: |r_n|^2, the tolerances, and of the step before a, b, P and |r|^2
+  double R[kBatchMaxRhs], bnorm2[kBatchMaxRhs], eps2[kBatchMaxRhs], sw_eps2[kBatchMaxRhs];
+  double a[kBatchMaxRhs], b[kBatchMaxRhs];             // this step's
+  double a1[kBatchMaxRhs], P1[kBatchMaxRhs], g1[kBatchMaxRhs];
+  double ru_g[kBatchMaxRhs], ru_c[kBatchMaxRhs];       // a reliable update's old |r|^2, Re r^H s
+  int iter[kBatchMaxRhs], halt[kBatchMaxRhs], status[kBatchMaxRhs];
+  int step[kBatchMaxRhs];      // this iteration takes a step
+  int ru[kBatchMaxRhs];        // r was replaced since the last step
+  int m[kBatchMaxRhs];         // steps composed since x_k and p_k were last written
+  int last[kBatchMaxRhs];      // ring step of the newest of them
+  int n_upd[kBatchMaxRhs][2], n_kept[kBatchMaxRhs][2];  // per phase: updates, residuals read
+  // per (q, sorted shift k), index q * 16 + k (k = 0: the driving system, zeta = 1)
   double zeta[kBatchMaxRhs * kBatchMaxShifts], zeta_prev[kBatchMaxRhs * kBatchMaxShifts];
-  double zk[kBatchMaxRhs * kBatchMaxShifts], ak[kBatchMaxRhs * kBatchMaxShifts];
-  double bk[kBatchMaxRhs * kBatchMaxShifts];
+  double cx[kMaxSteps + 1][kBatchMaxRhs * kBatchMaxShifts];  // the composed steps (RotState)
+  double cp[kMaxSteps + 1][kBatchMaxRhs * kBatchMaxShifts];
   int active[kBatchMaxRhs * kBatchMaxShifts], freeze_iter[kBatchMaxRhs * kBatchMaxShifts];
-  int upd_p[kBatchMaxRhs * kBatchMaxShifts], upd_x[kBatchMaxRhs * kBatchMaxShifts];
-  // BK3's update of (q, k) (upd_x, upd_p): x += cx[0] p_k + sum_{i<m} cx[i+1] r_i and
-  // p_k <- cp[0] p_k + sum_{i<m} cp[i+1] r_i + cp[m+1] r, the r_i being the residuals
-  // kept by the m BK3s that deferred (one step: m = 0)
-  double cx[kBatchMaxSteps][kBatchMaxRhs * kBatchMaxShifts];
-  double cp[kBatchMaxSteps + 1][kBatchMaxRhs * kBatchMaxShifts];
-  // the deferred steps of (q, k) composed as in DeferState
-  double dcx[kBatchMaxSteps][kBatchMaxRhs * kBatchMaxShifts];
-  double dcp[kBatchMaxSteps][kBatchMaxRhs * kBatchMaxShifts];
-  int dact[kBatchMaxRhs * kBatchMaxShifts], dupd[kBatchMaxRhs * kBatchMaxShifts];
-  // per right-hand side: steps deferred so far, BK3's kept residuals to read (m) and the
-  // slot it keeps r in (-1: none; slot 0 also keeps p, the direction x_0's deferred steps
-  // start from), and per phase (FP64, complex64) the shift-vector updates, kept-r
-  // passes, BK3s that updated x_0 and BK3s that kept p
-  int ndef[kBatchMaxRhs], m[kBatchMaxRhs], keep[kBatchMaxRhs];
-  int n_upd[kBatchMaxRhs][2], n_kept[kBatchMaxRhs][2];
-  int n_x0[kBatchMaxRhs][2], n_k0[kBatchMaxRhs][2];
+  int took[kBatchMaxRhs * kBatchMaxShifts];
   // per system
   double s[kBatchMaxShifts];
   int orig[kBatchMaxShifts];
   double sigma0;
-  int ns, nrhs, phase32, switch_pending, done, k3_enable, max_iter, n_reliable, iters_fp64, pad_;
+  int ns, nrhs, phase32, switch_pending, done;
+  int fresh;                   // 1: x_k and p_k were never written
+  int slot;                    // steps since the phase began: r lies in ring slot slot % ring
+  int max_iter, n_reliable, iters_fp64;
 };
 
 struct BatchSys {
   int kind;
-  int nchunks;            // chunks of this system (its partial array has 4 slots each)
+  int nchunks;            // chunks of this system (kBatchPartial partial sums each)
   int64_t n;
   Csr<double2> m64, mh64;
   Csr<float2> m32, mh32;
   int sell;               // the SpMVs read the system's sliced ELLPACK copies below
   Sell<double2> s64, sh64;
   Sell<float2> s32, sh32;
+  int links;              // link rows read in place of a stored copy (2 or 3), or 0
+  int vlinks;             // the same for the FP64 products of updates and verification
+  Stencil<double2> w64, v64;
+  Stencil<float2> w32;
   const double2* b;       // nrhs * n (rhs-major)
   double2* x;             // nrhs * ns * n (rhs-major, shift-major, caller order)
-  double2 *r64, *p64, *t64, *pk64, *u64;   // rhs-interleaved n x RR; pk: (ns-1) blocks
-  float2 *r32, *p32, *t32, *pk32;
-  void* rkeep[kBatchMaxSteps - 1];  // n x RR each: residuals kept by deferring BK3s
-                               // (complex128, or complex64 in the second phase)
-  void* pkeep0;           // n x RR: p at the first deferred step (x_0's composition)
+  // n x RR each: rhs-interleaved, on links rhs by rhs and colour by colour within; pk:
+  // [shift][rhs][row].  The complex64 vectors but pk32 lie where the FP64 phase's lay.
+  int ring;               // residual slots
+  double2 *ring64, *u64, *s64v, *pk64, *ru64;
+  float2 *slot32, *ring32, *u32, *s32v, *pk32;   // slot32: slot 0, ring32: the others
   BatchState* st;
   double* partial;
-  unsigned* tickets;      // 8 counters
+  unsigned* tickets;      // 4 sites
+  const double* sig;      // shifts, caller's order
+  double* res2;           // kMaxShifts per right-hand side
 };
 
 struct BatchArgs {
@@ -634,14 +632,15 @@ struct BatchArgs {
   int grid;
   int lanes;
   int rr;                 // right-hand sides per system, padded (1, 2 or 4)
-  int* active_systems;
-  int defer_ok;           // 1: this iteration's BK3 may defer the shifted update
-  int steps;              // steps of the shifted update folded into one pass (1..kBatchMaxSteps)
+  int* active_systems;    // unfinished systems in FP64 [0] and in complex64 [1]
+  int phases;             // phases an iteration steps: 1 FP64, 2 complex64 (3: both)
 };
 
 hipError_t launch_batch_init(const BatchArgs& a, hipStream_t s);
-hipError_t launch_batch_iteration(const BatchArgs& a, hipStream_t s);
+hipError_t launch_batch_iteration(const BatchArgs& a, bool flush, hipStream_t s);
 hipError_t launch_batch_reliable(const BatchArgs& a, hipStream_t s);
+// |b - (A + sigma_k) x_k|^2 of every system, right-hand side and shift into res2
+hipError_t launch_batch_verify(const BatchArgs& a, int nrhs, int ns, hipStream_t s);
 
 // grad.hip
 // out[3q..3q+2] = Re<gref, g_q>, Im<gref, g_q>, |g_q|^2 for q < kc (<= 16); g shift-major.
