@@ -64,10 +64,39 @@ template <> __device__ __forceinline__ float2 from_d<float>(const double2 v) {
 }
 template <> __device__ __forceinline__ double2 from_d<double>(const double2 v) { return v; }
 
-// Sum over the L consecutive lanes of a row group (L a power of two <= 64).
+// v of another lane of the same 16 (DPP control CTRL; every lane of them active).
+template <int CTRL> __device__ __forceinline__ double lane_move(double v) {
+  const uint64_t b = uint64_t(__double_as_longlong(v));
+  const int lo = __builtin_amdgcn_mov_dpp(int(uint32_t(b)), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(int(uint32_t(b >> 32)), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)((uint64_t(uint32_t(hi)) << 32) | uint32_t(lo)));
+}
+template <int CTRL> __device__ __forceinline__ float lane_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppSwap1 = 0xB1;      // quad lanes 1 0 3 2
+constexpr int kDppSwap2 = 0x4E;      // quad lanes 2 3 0 1
+constexpr int kDppMirror8 = 0x141;   // lane i of 8 reads 7 - i
+constexpr int kDppMirror16 = 0x140;  // lane i of 16 reads 15 - i
+
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const uint64_t b = uint64_t(__double_as_longlong(v));
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), lane));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b >> 32)), lane));
+  return __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
+}
+
+// Sum over the L consecutive lanes of a row group (L a power of two <= 64; 64: a double, every
+// lane active).  Within 16 lanes the adds take their operand across lanes (DPP), where a
+// shuffle is a round trip through the LDS hardware: it is on the chain of every iteration.
 template <int L, class T> __device__ __forceinline__ T group_sum(T v) {
-#pragma unroll
-  for (int off = L / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, L);
+  if constexpr (L >= 2) v += lane_move<kDppSwap1>(v);
+  if constexpr (L >= 4) v += lane_move<kDppSwap2>(v);
+  if constexpr (L >= 8) v += lane_move<kDppMirror8>(v);
+  if constexpr (L >= 16) v += lane_move<kDppMirror16>(v);
+  if constexpr (L == 32) v += __shfl_xor(v, 16, 32);
+  if constexpr (L == 64)
+    v = (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
   return v;
 }
 
