@@ -506,7 +506,7 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
   std::vector<int> sample_launch;
   std::vector<char> sample_flush;  // the sampled iteration applied composed steps
   while (!done) {
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < G;) {
       hipEvent_t* ev = nullptr;
       cur->sample = -1;
       // consecutive launches are sampled in runs as long as a folding cycle (the iterations
@@ -537,11 +537,23 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
                                     since > 0 && since % kRuCheck == 0);
       cur->ru_force = ru_period ? 1 : 0;
       cur->ru_check = ru ? 1 : 0;
-      const bool flush = ++pending >= steps;
+      // a small lattice: the iterations up to the next application, poll or update in one launch
+      int span = 1;
+      if (cur->small && prm.timing <= 0) {
+        auto update = [&](int k) {
+          return phase == MSC_PREC_MIXED && prm.reliable_every > 0 &&
+                 (k % prm.reliable_every == 0 || k % kRuCheck == 0);
+        };
+        while (span < std::min(G - g, steps - pending) && !update(since + span)) ++span;
+        cur->span = span;
+      }
+      pending += span;
+      const bool flush = pending >= steps;
       HIP_TRY(launch_iteration(phase, *cur, s, ev, flush));
       if (flush) pending = 0;
       cur->flushed = flush ? 1 : 0;
-      ++launched;
+      launched += span;
+      g += span;
     }
     const int slot = chunk & 1;
     HIP_TRY(hipEventRecord(op->ws.ev[slot], s));

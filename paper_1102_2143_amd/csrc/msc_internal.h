@@ -327,6 +327,8 @@ struct MsArgs {
   SweepOrder ord;        // slice order of the head and K2 on the sliced path
   int march, m1, m2;     // links: t-slices per column of the march, and whether K1 / K2 march
   int split;             // links: a wave for each direction
+  int small;             // links: the lattice fits one workgroup, which can take
+  int span;              // this many iterations in one launch (0: the pair of kernels)
   Stencil<double2> w64;
   Stencil<float2> w32;
   int sample;            // slot of SolveState::smp_* for this iteration, -1: not sampled

@@ -326,43 +326,28 @@ __device__ __forceinline__ StepPlan step_plan(const StepIn& i, double g, double 
   return p;
 }
 
-// The work of K2's extra workgroup: the shifts' scalars of step n (wave 0, lane j: shift
-// j): freezing, then, when the step runs, zeta^(n+1), a_j and b_j, composed with the
-// pending steps; the state of iteration n + 1, or of the halted sequence.  On small
-// operators it is the longest chain of the iteration: all it reads is read before the sums.
-__device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in, const Early& e) {
-  SolveState* st = a.st;
-  const RotState& rs = st->rot[a.par];
-  RotState& nx = st->rot[a.par ^ 1];
-  const int j = threadIdx.x, n = in.n;
-  const bool mine = j < st->ns;
+// Shift j's scalars and its composed steps, in its lane.
+struct ShiftSteps {
   double z = 1.0, zp = 1.0, s = 0.0, cx[kMaxSteps + 1], cp[kMaxSteps + 1];
   int act = 0, took = 0;
-#pragma unroll
-  for (int i = 0; i <= kMaxSteps; ++i) cx[i] = cp[i] = 0.0;
-  if (mine) {
+
+  __device__ __forceinline__ void load(const RotState& rs, double sj, int j) {
     z = rs.zeta[j];
     zp = rs.zeta_prev[j];
     act = rs.active[j];
     took = rs.took[j];
-    s = st->s[j];
+    s = sj;
 #pragma unroll
     for (int i = 0; i <= kMaxSteps; ++i) {
       cx[i] = rs.cx[i][j];
       cp[i] = rs.cp[i][j];
     }
   }
-  const int m = rs.m, fresh = rs.fresh, freeze = st->freeze;
-  double g, d;
-  both_sums(a, e, g, d);
-  const StepPlan p = step_plan(in, g, d);
-  if (j >= kWave) return;
-  // a flush since the last step leaves nothing pending
-  const bool flushed = a.flushed || in.ru;
-  const int m0 = flushed ? 0 : m;
-  const bool live = p.stop == 0;
-  const double eps2 = in.tol2 * (n == 0 ? g : in.bn2);
-  if (mine) {
+  // Iteration n with m0 steps pending: freezing (true: j froze), then, when the step runs
+  // (live), zeta^(n+1), a_j and b_j, composed with the pending steps.
+  __device__ __forceinline__ bool step(int j, int n, int m0, bool live, bool freeze, double g,
+                                       double eps2, double a, double b, double a1) {
+    bool froze = false;
     double zn = z;
     if (m0 == 0) {
       took = 0;
@@ -374,13 +359,13 @@ __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in
       if (i > m0) cx[i] = cp[i] = 0.0;
     if (act && j > 0 && freeze && z * z * g <= eps2) {
       act = 0;
-      st->freeze_iter[j] = n;
+      froze = true;
     }
     if (live && act) {
       if (j > 0)
-        zn = n == 0 ? z / (1.0 + s * p.a)
-                    : z * zp * in.a1 / (p.a * p.b * (zp - z) + zp * in.a1 * (1.0 + s * p.a));
-      const double ratio = z / zp, aj = p.a * zn / z, bj = p.b * ratio * ratio;
+        zn = n == 0 ? z / (1.0 + s * a)
+                    : z * zp * a1 / (a * b * (zp - z) + zp * a1 * (1.0 + s * a));
+      const double ratio = z / zp, aj = a * zn / z, bj = b * ratio * ratio;
 #pragma unroll
       for (int i = 0; i <= kMaxSteps; ++i) {
         if (i <= m0) cp[i] *= bj;
@@ -388,9 +373,14 @@ __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in
         if (i <= m0 + 1) cx[i] = fma(aj, cp[i], cx[i]);
       }
       took = 1;
+      zp = z;
+      z = zn;
     }
-    nx.zeta_prev[j] = live && act ? z : zp;
-    nx.zeta[j] = zn;
+    return froze;
+  }
+  __device__ __forceinline__ void store(RotState& nx, int j) const {
+    nx.zeta_prev[j] = zp;
+    nx.zeta[j] = z;
     nx.active[j] = act;
     nx.took[j] = took;
 #pragma unroll
@@ -398,6 +388,45 @@ __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in
       nx.cx[i][j] = cx[i];
       nx.cp[i][j] = cp[i];
     }
+  }
+};
+
+__device__ __forceinline__ void sequence_halts(const MsArgs& a, int fin, int n, double g, double eps2,
+                                               int stop) {
+  SolveState* st = a.st;
+  st->fin = fin;
+  st->iter = n;
+  st->R = g;
+  st->eps2 = eps2;
+  st->status = stop == 3 ? 1 : 0;
+  store_host_flag(a.hflag, 1 | (stop == 2 ? 2 : 0));
+}
+
+// The work of K2's extra workgroup: the shifts' scalars of step n (wave 0, lane j: shift
+// j): freezing, then, when the step runs, zeta^(n+1), a_j and b_j, composed with the
+// pending steps; the state of iteration n + 1, or of the halted sequence.  On small
+// operators it is the longest chain of the iteration: all it reads is read before the sums.
+__device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in, const Early& e) {
+  SolveState* st = a.st;
+  const RotState& rs = st->rot[a.par];
+  RotState& nx = st->rot[a.par ^ 1];
+  const int j = threadIdx.x, n = in.n;
+  const bool mine = j < st->ns;
+  ShiftSteps h;
+  if (mine) h.load(rs, st->s[j], j);
+  const int m = rs.m, fresh = rs.fresh, freeze = st->freeze;
+  double g, d;
+  both_sums(a, e, g, d);
+  const StepPlan p = step_plan(in, g, d);
+  if (j >= kWave) return;
+  // a flush since the last step leaves nothing pending
+  const bool flushed = a.flushed || in.ru;
+  const int m0 = flushed ? 0 : m;
+  const bool live = p.stop == 0;
+  const double eps2 = in.tol2 * (n == 0 ? g : in.bn2);
+  if (mine) {
+    if (h.step(j, n, m0, live, freeze != 0, g, eps2, p.a, p.b, in.a1)) st->freeze_iter[j] = n;
+    h.store(nx, j);
   }
   if (j == 0) {
     if (n == 0) st->bnorm2 = g;
@@ -409,14 +438,7 @@ __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in
     nx.m = live ? m0 + 1 : m0;
     nx.fresh = flushed ? 0 : fresh;
     nx.halt = live ? 0 : 1;
-    if (!live) {
-      st->fin = a.par ^ 1;
-      st->iter = n;
-      st->R = g;
-      st->eps2 = eps2;
-      st->status = p.stop == 3 ? 1 : 0;
-      store_host_flag(a.hflag, 1 | (p.stop == 2 ? 2 : 0));
-    }
+    if (!live) sequence_halts(a, a.par ^ 1, n, g, eps2, p.stop);
   }
 }
 
@@ -985,6 +1007,183 @@ __global__ __launch_bounds__(kBlock) void k2_split(MsArgs a) {
     __syncthreads();
   }
   store_partial(region(a, a.par ^ 1), acc);
+}
+
+// ---- the smallest lattices: several iterations in one workgroup ---------------------------------
+// Four lanes a site, a direction each: a lane keeps its link and forms both products with
+// it; r and u lie in LDS, so an iteration's halves and sums are four barriers apart instead
+// of two kernels.  The shifts' scalars of all a.span steps follow at the end, a shift per
+// lane; the state goes on as from a.span launches of the pair.  For lattices whose sites one
+// workgroup holds (256): an iteration in FP64 and mixed at 4^4 11.2 and 11.8 us with the
+// pair, 6.7 and 7.3 here, of which 1.6 are the launches and the applications; two sites a
+// lane, 4^3 x 6, took 27.8 (the links do not fit the registers) for 11.5.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallSites = kSmallBlock / 4;
+
+// Sum over the workgroup, in every thread; a barrier.  Callers alternate between two `part`s.
+__device__ __forceinline__ double small_sum(double v, double* part) {
+  constexpr int W = kSmallBlock / kWave;
+  v = group_sum<kWave>(v);
+  if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = v;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < W; ++i) s += part[i];
+  return s;
+}
+
+template <class R, int LR>
+__global__ __launch_bounds__(kSmallBlock) void k_small(MsArgs a) {
+  constexpr int K = 3 * LR;
+  __shared__ cplx<R> rl[3][kSmallSites], ul[3][kSmallSites], back[3][kSmallBlock];
+  __shared__ double part[2][kSmallBlock / kWave], hist[kMaxSteps][3];
+  SolveState* st = a.st;
+  StepIn in = step_in(a);
+  const int pe = (a.launch + a.span) & 1;  // the state this launch leaves
+  const int tid = threadIdx.x;
+  if (in.halt) {
+    if (tid == 0) st->rot[pe].halt = 1;
+    return;
+  }
+  const Stencil<cplx<R>> w = pick_w<R>(a);
+  const uint32_t vol = uint32_t(w.vol);
+  const int mu = tid % 4;
+  const cplx<R>* __restrict__ wm = w.w + int64_t(mu) * K * vol;
+  cplx<R>* __restrict__ sg = static_cast<cplx<R>*>(a.s[0]);
+  const uint32_t site = min(uint32_t(tid) / 4, vol - 1);
+  const bool row = uint32_t(tid) / 4 < vol && mu < 3;  // this lane finishes the row of colour mu
+  const int64_t i0 = int64_t(mu) * vol + site;
+  uint32_t fwd = site, bwd = site;
+  R te = R(2);
+  {
+    uint32_t rem = site, par = 0;
+#pragma unroll
+    for (int nu = 0; nu < 4; ++nu) {
+      const uint32_t L = uint32_t(w.L[nu]), sd = uint32_t(w.stride[nu]);
+      const uint32_t q = rem / L, xm = rem - q * L;
+      rem = q;
+      if (nu == mu) {
+        te = (par & 1u) ? R(-2) : R(2);
+        fwd = xm == L - 1 ? site - (L - 1) * sd : site + sd;
+        bwd = xm == 0 ? site + (L - 1) * sd : site - sd;
+      }
+      par += xm;
+    }
+  }
+  cplx<R> U[9], rr = czero<R>(), ss = czero<R>();
+#pragma unroll
+  for (int k = 0; k < K; ++k) U[k] = wm[k * vol + site];
+  if (row) {
+    rr = rslot<R>(a, a.launch)[i0];
+    ss = sg[i0];
+    rl[mu][site] = rr;
+  }
+  if constexpr (LR == 2) third_row<R>(U, te);
+  // This lane's row of (m + sign D) v, v in LDS and own its value there.  A lane forms both
+  // products with its one link, U v(s + mu) for its site and U^H v(s) for the site ahead.
+  auto product = [&](const cplx<R>(&v)[3][kSmallSites], int sign, const cplx<R>& own) {
+    cplx<R> h[3], g[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) h[c] = g[c] = czero<R>();
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const cplx<R> f = v[j][fwd], o = v[j][site];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        cfma<R>(h[c], U[3 * c + j], f);
+        cfma_conj<R>(g[c], U[3 * j + c], o);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) back[c][tid] = g[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const cplx<R> b = back[c][4 * bwd + mu];
+      h[c].x = group_sum<4>(h[c].x - b.x);
+      h[c].y = group_sum<4>(h[c].y - b.y);
+    }
+    const cplx<R> q = mu == 0 ? h[0] : mu == 1 ? h[1] : h[2];
+    const R m = R(w.mass);
+    return cplx<R>{fma(m, own.x, sign > 0 ? q.x : -q.x), fma(m, own.y, sign > 0 ? q.y : -q.y)};
+  };
+  double v = 0.0;
+  for (int i = tid; i < a.gg; i += kSmallBlock) v += region(a, a.par)[i];
+  double g = small_sum(v, part[1]);  // and r is in LDS
+  const int n0 = in.n;
+  int done = 0, stop = 0;
+  double a1 = in.a1;
+  for (; done < a.span; ++done) {
+    double acc = 0.0;
+    const cplx<R> uu = product(rl, 1, rr);
+    if (row) {
+      ul[mu][site] = uu;
+      acc = norm2d<R>(uu);
+    }
+    const double d = small_sum(acc, part[0]);
+    const StepPlan p = step_plan(in, g, d);
+    if (in.n == 0) in.bn2 = g;
+    stop = p.stop;
+    if (stop) break;
+    cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + done + 1);
+    const cplx<R> q = product(ul, -1, uu);
+    acc = 0.0;
+    if (row) {
+      cplx<R> sn, nv;
+      row_step<R>(p, in.sigma0, q, rr, ss, sn, nv);
+      ss = sn;
+      rr = nv;
+      rl[mu][site] = nv;
+      rn[i0] = nv;
+      acc = norm2d<R>(nv);
+    }
+    if (tid == 0) {
+      hist[done][0] = g;
+      hist[done][1] = p.a;
+      hist[done][2] = p.b;
+    }
+    in.g1 = g;
+    in.a1 = p.a;
+    in.P1 = p.P;
+    in.n += 1;
+    g = small_sum(acc, part[1]);
+    in.ru = 0;
+  }
+  if (row) sg[i0] = ss;
+  for (int i = tid; i < a.gg; i += kSmallBlock) region(a, pe)[i] = i == 0 ? g : 0.0;
+  if (tid >= kWave) return;
+  const int j = tid;
+  const RotState& rs = st->rot[a.par];
+  RotState& nx = st->rot[pe];
+  const int m = rs.m, fresh = rs.fresh;
+  const bool flushed = a.flushed || a.ru_check && st->ru_flag;
+  const int m0 = flushed ? 0 : m;
+  const double eps2 = in.tol2 * in.bn2;
+  if (j < st->ns) {
+    ShiftSteps h;
+    h.load(rs, st->s[j], j);
+    for (int k = 0; k < done; ++k) {
+      const double ak = hist[k][1];
+      if (h.step(j, n0 + k, m0 + k, true, st->freeze != 0, hist[k][0], eps2, ak, hist[k][2], a1))
+        st->freeze_iter[j] = n0 + k;
+      a1 = ak;
+    }
+    if (stop && h.step(j, in.n, m0 + done, false, st->freeze != 0, g, eps2, 0.0, 0.0, a1))
+      st->freeze_iter[j] = in.n;
+    h.store(nx, j);
+  }
+  if (j == 0) {
+    if (n0 == 0) st->bnorm2 = in.bn2;
+    nx.g = in.g1;
+    nx.a = in.a1;
+    nx.P = in.P1;
+    nx.iter = in.n;
+    nx.launch = a.launch + done;
+    nx.m = m0 + done;
+    nx.fresh = flushed ? 0 : fresh;
+    nx.halt = stop ? 1 : 0;
+    if (stop) sequence_halts(a, pe, in.n, g, eps2, stop);
+  }
 }
 
 // ---- the composed steps of every shift: x_j and p_j -------------------------------------------
@@ -1793,11 +1992,12 @@ template <class R> int site_grid(const MsArgs& a, int half, int& march) {
 
 template <class R> void prepare_impl(MsArgs& a) {
   const bool mhm = a.kind == MSC_A_MHM;
-  a.m1 = a.m2 = a.split = 0;
+  a.m1 = a.m2 = a.split = a.small = 0;
   if (a.sell && mhm && a.stencil) {
     // a direction per wave while every block of 64 sites gets a workgroup of its own (up to
     // 65536 sites; k1_split has the times on both sides)
     a.split = (a.w64.vol + kSiteBlock - 1) / kSiteBlock <= a.grid ? 1 : 0;
+    a.small = a.split && a.w64.vol <= kSmallSites ? 1 : 0;
     if (a.split) {
       a.gd = a.gg = grid_rows(a.w64.vol, kSiteBlock, a.grid);
       return;
@@ -1869,6 +2069,10 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
 
 template <class R, int LR> void launch_sites(const MsArgs& a, hipStream_t s, hipEvent_t* ev) {
   constexpr bool STREAM = std::is_same<R, double>::value;
+  if (a.span > 0) {
+    k_small<R, LR><<<1, kSmallBlock, 0, s>>>(a);
+    return;
+  }
   if (a.split) {
     launch_timed(k1_split<R, LR>, a.gd, s, ev, 0, a);
     launch_timed(k2_split<R, LR>, a.gg + 1, s, ev, 1, a);
@@ -1915,7 +2119,7 @@ hipError_t iteration_impl(const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool f
     MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, false>, a.gd, s, ev, 0, a)));
     MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_csr<R, LL, false>, a.gg + 1, s, ev, 1, a)));
   }
-  if (flush) return flush_impl<R>(a, a.par ^ 1, 0, s, ev);
+  if (flush) return flush_impl<R>(a, (a.launch + std::max(1, a.span)) & 1, 0, s, ev);
   return hipGetLastError();
 }
 
