@@ -56,7 +56,8 @@ enum { kCsr = 0, kSell = 1, kLinks3 = 2, kLinks2 = 3 };  // what an operator hal
 // systems), and two waves per SIMD with little each beat fewer, longer ones; the sliced
 // rows need few registers, and a larger group reads the matrix less often.  Ten systems at
 // 16^4 in FP64, whole solve: links, groups of 1 / 2 / 3 / 5 / 8: 33.0 / 28.7 / 29.7 / 33.4 /
-// 45.2 ms, and 30.8 ms with 768 workgroups; sliced copy (a gradient), groups of 2 / 3 / 4 /
+// 45.2 ms, and 30.8 ms with 768 workgroups (vectors colour by colour: 28.9 / 28.3 / 28.2 ms
+// with 1 on 768, 2 and 3; in row order 29.0 with 2; own rows past the caches 30.4); sliced copy (a gradient), groups of 2 / 3 / 4 /
 // 5 / 8 on 512: 61.1 / 59.6 / 58.4 / 55.9 / 58.2 ms; 5 on 768 and 1024: 51.3 and 53.8 ms.
 template <int ST> constexpr int group_max() { return ST == kCsr || ST == kSell ? 5 : 2; }
 template <int ST> constexpr int half_grid() { return ST == kCsr || ST == kSell ? 768 : 512; }
@@ -257,7 +258,8 @@ __device__ __forceinline__ void sell_row_group(const Sell<cplx<R>>& m,
 }
 
 // One half of the operator for this workgroup's systems and rows: body(row, out) with the
-// products out[u] of every system u < cnt at `row`; lanes with nothing to do skip it.
+// products out[u] of every system u < cnt at `row` of the vectors (on the links colour by
+// colour); lanes with nothing to do skip it.
 template <class R, int G, int ST, int L, class F>
 __device__ __forceinline__ void half(const BssArgs& a, bool second, const Share& h,
                                      const cplx<R>* const (&xs)[G], F body) {
@@ -320,7 +322,7 @@ __device__ __forceinline__ void half(const BssArgs& a, bool second, const Share&
           cplx<R> oc[G];
 #pragma unroll
           for (int q = 0; q < G; ++q) oc[q] = o[q][c];
-          body(3 * int64_t(site) + c, oc);
+          body(int64_t(c) * vol + site, oc);
         }
       }
     }
@@ -511,7 +513,7 @@ __device__ __forceinline__ void res_row(const ResArgs& v, int64_t row, const dou
       rt.y = fv.y - acc[q].y - v.sig[q] * xv.y;
       nrm[q] += fma(rt.x, rt.x, rt.y * rt.y);
       if (r) {
-        const int64_t idx = int64_t(v.j0 + q) * v.n + row;
+        const int64_t idx = int64_t(v.j0 + q) * v.n + (v.vol ? (row % 3) * v.vol + row / 3 : row);
         const cplx<R> rc = from_d<R>(rt);
         r[idx] = rc;
         p[idx] = rc;
@@ -601,11 +603,12 @@ __global__ __launch_bounds__(kBlock) void k_res_second_s(ResArgs v) {
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_accum(BssArgs a, XPtrs xp) {
   const int m = a.st->m;
+  const int64_t vol = a.links ? a.n / 3 : 0;  // colour by colour on the links
   for (int j = 0; j < m; ++j) {
     const cplx<R>* __restrict__ ev = static_cast<const cplx<R>*>(a.e) + int64_t(j) * a.n;
     double2* __restrict__ x = xp.x[j];
     for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < a.n; i += int64_t(gridDim.x) * kBlock) {
-      const double2 d = to_d(ev[i]);
+      const double2 d = to_d(ev[vol ? (i % 3) * vol + i / 3 : i]);
       double2 v = x[i];
       v.x += d.x;
       v.y += d.y;

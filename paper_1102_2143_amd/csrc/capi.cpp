@@ -728,6 +728,8 @@ msc_status batch_residual(msc_op op, int prec, int lanes, int m, const double* s
     }
     v.u = op->ws.u64;
     if (write_vectors) {
+      if (op->stencil && (prm.format == MSC_FORMAT_AUTO || prm.format == MSC_FORMAT_STENCIL))
+        v.vol = op->w64.vol;
       v.r = op->bws.r;
       v.p = op->bws.p;
       v.e = op->bws.e;

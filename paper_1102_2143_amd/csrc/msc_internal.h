@@ -553,6 +553,7 @@ struct ResArgs {
   Sell<double2> s1, s2;
   int mhm;
   int64_t n;
+  int64_t vol;              // > 0: r, p and e colour by colour (sites per colour), else in row order
   int kc;
   int j0;
   const double2* x[kResChunk];

@@ -215,8 +215,8 @@ __device__ __forceinline__ void stencil_dir(const Stencil<cplx<R>>& op, uint32_t
   }
 }
 
-// M (sign 1) or M^H (sign -1) times several vectors at one site: out[q][c] of xs[q], q <
-// cnt <= G.  A direction's two links are read and completed once for all of them.
+// M (sign 1) or M^H (sign -1) times several vectors at one site: out[q][c] of xs[q] (colour by
+// colour: value (s, c) at c vol + s), q < cnt <= G.  A direction's two links are read and completed once for all of them.
 template <class R, int LR, int G>
 __device__ __forceinline__ void stencil_site_group(const Stencil<cplx<R>>& op, uint32_t s, int sign,
                                                    const cplx<R>* const (&xs)[G], int cnt,
@@ -255,8 +255,8 @@ __device__ __forceinline__ void stencil_site_group(const Stencil<cplx<R>>& op, u
         cplx<R> gf[3], gb[3];
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-          gf[j] = xs[q][3 * int64_t(fwd) + j];
-          gb[j] = xs[q][3 * int64_t(bwd) + j];
+          gf[j] = xs[q][int64_t(j) * vol + fwd];
+          gb[j] = xs[q][int64_t(j) * vol + bwd];
           gb[j].x = -gb[j].x;
           gb[j].y = -gb[j].y;
         }
@@ -277,7 +277,7 @@ __device__ __forceinline__ void stencil_site_group(const Stencil<cplx<R>>& op, u
     if (q < cnt) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const cplx<R> own = xs[q][3 * int64_t(s) + c];
+        const cplx<R> own = xs[q][int64_t(c) * vol + s];
         out[q][c].x = fma(m, own.x, sign > 0 ? h[q][c].x : -h[q][c].x);
         out[q][c].y = fma(m, own.y, sign > 0 ? h[q][c].y : -h[q][c].y);
       }
