@@ -24,7 +24,7 @@
 // 122 + 140 us an iteration in complex64; without the tickets 83 + 104; a kernel per
 // precision 66 + 78; descriptors and state through the scalar cache (164 and 98 registers)
 // 53 + 70, FP64 83 + 111 (the vectors and links alone at 5.5 TB/s: 35 + 54 and 70 + 108).
-// The solve in mixed precision: 172 -> 85 ms.
+// The solve in mixed precision: 172 -> 85 ms; as stored matrices 175 -> 122.
 #include <type_traits>
 
 #include "dev_common.h"
@@ -125,9 +125,9 @@ template <class R> __device__ __forceinline__ Sell<cplx<R>> sell2(const BatchSys
 template <> __device__ __forceinline__ Sell<double2> sell2<double>(const BatchSys& S) { return S.sh64; }
 template <> __device__ __forceinline__ Sell<float2> sell2<float>(const BatchSys& S) { return S.sh32; }
 
-// Pairs per round trip of the RR-rhs product (more cost registers, hence waves: 4 rhs with two
-// pairs 93.7 ms, with one 91.9).
-template <int RR> constexpr int kp_rhs() { return RR >= 4 ? 1 : 2; }
+// Pairs per round trip of the RR-rhs product (the 64 systems as stored matrices, mixed and
+// FP64: one 145 and 179 ms, two 140 and 174, four 148 and 192).
+template <int RR> constexpr int kp_rhs() { return RR >= 4 ? 2 : 4; }
 
 // Workgroup partials of a chunk (K values): store, take the system's ticket; true in the
 // last chunk of the system, which then holds the totals in tot[].
@@ -371,12 +371,16 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
   double acc[RR];
 #pragma unroll
   for (int q = 0; q < RR; ++q) acc[q] = 0.0;
-  // one element: the step of rhs q (false: it takes none)
-  auto element = [&](int64_t idx, const cplx<R>& w, double a, double b) {
-    const double2 wd = to_d(w), rd = to_d(r[idx]), sd = to_d(ld_stream(&sv[idx]));
+  // one element's step; `stream` where a wave's s is one run (else its lines, shared by the
+  // right-hand sides of a row, would leave the caches between them)
+  auto element = [&](int64_t idx, const cplx<R>& w, double a, double b, auto stream) {
+    const double2 wd = to_d(w), rd = to_d(r[idx]), sd = to_d(stream ? ld_stream(&sv[idx]) : sv[idx]);
     const double2 t{fma(b, sd.x, fma(s0, rd.x, wd.x)), fma(b, sd.y, fma(s0, rd.y, wd.y))};
     const cplx<R> nr = from_d<R>(double2{fma(-a, t.x, rd.x), fma(-a, t.y, rd.y)});
-    st_stream(&sv[idx], from_d<R>(t));
+    if (stream)
+      st_stream(&sv[idx], from_d<R>(t));
+    else
+      sv[idx] = from_d<R>(t);
     rn[idx] = nr;
     return norm2d<R>(nr);
   };
@@ -390,7 +394,8 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
       if (t.live) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-          sum += element(int64_t(t.q) * S.n + c * S.w64.vol + t.site, w[c], a, b);
+          sum += element(int64_t(t.q) * S.n + c * S.w64.vol + t.site, w[c], a, b,
+                         std::true_type{});
       }
     }
     acc[0] = sum;
@@ -406,7 +411,7 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
     auto epilogue = [&](int64_t row, const cplx<R> (&w)[RR]) {
 #pragma unroll
       for (int q = 0; q < RR; ++q)
-        if (go[q]) acc[q] += element(row * RR + q, w[q], a[q], b[q]);
+        if (go[q]) acc[q] += element(row * RR + q, w[q], a[q], b[q], std::false_type{});
     };
     if (S.sell && mhm) {
       // one row per lane: the chunk's four slices, one per wave
@@ -447,7 +452,7 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
       const int64_t end = int64_t(ch.z) * RR;
       if (gq)
         for (int64_t e = int64_t(ch.y) * RR + threadIdx.x; e < end; e += kBlock)
-          sum += element(e, u[e], aq, bq);
+          sum += element(e, u[e], aq, bq, std::true_type{});
 #pragma unroll
       for (int k = 0; k < RR; ++k) acc[k] = k == q ? sum : 0.0;
     }
