@@ -39,15 +39,15 @@ WORKLOAD_NAMES = {
 # (FETCH_SIZE and WRITE_SIZE, KiB per dispatch, scaled by the calibration against a copy
 # kernel of known size); it is reported only while the kernel sources are unchanged since.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-KERNEL_NAMES = {("mixed", "head"): "k1_fused<float, true>",
+KERNEL_NAMES = {("mixed", "head"): "k1_sell<float>",
                 ("mixed", "K2"): "k2_sell<float>",
-                ("fp64", "head"): "k1_fused<double, true>",
+                ("fp64", "head"): "k1_sell<double>",
                 ("fp64", "K2"): "k2_sell<double>"}
-# the same kernels on the matrix-free staggered operator (M and M^H from the links, one
-# lattice site per lane; two rows per SU(3) link; the FP64 head forms its product by the
-# recurrence t' = M r + b t in all but one launch in 64; K2 and the heads march along t
-# where the lattice has enough blocks of 64 sites for it, as at 32^3x64, and not at
-# 16^4): the first name that the counter summary holds for the workload
+# the same kernels on the matrix-free staggered operator (M and M^H from the links, two rows
+# per SU(3) link; a lattice site per lane, marching along t where the lattice has enough
+# blocks of 64 sites for it, as at 32^3x64; lattices of up to 65536 sites run a form of
+# these with a direction per wave, reported under the first name): the first name that
+# the counter summary holds for the workload
 KERNEL_NAMES_MF = {("mixed", "head"): ("k1_site<float, 2, false, true>",
                                        "k1_site<float, 2, false, false>"),
                    ("mixed", "K2"): ("k2_site<float, 2, true>", "k2_site<float, 2, false>"),
@@ -359,7 +359,8 @@ def main():
                 continue
             kms = np.sum([inf[key + "_ms"] for inf in infos], axis=0)
             kby = np.sum([inf[key + "_bytes"] for inf in infos], axis=0)
-            # slot 2 (a separate update kernel) is empty when the update is fused into the head
+            # slot 2 (the application of the composed steps, apart) is empty where the library
+            # counts it with the first half ("head")
             names = ["head", "K2"] if kms[2] == 0 else ["K1", "K2", "K3"]
             for k, nm in enumerate(names):
                 # algorithmic bytes of the sampled launches (the library counts the shifts

@@ -100,11 +100,10 @@ typedef struct {
                                 reach mixed_margin * tol (0 < margin <= 1), so that the
                                 complex64 drift leaves few shifts above tol     (0.7)  */
     int32_t update_steps;    /* 1..8: consecutive steps of the all-shift update folded
-                                into one pass over x_0, x_k and p_k (the heads between
-                                defer theirs); same recurrences, 1/update_steps of the
-                                traffic of those vectors. 1: one step per iteration. The
-                                batched solve folds at most 4 (larger values act
-                                as 4 there)                                     (8)    */
+                                into one pass over x_0, x_k and p_k; same recurrences,
+                                1/update_steps of the traffic of those vectors. 1: one
+                                step per iteration. BiCGStab-M folds at most 4 (larger
+                                values act as 4 there)                          (8)    */
     int32_t sweep;           /* order of the rows the iteration kernels visit: 0 (auto)
                                 follows the operator's lattice structure where one was
                                 found at creation (planes and slabs of the staggered
@@ -125,15 +124,15 @@ typedef struct {
     double seconds;          /* wall time of the call                                   */
     double alg_bytes;        /* algorithmic HBM bytes moved by the call's kernels       */
     double kernel_ms[3];     /* with timing on: summed durations of the sampled launches,
-                                milliseconds: [0] the head (the previous iteration's
-                                all-shift update fused with the first operator half),
-                                [1] K2 (second half + residual update), [2] the separate
-                                all-shift update kernel of the CSR path (0 otherwise)  */
+                                milliseconds: [0] K1 (first operator half) and the
+                                applications of the composed shift steps, [1] K2 (second
+                                half + residual update), [2] those applications where
+                                the iteration runs on the CSR (then not in [0])        */
     int32_t kernel_samples;  /* number of sampled iterations behind kernel_ms          */
     int32_t iters_fp64;      /* iterations run in FP64 (all of them for MSC_PREC_FP64)  */
     double kernel_bytes[3];  /* algorithmic HBM bytes of the same sampled launches, summed
                                 like kernel_ms (each array touched once, gathers once;
-                                the head's depends on the shifts active at its iteration) */
+                                [0]'s depends on the shifts active at its applications) */
     double fp64_kernel_ms[3];    /* mixed solve: kernel_ms of the launches sampled in its
                                     FP64 phase (kernel_ms holds its complex64 phase);
                                     0 otherwise                                        */
@@ -187,10 +186,11 @@ msc_status msc_op_update_values(msc_op op, const double* d_vals, msc_stream stre
  *   eta_0 = 1, eta_mu(x) = (-1)^(x0 + ... + x_{mu-1}).
  * The library keeps eta/2 U in complex128 and complex64 (the links are copied; the
  * caller may free them) and also builds the equivalent scalar CSR of M (25 sorted
- * entries per row) with every copy msc_op_create_csr makes, which the reliable
- * updates, the verification, the refinement, the adjoint, msc_op_apply and the
- * batched solve use.  The multishift iteration applies M and M^H from the links
- * (msc_params.format AUTO or STENCIL).  MSC_EINVAL on an extent below 3, an oversized
+ * entries per row) with every copy msc_op_create_csr makes, which the verification, the
+ * FP64 residuals of the refinement, the gradient of the values and msc_op_apply in
+ * complex64 and on small lattices use.  The iterations (multishift with its reliable
+ * updates, refinement, batched solve) and msc_op_apply in FP64 on larger lattices apply
+ * M and M^H from the links (msc_params.format AUTO; STENCIL where it is accepted).  MSC_EINVAL on an extent below 3, an oversized
  * lattice, a non-finite mass or a null pointer.
  */
 msc_status msc_op_create_staggered(msc_op* out, const int32_t* dims, double mass,
@@ -228,7 +228,7 @@ msc_status msc_op_apply(msc_op op, int32_t prec, const double* d_in, double* d_o
 /*
  * msc_op_apply for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same product,
- * d_out = (A + shift I) d_in, computed by the same kernels, with its temporaries in a
+ * d_out = (A + shift I) d_in, computed by the same kernels, with its temporary in a
  * fixed device array of 64 MiB that the library keeps on each GPU it runs on until the
  * process ends.  Nothing is allocated, not even on the first call.  Limits: n <= 2^21
  * for MSC_PREC_FP64 with MSC_A_MHM, n <= 2^22 otherwise; larger operators get
