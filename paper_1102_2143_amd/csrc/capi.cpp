@@ -560,7 +560,7 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
     ++chunk;
     if (chunk >= 2) {
       HIP_TRY(hipEventSynchronize(op->ws.ev[slot ^ 1]));
-      // halt | switch_req << 1 of the newest state a head has written: at least as recent
+      // halt | switch_req << 1 of the newest state a kernel has written: at least as recent
       // as the end of that chunk (within a phase the halt only ever gets set)
       const int f = __atomic_load_n(op->ws.h_halt, __ATOMIC_ACQUIRE);
       if (f & 1) {

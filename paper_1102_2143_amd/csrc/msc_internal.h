@@ -134,7 +134,7 @@ template <class V> struct Stencil {
   double mass = 0.0;
 };
 
-// Order in which the waves of the iteration kernels (head and K2 on the sliced path) visit
+// Order in which the waves of the iteration kernels (K1 and K2 on the sliced path) visit
 // the slices of 64 rows, for operators with a lattice structure: rows s1 slices apart are
 // neighbours in one direction (a plane), rows s2 slices apart in the slowest one (a slab),
 // and a plane is cut into tiles of cs slices.  on = 0: every workgroup sweeps one
@@ -324,7 +324,7 @@ struct MsArgs {
   int ru_check;          // 1: this iteration begins with a reliable update where one is due
   int stencil;           // K1 and K2 apply M and M^H from links (kind MHM, sell = 1):
                          // 0 no, 3 full links, 2 two rows per link (w64 / w32 in that form)
-  SweepOrder ord;        // slice order of the head and K2 on the sliced path
+  SweepOrder ord;        // order of the slices, or of the links' blocks of 64 sites
   int march, m1, m2;     // links: t-slices per column of the march, and whether K1 / K2 march
   int split;             // links: a wave for each direction
   int small;             // links: the lattice fits one workgroup, which can take
