@@ -172,15 +172,17 @@ __device__ __forceinline__ void wave_partial(const BatchSys& S, const int4& ch, 
 
 // Their totals per rhs, in every thread's view of tot[] (kBatchMaxRhs).
 template <int RR> __device__ __forceinline__ void system_totals(const BatchSys& S, double* tot) {
-  constexpr int U = 4;
+  constexpr int U = 16;  // in flight together: all of a system of 4096 partials (with 4, and the
+                         // state read after the sums, the 64 systems took 86.8 for 85.0 ms)
   const int np = S.nchunks * (kBlock / kWave) * (S.links ? 1 : RR);
-  double a[U] = {0.0, 0.0, 0.0, 0.0};
+  double v = 0.0;
   for (int i = threadIdx.x; i < np; i += U * kBlock) {
+    double a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i + u * kBlock < np) a[u] += S.partial[i + u * kBlock];
+    for (int u = 0; u < U; ++u) a[u] = i + u * kBlock < np ? S.partial[i + u * kBlock] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v += a[u];
   }
-  double v = (a[0] + a[1]) + (a[2] + a[3]);
   // lanes of one rhs: those equal mod RR
 #pragma unroll
   for (int o = kWave / 2; o >= RR; o /= 2) v += __shfl_xor(v, o, kWave);
@@ -294,18 +296,21 @@ __device__ __forceinline__ void bk1_chunk(const BatchSys& S, const BatchState* s
 }
 
 // The scalars of the step, one workgroup per system.
-__device__ __forceinline__ void bs1_system(BatchState* st, const double* tot) {
+template <int RR>
+__device__ __forceinline__ void bs1_system(const BatchSys& S, BatchState* st, double* tot) {
   // lane = q * 16 + k: the scalars of step n of rhs q, and shift k's, composed with
-  // the pending steps; every lane reads the state before any lane writes it
+  // the pending steps; every lane reads the state before any lane writes it, and
+  // before the sums, whose round trip it shares
   const int lk = threadIdx.x;
-  if (lk >= kQK) return;
   const int q = lk / kBatchMaxShifts, k = lk % kBatchMaxShifts, ns = st->ns;
-  const bool live = q < st->nrhs && !st->halt[q];
+  const bool live = lk < kQK && q < st->nrhs && !st->halt[q];
   const int n = live ? st->iter[q] : 0, ru = live ? st->ru[q] : 0, m = live ? st->m[q] : 0;
   const double g = live ? st->R[q] : 1.0, g1 = live ? st->g1[q] : 1.0, a1 = live ? st->a1[q] : 1.0;
   const double P1 = live ? st->P1[q] : 1.0, rg = live ? st->ru_g[q] : 0.0, rc = live ? st->ru_c[q] : 0.0;
   const bool act = live && k < ns && (k == 0 || st->active[lk]);
-  const double z = k ? st->zeta[lk] : 1.0, zp = k ? st->zeta_prev[lk] : 1.0;
+  const double z = live && k ? st->zeta[lk] : 1.0, zp = live && k ? st->zeta_prev[lk] : 1.0;
+  const double sigma0 = st->sigma0, sk = live ? st->s[k] : 0.0;
+  const int slot = st->slot;
   const bool had = m > 0 && st->took[lk];
   double cx[kMaxSteps + 1], cp[kMaxSteps + 1];
 #pragma unroll
@@ -314,7 +319,9 @@ __device__ __forceinline__ void bs1_system(BatchState* st, const double* tot) {
     cp[i] = m > 0 && i <= m ? st->cp[i][lk] : 0.0;
   }
   if (m == 0) cp[0] = 1.0;
-  const double d = tot[q] + st->sigma0 * g;
+  system_totals<RR>(S, tot);
+  if (lk >= kQK) return;
+  const double d = tot[q] + sigma0 * g;
   const double b = n == 0 ? 0.0 : (ru ? rg : g) / g1;
   const double P = n == 0 ? d : (ru ? d + b * (2.0 * rc + b * P1) : d - b * g / a1);
   const bool ok = P > 0.0 && isfinite(P);
@@ -328,8 +335,8 @@ __device__ __forceinline__ void bs1_system(BatchState* st, const double* tot) {
   bool took = had;
   if (act) {
     const double zn = k == 0   ? 1.0
-                      : n == 0 ? z / (1.0 + st->s[k] * a)
-                               : z * zp * a1 / (a * b * (zp - z) + zp * a1 * (1.0 + st->s[k] * a));
+                      : n == 0 ? z / (1.0 + sk * a)
+                               : z * zp * a1 / (a * b * (zp - z) + zp * a1 * (1.0 + sk * a));
     const double ratio = z / zp, aj = a * zn / z, bj = b * ratio * ratio;
 #pragma unroll
     for (int i = 0; i <= kMaxSteps; ++i) {
@@ -353,7 +360,7 @@ __device__ __forceinline__ void bs1_system(BatchState* st, const double* tot) {
     st->P1[q] = P;
     st->g1[q] = g;
     st->m[q] = m + 1;
-    st->last[q] = st->slot;  // the newest of the composed steps
+    st->last[q] = slot;  // the newest of the composed steps
     st->ru[q] = 0;
   }
 }
@@ -460,19 +467,22 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
   wave_partial<RR>(S, ch, acc);
 }
 
-__device__ __forceinline__ void bs2_system(BatchState* st, const double* tot, int* active_systems) {
+template <int RR>
+__device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st, double* tot,
+                                           int* active_systems) {
   // one wave: lane = q * 16 + k; every lane reads the state before any lane
   // writes it, and system-wide decisions travel by ballot, not through memory
   const int lk = threadIdx.x;
-  if (lk >= kWave) return;
   const int q = lk / kBatchMaxShifts, k = lk % kBatchMaxShifts;
-  const bool live = q < st->nrhs && st->step[q] && !st->halt[q];
+  const bool live = lk < kWave && q < st->nrhs && st->step[q] && !st->halt[q];
   const int it = live ? st->iter[q] + 1 : 0;
   const double eps2 = live ? st->eps2[q] : 0.0, sw2 = live ? st->sw_eps2[q] : 0.0;
-  const double Rn = live ? tot[q] : 0.0;
   const int phase32 = st->phase32, max_iter = st->max_iter;
   const bool act = live && k >= 1 && k < st->ns && st->active[lk];
   const double z = act ? st->zeta[lk] : 0.0;
+  system_totals<RR>(S, tot);
+  if (lk >= kWave) return;
+  const double Rn = live ? tot[q] : 0.0;
   if (act && z * z * Rn <= eps2) {
     st->active[lk] = 0;
     st->freeze_iter[lk] = it;
@@ -880,8 +890,7 @@ template <int RR> __global__ __launch_bounds__(kBlock) void bs1(BatchArgs a) {
   const BatchSys S = load_const(a.sys + blockIdx.x);
   if (idle(a, S.st)) return;
   __shared__ double tot[kBatchMaxRhs];
-  system_totals<RR>(S, tot);
-  bs1_system(S.st, tot);
+  bs1_system<RR>(S, S.st, tot);  // its barriers come after every thread has looked
 }
 
 template <class R, int L, int RR>
@@ -901,8 +910,7 @@ template <int RR> __global__ __launch_bounds__(kBlock) void bs2(BatchArgs a) {
   const BatchSys S = load_const(a.sys + blockIdx.x);
   if (idle(a, S.st)) return;
   __shared__ double tot[kBatchMaxRhs];
-  system_totals<RR>(S, tot);  // its barriers come after every thread has looked
-  bs2_system(S.st, tot, a.active_systems);
+  bs2_system<RR>(S, S.st, tot, a.active_systems);
 }
 
 template <int RR>

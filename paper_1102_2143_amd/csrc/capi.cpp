@@ -1440,10 +1440,6 @@ struct BatchRun {
     }
     std::vector<double> r2all(size_t(total) * kMaxShifts, 0.0);
     if (prm.verify) {
-      for (int s = 0; s < nsys; ++s) {
-        msc_status rc = ensure_scratch(ops[s], sint);
-        if (rc != MSC_OK) return rc;
-      }
       HIP_TRY(launch_batch_verify(args(), max_rhs, max_ns, sint));
       HIP_TRY(hipMemcpyAsync(r2all.data(), d_res2, sizeof(double) * r2all.size(),
                              hipMemcpyDeviceToHost, sint));

@@ -918,7 +918,7 @@ __global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
 // and each row is then finished by a lane of its own.  Used while every block can have a
 // workgroup (prepare_impl): there an iteration is a chain of latencies.
 // An iteration in FP64, one lane per site and here: 4^4 16.8 and 12.2 us, 12^4 23.4 and 15.1,
-// 16^4 30.2 and 26.9, 18^4 37.9 and 43.0 (since the sums go by DPP: 8^4 12.0 -> 11.3, 12x10x14x18
+// 16^4 30.2 and 26.9, 18^4 37.9 and 43.0 (since the sums go by DPP: 8^4 11.8 -> 11.3, 12x10x14x18
 // 15.6 -> 14.9; 4^4 now has a form of its own below).
 template <class R> using DirParts = cplx<R>[4][3][kWave];
 
