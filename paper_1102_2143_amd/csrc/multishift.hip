@@ -318,11 +318,13 @@ __device__ __forceinline__ StepPlan step_plan(const StepIn& i, double g, double 
   p.b = i.n == 0 ? 0.0 : (i.ru ? i.ru_g : g) / i.g1;
   p.P = i.n == 0 ? d : (i.ru ? d + p.b * (2.0 * i.ru_c + p.b * i.P1) : d - p.b * g / i.a1);
   p.a = g / p.P;
-  const bool ok = isfinite(g) && p.P > 0.0 && isfinite(p.P);
-  p.stop = g <= i.tol2 * bn2 || i.n >= i.max_iter ? 1
-           : !ok                                  ? 3
-           : g <= i.sw2 * bn2                     ? 2
-                                                  : 0;
+  const bool ok = p.P > 0.0 && isfinite(p.P);
+  // |r|^2 first: an infinite |b|^2 would pass for its own limit
+  p.stop = !isfinite(g)                             ? 3
+           : g <= i.tol2 * bn2 || i.n >= i.max_iter ? 1
+           : !ok                                    ? 3
+           : g <= i.sw2 * bn2                       ? 2
+                                                    : 0;
   return p;
 }
 

@@ -220,8 +220,9 @@ __device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
   const double bn2 = n == 0 ? g : st->bnorm2, eps2 = st->tol2 * bn2;
   const double b = n == 0 ? 0.0 : g / rs.g;
   const double P = n == 0 ? d : d - b * g / rs.a;
-  const bool done = g <= eps2 || n >= st->max_iter;
-  const bool ok = done ? true : (isfinite(g) && P > 0.0 && isfinite(P));
+  // |r|^2 first: an infinite |b|^2 would pass for its own limit
+  const bool done = isfinite(g) && (g <= eps2 || n >= st->max_iter);
+  const bool ok = done || (isfinite(g) && P > 0.0 && isfinite(P));
   const bool live = !done && ok;
   const double step = live ? g / P : 0.0;
   const int m = m0 + (live ? 1 : 0);
