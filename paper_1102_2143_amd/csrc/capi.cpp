@@ -19,6 +19,7 @@
 #include <string>
 #include <vector>
 
+#include "alloc_all.h"
 #include "msc.h"
 #include "msc_internal.h"
 
@@ -109,10 +110,14 @@ msc_status ensure_workspace(msc_op op, int prec, int ns) {
     w.prec = MSC_PREC_FP64;
   }
   if (prec == MSC_PREC_MIXED && !w.ring32) {
-    HIP_TRY(hipMalloc(&w.ring32, sizeof(float2) * n * kRing));
-    HIP_TRY(hipMalloc(&w.u32, sizeof(float2) * n * two));
-    HIP_TRY(hipMalloc(&w.s32, sizeof(float2) * n * two));
-    HIP_TRY(hipMalloc(&w.pk32, sizeof(float2) * n * size_t(w.ns)));
+    // whole or not at all: the next solve takes a set ring32 for the whole set
+    const hipError_t e = alloc_all({{&w.ring32, sizeof(float2) * n * kRing},
+                                    {&w.u32, sizeof(float2) * n * two},
+                                    {&w.s32, sizeof(float2) * n * two},
+                                    {&w.pk32, sizeof(float2) * n * size_t(w.ns)}},
+                                   [](void** q, size_t b) { return hipMalloc(q, b); },
+                                   [](void* q) { (void)hipFree(q); });
+    HIP_TRY(e);
     w.prec = MSC_PREC_MIXED;
   }
   return MSC_OK;
