@@ -139,9 +139,9 @@ msc_status ensure_halt(HaltWord& w) {
 template <class F>
 msc_status run_to_halt(HaltWord& w, const msc_params& prm, int max_iter, hipStream_t s, F iteration) {
   const int G = std::max(1, prm.poll_every);
-  int launched = 0;
-  for (int chunk = 0; launched < max_iter + 2 * G; ++chunk) {
-    for (int g = 0; g < G; ++g) HIP_TRY(iteration(launched++));
+  int64_t launched = 0;
+  for (int chunk = 0; launched < int64_t(max_iter) + 2 * int64_t(G); ++chunk) {
+    for (int g = 0; g < G; ++g) HIP_TRY(iteration(int(launched++ & 1)));
     const int slot = chunk & 1;
     HIP_TRY(hipEventRecord(w.ev[slot], s));
     if (chunk >= 1) {
@@ -588,7 +588,7 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
         }
       }
     }
-    if (launched >= h.max_iter + 4 * G) done = true;
+    if (launched >= int64_t(h.max_iter) + 4 * int64_t(G)) done = true;
   }
   HIP_TRY(launch_final_flush(phase, *cur, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -876,7 +876,7 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
         // set by the last IK2 once every system is done (it only ever gets set)
         if (__atomic_load_n(op->bws.h_halt, __ATOMIC_ACQUIRE)) done = true;
       }
-      if (launched >= prm.refine_max_iter + 2 * G) done = true;
+      if (launched >= int64_t(prm.refine_max_iter) + 2 * int64_t(G)) done = true;
       ++chunk;
     }
     HIP_TRY(launch_accum(prec, a, xp, s));
@@ -1402,7 +1402,7 @@ struct BatchRun {
     const int G = std::max(1, prm.poll_every);
     const int ru_every = (prm.prec == MSC_PREC_MIXED && prm.reliable_every > 0)
                              ? std::max(1, prm.reliable_every / G) : 0;
-    const int max_replays = (prm.max_iter + G - 1) / G + 6;
+    const int64_t max_replays = (int64_t(prm.max_iter) + G - 1) / G + 6;
     int chunk = 0, phases = 1;
     bool done = false;
     while (!done) {
@@ -2481,8 +2481,8 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
   HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve sets the halt word now
   __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
   HIP_TRY(launch_bcg_start(a, s));
-  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int launch) {
-    a.par = launch & 1;
+  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int parity) {
+    a.par = parity;
     return launch_bcg_iteration(a, s);
   });
   if (rc != MSC_OK) return rc;
@@ -2713,8 +2713,8 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
   HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve sets the halt word now
   __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
   HIP_TRY(launch_real_start(prec, a, s));
-  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int launch) {
-    a.par = launch & 1;
+  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int parity) {
+    a.par = parity;
     return launch_real_iteration(prec, a, s);
   });
   if (rc != MSC_OK) return rc;
