@@ -17,8 +17,9 @@
 // The shifts take, per step,
 //   x(s) += al(s) p(s) + om(s) (z'/tau) s,
 //   p(s) <- (z'/tau') r' + be(s) [p(s) - (om(s)/al(s)) ((z/tau) r - (z'/tau) s)];
-// nothing else reads them, so up to kBcgSteps steps are composed against the first one's
-// p(s) and the r and s of the steps, which stay in rings, and BA applies them in one pass.
+// nothing else reads them, so msc_params::update_steps steps, at most kBcgSteps, are composed
+// against the first one's p(s) and the r and s of the steps, which stay in rings, and BA
+// applies them in one pass.
 // Complex scalars are FP64 throughout; the shadow vector is b.
 //
 // Bound by memory and, on grids that fit the caches, by latency.  64 x 48 x 50 points, 8
@@ -309,7 +310,7 @@ __device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) 
     stop = 1;
   }
   const bool live = stop == 0;
-  const bool apply = live ? m >= kBcgSteps : (m > 0 || rs.fresh);
+  const bool apply = live ? m >= a.steps : (m > 0 || rs.fresh);
   const bool list = apply && mine && (took || rs.fresh);
   const uint64_t mask = __ballot(list);
   if (list) {

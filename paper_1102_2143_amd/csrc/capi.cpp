@@ -2438,6 +2438,7 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
   };
   BcgArgs a{};
   a.n = n;
+  a.steps = std::min(std::max(int(prm.update_steps), 1), kBcgSteps);
   a.lanes = choose_lanes(op, prm);
   a.m = Csr<double2>{op->rowptr, op->col, op->val64};
   a.sell = op->sell && prm.format != MSC_FORMAT_CSR ? 1 : 0;

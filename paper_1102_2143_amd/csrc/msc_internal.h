@@ -384,7 +384,7 @@ hipError_t launch_apply_noalloc(ApplyArgs a, void* base, hipStream_t s);
 
 // bicgstab.hip -- multishift BiCGStab for a general A (complex FP64 scalars)
 constexpr int kBcgGrid = 1024;               // most workgroups of its kernels
-constexpr int kBcgSteps = 4;                 // steps of the shifts folded into one application
+constexpr int kBcgSteps = 4;                 // most steps of the shifts folded into one application
 constexpr int kBcgRing = kBcgSteps + 1;      // r_n in slot n % kBcgRing, s_n in n % kBcgSteps
 constexpr int kBcgTerms = 2 * kBcgSteps + 2; // p(s), r_0 .. r_D, s_0 .. s_{D-1}
 // State at the start of iteration n (indexed by n's parity; BA writes the other one, which
@@ -411,6 +411,7 @@ struct BcgState {
 struct BcgArgs {
   int64_t n;
   int lanes, par;
+  int steps;               // steps of the shifts folded into one application, <= kBcgSteps
   Csr<double2> m;
   int sell;                // read the sliced copy
   int64_t nslices;
