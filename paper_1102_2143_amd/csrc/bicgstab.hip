@@ -11,7 +11,7 @@
 // partials itself, in one order, and derives the scalars; vectors that the other kernel
 // left to be formed are formed at every gathered column as their owner forms them:
 //   BA   om_{n-1} = t^H s / t^H t, rho_n = w^H s - om w^H t, |r_n|^2 = |s|^2 - |t^H s|^2 /
-//        t^H t, be_n;  r_n = s - om t, p_n = r_n + be (p - om v), v_n = B p_n;  w^H v_n
+//        t^H t (both summed over r_n itself where they cancel), be_n;  r_n = s - om t, p_n = r_n + be (p - om v), v_n = B p_n;  w^H v_n
 //   BB   al_n = rho_n / w^H v_n;  s_n = r_n - al v_n, t_n = B s_n;  t^H s, t^H t, w^H s,
 //        w^H t, |s|^2
 // The shifts take, per step,
@@ -138,11 +138,17 @@ __device__ __forceinline__ double2 sell_f(const Sell<double2>& m, int64_t sl, in
   return acc;
 }
 
-// Partials: component k of a kernel's workgroup i at reg[k kBcgGrid + i]; BA's two in the
-// first region, BB's eight in the second.
+// Partials: component k of a kernel's workgroup i at reg[k kBcgGrid + i]; BA's two in region
+// 0, BB's eight in 1 and a checking BA's three in 2 (the BA that reads them writes region 0).
 __device__ __forceinline__ double* bcg_region(const BcgArgs& a, int which) {
-  return a.partial + which * 2 * kBcgGrid;
+  return a.partial + (which == 0 ? 0 : which == 1 ? 2 : 10) * kBcgGrid;
 }
+
+// |r_n|^2 = |s|^2 - |t^H s|^2 / |t|^2 and w^H r_n = w^H s - om w^H t carry the rounding of their
+// larger terms, about 1e-15 of them.  Where the first falls below this part of |s|^2, BA sums
+// both over r_n itself (a pass of its own) and the step ends in the next BA, so that no shift
+// stops, and no be follows, from rounding alone: |r_n| is then known to 1e-5 of itself.
+constexpr double kBcgCancel = 1e-10;
 
 template <int K> __device__ __forceinline__ void bcg_store(double* reg, double (&v)[K]) {
   block_sum_k<kBlock, K>(v);
@@ -202,14 +208,16 @@ __global__ __launch_bounds__(kBlock) void k_bcg_start(BcgArgs a) {
 // What BA does, shared through LDS.
 struct BcgPlan {
   double2 om, be;
+  int check;           // 1: this BA only sums r_n
   int live, apply, m, first, fresh, nact;  // composed steps: first .. first + m - 1
   double2 cx[kBcgTerms][kMaxShifts], cp[kBcgTerms][kMaxShifts];
   int64_t xo[kMaxShifts], po[kMaxShifts];
 };
 
 // BA's prologue (wave 0, lane j: shift j).  Step n - 1 (s, t, alpha, z', al(s) known)
-// ends here; every workgroup derives the same, workgroup 0 writes the next state.
-__device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) {
+// ends here; every workgroup derives the same, workgroup 0 writes the next state.  exact:
+// w^H r_n and |r_n|^2 where the BA before summed them (rs.check).
+__device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], const double (&exact)[3], BcgPlan& pl) {
   BcgState* st = a.st;
   const BcgRot& rs = st->rot[a.par];
   const int j = threadIdx.x;
@@ -247,6 +255,40 @@ __device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) 
     tau = taun = rs.tau[j];
   }
   int m = m0;
+  const bool check = step && !st->bad && !rs.check && tt > 0.0 && isfinite(tt) && cfinite(ts) &&
+                     ss - cabs2(ts) / tt <= kBcgCancel * ss;
+  if (check) {  // the state goes on as it is, with om for the sums
+    if (j == 0) {
+      pl.om = double2{ts.x / tt, ts.y / tt};
+      pl.check = 1;
+      pl.live = pl.apply = 0;
+    }
+    if (!head) return;
+    BcgRot& nx = st->rot[a.par ^ 1];
+    if (mine) {
+      nx.z[j] = rs.z[j];
+      nx.zo[j] = rs.zo[j];
+      nx.tau[j] = rs.tau[j];
+      nx.active[j] = rs.active[j];
+      nx.took[j] = rs.took[j];
+#pragma unroll
+      for (int e = 0; e < kBcgTerms; ++e) {
+        nx.cx[e][j] = rs.cx[e][j];
+        nx.cp[e][j] = rs.cp[e][j];
+      }
+    }
+    if (j == 0) {
+      nx.rho = rs.rho;
+      nx.be = rs.be;
+      nx.al = rs.al;
+      nx.iter = n;
+      nx.m = m0;
+      nx.fresh = rs.fresh;
+      nx.halt = 0;
+      nx.check = 1;
+    }
+    return;
+  }
   if (step && st->bad) {
     stop = 2;  // BB found w^H v = 0: no step n - 1
   } else if (step) {
@@ -260,8 +302,8 @@ __device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) 
       act = 0;
     } else {
       const double2 al = st->alpha;
-      rho = csub(ws, cmul(om, wt));
-      R = fmax(ss - cabs2(ts) / tt, 0.0);
+      rho = rs.check ? double2{exact[0], exact[1]} : csub(ws, cmul(om, wt));
+      R = rs.check ? exact[2] : ss - cabs2(ts) / tt;
       const bool rho_ok = rho.x != 0.0 || rho.y != 0.0, om_ok = om.x != 0.0 || om.y != 0.0;
       // be = (rho' / rho)(al / om); a vanishing rho' or om ends the sequence after this step
       if (rho_ok && om_ok) be = cmul(cdiv(rho, rs.rho), cdiv(al, om));
@@ -326,6 +368,7 @@ __device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) 
   if (j == 0) {
     pl.om = om;
     pl.be = be;
+    pl.check = 0;
     pl.live = live ? 1 : 0;
     pl.apply = apply ? 1 : 0;
     pl.m = m;
@@ -358,6 +401,7 @@ __device__ void bcg_plan(const BcgArgs& a, const double (&tot)[8], BcgPlan& pl) 
     nx.m = apply ? 0 : m;
     nx.fresh = apply ? 0 : rs.fresh;
     nx.halt = live ? 0 : 1;
+    nx.check = 0;
     if (n == 0) st->bnorm2 = ss;
     if (!live) {
       // a step that broke down before its end does not count
@@ -421,14 +465,15 @@ __global__ __launch_bounds__(kBlock) void k_bcg_a(BcgArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) st->rot[a.par ^ 1].halt = 1;
     return;
   }
-  double tot[8];
+  double tot[8], exact[3] = {0.0, 0.0, 0.0};
   bcg_sums<8>(bcg_region(a, 1), tot);
+  if (rs.check) bcg_sums<3>(bcg_region(a, 2), exact);
   __shared__ BcgPlan pl;
-  bcg_plan(a, tot, pl);
+  bcg_plan(a, tot, exact, pl);
   __syncthreads();
   const int n = rs.iter;
-  const bool live = pl.live != 0;
-  if (!live && !pl.apply) return;
+  const bool live = pl.live != 0, check = pl.check != 0;
+  if (!live && !pl.apply && !check) return;
   const double2 om = pl.om, be = pl.be;
   const double2* __restrict__ s = ring(a.s, a.n, n + kBcgSteps - 1, kBcgSteps);  // s_{n-1}
   const double2* __restrict__ t = a.t;
@@ -445,6 +490,22 @@ __global__ __launch_bounds__(kBlock) void k_bcg_a(BcgArgs a) {
   };
   int64_t beg, end;
   bcg_rows<ST, L>(a, beg, end);
+  if (check) {  // p and v move on with the parity
+    double c[3] = {0.0, 0.0, 0.0};
+    const int64_t stop = end < a.n ? end : a.n;
+    for (int64_t i = beg + threadIdx.x; i < stop; i += kBlock) {
+      const double2 r = r_of(i);
+      double2 wr{0.0, 0.0};
+      cdot_acc(wr, a.b[i], r);
+      c[0] += wr.x;
+      c[1] += wr.y;
+      c[2] += cabs2(r);
+      pn[i] = p[i];
+      vn[i] = v[i];
+    }
+    bcg_store<3>(bcg_region(a, 2), c);
+    return;
+  }
   if (live) {
     double2 wv{0.0, 0.0};
     bcg_product<ST, L>(a, beg, end, st->sigma0, [&](int32_t c) { return p_of(c); },
@@ -501,7 +562,7 @@ template <int ST, int L>
 __global__ __launch_bounds__(kBlock) void k_bcg_b(BcgArgs a) {
   BcgState* st = a.st;
   const BcgRot& rs = st->rot[a.par ^ 1];  // written by this iteration's BA
-  if (rs.halt) return;
+  if (rs.halt || rs.check) return;
   double wv[2];
   bcg_sums<2>(bcg_region(a, 0), wv);
   const double2 wvc{wv[0], wv[1]};

@@ -134,13 +134,13 @@ msc_status ensure_halt(HaltWord& w) {
   return MSC_OK;
 }
 
-// Queue iterations, poll_every at a time, until the halt word is set: that of one chunk is
-// read once the next one is queued.
+// Queue iterations, poll_every at a time, until the halt word is set, which `most` of them do
+// at the latest: that of one chunk is read once the next one is queued.
 template <class F>
-msc_status run_to_halt(HaltWord& w, const msc_params& prm, int max_iter, hipStream_t s, F iteration) {
+msc_status run_to_halt(HaltWord& w, const msc_params& prm, int64_t most, hipStream_t s, F iteration) {
   const int G = std::max(1, prm.poll_every);
   int64_t launched = 0;
-  for (int chunk = 0; launched < int64_t(max_iter) + 2 * int64_t(G); ++chunk) {
+  for (int chunk = 0; launched < most + 2 * int64_t(G); ++chunk) {
     for (int g = 0; g < G; ++g) HIP_TRY(iteration(int(launched++ & 1)));
     const int slot = chunk & 1;
     HIP_TRY(hipEventRecord(w.ev[slot], s));
@@ -2482,7 +2482,8 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
   HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve sets the halt word now
   __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
   HIP_TRY(launch_bcg_start(a, s));
-  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int parity) {
+  // a step may take two launches (BA's check)
+  rc = run_to_halt(op->halt, prm, 2 * int64_t(h.max_iter), s, [&](int parity) {
     a.par = parity;
     return launch_bcg_iteration(a, s);
   });

@@ -393,6 +393,7 @@ struct BcgRot {
   double2 rho, al, be;     // rho_n-1, al_{n-2}, be_{n-1} (in the one BB reads: of n)
   int iter, halt;          // n; 1: nothing left to do
   int m, fresh;            // steps composed so far; 1: x(s) and p(s) never written
+  int check, pad_;         // 1: the BA before only summed r_n, whose step this one ends
   double2 z[kMaxShifts], zo[kMaxShifts], tau[kMaxShifts];
   // p(s) now is sum_e cp[e] term_e and x(s) gained sum_e cx[e] term_e
   double2 cx[kBcgTerms][kMaxShifts], cp[kBcgTerms][kMaxShifts];
@@ -423,7 +424,7 @@ struct BcgArgs {
   double2 *p[2], *v[2], *t;
   double2* pk;            // ns directions, sorted order
   BcgState* st;
-  double* partial;        // >= 10 kBcgGrid doubles
+  double* partial;        // >= 13 kBcgGrid doubles
   int* hflag;             // host-coherent word: 1 once halted
 };
 hipError_t launch_bcg_start(const BcgArgs& a, hipStream_t s);
