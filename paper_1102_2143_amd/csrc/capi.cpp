@@ -315,9 +315,6 @@ MsArgs make_args(msc_op op, int lanes, const double* d_b, double* d_x) {
 }
 
 // The operator's matrices for one product (vectors, shift and temporary left to fill).
-// The links stand in for the stored matrix when they are SU(3) to rounding (two rows) or
-// through all nine values: the product is M's to rounding either way.
-constexpr double kApplySu3Tol = 1e-14;
 ApplyArgs apply_args(msc_op op, int prec, int lanes) {
   ApplyArgs a{};
   a.kind = op->kind;
@@ -336,9 +333,8 @@ ApplyArgs apply_args(msc_op op, int prec, int lanes) {
       a.sh64 = sell_view(op->sell_mh, op->sell_mh.val64, op->sell_mh.diag64, true);
   }
   if (op->stencil) {
-    const bool two = op->two_rows && op->su3_dev <= kApplySu3Tol;
-    a.links = two ? 2 : 3;
-    a.w64 = two ? op->wc64 : op->w64;
+    a.links = 1;
+    a.w64 = op->w64;
     a.ord = op->order_sites64;
     a.ord.on = a.ord.s1 > 0 ? 1 : 0;
   }
@@ -1180,9 +1176,8 @@ struct BatchRun {
         S.links = op->two_rows ? 2 : 3;
         S.w64 = op->two_rows ? op->wc64 : op->w64;
         S.w32 = op->two_rows ? op->wc32 : op->w32;
-        const ApplyArgs pa = apply_args(op, MSC_PREC_FP64, lanes);
-        S.vlinks = pa.links;
-        S.v64 = pa.w64;
+        S.vlinks = 3;
+        S.v64 = op->w64;
       }
       S.b = reinterpret_cast<const double2*>(d_b[s]);
       S.x = reinterpret_cast<double2*>(d_x[s]);
@@ -1581,7 +1576,6 @@ msc_status refresh_two_rows(msc_op op, const double2* d_links, hipStream_t s) {
   double dev = 0.0;
   std::memcpy(&dev, &bits, sizeof dev);
   op->two_rows = false;
-  op->su3_dev = dev;
   if (!(dev <= kSu3Tol)) return MSC_OK;
   if (!op->wc64.w) {
     double2* w64 = nullptr;

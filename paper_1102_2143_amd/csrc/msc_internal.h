@@ -247,7 +247,6 @@ struct msc_op_s {
   bool stencil = false;          // matrix-free staggered operator (links kept below)
   msc::Stencil<double2> w64;     // W_mu(x) = eta_mu(x)/2 U_mu(x), complex128 and
   msc::Stencil<float2> w32;      // complex64 copies (device memory owned by the op)
-  double su3_dev = 1.0;          // largest deviation of a link from SU(3)
   bool two_rows = false;         // every link is in SU(3): the iteration reads wc64 / wc32,
   msc::Stencil<double2> wc64;    // the first two rows of each W_mu(x) (6 values), and
   msc::Stencil<float2> wc32;     // rebuilds the third from them
@@ -360,7 +359,7 @@ struct ApplyArgs {
   int sell;                // FP64 may read the sliced copies below
   int64_t nslices;
   Sell<double2> s64, sh64;
-  int links;               // FP64 may read the links w64 (rows per link: 2 or 3; 0: none)
+  int links;               // FP64 may read the links w64 (all nine values)
   Stencil<double2> w64;
   SweepOrder ord;          // of the links' blocks of 64 sites
   const double2* in;

@@ -80,10 +80,11 @@ template <class R> constexpr int sell_kp();
 template <> constexpr int sell_kp<float>() { return MSC_SELL_KP32; }
 template <> constexpr int sell_kp<double>() { return MSC_SELL_KP64; }
 
-template <class R, int KP, bool FULL>
+// NA: sums kept apart, entry e of a chunk in acc[e % NA].
+template <class R, int KP, bool FULL, int NA>
 __device__ __forceinline__ void sell_gather_fma(const cplx<R>* __restrict__ x, int np,
                                                 const int2 (&cc)[KP], const cplx<R> (&v)[2 * KP],
-                                                cplx<R>& acc) {
+                                                cplx<R> (&acc)[NA]) {
   cplx<R> xv[2 * KP];
 #pragma unroll
   for (int u = 0; u < KP; ++u) {
@@ -95,17 +96,19 @@ __device__ __forceinline__ void sell_gather_fma(const cplx<R>* __restrict__ x, i
     }
   }
 #pragma unroll
-  for (int u = 0; u < 2 * KP; ++u) cfma<R>(acc, v[u], xv[u]);
+  for (int u = 0; u < 2 * KP; ++u) cfma<R>(acc[u % NA], v[u], xv[u]);
 }
 
 // Off-diagonal part of the product of one sliced ELLPACK row per lane with x; slice `sl`
 // is wavefront-uniform.  Pairs go KP at a time: a chunk's column and value loads, then
-// its gathers, are all issued before its first multiply-add.
-template <class R, bool NARROW>
+// its gathers, are all issued before its first multiply-add.  NA > 1 (a power of two): that
+// many sums added in pairs at the end, for products that are results themselves (a row of 24
+// entries in FP64: 1.4e-16 of rounding with eight, 2.6e-16 with one); init starts the last.
+template <class R, bool NARROW, int NA>
 __device__ __forceinline__ cplx<R> sell_row_cols(const Sell<cplx<R>>& m,
                                                  const cplx<R>* __restrict__ x, int64_t sl,
-                                                 int lane) {
-  constexpr int KP = sell_kp<R>();
+                                                 int lane, const cplx<R>& init) {
+  constexpr int KP = NA > 1 ? NA / 2 : sell_kp<R>();  // an entry of a chunk per sum
   int32_t c, c1;
   if (m.wp > 0) {
     c = int32_t(sl) * m.wp;
@@ -114,24 +117,36 @@ __device__ __forceinline__ cplx<R> sell_row_cols(const Sell<cplx<R>>& m,
     c = load_uniform(m.cptr, sl);
     c1 = load_uniform(m.cptr, sl + 1);
   }
-  cplx<R> acc = czero<R>();
+  cplx<R> acc[NA];
+#pragma unroll
+  for (int k = 0; k < NA; ++k) acc[k] = k == NA - 1 ? init : czero<R>();
   int2 cc[KP];
   cplx<R> v[2 * KP];
   for (; c + KP <= c1; c += KP) {
     sell_load<R, KP, true, NARROW>(m, c, KP, lane, cc, v);
-    sell_gather_fma<R, KP, true>(x, KP, cc, v, acc);
+    sell_gather_fma<R, KP, true, NA>(x, KP, cc, v, acc);
   }
   if (c < c1) {
     const int np = c1 - c;
     sell_load<R, KP, false, NARROW>(m, c, np, lane, cc, v);
-    sell_gather_fma<R, KP, false>(x, np, cc, v, acc);
+    sell_gather_fma<R, KP, false, NA>(x, np, cc, v, acc);
   }
-  return acc;
+#pragma unroll
+  for (int o = NA / 2; o > 0; o /= 2) {
+#pragma unroll
+    for (int k = 0; k < o; ++k) {
+      acc[k].x += acc[k + o].x;
+      acc[k].y += acc[k + o].y;
+    }
+  }
+  return acc[0];
 }
-template <class R>
+template <class R, int NA = 1>
 __device__ __forceinline__ cplx<R> sell_row(const Sell<cplx<R>>& m, const cplx<R>* __restrict__ x,
-                                            int64_t sl, int lane) {
-  return m.col16 ? sell_row_cols<R, true>(m, x, sl, lane) : sell_row_cols<R, false>(m, x, sl, lane);
+                                            int64_t sl, int lane,
+                                            const cplx<R>& init = czero<R>()) {
+  return m.col16 ? sell_row_cols<R, true, NA>(m, x, sl, lane, init)
+                 : sell_row_cols<R, false, NA>(m, x, sl, lane, init);
 }
 
 // most t-slices per column of the march along t
@@ -829,7 +844,7 @@ __device__ __forceinline__ void for_sites(const MsArgs& a, const Stencil<cplx<R>
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) own[c] = car.fw[c];
-        stencil_site_c<R, LR, true>(w, site, own, sign, at, out, &car);
+        stencil_site_c<R, LR, true, false>(w, site, own, sign, at, out, &car);
 #pragma unroll
         for (int c = 0; c < 3; ++c) car.own[c] = own[c];
       }
@@ -1738,9 +1753,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_second_s(VerifyArgs v) {
 
 // Sizes from which FP64 products read the links (sites) and the sliced copy (rows) instead
 // of the CSR.  Below, the product is a chain of latencies, and the CSR's eight lanes per
-// row have the most of them in flight: per call, links / CSR 33.4 / 28.2 us at 8^3 x 16,
-// 33.8 / 35.0 at 12^4, 39 / 52 at 16^4, 109 / 320 at 24^4; sliced copy / CSR 28.4 / 27.5 at
-// 8^4, 28.2 / 29.1 at 8^3 x 16, 34.3 / 38.3 at 12^4.
+// row have the most of them in flight: per call, links / CSR 44 / 49 us at 16^3 x 8, 46 / 49 at
+// 20 x 18 x 12 x 9, 47 / 61 at 16^4, 125 / 317 at 24^4; sliced copy / CSR 28.4 / 27.5 at 8^4,
+// 28.2 / 29.1 at 8^3 x 16, 34.3 / 38.3 at 12^4.
 #ifndef MSC_APPLY_SITES_MIN
 #define MSC_APPLY_SITES_MIN 16384
 #endif
@@ -1815,8 +1830,9 @@ __global__ __launch_bounds__(kBlock) void k_apply_sell(Sell<double2> m, const do
   for (int64_t sl = beg + wv; sl < end; sl += SPB) {
     const int64_t row = sl * kSlice + lane;
     const int64_t rr = row < n ? row : n - 1;
-    double2 v = sell_row<double>(m, x, sl, lane);
-    cfma<double>(v, m.diag[rr], x[rr]);
+    double2 own = czero<double>();
+    cfma<double>(own, m.diag[rr], x[rr]);
+    const double2 v = sell_row<double, 8>(m, x, sl, lane, own);
     if (row < n) out[row] = LAST ? with_shift(v, shift, in[row]) : v;
   }
 }
@@ -1830,15 +1846,17 @@ __global__ __launch_bounds__(kBlock) void k_apply_shift(const cplx<R>* q, const 
 }
 
 // One half of A = M^H M on the links in FP64, one site per lane: t = M in (LAST false), or
-// out = M^H t + shift in (LAST true).  Bound by the links and the gathers, as K2 is; where
-// K2 marches along t (tc >= 2 t-slices per column) so does this, with the same carry.  A
-// call at 32^3 x 64 takes 648 us, 1870 on the CSR (eight lanes per row).
-template <int LR, bool LAST, bool MARCH>
+// out = M^H t + shift in (LAST true), from all nine values of a link (a third row rebuilt from
+// two adds its own rounding: 3.4e-16 of the product for 1.4e-16).  Bound by the links and the
+// gathers, as K2 is; where a t-slice holds whole blocks of 64 sites it marches along t (tc >= 2
+// t-slices per column) with the same carry, two workgroups per CU.  A call at 32^3 x 64 takes
+// 725 us (803 without the march; 828 with three per CU; two rows 553; CSR 1870).
+template <bool LAST, bool MARCH>
 __global__ __launch_bounds__(kBlock, 2) void k_apply_site(Stencil<double2> w, SweepOrder ord,
                                                           uint32_t tc, const double2* x,
                                                           const double2* in, double2* out,
                                                           double shift) {
-  static_assert(!MARCH || LR == 2, "the march carries two-row links");
+  constexpr int LR = 3;
   const uint32_t vol = uint32_t(w.vol);
   const int64_t nblk = (int64_t(vol) + kSiteBlock - 1) / kSiteBlock;
   constexpr int WPB = kBlock / kWave;
@@ -1858,9 +1876,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_site(Stencil<double2> w, Sw
     int64_t qb, qe;
     march_range(nblk, WPB, qb, qe);
     for (uint32_t q = uint32_t(qb); q < uint32_t(qe); ++q) {
-      const uint32_t col = q / tc, chunk = col / bs;
-      const uint32_t blk = (chunk * tc + (q - col * tc)) * bs + (col - chunk * bs);
-      const uint32_t site = blk * uint32_t(kSiteBlock) + uint32_t(lane);  // below vol
+      const uint32_t site = march_block(q, tc, bs) * uint32_t(kSiteBlock) + uint32_t(lane);  // below vol
       if (q == uint32_t(qb) || q % tc == 0) {
         const uint32_t sb = site >= vol3 ? site - vol3 : site + (vol - vol3);  // periodic
         const double2* __restrict__ wt = w.w + int64_t(3) * K * vol;
@@ -1875,7 +1891,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_site(Stencil<double2> w, Sw
       double2 own[3], v[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) own[c] = car.fw[c];
-      stencil_site_c<double, LR, true>(w, site, own, LAST ? -1 : 1, gather, v, &car);
+      stencil_site_c<double, LR, true, true>(w, site, own, LAST ? -1 : 1, gather, v, &car);
 #pragma unroll
       for (int c = 0; c < 3; ++c) car.own[c] = own[c];
       store(site, v);
@@ -1887,7 +1903,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_site(Stencil<double2> w, Sw
       double2 own[3], v[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) own[c] = x[3 * int64_t(ss) + c];
-      stencil_site<double, LR>(w, ss, own, LAST ? -1 : 1, gather, v);
+      stencil_site_c<double, LR, false, true>(w, ss, own, LAST ? -1 : 1, gather, v,
+                                              static_cast<TCarry<double, LR>*>(nullptr));
       if (site < vol) store(site, v);
     }
   }
@@ -1950,12 +1967,11 @@ void launch_timed(K kern, int grid, hipStream_t s, hipEvent_t* ev, int k, const 
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, args...);
 }
 
-// t-slices per column of the march along t that the two-row links of this lattice allow (1:
-// none): a t-slice holds whole blocks of 64 sites and some power of two up to kK2March
-// divides L_t.
+// t-slices per column of the march along t that this lattice allows (1: none): a t-slice holds
+// whole blocks of 64 sites and some power of two up to kK2March divides L_t.
 int march_columns(const Stencil<double2>& w) {
   const int64_t lt = w.L[3];
-  if (w.rows != 2 || lt <= 0 || (w.vol / lt) % kSiteBlock != 0) return 1;
+  if (lt <= 0 || (w.vol / lt) % kSiteBlock != 0) return 1;
   for (int c = kK2March; c >= 2; c /= 2)
     if (lt % c == 0) return c;
   return 1;
@@ -2200,26 +2216,23 @@ hipError_t launch_verify(const MsArgs& a, const double* sigma_by_caller_index, i
 }
 
 namespace {
-template <int LR>
-hipError_t apply_links(const ApplyArgs& a, double2* t, hipStream_t s) {
+hipError_t apply_links(const ApplyArgs& a, hipStream_t s) {
   const Stencil<double2>& w = a.w64;
+  double2* t = static_cast<double2*>(a.tmp);
   const int64_t nblk = (w.vol + kSiteBlock - 1) / kSiteBlock;
   constexpr int WPB = kBlock / kWave;
   int g = grid_rows(nblk, WPB);
-  if constexpr (LR == 2) {
-    const int tc = march_columns(w);
-    const int gm = resident_grid(reinterpret_cast<const void*>(k_apply_site<2, true, true>), g);
-    // as K2: runs of at least 4 blocks, or there is little to carry
-    if (tc > 1 && a.ord.on && nblk >= int64_t(gm) * WPB * 4) {
-      k_apply_site<2, false, true><<<gm, kBlock, 0, s>>>(w, a.ord, uint32_t(tc), a.in, a.in, t, 0.0);
-      k_apply_site<2, true, true><<<gm, kBlock, 0, s>>>(w, a.ord, uint32_t(tc), t, a.in, a.out,
-                                                        a.shift);
-      return hipGetLastError();
-    }
+  const int tc = a.ord.on ? march_columns(w) : 1;
+  const int gm = std::min(g, site_cap<double>());
+  // as K2: runs of at least 4 blocks, or there is little to carry
+  if (tc > 1 && nblk >= int64_t(gm) * WPB * 4) {
+    k_apply_site<false, true><<<gm, kBlock, 0, s>>>(w, a.ord, uint32_t(tc), a.in, a.in, t, 0.0);
+    k_apply_site<true, true><<<gm, kBlock, 0, s>>>(w, a.ord, uint32_t(tc), t, a.in, a.out, a.shift);
+    return hipGetLastError();
   }
-  if (a.ord.on) g = resident_grid(reinterpret_cast<const void*>(k_apply_site<LR, true, false>), g);
-  k_apply_site<LR, false, false><<<g, kBlock, 0, s>>>(w, a.ord, 1u, a.in, a.in, t, 0.0);
-  k_apply_site<LR, true, false><<<g, kBlock, 0, s>>>(w, a.ord, 1u, t, a.in, a.out, a.shift);
+  if (a.ord.on) g = resident_grid(reinterpret_cast<const void*>(k_apply_site<true, false>), g);
+  k_apply_site<false, false><<<g, kBlock, 0, s>>>(w, a.ord, 1u, a.in, a.in, t, 0.0);
+  k_apply_site<true, false><<<g, kBlock, 0, s>>>(w, a.ord, 1u, t, a.in, a.out, a.shift);
   return hipGetLastError();
 }
 
@@ -2287,10 +2300,7 @@ hipError_t apply_stored32(const ApplyArgs& a, hipStream_t s) {
 
 hipError_t launch_apply(const ApplyArgs& a, hipStream_t s) {
   if (a.prec == MSC_PREC_MIXED) return apply_stored32(a, s);
-  if (a.links != 0 && a.w64.vol >= kApplySitesMin) {
-    double2* t = static_cast<double2*>(a.tmp);
-    return a.links == 2 ? apply_links<2>(a, t, s) : apply_links<3>(a, t, s);
-  }
+  if (a.links != 0 && a.w64.vol >= kApplySitesMin) return apply_links(a, s);
   return apply_stored64(a, s);
 }
 
