@@ -225,7 +225,7 @@ __device__ __forceinline__ void site_product(const BatchSys& S, const cplx<R>* _
 #pragma unroll
   for (int c = 0; c < 3; ++c) own[c] = vq[c * vol + t.site];
   auto at = [&](uint32_t s, int c) { return vq[c * vol + s]; };
-  if (S.links == 2)
+  if ((std::is_same<R, float>::value ? S.links32 : S.links) == 2)
     stencil_site<R, 2>(w, t.site, own, sign, at, out);
   else
     stencil_site<R, 3>(w, t.site, own, sign, at, out);

@@ -314,6 +314,16 @@ MsArgs make_args(msc_op op, int lanes, const double* d_b, double* d_x) {
   return a;
 }
 
+// Whether the batched CG and the batched solve read two rows per link in precision `prec`.
+// Links count as SU(3) up to 1e-12, far below what complex64 resolves.  In FP64 a third row
+// rebuilt from the others would be that far from M's own, so there only links that are SU(3) to
+// a few roundings are read so; nine values for all cost the 64-system batch 84 -> 95 ms and
+// ten right-hand sides at 16^4 28 -> 31.
+constexpr double kSu3Rounding = 4e-15;
+bool two_row_links(msc_op op, int prec) {
+  return op->two_rows && (prec == MSC_PREC_MIXED || op->su3_dev <= kSu3Rounding);
+}
+
 // The operator's matrices for one product (vectors, shift and temporary left to fill).
 ApplyArgs apply_args(msc_op op, int prec, int lanes) {
   ApplyArgs a{};
@@ -792,9 +802,10 @@ msc_status run_batched_cg(msc_op op, int prec, int m, const double* sig, const d
   // the multishift does
   a.sell = op->sell && prm.format != MSC_FORMAT_CSR ? 1 : 0;
   if (op->stencil && (prm.format == MSC_FORMAT_AUTO || prm.format == MSC_FORMAT_STENCIL)) {
-    a.links = op->two_rows ? 2 : 3;
-    a.w64 = op->two_rows ? op->wc64 : op->w64;
-    a.w32 = op->two_rows ? op->wc32 : op->w32;
+    const bool two = two_row_links(op, prec);
+    a.links = two ? 2 : 3;
+    a.w64 = two ? op->wc64 : op->w64;
+    a.w32 = two ? op->wc32 : op->w32;
   }
   if (a.sell) {
     const bool narrow = prm.format != MSC_FORMAT_SELL32;
@@ -1173,9 +1184,11 @@ struct BatchRun {
         }
       }
       if (use_links && op->stencil) {
-        S.links = op->two_rows ? 2 : 3;
-        S.w64 = op->two_rows ? op->wc64 : op->w64;
-        S.w32 = op->two_rows ? op->wc32 : op->w32;
+        const bool two64 = two_row_links(op, MSC_PREC_FP64), two32 = two_row_links(op, MSC_PREC_MIXED);
+        S.links = two64 ? 2 : 3;
+        S.links32 = two32 ? 2 : 3;
+        S.w64 = two64 ? op->wc64 : op->w64;
+        S.w32 = two32 ? op->wc32 : op->w32;
         S.vlinks = 3;
         S.v64 = op->w64;
       }
@@ -1523,7 +1536,7 @@ struct BatchRun {
           double bytes = 0.0;
           for (int ph = 0; ph < 2; ++ph) {
             const int prec = ph ? MSC_PREC_MIXED : MSC_PREC_FP64;
-            MatBytes mb = mat_bytes(op->kind, prec, nn, nz, nzh, ib, ibh, sys[s].links);
+            MatBytes mb = mat_bytes(op->kind, prec, nn, nz, nzh, ib, ibh, ph ? sys[s].links32 : sys[s].links);
             mb.m /= double(nrhs[s]);
             mb.mh /= double(nrhs[s]);
             bytes += batch_bytes(prec, nn, mb, h.n_upd[q][ph], ph ? it - i64 : i64, h.n_kept[q][ph]);
@@ -1576,6 +1589,7 @@ msc_status refresh_two_rows(msc_op op, const double2* d_links, hipStream_t s) {
   double dev = 0.0;
   std::memcpy(&dev, &bits, sizeof dev);
   op->two_rows = false;
+  op->su3_dev = dev;
   if (!(dev <= kSu3Tol)) return MSC_OK;
   if (!op->wc64.w) {
     double2* w64 = nullptr;

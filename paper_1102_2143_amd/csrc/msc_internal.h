@@ -247,6 +247,7 @@ struct msc_op_s {
   bool stencil = false;          // matrix-free staggered operator (links kept below)
   msc::Stencil<double2> w64;     // W_mu(x) = eta_mu(x)/2 U_mu(x), complex128 and
   msc::Stencil<float2> w32;      // complex64 copies (device memory owned by the op)
+  double su3_dev = 1.0;          // largest deviation of a link from SU(3)
   bool two_rows = false;         // every link is in SU(3): the iteration reads wc64 / wc32,
   msc::Stencil<double2> wc64;    // the first two rows of each W_mu(x) (6 values), and
   msc::Stencil<float2> wc32;     // rebuilds the third from them
@@ -610,7 +611,7 @@ struct BatchSys {
   int sell;               // the SpMVs read the system's sliced ELLPACK copies below
   Sell<double2> s64, sh64;
   Sell<float2> s32, sh32;
-  int links;              // link rows read in place of a stored copy (2 or 3), or 0
+  int links, links32;     // link rows read in place of a stored copy, FP64 and complex64 (2 or 3), or 0
   int vlinks;             // the same for the FP64 products of updates and verification
   Stencil<double2> w64, v64;
   Stencil<float2> w32;
