@@ -381,6 +381,21 @@ HalfBytes half_bytes(bool one, int prec, double n, const MatBytes& mb) {
   return {mb.m + 2.0 * w * n, mb.mh + 5.0 * w * n};
 }
 
+// The deviation of P from its short form beyond which an iteration without the direction takes
+// it up (multishift.hip).  Ordinary lattices and grids (condition up to 1e6) stay below 1e-13 in
+// FP64 and 3e-4 in complex64.  Steps of a 60 x 60 grid with a penalty of 1e8 / 1e10 / 1e12 / 1e14 on
+// an edge, FP64: 473 / 476 / 478 / 479, as with the direction from the start (without it at
+// all 516 / 567 / 687 / none); 1e4 / 1e6 / 1e8 in complex64: 468 / 482 / 570 (none without it).
+constexpr double kDevLimit64 = 1e-9, kDevLimit32 = 1e-2;
+// Largest deviation of the FP64 phase of a mixed solve for which the complex64 phase, whose
+// rounding is 5e8 times as large, starts without the direction.
+constexpr double kDevSwitch = 2e-12;
+// An FP64 sequence that has met its limit goes on where the driving system's true residual is
+// above it by more than rounding leaves: this factor, and 1e-13 |b|; while that helps, and at
+// most kGoOn times.
+constexpr double kTrueSlack = 1.02, kTrueFloor = 1e-13;
+constexpr int kGoOn = 4;
+
 // Bytes of applying composed steps: x_j (complex128) and p_j in and out, the kept residuals.
 double flush_bytes(int prec, double n, double shifts, double kept) {
   const double w = prec == MSC_PREC_MIXED ? 8.0 : 16.0;
@@ -474,6 +489,8 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
       a32.stencil = 3;
   }
   const bool mixed = prec == MSC_PREC_MIXED;
+  a64.dev_limit = kDevLimit64;
+  a32.dev_limit = kDevLimit32;
   prepare_iteration(MSC_PREC_FP64, a64);
   if (mixed) {
     set_vectors<float2>(a32, op, op->ws.ring32, op->ws.u32, op->ws.s32, op->ws.pk32);
@@ -508,6 +525,7 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
 
   const int G = std::max(1, prm.poll_every);
   const int steps = std::min(std::max(int(prm.update_steps), 1), kMaxSteps);
+  const bool small = a64.small && prm.timing <= 0;
   int phase = MSC_PREC_FP64;
   MsArgs* cur = &a64;
   int launched = 0, chunk = 0, launched_at_switch = -1, iter_at_switch = -1;
@@ -516,96 +534,167 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
   EventPool pool;
   std::vector<int> sample_launch;
   std::vector<char> sample_flush;  // the sampled iteration applied composed steps
-  while (!done) {
-    for (int g = 0; g < G;) {
-      hipEvent_t* ev = nullptr;
-      cur->sample = -1;
-      // consecutive launches are sampled in runs as long as a folding cycle (the iterations
-      // that compose and the one that applies), in both phases of a mixed solve;
-      // the FP64 phase of a mixed solve takes at most half of the records
-      const int cap = mixed && phase == MSC_PREC_FP64 ? kMaxSamples / 2 : kMaxSamples;
-      if (prm.timing > 0 && launched % prm.timing < std::max(2, prm.update_steps) &&
-          int(sample_launch.size()) < cap) {
-        ev = pool.next();
-        if (!ev) {
-          set_error("msc_solve: event creation failed");
-          return MSC_EHIP;
+  int resumed = 0;                 // times the halted sequence went on with the direction
+  int dir_from[2] = {-1, -1};      // per phase, the step it was taken up at
+  int useful = -1;                 // launches before the first of these
+  double last_true = HUGE_VAL;
+  // Go on from the halted state, its steps applied, with the direction and with r_n formed anew
+  // from x_0 in FP64.
+  auto take_direction = [&]() -> msc_status {
+    HIP_TRY(launch_final_flush(phase, *cur, s));
+    ApplyArgs ap = apply_args(op, MSC_PREC_FP64, lanes);
+    ap.in = cur->x + int64_t(order[0]) * op->n;
+    ap.out = op->ws.u64;
+    ap.shift = h.sigma0;
+    ap.tmp = op->ws.t64;
+    HIP_TRY(launch_apply(ap, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    __atomic_store_n(op->ws.h_halt, 0, __ATOMIC_RELEASE);
+    int at = 0;
+    HIP_TRY(hipMemcpy(&at, &op->ws.st->iter, sizeof(int), hipMemcpyDeviceToHost));
+    int& from = dir_from[phase == MSC_PREC_MIXED ? 1 : 0];
+    if (from < 0) from = at;
+    if (useful < 0)
+      useful = std::max(0, launched_at_switch) + at - std::max(0, iter_at_switch);
+    const bool load = cur->dir == 0;
+    cur->dir = 1;
+    cur->par = launched & 1;
+    cur->launch = launched;
+    cur->flushed = 0;
+    cur->resume = 1;
+    HIP_TRY(launch_direction(phase, *cur, load, ap.out, s));
+    ++resumed;
+    chunk = 0;
+    pending = 0;
+    return MSC_OK;
+  };
+  // FP64 true residuals |b - (A + sigma_k) x_k| / |b| of every shift, or of the driving one
+  auto true_residuals = [&](bool all, std::vector<double>& rel) -> msc_status {
+    const double bn = std::sqrt(h.bnorm2);
+    const int first = all ? 0 : order[0], last = all ? ns : first + 1;
+    for (int k0 = first; k0 < last; k0 += 8)
+      HIP_TRY(launch_verify(a64, op->sigma.data(), k0, std::min(8, last - k0), op->ws.u64, s));
+    std::vector<double> r2(ns);
+    HIP_TRY(hipMemcpyAsync(r2.data(), op->scratch.res2, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    rel.assign(ns, 0.0);
+    for (int k = first; k < last; ++k) rel[k] = bn > 0 ? std::sqrt(r2[k]) / bn : 0.0;
+    return MSC_OK;
+  };
+  for (;;) {
+    while (!done) {
+      for (int g = 0; g < G;) {
+        hipEvent_t* ev = nullptr;
+        cur->sample = -1;
+        // consecutive launches are sampled in runs as long as a folding cycle (the iterations
+        // that compose and the one that applies), in both phases of a mixed solve;
+        // the FP64 phase of a mixed solve takes at most half of the records
+        const int cap = mixed && phase == MSC_PREC_FP64 ? kMaxSamples / 2 : kMaxSamples;
+        if (prm.timing > 0 && resumed == 0 && launched % prm.timing < std::max(2, prm.update_steps) &&
+            int(sample_launch.size()) < cap) {
+          ev = pool.next();
+          if (!ev) {
+            set_error("msc_solve: event creation failed");
+            return MSC_EHIP;
+          }
+          cur->sample = int(sample_launch.size());
+          sample_launch.push_back(launched);
+          sample_flush.push_back(pending + 1 >= steps ? 1 : 0);
         }
-        cur->sample = int(sample_launch.size());
-        sample_launch.push_back(launched);
-        sample_flush.push_back(pending + 1 >= steps ? 1 : 0);
+        // launch `launched` takes its iteration's state from rot[launched & 1]; in the complex64
+        // phase the reliable update (r recomputed in FP64, with x_0 brought up to date) is
+        // launched every kRuCheck-th iteration and on its period: it runs on the period, or at
+        // a check when the recursive residual has fallen fast
+        cur->launch = launched;
+        cur->par = launched & 1;
+        const int since = launched - launched_at_switch;
+        const bool ru_period = phase == MSC_PREC_MIXED && prm.reliable_every > 0 && since > 0 &&
+                               since % prm.reliable_every == 0;
+        const bool ru = ru_period || (phase == MSC_PREC_MIXED && prm.reliable_every > 0 &&
+                                      since > 0 && since % kRuCheck == 0);
+        cur->ru_force = ru_period ? 1 : 0;
+        cur->ru_check = ru ? 1 : 0;
+        // a small lattice: the iterations up to the next application, poll or update in one launch
+        int span = 1;
+        cur->span = 0;
+        if (small && !cur->dir) {
+          auto update = [&](int k) {
+            return phase == MSC_PREC_MIXED && prm.reliable_every > 0 &&
+                   (k % prm.reliable_every == 0 || k % kRuCheck == 0);
+          };
+          while (span < std::min(G - g, steps - pending) && !update(since + span)) ++span;
+          cur->span = span;
+        }
+        pending += span;
+        const bool flush = pending >= steps;
+        HIP_TRY(launch_iteration(phase, *cur, s, ev, flush));
+        if (flush) pending = 0;
+        cur->flushed = flush ? 1 : 0;
+        cur->resume = 0;
+        launched += span;
+        g += span;
       }
-      // launch `launched` takes its iteration's state from rot[launched & 1]; in the complex64
-      // phase the reliable update (r recomputed in FP64, with x_0 brought up to date) is
-      // launched every kRuCheck-th iteration and on its period: it runs on the period, or at
-      // a check when the recursive residual has fallen fast
-      cur->launch = launched;
-      cur->par = launched & 1;
-      const int since = launched - launched_at_switch;
-      const bool ru_period = phase == MSC_PREC_MIXED && prm.reliable_every > 0 && since > 0 &&
-                             since % prm.reliable_every == 0;
-      const bool ru = ru_period || (phase == MSC_PREC_MIXED && prm.reliable_every > 0 &&
-                                    since > 0 && since % kRuCheck == 0);
-      cur->ru_force = ru_period ? 1 : 0;
-      cur->ru_check = ru ? 1 : 0;
-      // a small lattice: the iterations up to the next application, poll or update in one launch
-      int span = 1;
-      if (cur->small && prm.timing <= 0) {
-        auto update = [&](int k) {
-          return phase == MSC_PREC_MIXED && prm.reliable_every > 0 &&
-                 (k % prm.reliable_every == 0 || k % kRuCheck == 0);
-        };
-        while (span < std::min(G - g, steps - pending) && !update(since + span)) ++span;
-        cur->span = span;
-      }
-      pending += span;
-      const bool flush = pending >= steps;
-      HIP_TRY(launch_iteration(phase, *cur, s, ev, flush));
-      if (flush) pending = 0;
-      cur->flushed = flush ? 1 : 0;
-      launched += span;
-      g += span;
-    }
-    const int slot = chunk & 1;
-    HIP_TRY(hipEventRecord(op->ws.ev[slot], s));
-    ++chunk;
-    if (chunk >= 2) {
-      HIP_TRY(hipEventSynchronize(op->ws.ev[slot ^ 1]));
-      // halt | switch_req << 1 of the newest state a kernel has written: at least as recent
-      // as the end of that chunk (within a phase the halt only ever gets set)
-      const int f = __atomic_load_n(op->ws.h_halt, __ATOMIC_ACQUIRE);
-      if (f & 1) {
-        if ((f & 2) && phase == MSC_PREC_FP64 && mixed) {
-          // end of the FP64 phase: drain, convert the Krylov vectors, continue in complex64
-          HIP_TRY(hipStreamSynchronize(s));
-          __atomic_store_n(op->ws.h_halt, 0, __ATOMIC_RELEASE);
-          HIP_TRY(hipMemcpy(&iter_at_switch, &op->ws.st->iter, sizeof(int), hipMemcpyDeviceToHost));
-          HIP_TRY(launch_final_flush(MSC_PREC_FP64, a64, s));
-          a64.par = a32.par = launched & 1;
-          a32.launch = launched;
-          HIP_TRY(launch_switch_to_mixed(a64, a32, ns, s));
-          phase = MSC_PREC_MIXED;
-          cur = &a32;
-          launched_at_switch = launched;
-          chunk = 0;
-          pending = 0;
-        } else {
-          done = true;
+      const int slot = chunk & 1;
+      HIP_TRY(hipEventRecord(op->ws.ev[slot], s));
+      ++chunk;
+      if (chunk >= 2) {
+        HIP_TRY(hipEventSynchronize(op->ws.ev[slot ^ 1]));
+        // halt | switch_req << 1 of the newest state a kernel has written: at least as recent
+        // as the end of that chunk (within a phase the halt only ever gets set)
+        const int f = __atomic_load_n(op->ws.h_halt, __ATOMIC_ACQUIRE);
+        if (f & 1) {
+          if (f & 4) {
+            rc = take_direction();
+            if (rc != MSC_OK) return rc;
+          } else if ((f & 2) && phase == MSC_PREC_FP64 && mixed) {
+            // end of the FP64 phase: drain, convert the Krylov vectors, continue in complex64
+            HIP_TRY(hipStreamSynchronize(s));
+            __atomic_store_n(op->ws.h_halt, 0, __ATOMIC_RELEASE);
+            HIP_TRY(hipMemcpy(&iter_at_switch, &op->ws.st->iter, sizeof(int), hipMemcpyDeviceToHost));
+            double dev = 0.0;
+            HIP_TRY(hipMemcpy(&dev, &op->ws.st->dev, sizeof dev, hipMemcpyDeviceToHost));
+            HIP_TRY(launch_final_flush(MSC_PREC_FP64, a64, s));
+            a64.par = a32.par = launched & 1;
+            a32.launch = launched;
+            a32.dir = a64.dir || dev > kDevSwitch ? 1 : 0;
+            if (a32.dir) dir_from[1] = iter_at_switch;
+            HIP_TRY(launch_switch_to_mixed(a64, a32, ns, s));
+            phase = MSC_PREC_MIXED;
+            cur = &a32;
+            launched_at_switch = launched;
+            chunk = 0;
+            pending = 0;
+          } else {
+            done = true;
+          }
         }
       }
+      if (launched >= int64_t(h.max_iter) + 4 * int64_t(G) * (1 + resumed)) done = true;
     }
-    if (launched >= int64_t(h.max_iter) + 4 * int64_t(G)) done = true;
+    HIP_TRY(launch_final_flush(phase, *cur, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(hipMemcpy(&h, op->ws.st, sizeof h, hipMemcpyDeviceToHost));
+    rel_out->assign(ns, 0.0);
+    const bool check = !mixed && !(prm.verify && prm.refine) && h.iter > 0 && h.R <= h.eps2 && resumed < kGoOn;
+    if (h.status != 0 || !(prm.verify || check)) break;
+    rc = true_residuals(prm.verify != 0, *rel_out);
+    if (rc != MSC_OK) return rc;
+    const double rel0 = (*rel_out)[order[0]];
+    if (!prm.verify) rel_out->assign(ns, 0.0);
+    if (!check || !(rel0 > kTrueSlack * std::max(tol_stop, kTrueFloor)) || !(rel0 < 0.25 * last_true)) break;
+    last_true = rel0;
+    rc = take_direction();
+    if (rc != MSC_OK) return rc;
+    done = false;
   }
-  HIP_TRY(launch_final_flush(phase, *cur, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  HIP_TRY(hipMemcpy(&h, op->ws.st, sizeof h, hipMemcpyDeviceToHost));
   const int iters = h.iter;
   const int iters_fp64 = iter_at_switch >= 0 ? iter_at_switch : iters;
   if (info) {
     clear_timing(*info);
     // only iterations that did work are counted (the loop runs a little past the halt)
     const int first = launched_at_switch >= 0 ? launched_at_switch : 0;
-    const int useful_launches = first + (iters - (iter_at_switch >= 0 ? iter_at_switch : 0));
+    const int useful_launches =
+        useful >= 0 ? useful : first + (iters - (iter_at_switch >= 0 ? iter_at_switch : 0));
     const bool one = a64.sell && op->kind != MSC_A_MHM;  // a single kernel an iteration
     const double nn = double(op->n), nz = double(op->nnz), nzh = double(op->nnz_h);
     for (size_t q = 0; q < pool.groups.size(); ++q) {
@@ -652,7 +741,10 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
   auto phase_bytes = [&](int ph, const MsArgs& a, double count, int q) {
     const HalfBytes hb = half_bytes(a.sell && op->kind != MSC_A_MHM, ph, nn,
                                     mat_bytes(op->kind, ph, nn, nz, nzh, ib, ibh, a.stencil));
-    return count * (hb.k1 + hb.k2) + flush_bytes(ph, nn, h.n_upd[q], h.n_kept[q]);
+    // the direction's update reads r and p and writes p; K2 then writes no s, but x_0 in and out
+    const double dir_steps = dir_from[q] < 0 ? 0.0 : (q ? iters : iters_fp64) - dir_from[q];
+    return count * (hb.k1 + hb.k2) + dir_steps * (2.0 * (q ? 8.0 : 16.0) + 32.0) * nn +
+           flush_bytes(ph, nn, h.n_upd[q], h.n_kept[q]);
   };
   // a reliable update reads the FP64 operator, x_0, b and s and writes r
   const MatBytes rb = mat_bytes(op->kind, MSC_PREC_FP64, nn, nz, nzh, ib, ibh, a32.stencil);
@@ -661,18 +753,8 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
                double(h.n_reliable) * (rb.m + rb.mh + nn * (16.0 * 3 + 8.0 * 2));
   if (info) info->iters_fp64 = iters_fp64;
 
-  rel_out->assign(ns, 0.0);
   *bnorm_out = std::sqrt(h.bnorm2);
   if (prm.verify && h.status == 0) {
-    const double bn = std::sqrt(h.bnorm2);
-    for (int k0 = 0; k0 < ns; k0 += 8) {
-      const int kc = std::min(8, ns - k0);
-      HIP_TRY(launch_verify(a64, op->sigma.data(), k0, kc, op->ws.u64, s));
-    }
-    std::vector<double> r2(ns);
-    HIP_TRY(hipMemcpyAsync(r2.data(), op->scratch.res2, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    for (int k = 0; k < ns; ++k) (*rel_out)[k] = bn > 0 ? std::sqrt(r2[k]) / bn : 0.0;
     const double nvec = op->kind == MSC_A_MHM ? 2.0 : 1.0;
     *bytes_out += (nz * (16.0 + ib) + nzh * (16.0 + ibh) + nvec * 4.0 * (nn + 1)) * std::ceil(ns / 8.0) +
                   double(op->n) * 16.0 * ns * (op->kind == MSC_A_MHM ? 4.0 : 2.0) + 16.0 * op->n;

@@ -63,11 +63,13 @@ struct SolveState {
   double bnorm2;
   int max_iter, ns, freeze;
   int n_reliable;
-  // reliable update of the iteration at hand: whether it runs, the recursive residual's g_n,
-  // Re(r_n^H (A + sigma0) p_{n-1}) of the replaced residual; g right after the last one (or
-  // the precision switch)
+  // replaced residual of the iteration at hand (reliable update, direction taken up): whether
+  // it was, and the recursive residual's g_n; g right after the last one (or the precision
+  // switch)
   int ru_flag, pad_;
-  double ru_g, ru_c, R_ru;
+  double ru_g, R_ru;
+  double dev;                   // largest deviation of P from its short form (step_plan)
+  double g_n, c_n;              // summed by K1 for K2 (multishift.hip)
   double s[kMaxShifts];         // sigma_j - sigma0
   int freeze_iter[kMaxShifts];
   int orig[kMaxShifts];         // caller's index of sorted shift j
@@ -75,6 +77,7 @@ struct SolveState {
   // breakdown
   int fin, iter, status, pad2_;
   double R, eps2;
+  double c;                     // Re(r_n^H s_{n-1}) there
   RotState rot[2];
   // per sampled iteration (MsArgs::sample) that applied its steps: shifts listed and
   // residuals read; per phase (0: FP64, 1: complex64) the sums over all applications
@@ -307,7 +310,7 @@ struct MsArgs {
   Csr<double2> m64, mh64;
   Csr<float2> m32, mh32;
   int launch, par;       // the launch, and its parity: its iteration's state is st->rot[par]
-  int gd, gg;            // workgroups that leave partials of d_n (K1) and of g_n (K2)
+  int gd, gg;            // workgroups that leave partials of d_n (K1) and of g_n, c_n (K2)
   int sell;              // K1/K2 read the sliced ELLPACK copies below
   int64_t nslices;
   Sell<double2> s64, sh64;
@@ -318,7 +321,10 @@ struct MsArgs {
   void* u;               // u = M r (A = M^H M), A r (A given, CSR)
   void *w[2], *s[2];     // A given, sliced copy: w and s alternate; else s[0] alone
   void* pk;              // ns directions, sorted order
-  int* hflag;            // host-coherent word: halt | switch request << 1
+  int* hflag;            // host-coherent word: halt | switch request << 1 | direction request << 2
+  int dir;               // 1: the iterations carry the direction p, in s[0], and x_0
+  int resume;            // 1: the first iteration after launch_direction
+  double dev_limit;      // without it: the deviation of P from which on it is taken up
   int flushed;           // 1: the composed steps were applied after the last iteration
   int ru_force;          // reliable update: 1 runs it whatever the residual
   int ru_check;          // 1: this iteration begins with a reliable update where one is due
@@ -345,6 +351,10 @@ hipError_t launch_init(const MsArgs& a, hipStream_t s);
 hipError_t launch_iteration(int prec, const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool flush);
 // The composed steps of a halted sequence.
 hipError_t launch_final_flush(int prec, const MsArgs& a, hipStream_t s);
+// The halted sequence goes on at a.par and a.launch (after launch_final_flush) carrying its
+// direction (`load`: taken up now, from those of the shifts) and with r_n = b - ax, `ax` being
+// (A + sigma0) x_0.
+hipError_t launch_direction(int prec, const MsArgs& a, bool load, const double2* ax, hipStream_t s);
 // Second phase of a mixed solve: copy r, s, p_j of a64 (complex128) into a32's complex64
 // buffers and re-arm the state at a32.par (after launch_final_flush).
 hipError_t launch_switch_to_mixed(const MsArgs& a64, const MsArgs& a32, int ns, hipStream_t s);

@@ -12,6 +12,20 @@
 // For A given, on the sliced copy, it is one kernel, which forms r_{n+1} at every gathered
 // column and the next w with it; on the CSR, K1 forms w and K2 is elementwise.
 //
+// What s_n = (A + sigma0) p_n and a_n's denominator P = p_n^H (A + sigma0) p_n suppose is that
+// r_n is orthogonal to s's part of the direction before it.  Where A has eigenvalues far above
+// the rest (a stiff constraint on few rows) rounding breaks that: s drifts from its product and
+// P from its form (in complex64 from a condition of about 1e7 on, in FP64 far beyond).  K2
+// therefore also sums c_n = Re(r_n^H s_{n-1}), from which
+//   P = d_n + b_n (2 c_n + b_n P_{n-1})
+// is the form of the vectors held, and the sequence takes the direction up as soon as P has
+// left its short form: k_dir updates p_n = r_n + b_n p_{n-1} (from the driving system's p_0,
+// which the applications keep), K1 and K2 form s_n and P from it, and a breakdown is reported
+// only where that P is not positive.  So does an FP64 sequence whose x_0 misses the tolerance
+// that its recursive residual has met.  Steps, shifts and their scalars go on as they were.
+// Measured deviations |P - short form| / P: below 1e-13 in FP64 and 3e-4 in complex64 on lattices
+// and grids of condition 1e6; a penalty of 1e4 on one edge of a 60 x 60 grid 4e-11 and above 1.
+//
 // Nothing reads x_j and p_j but their own update, so K2 only composes each step: the
 // coefficients of x_j's increment and of p_j against the first pending step's p_j and the
 // residuals of the steps, which stay in a ring.  Every update_steps-th iteration (eight), a
@@ -236,7 +250,7 @@ __device__ __forceinline__ double sum_partials(const double* partial, int count,
 
 // ---- the iteration's reductions ------------------------------------------------------
 // One partial per workgroup: of g_n in region n % 2, of d_n (|u|^2, or r^H w) in region
-// 2 + n % 2; the reliable update's in 4 and 5.  The consuming kernel's workgroups each add
+// 2 + n % 2, of c_n in 6 + n % 2; the reliable update's in 4 and 5.  The consuming kernel's workgroups each add
 // all of them up in the same order; the producer was another kernel, so plain loads do.
 __device__ __forceinline__ double* region(const MsArgs& a, int k) {
   return a.sc.partial + k * kMaxGrid;
@@ -247,58 +261,101 @@ __device__ __forceinline__ void store_partial(double* reg, double acc) {
   if (threadIdx.x == 0) store_agent(&reg[blockIdx.x], tot);
 }
 
-// Partials are loaded early (four per thread and region, covering grids of up to 1024
-// workgroups) so that their round trip overlaps the caller's own first loads.
+// K2's: g_{n+1} and, without the direction, c_{n+1}.
+template <bool DIR> __device__ __forceinline__ void store_k2(const MsArgs& a, double g, double c) {
+  const int nx = a.par ^ 1;
+  if constexpr (DIR) {
+    store_partial(region(a, nx), g);
+  } else {
+    double v[2] = {g, c};
+    block_sum_k<kBlock, 2>(v);
+    if (threadIdx.x == 0) {
+      store_agent(&region(a, nx)[blockIdx.x], v[0]);
+      store_agent(&region(a, 6 + nx)[blockIdx.x], v[1]);
+    }
+  }
+}
+
+// The sums of `count` partials in each of K regions, in every thread (the same in every workgroup).
+template <int K>
+__device__ __forceinline__ void region_sums(const MsArgs& a, const int (&which)[K], int count,
+                                            double (&v)[K]) {
+  __shared__ double total[K];
+  constexpr int U = 4;  // in flight together
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = 0.0;
+  for (int i0 = threadIdx.x; i0 < count; i0 += U * kBlock) {
+    double w[K][U];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[k][u] = i0 + u * kBlock < count ? region(a, which[k])[i0 + u * kBlock] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[k] += w[k][u];
+    }
+  }
+  block_sum_k<kBlock, K>(v);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) total[k] = v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = total[k];
+}
+
+// The work of K1's extra workgroup, the last: g_n and c_n for K2, which then sums d_n alone.
+__device__ __forceinline__ bool k1_totals(const MsArgs& a) {
+  if (int(blockIdx.x) != a.gd) return false;
+  const int which[2] = {a.par, 6 + a.par};
+  double v[2];
+  region_sums(a, which, a.gg, v);
+  if (threadIdx.x == 0) {
+    a.st->g_n = v[0];
+    a.st->c_n = v[1];
+  }
+  return true;
+}
+
+// K1's partials are loaded early (four per thread, covering grids of up to 1024 workgroups)
+// so that their round trip overlaps the caller's own first loads.
 constexpr int kEarly = 4;
 struct Early {
-  double g[kEarly], d[kEarly];
+  double d[kEarly];
 };
 
 __device__ __forceinline__ void load_early(const MsArgs& a, Early& e) {
-  const double *rg = region(a, a.par), *rd = region(a, 2 + a.par);
+  const double* rd = region(a, 2 + a.par);
 #pragma unroll
   for (int u = 0; u < kEarly; ++u) {
     const int i = threadIdx.x + u * kBlock;
-    e.g[u] = i < a.gg ? rg[i] : 0.0;
     e.d[u] = i < a.gd ? rd[i] : 0.0;
   }
 }
 
-// g_n and r_n^H A r_n in every thread.
-__device__ __forceinline__ void both_sums(const MsArgs& a, const Early& e, double& g, double& d) {
-  __shared__ double total[2];
-  const double *rg = region(a, a.par), *rd = region(a, 2 + a.par);
-  double v[2] = {0.0, 0.0};
-#pragma unroll
-  for (int u = 0; u < kEarly; ++u) {
-    v[0] += e.g[u];
-    v[1] += e.d[u];
-  }
-  for (int i = threadIdx.x + kEarly * kBlock; i < a.gg; i += kBlock) v[0] += rg[i];
-  for (int i = threadIdx.x + kEarly * kBlock; i < a.gd; i += kBlock) v[1] += rd[i];
-  block_sum_k<kBlock, 2>(v);
-  if (threadIdx.x == 0) {
-    total[0] = v[0];
-    total[1] = v[1];
-  }
-  __syncthreads();
-  g = total[0];
-  d = total[1];
-}
+// g_n, d_n of K1's vector and c_n (of no use with the direction).
+struct Sums {
+  double g, d, c;
+};
 
 // Step n's scalars, the same in every workgroup.
 struct StepPlan {
   double a, b;  // a_n, b_n
   double P;     // p_n^H (A + sigma0) p_n
+  double off;   // |P - its short form|
   int stop;     // 0: step n runs; 1: converged or at the limit; 2: end of the FP64 phase of
-                // a mixed solve; 3: breakdown (P <= 0 or not finite: A + sigma0 not PD)
+                // a mixed solve; 3: breakdown (P <= 0 or not finite: A + sigma0 not PD);
+                // 4: the direction is to be taken up
 };
 
 // What the step needs of the state, read before the partials are summed.
 struct StepIn {
   double g1, a1, P1;           // g_{n-1}, a_{n-1}, P_{n-1}
   double bn2, tol2, sw2, sigma0;
-  double ru_g, ru_c;
+  double ru_g;
   int n, halt, max_iter, ru;
 };
 
@@ -316,30 +373,75 @@ __device__ __forceinline__ StepIn step_in(const MsArgs& a) {
   i.sw2 = st->sw2;
   i.sigma0 = st->sigma0;
   i.max_iter = st->max_iter;
-  i.ru = a.ru_check ? st->ru_flag : 0;
+  i.ru = a.ru_check || a.resume ? st->ru_flag : 0;
   i.ru_g = st->ru_g;
-  i.ru_c = st->ru_c;
   return i;
 }
 
-// d: r_n^H A r_n.  After a reliable update has replaced r_n, b_n keeps the recursive
-// residual's g_n (the direction is the sequence's) and P takes r_n^H (A + sigma0) p_{n-1} as
-// measured (ru_c): the shorter form of P supposes a residual orthogonal to the direction
-// before it.
-__device__ __forceinline__ StepPlan step_plan(const StepIn& i, double g, double d) {
-  d += i.sigma0 * g;
+// In every thread.  ONE: one kernel an iteration, which left all partials itself.
+template <bool ONE>
+__device__ __forceinline__ Sums all_sums(const MsArgs& a, const Early& e) {
+  if constexpr (ONE) {
+    const int which[3] = {a.par, 2 + a.par, 6 + a.par};
+    double v[3];
+    region_sums(a, which, a.gg, v);
+    return Sums{v[0], v[1], v[2]};
+  }
+  __shared__ double total;
+  // K1's totals are read here: held during K2's first product they cost it 15 us of 265 (FP64, 32^3 x
+  // 64: its loads then go out in more parts)
+  const double g = a.st->g_n, c = a.st->c_n;
+  const double* rd = region(a, 2 + a.par);
+  double d = 0.0;
+#pragma unroll
+  for (int u = 0; u < kEarly; ++u) d += e.d[u];
+  for (int i = threadIdx.x + kEarly * kBlock; i < a.gd; i += kBlock) d += rd[i];
+  d = block_sum<kBlock>(d);
+  if (threadIdx.x == 0) total = d;
+  __syncthreads();
+  return Sums{g, total, c};
+}
+
+// b_n: where r_n was replaced it keeps the recursive residual's g_n (the direction is the
+// sequence's).
+__device__ __forceinline__ double step_b(const StepIn& i, double g) {
+  return i.n == 0 ? 0.0 : (i.ru ? i.ru_g : g) / i.g1;
+}
+
+// Converged, at the limit, at the end of the FP64 phase, or |r|^2 not finite.
+__device__ __forceinline__ bool step_ends(const StepIn& i, double g, double bn2) {
+  return !isfinite(g) || g <= i.tol2 * bn2 || i.n >= i.max_iter || g <= i.sw2 * bn2;
+}
+
+// t.d: with the direction P itself, else r_n^H A r_n.  The short form of P supposes c_n = -b_n
+// P_{n-1}, which a replaced r_n never fulfils; it is taken where c_n is not known (has_c).
+__device__ __forceinline__ StepPlan step_plan(const MsArgs& a, const StepIn& i, const Sums& t,
+                                              bool has_c = true) {
+  const double g = t.g;
   const double bn2 = i.n == 0 ? g : i.bn2;
   StepPlan p;
-  p.b = i.n == 0 ? 0.0 : (i.ru ? i.ru_g : g) / i.g1;
-  p.P = i.n == 0 ? d : (i.ru ? d + p.b * (2.0 * i.ru_c + p.b * i.P1) : d - p.b * g / i.a1);
+  p.b = step_b(i, g);
+  p.P = t.d;
+  p.off = 0.0;
+  if (!a.dir) {
+    p.P += i.sigma0 * g;
+    if (i.n > 0) {
+      const double plain = p.P - p.b * g / i.a1;
+      p.P = has_c ? p.P + p.b * (2.0 * t.c + p.b * i.P1) : plain;
+      if (!i.ru) p.off = fabs(p.P - plain);
+    }
+  }
   p.a = g / p.P;
   const bool ok = p.P > 0.0 && isfinite(p.P);
-  // |r|^2 first: an infinite |b|^2 would pass for its own limit
-  p.stop = !isfinite(g)                             ? 3
-           : g <= i.tol2 * bn2 || i.n >= i.max_iter ? 1
-           : !ok                                    ? 3
-           : g <= i.sw2 * bn2                       ? 2
-                                                    : 0;
+  p.stop = 0;
+  if (step_ends(i, g, bn2) || !ok || !(p.off <= a.dev_limit * p.P)) {
+    // |r|^2 first: an infinite |b|^2 would pass for its own limit
+    p.stop = !isfinite(g)                             ? 3
+             : g <= i.tol2 * bn2 || i.n >= i.max_iter ? 1
+             : (a.dir || i.n == 0) && !ok             ? 3
+             : g <= i.sw2 * bn2                       ? 2
+                                                      : 4;
+  }
   return p;
 }
 
@@ -408,21 +510,23 @@ struct ShiftSteps {
   }
 };
 
-__device__ __forceinline__ void sequence_halts(const MsArgs& a, int fin, int n, double g, double eps2,
-                                               int stop) {
+__device__ __forceinline__ void sequence_halts(const MsArgs& a, int fin, int n, const Sums& t,
+                                               double eps2, int stop) {
   SolveState* st = a.st;
   st->fin = fin;
   st->iter = n;
-  st->R = g;
+  st->R = t.g;
+  st->c = t.c;
   st->eps2 = eps2;
   st->status = stop == 3 ? 1 : 0;
-  store_host_flag(a.hflag, 1 | (stop == 2 ? 2 : 0));
+  store_host_flag(a.hflag, 1 | (stop == 2 ? 2 : 0) | (stop == 4 ? 4 : 0));
 }
 
 // The work of K2's extra workgroup: the shifts' scalars of step n (wave 0, lane j: shift
 // j): freezing, then, when the step runs, zeta^(n+1), a_j and b_j, composed with the
 // pending steps; the state of iteration n + 1, or of the halted sequence.  On small
 // operators it is the longest chain of the iteration: all it reads is read before the sums.
+template <bool ONE>
 __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in, const Early& e) {
   SolveState* st = a.st;
   const RotState& rs = st->rot[a.par];
@@ -432,9 +536,9 @@ __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in
   ShiftSteps h;
   if (mine) h.load(rs, st->s[j], j);
   const int m = rs.m, fresh = rs.fresh, freeze = st->freeze;
-  double g, d;
-  both_sums(a, e, g, d);
-  const StepPlan p = step_plan(in, g, d);
+  const Sums t = all_sums<ONE>(a, e);
+  const double g = t.g;
+  const StepPlan p = step_plan(a, in, t);
   if (j >= kWave) return;
   // a flush since the last step leaves nothing pending
   const bool flushed = a.flushed || in.ru;
@@ -455,31 +559,32 @@ __device__ __forceinline__ void plan_workgroup(const MsArgs& a, const StepIn& in
     nx.m = live ? m0 + 1 : m0;
     nx.fresh = flushed ? 0 : fresh;
     nx.halt = live ? 0 : 1;
-    if (!live) sequence_halts(a, a.par ^ 1, n, g, eps2, p.stop);
+    if (live && p.off > st->dev * p.P) st->dev = p.off / p.P;
+    if (!live) sequence_halts(a, a.par ^ 1, n, t, eps2, p.stop);
   }
 }
 
 // K2's prologue: true in a workgroup that goes on to the rows (with e and in loaded); a
 // halted iteration hands the halt on, the extra workgroup does the plan.
+template <bool ONE = false>
 __device__ __forceinline__ bool k2_begin(const MsArgs& a, Early& e, StepIn& in) {
-  load_early(a, e);
+  if (!ONE) load_early(a, e);
   in = step_in(a);
   if (int(blockIdx.x) != a.gg) return true;
   if (in.halt) {
     if (threadIdx.x == 0) a.st->rot[a.par ^ 1].halt = 1;
   } else {
-    plan_workgroup(a, in, e);
+    plan_workgroup<ONE>(a, in, e);
   }
   return false;
 }
 
 // The sums and the step in every other workgroup; false where no step runs.
+template <bool ONE = false>
 __device__ __forceinline__ bool k2_step(const MsArgs& a, const Early& e, const StepIn& in, StepPlan& p) {
   p.stop = 1;
   if (in.halt) return false;
-  double g, d;
-  both_sums(a, e, g, d);
-  p = step_plan(in, g, d);
+  p = step_plan(a, in, all_sums<ONE>(a, e));
   return p.stop == 0;
 }
 
@@ -501,38 +606,82 @@ __device__ __forceinline__ void march_range(int64_t n, int wpb, int64_t& beg, in
 }
 
 // s_n = q + sigma0 r + b s, r_{n+1} = r - a s_n at one row (q = (A r_n)_row), formed in FP64
-// and rounded once each.
-template <class R>
+// and rounded once each.  DIR: q = (A p_n)_row and s is p_n there, s_n = q + sigma0 p_n.
+template <class R, bool DIR = false>
 __device__ __forceinline__ void row_step(const StepPlan& p, double sigma0, const cplx<R>& q,
                                          const cplx<R>& r, const cplx<R>& s, cplx<R>& sn,
                                          cplx<R>& rn) {
   const double2 qd = to_d(q), rd = to_d(r), sd = to_d(s);
-  const double2 v{fma(p.b, sd.x, fma(sigma0, rd.x, qd.x)), fma(p.b, sd.y, fma(sigma0, rd.y, qd.y))};
+  const double2 v = DIR ? double2{fma(sigma0, sd.x, qd.x), fma(sigma0, sd.y, qd.y)}
+                        : double2{fma(p.b, sd.x, fma(sigma0, rd.x, qd.x)),
+                                  fma(p.b, sd.y, fma(sigma0, rd.y, qd.y))};
   sn = from_d<R>(v);
   rn = from_d<R>(double2{fma(-p.a, v.x, rd.x), fma(-p.a, v.y, rd.y)});
 }
 
+// K1's vector: r_n, or p_n.
+template <class R, bool DIR> __device__ __forceinline__ const cplx<R>* k1_vec(const MsArgs& a) {
+  return DIR ? static_cast<const cplx<R>*>(a.s[0]) : rslot<R>(a, a.launch);
+}
+
+// K1's term of one row, u = (M v)_row or (A v)_row: v^H A v's, with sigma0 |v|^2's where v = p_n.
+template <class R, bool MHM, bool DIR>
+__device__ __forceinline__ double k1_term(const cplx<R>& u, const cplx<R>& v, double sigma0) {
+  const double t = MHM ? norm2d<R>(u) : double(v.x) * double(u.x) + double(v.y) * double(u.y);
+  return DIR ? fma(sigma0, norm2d<R>(v), t) : t;
+}
+
+// x_0 += a_n p_n at one row: with the direction the driving system's own x takes each step as it
+// is (composed, its increments would differ from A^-1 of s's by rounding that stiff rows blow up).
+template <class R>
+__device__ __forceinline__ void x0_step(double2* x0, int64_t row, double a, const cplx<R>& p) {
+  const double2 pd = to_d(p), x = x0[row];
+  x0[row] = double2{fma(a, pd.x, x.x), fma(a, pd.y, x.y)};
+}
+__device__ __forceinline__ double2* x0_of(const MsArgs& a) {
+  return a.x + int64_t(a.st->orig[0]) * a.n;
+}
+
+// c's term of one row.
+template <class R>
+__device__ __forceinline__ double c_term(const cplx<R>& rn, const cplx<R>& sn) {
+  return fma(double(rn.x), double(sn.x), double(rn.y) * double(sn.y));
+}
+
+// p_n = r_n + b_n p_{n-1}, in the order of the ring, where step n may run.
+template <class R> __global__ __launch_bounds__(kBlock) void k_dir(MsArgs a) {
+  const StepIn in = step_in(a);
+  if (in.halt) return;
+  const int which[1] = {a.par};
+  double g[1];
+  region_sums(a, which, a.gg, g);
+  if (step_ends(in, g[0], in.n == 0 ? g[0] : in.bn2)) return;
+  const double b = step_b(in, g[0]);
+  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.s[0]);
+  for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < a.n; i += int64_t(gridDim.x) * kBlock) {
+    const double2 rd = to_d(r[i]), pd = to_d(p[i]);
+    p[i] = from_d<R>(double2{fma(b, pd.x, rd.x), fma(b, pd.y, rd.y)});
+  }
+}
+
 // ---- A = M^H M or the CSR: K1 u = M r_n (A r_n for A given) and d_n's partials -----------
-template <class R, int L, bool MHM>
+template <class R, int L, bool MHM, bool DIR>
 __global__ __launch_bounds__(kBlock) void k1_csr(MsArgs a) {
   const RotState& rs = a.st->rot[a.par];
-  if (rs.halt) return;
+  if (rs.halt || k1_totals(a)) return;
   const Csr<cplx<R>> m = pick_m<R>(a);
-  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const cplx<R>* __restrict__ r = k1_vec<R, DIR>(a);
+  const double sigma0 = a.st->sigma0;
   cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
   constexpr int GPB = kBlock / L;
   const int lane = threadIdx.x % L, grp = threadIdx.x / L;
   int64_t beg, end;
-  block_range(a.n, GPB, beg, end);
+  block_range(a.n, GPB, beg, end, a.gd);
   double acc = 0.0;
   auto epilogue = [&](int64_t row, const cplx<R>& v) {
     u[row] = v;
-    if (MHM) {
-      acc += norm2d<R>(v);
-    } else {
-      const cplx<R> rr = r[row];
-      acc += double(rr.x) * double(v.x) + double(rr.y) * double(v.y);
-    }
+    acc += k1_term<R, MHM, DIR>(v, MHM && !DIR ? v : r[row], sigma0);
   };
   for (int64_t row = beg + grp; row < end; row += 2 * GPB) {
     const int64_t row1 = row + GPB;
@@ -547,8 +696,8 @@ __global__ __launch_bounds__(kBlock) void k1_csr(MsArgs a) {
   store_partial(region(a, 2 + a.par), acc);
 }
 
-// K2: w = M^H u (u itself for A given), s_n, r_{n+1}, g_{n+1}'s partials.
-template <class R, int L, bool MHM>
+// K2: w = M^H u (u itself for A given), s_n, r_{n+1}, g_{n+1}'s and c_{n+1}'s partials.
+template <class R, int L, bool MHM, bool DIR>
 __global__ __launch_bounds__(kBlock) void k2_csr(MsArgs a) {
   Early e;
   StepIn in;
@@ -559,15 +708,20 @@ __global__ __launch_bounds__(kBlock) void k2_csr(MsArgs a) {
   const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
   cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
   cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  double2* __restrict__ x0 = x0_of(a);
   const double sigma0 = in.sigma0;
   int64_t beg, end;
-  double acc = 0.0;
+  double acc = 0.0, ac = 0.0;
   auto epilogue = [&](int64_t row, const cplx<R>& q) {
     cplx<R> sv, nv;
-    row_step<R>(p, sigma0, q, r[row], s[row], sv, nv);
-    s[row] = sv;
+    row_step<R, DIR>(p, sigma0, q, r[row], s[row], sv, nv);
+    if (DIR)
+      x0_step<R>(x0, row, p.a, s[row]);
+    else
+      s[row] = sv;
     rn[row] = nv;
     acc += norm2d<R>(nv);
+    if (!DIR) ac += c_term<R>(nv, sv);
   };
   if constexpr (MHM) {
     const Csr<cplx<R>> mh = pick_mh<R>(a);
@@ -588,20 +742,22 @@ __global__ __launch_bounds__(kBlock) void k2_csr(MsArgs a) {
     block_range(a.n, kBlock, beg, end, a.gg);
     for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) epilogue(i, u[i]);
   }
-  store_partial(region(a, a.par ^ 1), acc);
+  store_k2<DIR>(a, acc, ac);
 }
 
 // ---- the sliced ELLPACK copies: one row per lane, one slice per wave ----------------------
-template <class R>
+// (A given, MHM false: with the direction only, with the CSR's K2; else k_herm below)
+template <class R, bool MHM, bool DIR>
 __global__ __launch_bounds__(kBlock) void k1_sell(MsArgs a) {
   const RotState& rs = a.st->rot[a.par];
-  if (rs.halt) return;
+  if (rs.halt || k1_totals(a)) return;
   const Sell<cplx<R>> m = pick_sm<R>(a);
-  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const cplx<R>* __restrict__ r = k1_vec<R, DIR>(a);
+  const double sigma0 = a.st->sigma0;
   cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
   const int lane = threadIdx.x % kSlice;
   double acc = 0.0;
-  for (Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice); sw.more(); sw.next()) {
+  for (Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice, a.gd); sw.more(); sw.next()) {
     const int64_t sl = sw.slice();
     const int64_t row = sl * kSlice + lane;
     const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
@@ -610,13 +766,13 @@ __global__ __launch_bounds__(kBlock) void k1_sell(MsArgs a) {
     cfma<R>(v, d, own);
     if (row < a.n) {
       u[row] = v;
-      acc += norm2d<R>(v);
+      acc += k1_term<R, MHM, DIR>(v, own, sigma0);
     }
   }
   store_partial(region(a, 2 + a.par), acc);
 }
 
-template <class R>
+template <class R, bool DIR>
 __global__ __launch_bounds__(kBlock) void k2_sell(MsArgs a) {
   Early e;
   StepIn in;
@@ -626,6 +782,7 @@ __global__ __launch_bounds__(kBlock) void k2_sell(MsArgs a) {
   const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
   cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
   cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  double2* __restrict__ x0 = x0_of(a);
   const double sigma0 = in.sigma0;
   const int lane = threadIdx.x % kSlice;
   struct Row {
@@ -644,15 +801,19 @@ __global__ __launch_bounds__(kBlock) void k2_sell(MsArgs a) {
     return o;
   };
   StepPlan p;
-  double acc = 0.0;
+  double acc = 0.0, ac = 0.0;
   auto epilogue = [&](int64_t sl, const Row& o) {
     const int64_t row = sl * kSlice + lane;
     if (row >= a.n) return;
     cplx<R> sv, nv;
-    row_step<R>(p, sigma0, o.q, o.r, o.s, sv, nv);
-    st_stream(&s[row], sv);
+    row_step<R, DIR>(p, sigma0, o.q, o.r, o.s, sv, nv);
+    if (DIR)
+      x0_step<R>(x0, row, p.a, o.s);
+    else
+      st_stream(&s[row], sv);
     rn[row] = nv;
     acc += norm2d<R>(nv);
+    if (!DIR) ac += c_term<R>(nv, sv);
   };
   // the first slice's product runs while the partials are on their way
   Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice, a.gg);
@@ -666,7 +827,7 @@ __global__ __launch_bounds__(kBlock) void k2_sell(MsArgs a) {
     const int64_t sl = sw.slice();
     epilogue(sl, product(sl));
   }
-  store_partial(region(a, a.par ^ 1), acc);
+  store_k2<DIR>(a, acc, ac);
 }
 
 // A given: one kernel.  r_{n+1} is formed at every gathered column from r, w and s, rounded
@@ -713,9 +874,9 @@ __device__ __forceinline__ cplx<R> sell_row_any(const Sell<cplx<R>>& m, int64_t 
 template <class R> __global__ __launch_bounds__(kBlock) void k_herm(MsArgs a) {
   Early e;
   StepIn in;
-  if (!k2_begin(a, e, in)) return;
+  if (!k2_begin<true>(a, e, in)) return;
   StepPlan p;
-  if (!k2_step(a, e, in, p)) return;
+  if (!k2_step<true>(a, e, in, p)) return;
   const Sell<cplx<R>> m = pick_sm<R>(a);
   const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
   cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
@@ -730,7 +891,7 @@ template <class R> __global__ __launch_bounds__(kBlock) void k_herm(MsArgs a) {
     row_step<R>(p, sigma0, w[c], r[c], s[c], sv, nv);
     return nv;
   };
-  double ag = 0.0, ad = 0.0;
+  double ag = 0.0, ad = 0.0, ac = 0.0;
   for (Sweep sw = make_sweep(a.nslices, a.ord, kBlock / kSlice, a.gg); sw.more(); sw.next()) {
     const int64_t sl = sw.slice();
     const int64_t row = sl * kSlice + lane;
@@ -745,14 +906,15 @@ template <class R> __global__ __launch_bounds__(kBlock) void k_herm(MsArgs a) {
       sn[row] = sv;
       wn[row] = v;
       ag += norm2d<R>(own);
-      ad += double(own.x) * double(v.x) + double(own.y) * double(v.y);
+      ad += k1_term<R, false, false>(v, own, 0.0);
+      ac += c_term<R>(own, sv);
     }
   }
-  double v[2] = {ag, ad};
-  block_sum_k<kBlock, 2>(v);
+  double v[3] = {ag, ad, ac};
+  block_sum_k<kBlock, 3>(v);
   if (threadIdx.x == 0) {
-    store_agent(&region(a, a.par ^ 1)[blockIdx.x], v[0]);
-    store_agent(&region(a, 2 + (a.par ^ 1))[blockIdx.x], v[1]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) store_agent(&region(a, (k < 2 ? 2 * k : 6) + (a.par ^ 1))[blockIdx.x], v[k]);
   }
 }
 
@@ -803,7 +965,7 @@ __device__ __forceinline__ uint32_t march_block(uint32_t q, uint32_t tc, uint32_
   return (chunk * tc + (q - col * tc)) * bs + (col - chunk * bs);
 }
 
-// body(site, out) for this wave's sites, out = (m + sign D) v there; lanes past the volume
+// body(site, out, own) for this wave's sites, out = (m + sign D) v and own = v there; lanes past the volume
 // are left out.  first(): called once by every wave of the workgroup, between its first
 // product (if it has any) and the rest; false ends the work.  g: workgroups that share the
 // sites.
@@ -850,7 +1012,7 @@ __device__ __forceinline__ void for_sites(const MsArgs& a, const Stencil<cplx<R>
       }
       if (q == uint32_t(qb) && !first()) return;
       if (!has) return;
-      body(site, out);
+      body(site, out, own);
     }
   } else {
     Sweep sw = make_sweep(nblk, a.ord, WPB, g);
@@ -867,37 +1029,39 @@ __device__ __forceinline__ void for_sites(const MsArgs& a, const Stencil<cplx<R>
       }
       if (begin && !first()) return;
       if (!has) return;
-      if (site < vol) body(site, out);
+      if (site < vol) body(site, out, own);
     }
   }
 }
 
 // STREAM (FP64): u goes out with streaming stores (32^3 x 64: 240 -> 235 us; in complex64
 // they make no difference).
-template <class R, int LR, bool STREAM, bool MARCH>
+template <class R, int LR, bool STREAM, bool MARCH, bool DIR>
 __global__ __launch_bounds__(kBlock, 2) void k1_site(MsArgs a) {
   static_assert(!MARCH || LR == 2, "the march carries two-row links");
   // looked at after the first block's product: its loads do not wait for the state
   const int halt = a.st->rot[a.par].halt;
+  if (k1_totals(a)) return;
   const Stencil<cplx<R>> w = pick_w<R>(a);
   cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
+  const double sigma0 = a.st->sigma0;
   double acc = 0.0;
   for_sites<R, LR, MARCH>(
-      a, w, rslot<R>(a, a.launch), 1, gridDim.x, [&] { return halt == 0; },
-      [&](uint32_t site, const cplx<R>(&out)[3]) {
+      a, w, k1_vec<R, DIR>(a), 1, a.gd, [&] { return halt == 0; },
+      [&](uint32_t site, const cplx<R>(&out)[3], const cplx<R>(&own)[3]) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           if constexpr (STREAM)
             st_stream(&u[c * w.vol + site], out[c]);
           else
             u[c * w.vol + site] = out[c];
-          acc += norm2d<R>(out[c]);
+          acc += k1_term<R, true, DIR>(out[c], own[c], sigma0);
         }
       });
   if (!halt) store_partial(region(a, 2 + a.par), acc);
 }
 
-template <class R, int LR, bool MARCH>
+template <class R, int LR, bool MARCH, bool DIR>
 __global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
   static_assert(!MARCH || LR == 2, "the march carries two-row links");
   Early e;
@@ -907,26 +1071,37 @@ __global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
   const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
   cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
   cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  double2* __restrict__ x0 = x0_of(a);
   const double sigma0 = in.sigma0;
   StepPlan p;
-  double acc = 0.0;
+  double acc = 0.0, ac = 0.0;
   for_sites<R, LR, MARCH>(
       a, w, static_cast<const cplx<R>*>(a.u), -1, a.gg,
       // the first block's product runs while the partials are on their way
       [&] { return k2_step(a, e, in, p); },
-      [&](uint32_t site, const cplx<R>(&out)[3]) {
+      [&](uint32_t site, const cplx<R>(&out)[3], const cplx<R>(&)[3]) {
+        cplx<R> ro[3], so[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          ro[c] = ld_stream(&r[c * w.vol + site]);
+          so[c] = ld_stream(&s[c * w.vol + site]);
+        }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const int64_t i = c * w.vol + site;
           cplx<R> sv, nv;
-          row_step<R>(p, sigma0, out[c], ld_stream(&r[i]), ld_stream(&s[i]), sv, nv);
-          st_stream(&s[i], sv);
+          row_step<R, DIR>(p, sigma0, out[c], ro[c], so[c], sv, nv);
+          if (DIR)
+            x0_step<R>(x0, 3 * int64_t(site) + c, p.a, so[c]);
+          else
+            st_stream(&s[i], sv);
           st_stream(&rn[i], nv);
           acc += norm2d<R>(nv);
+          if (!DIR) ac += c_term<R>(nv, sv);
         }
       });
   if (p.stop) return;
-  store_partial(region(a, a.par ^ 1), acc);
+  store_k2<DIR>(a, acc, ac);
 }
 
 // ---- the links of small lattices: one direction per wave --------------------------------------
@@ -939,19 +1114,19 @@ __global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
 // 15.6 -> 14.9; 4^4 now has a form of its own below).
 template <class R> using DirParts = cplx<R>[4][3][kWave];
 
-// (m + sign D) v at this thread's row of block `blk` (thread t < 192: colour t / 64 of site t %
+// (m + sign D) v, and v itself (own), at this thread's row of block `blk` (thread t < 192: colour t / 64 of site t %
 // 64; live: the row exists), after a barrier of its own; the caller's rows are free to use
 // `part` again once every thread has passed the next one.
 template <class R, int LR>
 __device__ __forceinline__ cplx<R> split_row(const Stencil<cplx<R>>& w, const cplx<R>* __restrict__ v,
-                                             int sign, int64_t blk, DirParts<R>& part) {
+                                             int sign, int64_t blk, DirParts<R>& part, cplx<R>& own) {
   const uint32_t vol = uint32_t(w.vol);
   const int lane = threadIdx.x % kWave;
   const int mu = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
   const uint32_t site = uint32_t(blk * kSiteBlock) + uint32_t(lane);
   const uint32_t ss = site < vol ? site : vol - 1;  // lanes past the volume: unused
   const int c = mu < 3 ? mu : 0;
-  const cplx<R> own = v[int64_t(c) * vol + ss];
+  own = v[int64_t(c) * vol + ss];
   cplx<R> h[3];
   stencil_dir<R, LR>(w, ss, mu, [&](uint32_t s, int k) { return v[int64_t(k) * vol + s]; }, h);
 #pragma unroll
@@ -973,29 +1148,32 @@ __device__ __forceinline__ int64_t split_index(int64_t vol, int64_t blk) {
   return threadIdx.x < 3 * kWave && site < vol ? int64_t(threadIdx.x / kWave) * vol + site : -1;
 }
 
-template <class R, int LR>
+template <class R, int LR, bool DIR>
 __global__ __launch_bounds__(kBlock) void k1_split(MsArgs a) {
   const int halt = a.st->rot[a.par].halt;
+  if (k1_totals(a)) return;
   const Stencil<cplx<R>> w = pick_w<R>(a);
-  const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const cplx<R>* __restrict__ r = k1_vec<R, DIR>(a);
+  const double sigma0 = a.st->sigma0;
   cplx<R>* __restrict__ u = static_cast<cplx<R>*>(a.u);
   const int64_t nblk = (w.vol + kSiteBlock - 1) / kSiteBlock;
   __shared__ DirParts<R> part;
   double acc = 0.0;
-  for (int64_t blk = logical_block(); blk < nblk; blk += gridDim.x) {
-    const cplx<R> v = split_row<R, LR>(w, r, 1, blk, part);
+  for (int64_t blk = logical_block(a.gd); blk < nblk; blk += a.gd) {
+    cplx<R> own;
+    const cplx<R> v = split_row<R, LR>(w, r, 1, blk, part, own);
     if (halt) return;
     const int64_t i = split_index(w.vol, blk);
     if (i >= 0) {
       u[i] = v;
-      acc += norm2d<R>(v);
+      acc += k1_term<R, true, DIR>(v, own, sigma0);
     }
     __syncthreads();
   }
   store_partial(region(a, 2 + a.par), acc);
 }
 
-template <class R, int LR>
+template <class R, int LR, bool DIR>
 __global__ __launch_bounds__(kBlock) void k2_split(MsArgs a) {
   Early e;
   StepIn in;
@@ -1005,32 +1183,41 @@ __global__ __launch_bounds__(kBlock) void k2_split(MsArgs a) {
   const cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
   cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + 1);
   cplx<R>* __restrict__ s = static_cast<cplx<R>*>(a.s[0]);
+  double2* __restrict__ x0 = x0_of(a);
   const int64_t nblk = (w.vol + kSiteBlock - 1) / kSiteBlock;
   __shared__ DirParts<R> part;
   StepPlan p;
   p.stop = -1;
-  double acc = 0.0;
+  double acc = 0.0, ac = 0.0;
   for (int64_t blk = logical_block(a.gg); blk < nblk; blk += a.gg) {
     const int64_t i = split_index(w.vol, blk);
     const cplx<R> rv = i >= 0 ? r[i] : czero<R>(), sv = i >= 0 ? s[i] : czero<R>();
-    const cplx<R> q = split_row<R, LR>(w, u, -1, blk, part);
+    cplx<R> own;
+    const cplx<R> q = split_row<R, LR>(w, u, -1, blk, part, own);
     if (p.stop < 0 && !k2_step(a, e, in, p)) return;
     if (i >= 0) {
       cplx<R> sn, nv;
-      row_step<R>(p, in.sigma0, q, rv, sv, sn, nv);
-      s[i] = sn;
+      row_step<R, DIR>(p, in.sigma0, q, rv, sv, sn, nv);
+      if (DIR)  // i is colour by colour
+        x0_step<R>(x0, 3 * (i % w.vol) + i / w.vol, p.a, sv);
+      else
+        s[i] = sn;
       rn[i] = nv;
       acc += norm2d<R>(nv);
+      if (!DIR) ac += c_term<R>(nv, sn);
     }
     __syncthreads();
   }
-  store_partial(region(a, a.par ^ 1), acc);
+  store_k2<DIR>(a, acc, ac);
 }
 
 // ---- the smallest lattices: several iterations in one workgroup ---------------------------------
 // Four lanes a site, a direction each: a lane keeps its link and forms both products with
 // it; r and u lie in LDS, so an iteration's halves and sums are four barriers apart instead
-// of two kernels.  The shifts' scalars of all a.span steps follow at the end, a shift per
+// of two kernels.  c_n is summed at the end of a launch (in every step it costs registers that
+// are not there, and the direction from the start a barrier: 2.53 and 2.10 ms for the solve at
+// 4^4 that takes 1.98), so P's form is looked at once in up to eight steps; where it is not
+// positive in between, the direction is taken up there, by the pair of kernels.  The shifts' scalars of all a.span steps follow at the end, a shift per
 // lane; the state goes on as from a.span launches of the pair.  For lattices whose sites one
 // workgroup holds (256): an iteration in FP64 and mixed at 4^4 11.2 and 11.8 us with the
 // pair, 6.7 and 7.3 here, of which 1.6 are the launches and the applications; two sites a
@@ -1125,12 +1312,20 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(MsArgs a) {
     const R m = R(w.mass);
     return cplx<R>{fma(m, own.x, sign > 0 ? q.x : -q.x), fma(m, own.y, sign > 0 ? q.y : -q.y)};
   };
-  double v = 0.0;
-  for (int i = tid; i < a.gg; i += kSmallBlock) v += region(a, a.par)[i];
+  double v = 0.0, c = 0.0;
+  for (int i = tid; i < a.gg; i += kSmallBlock) {
+    v += region(a, a.par)[i];
+    c += region(a, 6 + a.par)[i];
+  }
+  c = group_sum<kWave>(c);
+  if (tid % kWave == 0) part[0][tid / kWave] = c;
   double g = small_sum(v, part[1]);  // and r is in LDS
+  c = 0.0;
+#pragma unroll
+  for (int i = 0; i < kSmallBlock / kWave; ++i) c += part[0][i];
   const int n0 = in.n;
   int done = 0, stop = 0;
-  double a1 = in.a1;
+  double a1 = in.a1, dev = 0.0;
   for (; done < a.span; ++done) {
     double acc = 0.0;
     const cplx<R> uu = product(rl, 1, rr);
@@ -1139,10 +1334,11 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(MsArgs a) {
       acc = norm2d<R>(uu);
     }
     const double d = small_sum(acc, part[0]);
-    const StepPlan p = step_plan(in, g, d);
+    const StepPlan p = step_plan(a, in, Sums{g, d, c}, done == 0);
     if (in.n == 0) in.bn2 = g;
     stop = p.stop;
     if (stop) break;
+    if (done == 0) dev = p.off / p.P;
     cplx<R>* __restrict__ rn = rslot<R>(a, a.launch + done + 1);
     const cplx<R> q = product(ul, -1, uu);
     acc = 0.0;
@@ -1168,13 +1364,17 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(MsArgs a) {
     in.ru = 0;
   }
   if (row) sg[i0] = ss;
-  for (int i = tid; i < a.gg; i += kSmallBlock) region(a, pe)[i] = i == 0 ? g : 0.0;
+  if (done > 0) c = small_sum(row ? c_term<R>(rr, ss) : 0.0, part[stop ? 1 : 0]);
+  for (int i = tid; i < a.gg; i += kSmallBlock) {
+    region(a, pe)[i] = i == 0 ? g : 0.0;
+    region(a, 6 + pe)[i] = i == 0 ? c : 0.0;
+  }
   if (tid >= kWave) return;
   const int j = tid;
   const RotState& rs = st->rot[a.par];
   RotState& nx = st->rot[pe];
   const int m = rs.m, fresh = rs.fresh;
-  const bool flushed = a.flushed || a.ru_check && st->ru_flag;
+  const bool flushed = a.flushed || (a.ru_check && st->ru_flag);
   const int m0 = flushed ? 0 : m;
   const double eps2 = in.tol2 * in.bn2;
   if (j < st->ns) {
@@ -1200,7 +1400,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(MsArgs a) {
     nx.m = m0 + done;
     nx.fresh = flushed ? 0 : fresh;
     nx.halt = stop ? 1 : 0;
-    if (stop) sequence_halts(a, pe, in.n, g, eps2, stop);
+    if (dev > st->dev) st->dev = dev;
+    if (stop) sequence_halts(a, pe, in.n, Sums{g, 0.0, c}, eps2, stop);
   }
 }
 
@@ -1231,10 +1432,10 @@ __global__ __launch_bounds__(kBlock) void k_flush(MsArgs a, int par, int when) {
   }
   int flushed = a.flushed;
   if (when == 1) {
-    Early e;
-    load_early(a, e);
-    double g, d;
-    both_sums(a, e, g, d);
+    const int which[1] = {a.par};
+    double sum[1];
+    region_sums(a, which, a.gg, sum);
+    const double g = sum[0];
     const bool due = a.ru_force || g < kRuDelta2 * st->R_ru;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       st->ru_flag = due ? 1 : 0;
@@ -1248,7 +1449,8 @@ __global__ __launch_bounds__(kBlock) void k_flush(MsArgs a, int par, int when) {
   __shared__ FlushPlan pl;
   const int j = threadIdx.x;
   if (j < kWave) {
-    const bool list = j < st->ns && ((rs.m > 0 && rs.took[j]) || rs.fresh);
+    // with the direction K2 keeps x_0 and p_0
+    const bool list = j < st->ns && ((rs.m > 0 && rs.took[j]) || rs.fresh) && !(a.dir && j == 0);
     const uint64_t mask = __ballot(list);
     if (list) {
       const int pos = __popcll(mask & ((uint64_t(1) << j) - 1));
@@ -1373,14 +1575,20 @@ __global__ __launch_bounds__(kBlock) void k_switch(MsArgs a64, MsArgs a32, int n
       pk32[idx - n] = from_d<float>(pk[idx - n]);
     }
   }
-  // partials of g: the sum the halted iteration formed
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < kMaxGrid; i += kBlock) region(a64, a64.par)[i] = i ? 0.0 : st->R;
+  // partials of g and c: the sums the halted iteration formed
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < kMaxGrid; i += kBlock) {
+      region(a64, a64.par)[i] = i ? 0.0 : st->R;
+      region(a64, 6 + a64.par)[i] = i ? 0.0 : st->c;
+    }
+  }
 }
 
-// The complex64 phase's state at its first iteration, from the halted one's (which may be
-// the same of the two: a lane reads before it writes).
-__global__ __launch_bounds__(kBlock) void k_switch_state(MsArgs a) {
+// The state of the halted sequence's next iteration, a.launch of parity a.par, from the halted
+// one's (which may be the same of the two: a lane reads before it writes): the complex64
+// phase's first, or (`replaced`) one with the direction taken up, whose r_n may differ from
+// the recursive one.
+__global__ __launch_bounds__(kBlock) void k_go_on(MsArgs a, int replaced) {
   SolveState* st = a.st;
   const RotState& fin = st->rot[st->fin];
   RotState& rs = st->rot[a.par];
@@ -1388,7 +1596,8 @@ __global__ __launch_bounds__(kBlock) void k_switch_state(MsArgs a) {
   if (j < kMaxShifts) {
     rs.zeta[j] = fin.zeta[j];
     rs.zeta_prev[j] = fin.zeta_prev[j];
-    rs.active[j] = fin.active[j];
+    // repeats of the driving shift stopped with it and go on with it
+    rs.active[j] = fin.active[j] || (replaced && j < st->ns && st->s[j] == 0.0);
     rs.took[j] = 0;
   }
   if (j == 0) {
@@ -1400,15 +1609,46 @@ __global__ __launch_bounds__(kBlock) void k_switch_state(MsArgs a) {
     rs.m = 0;
     rs.fresh = 0;
     rs.halt = 0;
-    st->sw2 = 0.0;
-    st->R_ru = st->R;
+    if (replaced) {
+      st->ru_flag = 1;
+      st->ru_g = st->R;
+    } else {
+      st->sw2 = 0.0;
+      st->R_ru = st->R;
+    }
   }
+}
+
+// p_{n-1}, kept as the driving system's direction until now, in the order of the ring.
+template <class R, bool COLOURS> __global__ __launch_bounds__(kBlock) void k_load_p(MsArgs a) {
+  const cplx<R>* __restrict__ pk = static_cast<const cplx<R>*>(a.pk);
+  cplx<R>* __restrict__ p = static_cast<cplx<R>*>(a.s[0]);
+  const int64_t vol = a.n / 3;
+  for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < a.n; i += int64_t(gridDim.x) * kBlock)
+    p[COLOURS ? (i % 3) * vol + i / 3 : i] = pk[i];
+}
+
+// r_n = b - ax into the ring slot of launch a.launch; its g's partials.
+template <class R, bool COLOURS>
+__global__ __launch_bounds__(kBlock) void k_load_r(MsArgs a, const double2* __restrict__ ax) {
+  cplx<R>* __restrict__ r = rslot<R>(a, a.launch);
+  const int64_t vol = a.n / 3;
+  int64_t beg, end;
+  block_range(a.n, kBlock, beg, end);
+  double acc = 0.0;
+  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
+    const double2 bv = a.b[i], av = ax[i];
+    const cplx<R> v = from_d<R>(double2{bv.x - av.x, bv.y - av.y});
+    r[COLOURS ? (i % 3) * vol + i / 3 : i] = v;
+    acc += norm2d<R>(v);
+  }
+  store_partial(region(a, a.par), acc);
 }
 
 // ---- reliable update: r_n = b - (A + sigma0) x_0 in FP64, before iteration n ------------------
 // k_flush has brought x_0 up to date and decided whether it runs (st->ru_flag).  The last
-// workgroup replaces g_n's partials and keeps r_n^H s_{n-1}; a non-finite residual ends the
-// sequence in iteration n (breakdown).
+// workgroup replaces g_n's partials and c_n's (with the direction, which s then is, unused); a
+// non-finite residual ends the sequence in iteration n (breakdown).
 __device__ __forceinline__ bool ru_runs(const MsArgs& a) {
   return a.st->ru_flag != 0 && !a.st->rot[a.par].halt;
 }
@@ -1424,11 +1664,12 @@ __device__ void ru_finish(const MsArgs& a, double acc, double dot) {
   if (!arrive_last(a.sc.tickets + 2 * kTicketSite)) return;
   const double Rt = sum_partials(region(a, 4), gridDim.x, 1, 0);
   const double ct = sum_partials(region(a, 5), gridDim.x, 1, 0);
-  for (int i = threadIdx.x + 1; i < a.gg; i += kBlock) region(a, a.par)[i] = 0.0;
+  for (int i = threadIdx.x; i < a.gg; i += kBlock) {
+    region(a, a.par)[i] = i ? 0.0 : Rt;
+    region(a, 6 + a.par)[i] = i ? 0.0 : ct;
+  }
   if (threadIdx.x == 0) {
-    region(a, a.par)[0] = Rt;
     st->R_ru = Rt;
-    st->ru_c = ct;
     st->n_reliable += 1;
   }
 }
@@ -1985,8 +2226,8 @@ template <class R> constexpr int site_cap() { return std::is_same<R, double>::va
 
 template <class R, int LR, bool MARCH> const void* site_kernel(int half) {
   constexpr bool STREAM = std::is_same<R, double>::value;
-  return half == 1 ? reinterpret_cast<const void*>(k1_site<R, LR, STREAM, MARCH>)
-                   : reinterpret_cast<const void*>(k2_site<R, LR, MARCH>);
+  return half == 1 ? reinterpret_cast<const void*>(k1_site<R, LR, STREAM, MARCH, false>)
+                   : reinterpret_cast<const void*>(k2_site<R, LR, MARCH, false>);
 }
 
 // The grid of a links' half, and whether it marches: it does when every resident wave gets
@@ -2030,8 +2271,8 @@ template <class R> void prepare_impl(MsArgs& a) {
       return a.ord.on ? resident_grid(kern, g) : g;
     };
     if (mhm) {
-      a.gd = grid(reinterpret_cast<const void*>(k1_sell<R>));
-      a.gg = grid(reinterpret_cast<const void*>(k2_sell<R>));
+      a.gd = grid(reinterpret_cast<const void*>(k1_sell<R, true, false>));
+      a.gg = grid(reinterpret_cast<const void*>(k2_sell<R, false>));
     } else {
       a.gd = a.gg = grid(reinterpret_cast<const void*>(k_herm<R>));
     }
@@ -2072,7 +2313,7 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
       k_ru_second_s<R, true><<<gs, kBlock, 0, s>>>(a);
     } else {
       k_ru_second_s<R, false><<<gs, kBlock, 0, s>>>(a);
-      k_herm_w<R><<<a.gd, kBlock, 0, s>>>(a, 1);
+      if (!a.dir) k_herm_w<R><<<a.gd, kBlock, 0, s>>>(a, 1);
     }
     return hipGetLastError();
   }
@@ -2086,60 +2327,91 @@ hipError_t reliable_impl(const MsArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <class R, int LR> void launch_sites(const MsArgs& a, hipStream_t s, hipEvent_t* ev) {
+template <class R, int LR, bool DIR> void launch_sites(const MsArgs& a, hipStream_t s, hipEvent_t* ev) {
   constexpr bool STREAM = std::is_same<R, double>::value;
-  if (a.span > 0) {
-    k_small<R, LR><<<1, kSmallBlock, 0, s>>>(a);
-    return;
-  }
   if (a.split) {
-    launch_timed(k1_split<R, LR>, a.gd, s, ev, 0, a);
-    launch_timed(k2_split<R, LR>, a.gg + 1, s, ev, 1, a);
+    launch_timed(k1_split<R, LR, DIR>, a.gd + 1, s, ev, 0, a);
+    launch_timed(k2_split<R, LR, DIR>, a.gg + 1, s, ev, 1, a);
     return;
   }
   if constexpr (LR == 2) {
     if (a.m1)
-      launch_timed(k1_site<R, 2, STREAM, true>, a.gd, s, ev, 0, a);
+      launch_timed(k1_site<R, 2, STREAM, true, DIR>, a.gd + 1, s, ev, 0, a);
     else
-      launch_timed(k1_site<R, 2, STREAM, false>, a.gd, s, ev, 0, a);
+      launch_timed(k1_site<R, 2, STREAM, false, DIR>, a.gd + 1, s, ev, 0, a);
     if (a.m2)
-      launch_timed(k2_site<R, 2, true>, a.gg + 1, s, ev, 1, a);
+      launch_timed(k2_site<R, 2, true, DIR>, a.gg + 1, s, ev, 1, a);
     else
-      launch_timed(k2_site<R, 2, false>, a.gg + 1, s, ev, 1, a);
+      launch_timed(k2_site<R, 2, false, DIR>, a.gg + 1, s, ev, 1, a);
   } else {
-    launch_timed(k1_site<R, LR, STREAM, false>, a.gd, s, ev, 0, a);
-    launch_timed(k2_site<R, LR, false>, a.gg + 1, s, ev, 1, a);
+    launch_timed(k1_site<R, LR, STREAM, false, DIR>, a.gd + 1, s, ev, 0, a);
+    launch_timed(k2_site<R, LR, false, DIR>, a.gg + 1, s, ev, 1, a);
   }
 }
 
-// One iteration: the reliable update where one is due, the operator halves (K2 has a
-// workgroup more than the rows need), then with `flush` the composed steps.
-template <class R>
-hipError_t iteration_impl(const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool flush) {
-  if (a.ru_check) {
-    const hipError_t e = reliable_impl<R>(a, s);
-    if (e != hipSuccess) return e;
-  }
+// The operator halves (each has a workgroup more than the rows need); with the direction its
+// update goes first.
+template <class R, bool DIR>
+hipError_t halves_impl(const MsArgs& a, hipStream_t s, hipEvent_t* ev) {
   const bool mhm = a.kind == MSC_A_MHM;
+  if (DIR) k_dir<R><<<grid_rows(a.n, kBlock), kBlock, 0, s>>>(a);
   if (a.sell && mhm && a.stencil) {
     if (a.stencil == 2)
-      launch_sites<R, 2>(a, s, ev);
+      launch_sites<R, 2, DIR>(a, s, ev);
     else
-      launch_sites<R, 3>(a, s, ev);
+      launch_sites<R, 3, DIR>(a, s, ev);
   } else if (a.sell && mhm) {
-    launch_timed(k1_sell<R>, a.gd, s, ev, 0, a);
-    launch_timed(k2_sell<R>, a.gg + 1, s, ev, 1, a);
+    launch_timed(k1_sell<R, true, DIR>, a.gd + 1, s, ev, 0, a);
+    launch_timed(k2_sell<R, DIR>, a.gg + 1, s, ev, 1, a);
   } else if (a.sell) {
-    launch_timed(k_herm<R>, a.gg + 1, s, ev, 0, a);
+    if constexpr (DIR) {
+      launch_timed(k1_sell<R, false, true>, a.gd + 1, s, ev, 0, a);
+      launch_timed(k2_csr<R, 4, false, true>, a.gg + 1, s, ev, 1, a);
+    } else {
+      launch_timed(k_herm<R>, a.gg + 1, s, ev, 0, a);
+    }
   } else if (mhm) {
-    MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, true>, a.gd, s, ev, 0, a)));
-    MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_csr<R, LL, true>, a.gg + 1, s, ev, 1, a)));
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, true, DIR>, a.gd + 1, s, ev, 0, a)));
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_csr<R, LL, true, DIR>, a.gg + 1, s, ev, 1, a)));
   } else {
-    MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, false>, a.gd, s, ev, 0, a)));
-    MSC_LANES_SWITCH(a.lanes, (launch_timed(k2_csr<R, LL, false>, a.gg + 1, s, ev, 1, a)));
+    MSC_LANES_SWITCH(a.lanes, (launch_timed(k1_csr<R, LL, false, DIR>, a.gd + 1, s, ev, 0, a)));
+    launch_timed(k2_csr<R, 4, false, DIR>, a.gg + 1, s, ev, 1, a);
   }
-  if (flush) return flush_impl<R>(a, (a.launch + std::max(1, a.span)) & 1, 0, s, ev);
   return hipGetLastError();
+}
+
+// One iteration: the reliable update where one is due, the operator halves, then with `flush`
+// the composed steps.
+template <class R>
+hipError_t iteration_impl(const MsArgs& a, hipStream_t s, hipEvent_t* ev, bool flush) {
+  hipError_t e = a.ru_check ? reliable_impl<R>(a, s) : hipSuccess;
+  if (e != hipSuccess) return e;
+  if (a.span > 0) {
+    if (a.stencil == 2)
+      k_small<R, 2><<<1, kSmallBlock, 0, s>>>(a);
+    else
+      k_small<R, 3><<<1, kSmallBlock, 0, s>>>(a);
+    e = hipGetLastError();
+  } else {
+    e = a.dir ? halves_impl<R, true>(a, s, ev) : halves_impl<R, false>(a, s, ev);
+  }
+  if (e != hipSuccess) return e;
+  return flush ? flush_impl<R>(a, (a.launch + std::max(1, a.span)) & 1, 0, s, ev) : hipSuccess;
+}
+
+template <class R, bool COLOURS>
+void direction_impl(const MsArgs& a, bool load, const double2* ax, hipStream_t s) {
+  if (load) k_load_p<R, COLOURS><<<grid_rows(a.n, kBlock), kBlock, 0, s>>>(a);
+  if (!ax) return;
+  k_load_r<R, COLOURS><<<a.gg, kBlock, 0, s>>>(a, ax);
+  k_go_on<<<1, kBlock, 0, s>>>(a, 1);
+}
+void load_direction(int prec, const MsArgs& a, bool load, const double2* ax, hipStream_t s) {
+  const bool colours = a.sell && a.stencil;
+  if (prec == MSC_PREC_MIXED)
+    colours ? direction_impl<float, true>(a, load, ax, s) : direction_impl<float, false>(a, load, ax, s);
+  else
+    colours ? direction_impl<double, true>(a, load, ax, s) : direction_impl<double, false>(a, load, ax, s);
 }
 
 }  // namespace
@@ -2168,11 +2440,19 @@ hipError_t launch_final_flush(int prec, const MsArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_switch_to_mixed(const MsArgs& a64, const MsArgs& a32, int ns, hipStream_t s) {
-  const bool herm = a64.sell && a64.kind != MSC_A_MHM;
+  const bool herm = a64.sell && a64.kind != MSC_A_MHM && !a64.dir;
   const int g = grid_rows(int64_t(ns + 1) * a64.n, kBlock);
   k_switch<<<g, kBlock, 0, s>>>(a64, a32, ns, herm ? 1 : 0);
-  k_switch_state<<<1, kBlock, 0, s>>>(a32);
-  if (herm) k_herm_w<float><<<a32.gd, kBlock, 0, s>>>(a32, 0);
+  k_go_on<<<1, kBlock, 0, s>>>(a32, 0);
+  if (a32.dir)
+    load_direction(MSC_PREC_MIXED, a32, !a64.dir, nullptr, s);
+  else if (herm)
+    k_herm_w<float><<<a32.gd, kBlock, 0, s>>>(a32, 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_direction(int prec, const MsArgs& a, bool load, const double2* ax, hipStream_t s) {
+  load_direction(prec, a, load, ax, s);
   return hipGetLastError();
 }
 
