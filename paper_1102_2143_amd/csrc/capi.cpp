@@ -135,13 +135,14 @@ msc_status ensure_halt(HaltWord& w) {
 }
 
 // Queue iterations, poll_every at a time, until the halt word is set, which `most` of them do
-// at the latest: that of one chunk is read once the next one is queued.
+// at the latest: that of one chunk is read once the next one is queued.  parity: the next one's.
 template <class F>
-msc_status run_to_halt(HaltWord& w, const msc_params& prm, int64_t most, hipStream_t s, F iteration) {
+msc_status run_to_halt(HaltWord& w, const msc_params& prm, int64_t most, int& parity, hipStream_t s,
+                       F iteration) {
   const int G = std::max(1, prm.poll_every);
   int64_t launched = 0;
   for (int chunk = 0; launched < most + 2 * int64_t(G); ++chunk) {
-    for (int g = 0; g < G; ++g) HIP_TRY(iteration(int(launched++ & 1)));
+    for (int g = 0; g < G; ++g, ++launched, parity ^= 1) HIP_TRY(iteration(parity));
     const int slot = chunk & 1;
     HIP_TRY(hipEventRecord(w.ev[slot], s));
     if (chunk >= 1) {
@@ -2573,8 +2574,9 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
   __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
   HIP_TRY(launch_bcg_start(a, s));
   // a step may take two launches (BA's check)
-  rc = run_to_halt(op->halt, prm, 2 * int64_t(h.max_iter), s, [&](int parity) {
-    a.par = parity;
+  int parity = 0;
+  rc = run_to_halt(op->halt, prm, 2 * int64_t(h.max_iter), parity, s, [&](int par) {
+    a.par = par;
     return launch_bcg_iteration(a, s);
   });
   if (rc != MSC_OK) return rc;
@@ -2805,26 +2807,50 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
   HIP_TRY(hipStreamSynchronize(s));  // nothing of an earlier solve sets the halt word now
   __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
   HIP_TRY(launch_real_start(prec, a, s));
-  rc = run_to_halt(op->halt, prm, h.max_iter, s, [&](int parity) {
-    a.par = parity;
-    return launch_real_iteration(prec, a, s);
-  });
-  if (rc != MSC_OK) return rc;
-  HIP_TRY(hipMemcpyAsync(&h, a.st, sizeof h, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  a.dir = prec == MSC_PREC_MIXED ? 1 : 0;
   std::vector<double> rel(ns, 0.0);
-  const double bn = std::sqrt(h.bnorm2);
-  if (prm.verify && h.status == 0 && bn > 0.0) {
-    for (int k0 = 0; k0 < ns; k0 += kRealCheck) {
-      RealSigma sg{};
-      const int cnt = std::min(kRealCheck, ns - k0);
-      for (int q = 0; q < cnt; ++q) sg.v[q] = op->sigma[k0 + q];
-      HIP_TRY(launch_real_verify(a, d_x + int64_t(k0) * n, sg, cnt, d_res2 + k0, s));
-    }
-    std::vector<double> r2(ns);
-    HIP_TRY(hipMemcpyAsync(r2.data(), d_res2, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
+  double bn = 0.0, last_true = HUGE_VAL;
+  int parity = 0, dir_from = a.dir ? 0 : -1;
+  for (int resumed = 0;;) {
+    rc = run_to_halt(op->halt, prm, h.max_iter, parity, s, [&](int par) {
+      a.par = par;
+      const hipError_t e = launch_real_iteration(prec, a, s);
+      a.resume = 0;
+      return e;
+    });
+    if (rc != MSC_OK) return rc;
+    HIP_TRY(hipMemcpyAsync(&h, a.st, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    for (int k = 0; k < ns; ++k) rel[k] = std::sqrt(r2[k]) / bn;
+    if (!(__atomic_load_n(op->halt.host, __ATOMIC_ACQUIRE) & 4)) {
+      bn = std::sqrt(h.bnorm2);
+      // FP64: the driving system's true residual is looked at in any case (see run_multishift)
+      const bool check = prec == MSC_PREC_FP64 && h.iter > 0 && h.R <= h.eps2 && resumed < kGoOn;
+      if (h.status != 0 || !(bn > 0.0) || !(prm.verify || check)) break;
+      const int k_first = prm.verify ? 0 : order[0], k_last = prm.verify ? ns : k_first + 1;
+      for (int k0 = k_first; k0 < k_last; k0 += kRealCheck) {
+        RealSigma sg{};
+        const int cnt = std::min(kRealCheck, k_last - k0);
+        for (int q = 0; q < cnt; ++q) sg.v[q] = op->sigma[k0 + q];
+        HIP_TRY(launch_real_verify(a, d_x + int64_t(k0) * n, sg, cnt, d_res2 + k0, s));
+      }
+      std::vector<double> r2(ns);
+      HIP_TRY(hipMemcpyAsync(r2.data(), d_res2, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      const double rel0 = std::sqrt(r2[order[0]]) / bn;
+      if (prm.verify)
+        for (int k = 0; k < ns; ++k) rel[k] = std::sqrt(r2[k]) / bn;
+      if (!check || !(rel0 > kTrueSlack * std::max(prm.tol, kTrueFloor)) || !(rel0 < 0.25 * last_true))
+        break;
+      last_true = rel0;
+      ++resumed;
+    }
+    // go on with the direction
+    __atomic_store_n(op->halt.host, 0, __ATOMIC_RELEASE);
+    const bool load = a.dir == 0;
+    if (load) dir_from = h.iter;
+    a.par = parity;
+    a.dir = a.resume = 1;
+    HIP_TRY(launch_real_direction(prec, a, load, s));
   }
   if (info) {
     clear_timing(*info);
@@ -2834,11 +2860,13 @@ msc_status msc_solve_real(msc_op op, const double* d_b, double* d_x, const msc_p
     info->n_refined = 0;
     info->iters_fp64 = prec == MSC_PREC_FP64 ? h.iter : 0;
     const double w = double(el), nn = double(n);
-    // per iteration: matrix (value + index per stored entry), r, w and s in and out; per
-    // application: x_k r/w (FP64) and p_k r/w of each listed system, the kept residuals
+    // per iteration: matrix (value + index per stored entry), r, w and s in and out (with the
+    // direction r, p, t and x_0 in and out, r and p once more); per application: x_k r/w
+    // (FP64) and p_k r/w of each listed system, the kept residuals
     const double ib = sm.col16 ? 2.0 : 4.0;
     const double mat = double(op->nnz) * (w + ib) + 4.0 * (nn + 1);
     info->alg_bytes = double(h.iter) * (mat + nn * (2 * w + 32.0)) +
+                      (dir_from < 0 ? 0.0 : double(h.iter - dir_from) * nn * (w + 24.0)) +
                       double(h.n_upd) * nn * (16.0 + 2 * w) + double(h.n_kept) * nn * w;
     if (info->true_rel_res)
       for (int k = 0; k < ns; ++k) info->true_rel_res[k] = rel[k];

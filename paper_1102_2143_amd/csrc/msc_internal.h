@@ -459,7 +459,7 @@ struct RealSigma {
 // State at the start of iteration n's kernel (indexed by n's parity; the kernel's
 // workgroup 0 writes the other one).  Shifts sorted ascending, j = 0 driving.
 struct RealRot {
-  double g, a;             // |r_{n-1}|^2 and a_{n-1}
+  double g, a, P;          // |r_{n-1}|^2, a_{n-1} and p_{n-1}.(A + sigma0) p_{n-1}
   int iter, halt;          // n; 1: nothing left to do
   int m, fresh;            // steps composed so far; 1: x and p never written
   double zeta[kMaxShifts], zeta_prev[kMaxShifts];
@@ -470,6 +470,8 @@ struct RealRot {
 };
 struct RealState {
   double sigma0, tol2, bnorm2, R, eps2;
+  double ru_g;             // |r_n|^2 of the recursive residual that RealArgs::resume replaced
+  int fin;                 // the halted sequence's state in rot
   int iter, max_iter, ns, status, freeze;
   int n_upd, n_kept;       // x_j/p_j updates and residuals read by applications
   double s[kMaxShifts];
@@ -479,6 +481,8 @@ struct RealState {
 struct RealArgs {
   int64_t n, nslices;
   int par, steps;          // parity of the iteration; steps folded into one application
+  int dir;                 // 1: the iteration carries the direction p (in s) and x_0
+  int resume;              // 1: the first one after launch_real_direction
   SellReal<double> m64;
   SellReal<float> m32;
   const double* b;
@@ -489,12 +493,15 @@ struct RealArgs {
   RealState* st;
   double* partial;
   unsigned* tickets;       // one ticket site
-  int* hflag;              // host-coherent word: 1 once halted
+  int* hflag;              // host-coherent word: 1 once halted | 4 the direction is to be taken up
 };
 hipError_t launch_real_extract(const double2* v64, double* r64, float* r32, int64_t count,
                                unsigned long long* imax, hipStream_t s);
 hipError_t launch_real_start(int prec, const RealArgs& a, hipStream_t s);
 hipError_t launch_real_iteration(int prec, const RealArgs& a, hipStream_t s);
+// The halted sequence goes on at a.par with r_n = b - (A + sigma0) x_0 and its direction (`load`:
+// taken up now, from the shifts').
+hipError_t launch_real_direction(int prec, const RealArgs& a, bool load, hipStream_t s);
 hipError_t launch_real_verify(const RealArgs& a, const double* x, const RealSigma& sg, int cnt,
                               double* out, hipStream_t s);
 

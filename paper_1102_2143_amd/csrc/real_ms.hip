@@ -19,11 +19,20 @@
 // are composed against the first one's p_k and the residuals of the steps, which stay in a
 // ring, and applied in one pass.
 //
+// P = d_n - b_n g_n / a_{n-1} and the recurred s suppose that r_n is orthogonal to s_{n-1}.  Where A
+// has eigenvalues far above the rest, rounding breaks that (multishift.hip).  The kernel also sums
+// c_n = r_n.s_{n-1}, so that P = d_n + b_n (2 c_n + b_n P_{n-1}) is that of the vectors held, and
+// once P leaves its short form, or x_0 misses the tolerance that its recursive residual has met,
+// the sequence goes on with its direction, in two kernels (k_r_dir, k_r_step), s_n and P from p_n
+// and x_0 updated step by step.  In single precision it does so from the start: a penalty of 100
+// on one edge of a grid is too much for the residuals' rounding without it.
+//
 // Bound by memory: a row moves its matrix entries (10 bytes each), r, w and s in and out
 // (w and s in FP64 always: recurred in single precision, s would add an error of its own),
-// and an eighth of 32 bytes per live shift.  1000 x 1000 points, 15 shifts: 63.2 us an
-// iteration in FP64 and 50.4 in single precision with three kernels (t = A p; r; the
-// shifts' step, unfolded), 29.3 and 26.2 here; 60 x 50 points 24.6 and 10.3 us.
+// and an eighth of 32 bytes per live shift.  1000 x 1000 points, 15 shifts: 62.6 us an
+// iteration in FP64 and 49.8 in single precision with three kernels (t = A p; r; the
+// shifts' step, unfolded), 28.7 and (with the direction) 32.0 here; 60 x 50 points 24.0 and 24.0,
+// 10.0 and 13.4.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -150,18 +159,50 @@ __device__ __forceinline__ double r_row_f(const SellReal<T>& m, F val, T own, in
   return acc;
 }
 
-// Partials of g and d of the kernel of parity par (their reader's parity).
+// Partials of g (0), d (1) and c (2) of the kernel of parity par (their reader's parity).
 __device__ __forceinline__ double* r_region(const RealArgs& a, int par, int which) {
-  return a.partial + (2 * par + which) * kMaxGrid;
+  return a.partial + (3 * par + which) * kMaxGrid;
 }
 
-__device__ __forceinline__ void r_store_partials(const RealArgs& a, int par, double g, double d) {
-  double v[2] = {g, d};
-  block_sum_k<kBlock, 2>(v);
+__device__ __forceinline__ void r_store_partials(const RealArgs& a, int par, double g, double d, double c) {
+  double v[3] = {g, d, c};
+  block_sum_k<kBlock, 3>(v);
   if (threadIdx.x == 0) {
-    store_agent(&r_region(a, par, 0)[blockIdx.x], v[0]);
-    store_agent(&r_region(a, par, 1)[blockIdx.x], v[1]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) store_agent(&r_region(a, par, k)[blockIdx.x], v[k]);
   }
+}
+__device__ __forceinline__ void r_store_one(const RealArgs& a, int par, int which, double v) {
+  v = block_sum<kBlock>(v);
+  if (threadIdx.x == 0) store_agent(&r_region(a, par, which)[blockIdx.x], v);
+}
+
+// The sums of the first K of them (a.par's), in every thread: plain loads, which the XCD's L2
+// serves to all but its first workgroup.
+template <int K> __device__ __forceinline__ void r_sums(const RealArgs& a, double (&tot)[K]) {
+  __shared__ double sh[K];
+  constexpr int kPer = kRealGrid / kBlock;
+  double v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    double w[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = threadIdx.x + u * kBlock;
+      w[u] = i < int(gridDim.x) ? r_region(a, a.par, k)[i] : 0.0;
+    }
+    v[k] = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) v[k] += w[u];
+  }
+  block_sum_k<kBlock, K>(v);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[k] = v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) tot[k] = sh[k];
 }
 
 // r_0 = b in ring slot 0, s = 0, w_0 = A r_0 and the partials of g_0 and d_0.
@@ -192,7 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_r_start(RealArgs a) {
       d += rd * v + sigma0 * rd * rd;
     }
   }
-  r_store_partials(a, 0, g, d);
+  r_store_partials(a, 0, g, d, 0.0);
 }
 
 // What an iteration's kernel does, shared through LDS.
@@ -207,10 +248,23 @@ struct RealPlan {
   int64_t xo[kMaxShifts], po[kMaxShifts];
 };
 
+// The deviation of P from its short form beyond which the direction is taken up: ordinary grids
+// stay below 1e-13 (multishift.hip and its limits' comment).
+constexpr double kRealDev = 1e-9;
+
+__device__ __forceinline__ double r_b(const RealArgs& a, const RealRot& rs, double g) {
+  return rs.iter == 0 ? 0.0 : (a.resume ? a.st->ru_g : g) / rs.g;
+}
+// Converged, at the limit, or |r|^2 not finite.
+__device__ __forceinline__ bool r_ends(const RealArgs& a, const RealRot& rs, double g) {
+  const double bn2 = rs.iter == 0 ? g : a.st->bnorm2;
+  return !isfinite(g) || g <= a.st->tol2 * bn2 || rs.iter >= a.st->max_iter;
+}
+
 // Every workgroup derives a_n, b_n and whether step n runs; the shifts' scalars (wave 0,
 // lane j) are needed by workgroup 0, which writes the next state, and by all where the
-// composed steps are applied.
-__device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
+// composed steps are applied.  d: r_n.(A + sigma0) r_n, with the direction P itself.
+__device__ void r_plan(const RealArgs& a, double g, double d, double c, RealPlan& pl) {
   RealState* st = a.st;
   const RealRot& rs = st->rot[a.par];
   const int j = threadIdx.x;
@@ -218,11 +272,16 @@ __device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
   const bool head = blockIdx.x == 0;
   const int n = rs.iter, m0 = rs.m;
   const double bn2 = n == 0 ? g : st->bnorm2, eps2 = st->tol2 * bn2;
-  const double b = n == 0 ? 0.0 : g / rs.g;
-  const double P = n == 0 ? d : d - b * g / rs.a;
+  const double b = r_b(a, rs, g);
+  double P = d, off = 0.0;
+  if (!a.dir && n > 0) {
+    P = d + b * (2.0 * c + b * rs.P);
+    off = fabs(P - (d - b * g / rs.a));
+  }
   // |r|^2 first: an infinite |b|^2 would pass for its own limit
   const bool done = isfinite(g) && (g <= eps2 || n >= st->max_iter);
-  const bool ok = done || (isfinite(g) && P > 0.0 && isfinite(P));
+  const bool ok = done || (isfinite(g) && P > 0.0 && isfinite(P) && off <= kRealDev * P);
+  const bool take = !ok && isfinite(g) && !a.dir && n > 0;  // the direction is to be taken up
   const bool live = !done && ok;
   const double step = live ? g / P : 0.0;
   const int m = m0 + (live ? 1 : 0);
@@ -271,7 +330,7 @@ __device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
         if (i <= m) cx[i] = fma(aj, cp[i], cx[i]);
       took = 1;
     }
-    const bool list = apply && mine && (took || rs.fresh);
+    const bool list = apply && mine && (took || rs.fresh) && !(a.dir && j == 0);
     const uint64_t mask = __ballot(list);
     if (list) {
       const int pos = __popcll(mask & ((uint64_t(1) << j) - 1));
@@ -301,8 +360,10 @@ __device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
         }
       }
       if (j == 0) {
-        nx.g = g;
-        nx.a = step;
+        // of the last step taken
+        nx.g = live ? g : rs.g;
+        nx.a = live ? step : rs.a;
+        nx.P = live ? P : rs.P;
         nx.iter = live ? n + 1 : n;
         nx.m = apply ? 0 : m;
         nx.fresh = apply ? 0 : rs.fresh;
@@ -316,8 +377,9 @@ __device__ void r_plan(const RealArgs& a, double g, double d, RealPlan& pl) {
           st->iter = n;
           st->R = g;
           st->eps2 = eps2;
-          st->status = ok ? 0 : 1;
-          store_host_flag(a.hflag, 1);
+          st->status = ok || take ? 0 : 1;
+          st->fin = a.par ^ 1;
+          store_host_flag(a.hflag, take ? 5 : 1);
         }
       }
     }
@@ -377,7 +439,6 @@ __device__ __forceinline__ void r_apply_row(const RealArgs& a, const RealPlan& p
 }
 
 // ---- one iteration --------------------------------------------------------------------
-template <class T>
 __global__ __launch_bounds__(kBlock) void k_r_iter(RealArgs a) {
   RealState* st = a.st;
   const RealRot& rs = st->rot[a.par];
@@ -385,42 +446,18 @@ __global__ __launch_bounds__(kBlock) void k_r_iter(RealArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) st->rot[a.par ^ 1].halt = 1;
     return;
   }
-  // the previous kernel's partials: plain loads, which the XCD's L2 serves to all but its
-  // first workgroup
-  constexpr int kPer = kRealGrid / kBlock;
-  double g = 0.0, d = 0.0, gv[kPer], dv[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int i = threadIdx.x + u * kBlock;
-    const bool in = i < int(gridDim.x);
-    gv[u] = in ? r_region(a, a.par, 0)[i] : 0.0;
-    dv[u] = in ? r_region(a, a.par, 1)[i] : 0.0;
-  }
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    g += gv[u];
-    d += dv[u];
-  }
-  __shared__ double tot[2];
+  double tot[3];
+  r_sums(a, tot);
   __shared__ RealPlan pl;
-  {
-    double v[2] = {g, d};
-    block_sum_k<kBlock, 2>(v);
-    if (threadIdx.x == 0) {
-      tot[0] = v[0];
-      tot[1] = v[1];
-    }
-  }
-  __syncthreads();
   const int n = rs.iter;
-  r_plan(a, tot[0], tot[1], pl);
+  r_plan(a, tot[0], tot[1], tot[2], pl);
   __syncthreads();
   const bool live = pl.live != 0, apply = pl.apply != 0;
   if (!live && !apply) return;
-  const SellReal<T> m = rmat<T>(a);
-  T* ring = static_cast<T*>(a.r);
-  const T* __restrict__ r = ring + int64_t(n % kRealRing) * a.n;
-  T* __restrict__ rn = ring + int64_t((n + 1) % kRealRing) * a.n;
+  const SellReal<double> m = rmat<double>(a);
+  double* ring = static_cast<double*>(a.r);
+  const double* __restrict__ r = ring + int64_t(n % kRealRing) * a.n;
+  double* __restrict__ rn = ring + int64_t((n + 1) % kRealRing) * a.n;
   const double* __restrict__ w = a.w[a.par];
   const double* __restrict__ s = a.s[a.par];
   double* __restrict__ wn = a.w[a.par ^ 1];
@@ -428,34 +465,173 @@ __global__ __launch_bounds__(kBlock) void k_r_iter(RealArgs a) {
   const double step = pl.a, b = pl.b, sigma0 = st->sigma0;
   // s_n and r_{n+1} at a row, rounded once each: the same bits wherever they are formed
   auto s_of = [&](int64_t c) {
-    return fma(b, s[c], fma(sigma0, double(r[c]), w[c]));
+    return fma(b, s[c], fma(sigma0, r[c], w[c]));
   };
-  auto r_of = [&](int64_t c) { return T(fma(-step, s_of(c), double(r[c]))); };
+  auto r_of = [&](int64_t c) { return fma(-step, s_of(c), r[c]); };
   constexpr int SPB = kBlock / kSlice;
   const int lane = threadIdx.x % kSlice;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
   int64_t beg, end;
   block_range(a.nslices, SPB, beg, end);
-  g = d = 0.0;
+  double g = 0.0, d = 0.0, cs = 0.0;
   for (int64_t sl = beg + wv; sl < end; sl += SPB) {
     const int64_t row = sl * kSlice + lane;
     const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
     if (live) {
       const double sv = s_of(rr);
-      const T own = T(fma(-step, sv, double(r[rr])));
-      const double v = r_row_f<T>(m, [&](int32_t c) { return r_of(c); }, own, sl, lane, rr);
+      const double own = fma(-step, sv, r[rr]);
+      const double v = r_row_f<double>(m, [&](int32_t c) { return r_of(c); }, own, sl, lane, rr);
       if (row < a.n) {
         rn[row] = own;
         sn[row] = sv;
         wn[row] = v;
-        const double rd = double(own);
-        g = fma(rd, rd, g);
-        d += rd * v + sigma0 * rd * rd;
+        g = fma(own, own, g);
+        d += own * v + sigma0 * own * own;
+        cs = fma(own, sv, cs);
       }
     }
-    if (apply && row < a.n) r_apply_row<T>(a, pl, n, row);
+    if (apply && row < a.n) r_apply_row<double>(a, pl, n, row);
   }
-  if (live) r_store_partials(a, a.par ^ 1, g, d);
+  if (live) r_store_partials(a, a.par ^ 1, g, d, cs);
+}
+
+// ---- one iteration with the direction ---------------------------------------------------
+// p_n = r_n + b_n p_{n-1}, t = A p_n (into w) and P's partials.  p, rounded to T, is formed at
+// every gathered column as its owner forms it.
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_r_dir(RealArgs a) {
+  RealState* st = a.st;
+  const RealRot& rs = st->rot[a.par];
+  if (rs.halt) return;
+  double g[1];
+  r_sums(a, g);
+  if (r_ends(a, rs, g[0])) return;
+  const double b = r_b(a, rs, g[0]), sigma0 = st->sigma0;
+  const SellReal<T> m = rmat<T>(a);
+  const T* __restrict__ r = static_cast<const T*>(a.r) + int64_t(rs.iter % kRealRing) * a.n;
+  const double* __restrict__ p = a.s[a.par];
+  double* __restrict__ pn = a.s[a.par ^ 1];
+  double* __restrict__ t = a.w[a.par ^ 1];
+  auto p_of = [&](int64_t c) { return T(fma(b, p[c], double(r[c]))); };
+  constexpr int SPB = kBlock / kSlice;
+  const int lane = threadIdx.x % kSlice;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+  int64_t beg, end;
+  block_range(a.nslices, SPB, beg, end);
+  double P = 0.0;
+  for (int64_t sl = beg + wv; sl < end; sl += SPB) {
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;  // lanes past n read a valid row, unused
+    const T own = p_of(rr);
+    const double v = r_row_f<T>(m, [&](int32_t c) { return p_of(c); }, own, sl, lane, rr);
+    if (row < a.n) {
+      const double pd = double(own);
+      pn[row] = pd;
+      t[row] = v;
+      P += pd * v + sigma0 * pd * pd;
+    }
+  }
+  r_store_one(a, a.par, 1, P);
+}
+
+// r_{n+1} = r_n - a_n (t + sigma0 p_n), x_0 += a_n p_n and the other systems' composed steps.
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_r_step(RealArgs a) {
+  RealState* st = a.st;
+  const RealRot& rs = st->rot[a.par];
+  if (rs.halt) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->rot[a.par ^ 1].halt = 1;
+    return;
+  }
+  double tot[2];
+  r_sums(a, tot);
+  __shared__ RealPlan pl;
+  const int n = rs.iter;
+  r_plan(a, tot[0], tot[1], 0.0, pl);
+  __syncthreads();
+  const bool live = pl.live != 0, apply = pl.apply != 0;
+  if (!live && !apply) return;
+  T* ring = static_cast<T*>(a.r);
+  const T* __restrict__ r = ring + int64_t(n % kRealRing) * a.n;
+  T* __restrict__ rn = ring + int64_t((n + 1) % kRealRing) * a.n;
+  const double* __restrict__ p = a.s[a.par ^ 1];
+  const double* __restrict__ t = a.w[a.par ^ 1];
+  double* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
+  const double step = pl.a, sigma0 = st->sigma0;
+  int64_t beg, end;
+  block_range(a.n, kBlock, beg, end);
+  double g = 0.0;
+  for (int64_t i = beg + threadIdx.x; i < end; i += kBlock) {
+    if (live) {
+      const double pv = p[i];
+      const T v = T(fma(-step, fma(sigma0, pv, t[i]), double(r[i])));
+      rn[i] = v;
+      x0[i] = fma(step, pv, n == 0 ? 0.0 : x0[i]);
+      g = fma(double(v), double(v), g);
+    } else if (n == 0) {
+      x0[i] = 0.0;
+    }
+    if (apply) r_apply_row<T>(a, pl, n, i);
+  }
+  if (live) r_store_one(a, a.par ^ 1, 0, g);
+}
+
+// Go on after a halt: r_n = b - (A + sigma0) x_0 in FP64, its g's partials, and p_{n-1} in s[a.par]
+// (load: from the driving system's direction, else from the other buffer where it lies there).
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_r_load(RealArgs a, int load) {
+  const RealState* st = a.st;
+  const RealRot& fin = st->rot[st->fin];
+  const SellReal<double> m = rmat<double>(a);
+  T* __restrict__ r = static_cast<T*>(a.r) + int64_t(fin.iter % kRealRing) * a.n;
+  const double* __restrict__ x0 = a.x + int64_t(st->orig[0]) * a.n;
+  const T* __restrict__ pk = static_cast<const T*>(a.pk);
+  const double* from = a.s[st->fin ^ 1];
+  double* to = a.s[a.par];
+  const double sigma0 = st->sigma0;
+  constexpr int SPB = kBlock / kSlice;
+  const int lane = threadIdx.x % kSlice;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kSlice));
+  int64_t beg, end;
+  block_range(a.nslices, SPB, beg, end);
+  double g = 0.0;
+  for (int64_t sl = beg + wv; sl < end; sl += SPB) {
+    const int64_t row = sl * kSlice + lane;
+    const int64_t rr = row < a.n ? row : a.n - 1;
+    const double v = r_row<double>(m, x0, sl, lane, rr);
+    if (row < a.n) {
+      const T o = T(a.b[row] - v - sigma0 * x0[row]);
+      r[row] = o;
+      g = fma(double(o), double(o), g);
+      to[row] = load ? double(pk[row]) : from[row];
+    }
+  }
+  r_store_one(a, a.par, 0, g);
+}
+
+// Its state (which may be the halted one's: a lane reads before it writes).
+__global__ __launch_bounds__(kBlock) void k_r_go_on(RealArgs a) {
+  RealState* st = a.st;
+  const RealRot& fin = st->rot[st->fin];
+  RealRot& rs = st->rot[a.par];
+  const int j = threadIdx.x;
+  if (j < kMaxShifts) {
+    rs.zeta[j] = fin.zeta[j];
+    rs.zeta_prev[j] = fin.zeta_prev[j];
+    // repeats of the driving shift stopped with it and go on with it
+    rs.active[j] = fin.active[j] || (j < st->ns && st->s[j] == 0.0);
+    rs.took[j] = 0;
+  }
+  if (j == 0) {
+    rs.g = fin.g;
+    rs.a = fin.a;
+    rs.P = fin.P;
+    rs.iter = fin.iter;
+    rs.m = 0;
+    rs.fresh = 0;
+    rs.halt = 0;
+    st->ru_g = st->R;
+  }
 }
 
 // ---- FP64 true residuals |b - (A + sigma_k) x_k|^2 of up to kRealCheck systems ----------
@@ -545,10 +721,25 @@ hipError_t launch_real_start(int prec, const RealArgs& a, hipStream_t s) {
 
 hipError_t launch_real_iteration(int prec, const RealArgs& a, hipStream_t s) {
   const int g = r_grid(a.nslices);
+  if (prec == MSC_PREC_MIXED) {  // always with the direction
+    k_r_dir<float><<<g, kBlock, 0, s>>>(a);
+    k_r_step<float><<<g, kBlock, 0, s>>>(a);
+  } else if (a.dir) {
+    k_r_dir<double><<<g, kBlock, 0, s>>>(a);
+    k_r_step<double><<<g, kBlock, 0, s>>>(a);
+  } else {
+    k_r_iter<<<g, kBlock, 0, s>>>(a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_real_direction(int prec, const RealArgs& a, bool load, hipStream_t s) {
+  const int g = r_grid(a.nslices);
   if (prec == MSC_PREC_MIXED)
-    k_r_iter<float><<<g, kBlock, 0, s>>>(a);
+    k_r_load<float><<<g, kBlock, 0, s>>>(a, load ? 1 : 0);
   else
-    k_r_iter<double><<<g, kBlock, 0, s>>>(a);
+    k_r_load<double><<<g, kBlock, 0, s>>>(a, load ? 1 : 0);
+  k_r_go_on<<<1, kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
