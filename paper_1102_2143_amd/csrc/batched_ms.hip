@@ -11,6 +11,10 @@
 // converts a system whose right-hand sides have all reached switch_tol to complex64 (it
 // waits for that BF); reliable updates run between BFs.
 //
+// As there, BK2 also sums c = Re r^H s, and a system whose P leaves its short form (or whose FP64
+// phase says that it would in complex64) waits for the next BF, which hands its right-hand sides
+// their directions; from then on BP updates p, BK1 and BK2 form P and s from it and BK2 keeps x_0.
+//
 // Operators made from links read them: a wave takes 64 sites of one right-hand side, whose
 // vectors lie apart, colour by colour; the waves of the other right-hand sides on the same
 // sites share its links in the caches.  Stored matrices: the right-hand sides of a system
@@ -153,47 +157,65 @@ __device__ __forceinline__ bool chunk_reduce(double (&v)[K], const BatchSys& S, 
 
 // The iteration kernels' partial sums, one set per wave and chunk, added by the system's
 // workgroup of the next kernel: no wave waits for another.  On links a wave has one
-// right-hand side's (wave % RR), else all of them; either way entry % RR is its q.
+// right-hand side's (wave % RR), else all of them; either way entry % RR is its q.  set: 0 for
+// d_n and g_{n+1}, 1 for c_{n+1}.
+__device__ __forceinline__ double* partial_set(const BatchSys& S, int set) {
+  return S.partial + int64_t(set) * S.nchunks * (kBatchPartial / 2);
+}
 template <int RR>
-__device__ __forceinline__ void wave_partial(const BatchSys& S, const int4& ch, double (&v)[RR]) {
+__device__ __forceinline__ void wave_partial(const BatchSys& S, const int4& ch, int set, double (&v)[RR]) {
   const int wv = threadIdx.x / kWave;
+  double* __restrict__ to = partial_set(S, set);
   if (S.links) {
     const double t = group_sum<kWave>(v[0]);
-    if (threadIdx.x % kWave == 0) S.partial[ch.w * (kBlock / kWave) + wv] = t;
+    if (threadIdx.x % kWave == 0) to[ch.w * (kBlock / kWave) + wv] = t;
     return;
   }
 #pragma unroll
   for (int q = 0; q < RR; ++q) v[q] = group_sum<kWave>(v[q]);
   if (threadIdx.x % kWave == 0) {
 #pragma unroll
-    for (int q = 0; q < RR; ++q) S.partial[(ch.w * (kBlock / kWave) + wv) * RR + q] = v[q];
+    for (int q = 0; q < RR; ++q) to[(ch.w * (kBlock / kWave) + wv) * RR + q] = v[q];
   }
 }
 
-// Their totals per rhs, in every thread's view of tot[] (kBatchMaxRhs).
-template <int RR> __device__ __forceinline__ void system_totals(const BatchSys& S, double* tot) {
+// The totals of the first SETS sets per rhs, in every thread's view of tot[set][] (kBatchMaxRhs).
+template <int RR, int SETS>
+__device__ __forceinline__ void system_totals(const BatchSys& S, double (*tot)[kBatchMaxRhs]) {
   constexpr int U = 16;  // in flight together: all of a system of 4096 partials (with 4, and the
                          // state read after the sums, the 64 systems took 86.8 for 85.0 ms)
   const int np = S.nchunks * (kBlock / kWave) * (S.links ? 1 : RR);
-  double v = 0.0;
+  double v[SETS];
+#pragma unroll
+  for (int t = 0; t < SETS; ++t) v[t] = 0.0;
   for (int i = threadIdx.x; i < np; i += U * kBlock) {
-    double a[U];
+    double a[SETS][U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = i + u * kBlock < np ? S.partial[i + u * kBlock] : 0.0;
+    for (int t = 0; t < SETS; ++t) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) v += a[u];
+      for (int u = 0; u < U; ++u) a[t][u] = i + u * kBlock < np ? partial_set(S, t)[i + u * kBlock] : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < SETS; ++t) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[t] += a[t][u];
+    }
   }
-  // lanes of one rhs: those equal mod RR
+  __shared__ double part[SETS][kBlock / kWave][kBatchMaxRhs];
 #pragma unroll
-  for (int o = kWave / 2; o >= RR; o /= 2) v += __shfl_xor(v, o, kWave);
-  __shared__ double part[kBlock / kWave][kBatchMaxRhs];
-  if (int(threadIdx.x % kWave) < RR) part[threadIdx.x / kWave][threadIdx.x % kWave] = v;
+  for (int t = 0; t < SETS; ++t) {
+    // lanes of one rhs: those equal mod RR
+#pragma unroll
+    for (int o = kWave / 2; o >= RR; o /= 2) v[t] += __shfl_xor(v[t], o, kWave);
+    if (int(threadIdx.x % kWave) < RR) part[t][threadIdx.x / kWave][threadIdx.x % kWave] = v[t];
+  }
   __syncthreads();
-  if (threadIdx.x < kBatchMaxRhs) {
+  if (threadIdx.x < SETS * kBatchMaxRhs) {
+    const int t = threadIdx.x / kBatchMaxRhs, q = threadIdx.x % kBatchMaxRhs;
     double s = 0.0;
-    if (int(threadIdx.x) < RR)
-      for (int w = 0; w < kBlock / kWave; ++w) s += part[w][threadIdx.x];
-    tot[threadIdx.x] = s;
+    if (q < RR)
+      for (int w = 0; w < kBlock / kWave; ++w) s += part[t][w][q];
+    tot[t][q] = s;
   }
   __syncthreads();
 }
@@ -231,10 +253,13 @@ __device__ __forceinline__ void site_product(const BatchSys& S, const cplx<R>* _
     stencil_site<R, 3>(w, t.site, own, sign, at, out);
 }
 
-// ---- BK1: u = M r (A r for A given) for every rhs and d's share: |u|^2 or Re r^H u --------
+// ---- BK1: u = M r (A r for A given) for every rhs and d's share: |u|^2 or Re r^H u (with the
+// direction of p instead, and sigma0 |p|^2 besides) ------------------------------------------
 template <class R, int L, int RR>
 __device__ __forceinline__ void bk1_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
-  const cplx<R>* __restrict__ r = bslot<R, RR>(S, load_const(&st->slot));
+  const bool dir = load_const(&st->dir) != 0;
+  const cplx<R>* __restrict__ r = dir ? BVec<R>::s(S) : bslot<R, RR>(S, load_const(&st->slot));
+  const double sd = dir ? load_const(&st->sigma0) : 0.0;
   cplx<R>* __restrict__ u = BVec<R>::u(S);
   const bool mhm = S.kind == MSC_A_MHM;
   double acc[RR];
@@ -246,6 +271,7 @@ __device__ __forceinline__ void bk1_chunk(const BatchSys& S, const BatchState* s
       u[row * RR + q] = v[q];
       acc[q] += mhm ? norm2d<R>(v[q])
                     : double(rr[q].x) * double(v[q].x) + double(rr[q].y) * double(v[q].y);
+      acc[q] = fma(sd, norm2d<R>(rr[q]), acc[q]);
     }
   };
   if (S.links) {
@@ -258,6 +284,11 @@ __device__ __forceinline__ void bk1_chunk(const BatchSys& S, const BatchState* s
       for (int c = 0; c < 3; ++c) {
         u[int64_t(t.q) * S.n + c * S.w64.vol + t.site] = v[c];
         sum += norm2d<R>(v[c]);
+      }
+      if (dir) {  // read again: the registers are full
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          sum = fma(sd, norm2d<R>(r[int64_t(t.q) * S.n + c * S.w64.vol + t.site]), sum);
       }
     }
     acc[0] = sum;
@@ -292,12 +323,13 @@ __device__ __forceinline__ void bk1_chunk(const BatchSys& S, const BatchState* s
       }
     }
   }
-  wave_partial<RR>(S, ch, acc);
+  wave_partial<RR>(S, ch, 0, acc);
 }
 
 // The scalars of the step, one workgroup per system.
 template <int RR>
-__device__ __forceinline__ void bs1_system(const BatchSys& S, BatchState* st, double* tot) {
+__device__ __forceinline__ void bs1_system(const BatchSys& S, BatchState* st,
+                                           double (*tot)[kBatchMaxRhs]) {
   // lane = q * 16 + k: the scalars of step n of rhs q, and shift k's, composed with
   // the pending steps; every lane reads the state before any lane writes it, and
   // before the sums, whose round trip it shares
@@ -306,7 +338,9 @@ __device__ __forceinline__ void bs1_system(const BatchSys& S, BatchState* st, do
   const bool live = lk < kQK && q < st->nrhs && !st->halt[q];
   const int n = live ? st->iter[q] : 0, ru = live ? st->ru[q] : 0, m = live ? st->m[q] : 0;
   const double g = live ? st->R[q] : 1.0, g1 = live ? st->g1[q] : 1.0, a1 = live ? st->a1[q] : 1.0;
-  const double P1 = live ? st->P1[q] : 1.0, rg = live ? st->ru_g[q] : 0.0, rc = live ? st->ru_c[q] : 0.0;
+  const double P1 = live ? st->P1[q] : 1.0, rg = live ? st->ru_g[q] : 0.0, rc = live ? st->c[q] : 0.0;
+  const int dir = st->dir;
+  const double limit = st->phase32 ? kDevLimit32 : kDevLimit64, dev = live ? st->dev[q] : 0.0;
   const bool act = live && k < ns && (k == 0 || st->active[lk]);
   const double z = live && k ? st->zeta[lk] : 1.0, zp = live && k ? st->zeta_prev[lk] : 1.0;
   const double sigma0 = st->sigma0, sk = live ? st->s[k] : 0.0;
@@ -319,12 +353,20 @@ __device__ __forceinline__ void bs1_system(const BatchSys& S, BatchState* st, do
     cp[i] = m > 0 && i <= m ? st->cp[i][lk] : 0.0;
   }
   if (m == 0) cp[0] = 1.0;
-  system_totals<RR>(S, tot);
+  system_totals<RR, 1>(S, tot);
   if (lk >= kQK) return;
-  const double d = tot[q] + sigma0 * g;
+  const double d = dir ? tot[0][q] : tot[0][q] + sigma0 * g;
   const double b = n == 0 ? 0.0 : (ru ? rg : g) / g1;
-  const double P = n == 0 ? d : (ru ? d + b * (2.0 * rc + b * P1) : d - b * g / a1);
+  const double P = n == 0 || dir ? d : d + b * (2.0 * rc + b * P1);
+  const double off = n == 0 || dir || ru ? 0.0 : fabs(P - (d - b * g / a1));
   const bool ok = P > 0.0 && isfinite(P);
+  // a right-hand side that needs its direction: none of the system steps until BF has
+  // handed them out
+  if (__ballot(live && !dir && n > 0 && (!ok || !(off <= limit * P)))) {
+    if (k == 0 && q < kBatchMaxRhs) st->step[q] = 0;
+    if (lk == 0) st->wait |= 2;
+    return;
+  }
   const double a = g / P;
   if (k == 0 && q < kBatchMaxRhs) st->step[q] = live && ok ? 1 : 0;
   if (live && !ok && k == 0) {
@@ -362,6 +404,7 @@ __device__ __forceinline__ void bs1_system(const BatchSys& S, BatchState* st, do
     st->m[q] = m + 1;
     st->last[q] = slot;  // the newest of the composed steps
     st->ru[q] = 0;
+    if (off > dev * P) st->dev[q] = off / P;
   }
 }
 
@@ -374,38 +417,45 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
   cplx<R>* __restrict__ rn = bslot<R, RR>(S, slot + 1);
   cplx<R>* __restrict__ sv = BVec<R>::s(S);
   const double s0 = load_const(&st->sigma0);
-  const bool mhm = S.kind == MSC_A_MHM;
-  double acc[RR];
+  const bool mhm = S.kind == MSC_A_MHM, dir = load_const(&st->dir) != 0;
+  const double cr = dir ? 0.0 : s0;  // s = w + cr r + cs s_old, s_old being p with the direction
+  double2* __restrict__ x0 = S.x + int64_t(load_const(&st->orig[0])) * S.n;
+  const int64_t xq = int64_t(load_const(&st->ns)) * S.n;
+  double acc[RR], ac[RR];
 #pragma unroll
-  for (int q = 0; q < RR; ++q) acc[q] = 0.0;
-  // one element's step; `stream` where a wave's s is one run (else its lines, shared by the
+  for (int q = 0; q < RR; ++q) acc[q] = ac[q] = 0.0;
+  // one element's step (row i of right-hand side q in the caller's order); `stream` where a wave's s is one run (else its lines, shared by the
   // right-hand sides of a row, would leave the caches between them)
-  auto element = [&](int64_t idx, const cplx<R>& w, double a, double b, auto stream) {
+  auto element = [&](int64_t idx, int64_t i, int q, const cplx<R>& w, double a, double cs, auto stream,
+                     double& g, double& c) {
     const double2 wd = to_d(w), rd = to_d(r[idx]), sd = to_d(stream ? ld_stream(&sv[idx]) : sv[idx]);
-    const double2 t{fma(b, sd.x, fma(s0, rd.x, wd.x)), fma(b, sd.y, fma(s0, rd.y, wd.y))};
-    const cplx<R> nr = from_d<R>(double2{fma(-a, t.x, rd.x), fma(-a, t.y, rd.y)});
-    if (stream)
-      st_stream(&sv[idx], from_d<R>(t));
-    else
-      sv[idx] = from_d<R>(t);
+    const double2 t{fma(cs, sd.x, fma(cr, rd.x, wd.x)), fma(cs, sd.y, fma(cr, rd.y, wd.y))};
+    const cplx<R> nr = from_d<R>(double2{fma(-a, t.x, rd.x), fma(-a, t.y, rd.y)}), ts = from_d<R>(t);
+    if (dir) {
+      double2* x = x0 + (q * xq + i);
+      *x = double2{fma(a, sd.x, x->x), fma(a, sd.y, x->y)};
+    } else if (stream) {
+      st_stream(&sv[idx], ts);
+    } else {
+      sv[idx] = ts;
+    }
     rn[idx] = nr;
-    return norm2d<R>(nr);
+    g += norm2d<R>(nr);
+    c = fma(double(nr.x), double(ts.x), fma(double(nr.y), double(ts.y), c));
   };
   if (S.links) {
     const SiteTask t = site_task<RR>(ch);
-    double sum = 0.0;
     if (t.q < load_const(&st->nrhs) && load_const(&st->step[t.q])) {
       cplx<R> own[3], w[3];
       site_product<R>(S, u, t, -1, own, w);
-      const double a = load_const(&st->a[t.q]), b = load_const(&st->b[t.q]);
+      const double a = load_const(&st->a[t.q]), cs = dir ? s0 : load_const(&st->b[t.q]);
       if (t.live) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-          sum += element(int64_t(t.q) * S.n + c * S.w64.vol + t.site, w[c], a, b,
-                         std::true_type{});
+          element(int64_t(t.q) * S.n + c * S.w64.vol + t.site, 3 * int64_t(t.site) + c, t.q, w[c], a,
+                  cs, std::true_type{}, acc[0], ac[0]);
       }
     }
-    acc[0] = sum;
   } else {
     double a[RR], b[RR];
     bool go[RR];
@@ -413,12 +463,13 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
     for (int q = 0; q < RR; ++q) {
       go[q] = q < load_const(&st->nrhs) && load_const(&st->step[q]);
       a[q] = go[q] ? load_const(&st->a[q]) : 0.0;
-      b[q] = go[q] ? load_const(&st->b[q]) : 0.0;
+      b[q] = dir ? s0 : go[q] ? load_const(&st->b[q]) : 0.0;
     }
     auto epilogue = [&](int64_t row, const cplx<R> (&w)[RR]) {
 #pragma unroll
       for (int q = 0; q < RR; ++q)
-        if (go[q]) acc[q] += element(row * RR + q, w[q], a[q], b[q], std::false_type{});
+        if (go[q])
+          element(row * RR + q, row, q, w[q], a[q], b[q], std::false_type{}, acc[q], ac[q]);
     };
     if (S.sell && mhm) {
       // one row per lane: the chunk's four slices, one per wave
@@ -446,7 +497,7 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
       }
     } else {  // A given: u is A r already
       const int q = threadIdx.x % RR;  // kBlock is a multiple of RR: this thread's rhs
-      double sum = 0.0, aq = 0.0, bq = 0.0;
+      double sum = 0.0, sc = 0.0, aq = 0.0, bq = 0.0;
       bool gq = false;
 #pragma unroll
       for (int k = 0; k < RR; ++k) {
@@ -459,16 +510,37 @@ __device__ __forceinline__ void bk2_chunk(const BatchSys& S, const BatchState* s
       const int64_t end = int64_t(ch.z) * RR;
       if (gq)
         for (int64_t e = int64_t(ch.y) * RR + threadIdx.x; e < end; e += kBlock)
-          sum += element(e, u[e], aq, bq, std::true_type{});
+          element(e, e / RR, q, u[e], aq, bq, std::true_type{}, sum, sc);
 #pragma unroll
-      for (int k = 0; k < RR; ++k) acc[k] = k == q ? sum : 0.0;
+      for (int k = 0; k < RR; ++k) {
+        acc[k] = k == q ? sum : 0.0;
+        ac[k] = k == q ? sc : 0.0;
+      }
     }
   }
-  wave_partial<RR>(S, ch, acc);
+  wave_partial<RR>(S, ch, 0, acc);
+  wave_partial<RR>(S, ch, 1, ac);
+}
+
+// ---- BP: p <- r + b p of a system with directions, before BK1 --------------------------------
+template <class R, int RR>
+__device__ __forceinline__ void bp_chunk(const BatchSys& S, const BatchState* st, const int4& ch) {
+  const cplx<R>* __restrict__ r = bslot<R, RR>(S, st->slot);
+  cplx<R>* __restrict__ p = BVec<R>::s(S);
+  const int rows = ch.z - ch.y, elems = rows * st->nrhs;
+  for (int e = threadIdx.x; e < elems; e += kBlock) {
+    const int q = e / rows;
+    if (st->halt[q]) continue;
+    const double b = (st->ru[q] ? st->ru_g[q] : st->R[q]) / st->g1[q];
+    const int64_t idx = bidx<RR>(S, ch.y + e % rows, q);
+    const double2 rd = to_d(r[idx]), pd = to_d(p[idx]);
+    p[idx] = from_d<R>(double2{fma(b, pd.x, rd.x), fma(b, pd.y, rd.y)});
+  }
 }
 
 template <int RR>
-__device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st, double* tot,
+__device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st,
+                                           double (*tot)[kBatchMaxRhs],
                                            int* active_systems) {
   // one wave: lane = q * 16 + k; every lane reads the state before any lane
   // writes it, and system-wide decisions travel by ballot, not through memory
@@ -480,9 +552,11 @@ __device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st, do
   const int phase32 = st->phase32, max_iter = st->max_iter;
   const bool act = live && k >= 1 && k < st->ns && st->active[lk];
   const double z = act ? st->zeta[lk] : 0.0;
-  system_totals<RR>(S, tot);
+  const int dir = st->dir;
+  const double dev = fmax(fmax(st->dev[0], st->dev[1]), fmax(st->dev[2], st->dev[3]));
+  system_totals<RR, 2>(S, tot);
   if (lk >= kWave) return;
-  const double Rn = live ? tot[q] : 0.0;
+  const double Rn = live ? tot[0][q] : 0.0;
   if (act && z * z * Rn <= eps2) {
     st->active[lk] = 0;
     st->freeze_iter[lk] = it;
@@ -490,6 +564,7 @@ __device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st, do
   bool halted_after = true, below = true;
   if (k == 0 && live) {
     st->R[q] = Rn;
+    st->c[q] = tot[1][q];
     st->iter[q] = it;
     if (!isfinite(Rn)) {
       st->status[q] = 1;
@@ -508,8 +583,9 @@ __device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st, do
     if (all_halted) {
       st->done = 1;
       atomicSub(&active_systems[phase32], 1);
+      if (dir) atomicSub(&active_systems[2], 1);
     } else if (!phase32 && all_below) {
-      st->switch_pending = 1;
+      st->wait = !dir && dev > kDevSwitch ? 3 : 1;
       st->iters_fp64 = it;
     }
   }
@@ -526,6 +602,7 @@ struct BFlush {
   int took[kQK], orig[kBatchMaxShifts];
   int m[kBatchMaxRhs], last[kBatchMaxRhs];
   int nrhs, ns, fresh, slot;
+  int dir, take;  // with directions (BK2 keeps x_0 and p_0); they are handed out here
 };
 
 template <class R, class W, int RR>
@@ -550,11 +627,13 @@ __device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, cons
     f.ns = st->ns;
     f.fresh = st->fresh;
     f.slot = st->slot;
+    f.dir = st->dir;
+    f.take = st->wait & 2;
   }
   __syncthreads();
   constexpr bool same = std::is_same<R, W>::value;
   const int64_t n = S.n;
-  const int ns = f.ns, fresh = f.fresh;
+  const int ns = f.ns, fresh = f.fresh, kf = f.dir ? 1 : 0;
   cplx<R>* __restrict__ pk = BVec<R>::pk(S);
   cplx<W>* __restrict__ pw = BVec<W>::pk(S);
   // one (row, rhs) per thread: fewer vectors of the others between two of its loads
@@ -568,7 +647,7 @@ __device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, cons
       BVec<W>::s(S)[idx] = from_d<W>(to_d(BVec<R>::s(S)[idx]));
     }
     const int m = f.m[q];
-    if (same && m == 0 && !fresh) continue;
+    if (same && m == 0 && !fresh && !f.take) continue;
     double2 rv[kMaxSteps];
 #pragma unroll
     for (int k = 0; k < kMaxSteps; ++k)
@@ -580,8 +659,8 @@ __device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, cons
 #pragma unroll
       for (int u = 0; u < G; ++u) {
         const int k = k0 + u;
-        ux[u] = k < ns && ((m > 0 && f.took[q * kBatchMaxShifts + k]) || fresh);
-        ld[u] = k < ns && (ux[u] || !same);
+        ux[u] = k >= kf && k < ns && ((m > 0 && f.took[q * kBatchMaxShifts + k]) || fresh);
+        ld[u] = k >= kf && k < ns && (ux[u] || !same || (f.take && k == 0));
         pj[u] = xv[u] = double2{0.0, 0.0};
         if (ld[u] && !fresh) pj[u] = to_d(ld_stream(&pk[(int64_t(k) * RR + q) * n + i]));
         if (ux[u] && !fresh) xv[u] = ld_stream(&S.x[(int64_t(q) * ns + f.orig[k]) * n + i]);
@@ -613,6 +692,7 @@ __device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, cons
           st_stream(&S.x[(int64_t(q) * ns + f.orig[k]) * n + i], xs);
         }
         st_stream(&pw[(int64_t(k) * RR + q) * n + i], from_d<W>(np));
+        if (f.take && k == 0) BVec<W>::s(S)[idx] = from_d<W>(np);
       }
     }
   }
@@ -621,7 +701,7 @@ __device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, cons
   if (tid < kBatchMaxRhs) {
     const int ph = sizeof(R) == 4 ? 1 : 0, m = f.m[tid];
     int upd = 0;
-    for (int k = 0; k < ns; ++k)
+    for (int k = kf; k < ns; ++k)
       upd += (m > 0 && f.took[tid * kBatchMaxShifts + k]) || fresh ? 1 : 0;
     if (tid < f.nrhs) {
       st->n_upd[tid][ph] += upd;
@@ -631,9 +711,13 @@ __device__ __forceinline__ void bf_chunk(const BatchSys& S, BatchState* st, cons
   }
   if (tid == 0) {
     st->fresh = 0;
+    st->wait = 0;
+    if (f.take) {
+      st->dir = 1;
+      if (!st->done) atomicAdd(&active[2], 1);
+    }
     if (!same) {
       st->phase32 = 1;
-      st->switch_pending = 0;
       st->slot = 0;
       if (!st->done) {
         atomicSub(&active[0], 1);
@@ -811,7 +895,7 @@ __device__ __forceinline__ void bru2_chunk(const BatchSys& S, BatchState* st, co
     if (!st->halt[q]) {
       if (!st->ru[q]) st->ru_g[q] = st->R[q];
       st->ru[q] = 1;
-      st->ru_c[q] = tot[kBatchMaxRhs + q];
+      st->c[q] = tot[kBatchMaxRhs + q];
       st->R[q] = tot[q];
       if (!isfinite(tot[q])) {
         st->status[q] = 1;
@@ -874,22 +958,35 @@ __global__ __launch_bounds__(kBlock, waves_per_simd<R>()) void bk1(BatchArgs a) 
     const BatchSys S = load_const(a.sys + ch.x);
     const BatchState* st = S.st;
     if (load_const(&st->phase32) != int(sizeof(R) == 4) || load_const(&st->done) ||
-        load_const(&st->switch_pending))
+        load_const(&st->wait) || (load_const(&st->dir) && !(a.phases & 4)))
       continue;
     bk1_chunk<R, L, RR>(S, st, ch);
   }
 }
 
-// A system with no step in this launch: finished, waiting for the switch, or in a phase that
-// the launch leaves out.
+// A system with no step in this launch: finished, waiting for the next BF, or in a phase or
+// with directions that the launch leaves out.
 __device__ __forceinline__ bool idle(const BatchArgs& a, const BatchState* st) {
-  return st->done || st->switch_pending || !(a.phases & (st->phase32 ? 2 : 1));
+  return st->done || st->wait || !(a.phases & (st->phase32 ? 2 : 1)) || (st->dir && !(a.phases & 4));
+}
+
+template <int RR> __global__ __launch_bounds__(kBlock) void bp(BatchArgs a) {
+  for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
+    const int4 ch = load_const(a.chunks + c);
+    const BatchSys S = load_const(a.sys + ch.x);
+    const BatchState* st = S.st;
+    if (!st->dir || idle(a, st)) continue;
+    if (st->phase32)
+      bp_chunk<float, RR>(S, st, ch);
+    else
+      bp_chunk<double, RR>(S, st, ch);
+  }
 }
 
 template <int RR> __global__ __launch_bounds__(kBlock) void bs1(BatchArgs a) {
   const BatchSys S = load_const(a.sys + blockIdx.x);
   if (idle(a, S.st)) return;
-  __shared__ double tot[kBatchMaxRhs];
+  __shared__ double tot[1][kBatchMaxRhs];
   bs1_system<RR>(S, S.st, tot);  // its barriers come after every thread has looked
 }
 
@@ -900,7 +997,7 @@ __global__ __launch_bounds__(kBlock, waves_per_simd<R>()) void bk2(BatchArgs a) 
     const BatchSys S = load_const(a.sys + ch.x);
     const BatchState* st = S.st;
     if (load_const(&st->phase32) != int(sizeof(R) == 4) || load_const(&st->done) ||
-        load_const(&st->switch_pending))
+        load_const(&st->wait) || (load_const(&st->dir) && !(a.phases & 4)))
       continue;
     bk2_chunk<R, L, RR>(S, st, ch);
   }
@@ -909,7 +1006,7 @@ __global__ __launch_bounds__(kBlock, waves_per_simd<R>()) void bk2(BatchArgs a) 
 template <int RR> __global__ __launch_bounds__(kBlock) void bs2(BatchArgs a) {
   const BatchSys S = load_const(a.sys + blockIdx.x);
   if (idle(a, S.st)) return;
-  __shared__ double tot[kBatchMaxRhs];
+  __shared__ double tot[2][kBatchMaxRhs];
   bs2_system<RR>(S, S.st, tot, a.active_systems);
 }
 
@@ -921,10 +1018,10 @@ __global__ __launch_bounds__(kBlock, 4) void bf(BatchArgs a) {
     const BatchSys S = load_const(a.sys + ch.x);
     BatchState* st = S.st;
     const int any = st->m[0] | st->m[1] | st->m[2] | st->m[3] | st->fresh;
-    if (!any && !st->switch_pending) continue;
+    if (!any && !st->wait) continue;
     if (st->phase32)
       bf_chunk<float, float, RR>(S, st, ch, f, a.active_systems);
-    else if (st->switch_pending)
+    else if (st->wait & 1)
       bf_chunk<double, float, RR>(S, st, ch, f, a.active_systems);
     else
       bf_chunk<double, double, RR>(S, st, ch, f, a.active_systems);
@@ -1004,6 +1101,7 @@ hipError_t launch_batch_init(const BatchArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_batch_iteration(const BatchArgs& a, bool flush, hipStream_t s) {
+  if (a.phases & 4) MSC_BATCH_RHS((bp<RP><<<a.grid, kBlock, 0, s>>>(a)));
   if (a.phases & 1) MSC_BATCH_RHS(MSC_BATCH_LANES((bk1<double, LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
   if (a.phases & 2) MSC_BATCH_RHS(MSC_BATCH_LANES((bk1<float, LL, RP><<<a.grid, kBlock, 0, s>>>(a))));
   MSC_BATCH_RHS((bs1<RP><<<a.nsys, kBlock, 0, s>>>(a)));

@@ -382,15 +382,6 @@ HalfBytes half_bytes(bool one, int prec, double n, const MatBytes& mb) {
   return {mb.m + 2.0 * w * n, mb.mh + 5.0 * w * n};
 }
 
-// The deviation of P from its short form beyond which an iteration without the direction takes
-// it up (multishift.hip).  Ordinary lattices and grids (condition up to 1e6) stay below 1e-13 in
-// FP64 and 3e-4 in complex64.  Steps of a 60 x 60 grid with a penalty of 1e8 / 1e10 / 1e12 / 1e14 on
-// an edge, FP64: 473 / 476 / 478 / 479, as with the direction from the start (without it at
-// all 516 / 567 / 687 / none); 1e4 / 1e6 / 1e8 in complex64: 468 / 482 / 570 (none without it).
-constexpr double kDevLimit64 = 1e-9, kDevLimit32 = 1e-2;
-// Largest deviation of the FP64 phase of a mixed solve for which the complex64 phase, whose
-// rounding is 5e8 times as large, starts without the direction.
-constexpr double kDevSwitch = 2e-12;
 // An FP64 sequence that has met its limit goes on where the driving system's true residual is
 // above it by more than rounding leaves: this factor, and 1e-13 |b|; while that helps, and at
 // most kGoOn times.
@@ -1134,15 +1125,15 @@ struct BatchRun {
   BatchState* d_st = nullptr;
   unsigned* d_tickets = nullptr;
   int* d_active = nullptr;
-  int active0[2] = {0, 0};
+  int active0[3] = {0, 0, 0};
   double *d_sig = nullptr, *d_res2 = nullptr;
   std::vector<double> hsig;
   int* h_poll = nullptr;
   hipStream_t sint = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   hipEvent_t ev_sync = nullptr;
-  hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};  // by the phases it steps
-  hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipGraph_t graph[8] = {};  // by what it steps (BatchArgs::phases)
+  hipGraphExec_t gexec[8] = {};
   int replays = 0, n_reliable_launches = 0;
 
   ~BatchRun() {
@@ -1333,7 +1324,7 @@ struct BatchRun {
         }
       }
     }
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h_poll), 4 * sizeof(int), hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h_poll), 6 * sizeof(int), hipHostMallocDefault));
     HIP_TRY(hipStreamCreateWithFlags(&sint, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
@@ -1358,7 +1349,7 @@ struct BatchRun {
   // upload the descriptors and the initial state, then r = b, s = 0
   msc_status reset(hipStream_t s) {
     active0[0] = nsys;
-    active0[1] = 0;
+    active0[1] = active0[2] = 0;
     HIP_TRY(hipMemcpyAsync(d_sys, sys.data(), sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d_chunks, chunks.data(), sizeof(int4) * nchunks, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d_st, hst.data(), sizeof(BatchState) * nsys, hipMemcpyHostToDevice, s));
@@ -1489,11 +1480,11 @@ struct BatchRun {
     if (rc != MSC_OK) return rc;
     // G iterations captured once for the phases they step, replayed until every system has
     // finished.  A replay steps the phases that the last poll saw, one replay back: a system
-    // that switched since then waits for the next.
+    // that switched, or took its directions up, since then waits for the next.
     const int G = std::max(1, prm.poll_every);
     const int ru_every = (prm.prec == MSC_PREC_MIXED && prm.reliable_every > 0)
                              ? std::max(1, prm.reliable_every / G) : 0;
-    const int64_t max_replays = (int64_t(prm.max_iter) + G - 1) / G + 6;
+    const int64_t max_replays = (int64_t(prm.max_iter) + G - 1) / G + 10;
     int chunk = 0, phases = 1;
     bool done = false;
     while (!done) {
@@ -1508,13 +1499,14 @@ struct BatchRun {
         ++n_reliable_launches;
       }
       const int slot = chunk & 1;
-      HIP_TRY(hipMemcpyAsync(&h_poll[2 * slot], d_active, 2 * sizeof(int), hipMemcpyDeviceToHost, sint));
+      HIP_TRY(hipMemcpyAsync(&h_poll[3 * slot], d_active, 3 * sizeof(int), hipMemcpyDeviceToHost, sint));
       HIP_TRY(hipEventRecord(ev[slot], sint));
       ++chunk;
       if (chunk >= 2) {
         HIP_TRY(hipEventSynchronize(ev[slot ^ 1]));
-        const int* seen = &h_poll[2 * (slot ^ 1)];
+        const int* seen = &h_poll[3 * (slot ^ 1)];
         phases = (seen[0] > 0 ? 1 : 0) | (seen[1] > 0 ? 2 : 0);
+        if (phases != 0 && seen[2] > 0) phases |= 4;
         if (phases == 0) done = true;
       }
       if (replays >= max_replays) done = true;

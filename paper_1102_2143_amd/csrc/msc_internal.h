@@ -27,6 +27,15 @@ constexpr int kTicketSite = 9 * kTicketStride;
 constexpr int kRuCheck = 10;
 constexpr double kRuDelta2 = 1e-2;
 
+// The deviation of P from its short form beyond which an iteration without the direction takes
+// it up (multishift.hip).  Ordinary lattices and grids (condition up to 1e6) stay below 1e-13 in
+// FP64 and 3e-4 in complex64.  Steps of a 60 x 60 grid with a penalty of 1e8 / 1e10 / 1e12 / 1e14 on
+// an edge, FP64: 473 / 476 / 478 / 479, as with the direction from the start (without it at
+// all 516 / 567 / 687 / none); 1e4 / 1e6 / 1e8 in complex64: 468 / 482 / 570 (none without it).
+constexpr double kDevLimit64 = 1e-9, kDevLimit32 = 1e-2;
+// Largest deviation of the FP64 phase of a mixed solve for which the complex64 phase, whose
+// rounding is 5e8 times as large, starts without the direction.
+constexpr double kDevSwitch = 2e-12;
 // Head launches whose update mode is recorded for the byte model of sampled timings.
 constexpr int kMaxSamples = 256;
 
@@ -589,14 +598,16 @@ struct ResArgs {
 constexpr int kBatchMaxRhs = 4;
 constexpr int kBatchMaxShifts = 16;
 constexpr int kBatchChunkRows = 256;
-constexpr int kBatchPartial = 4 * kBatchMaxRhs;  // partial sums of a chunk: one set per wave
+constexpr int kBatchPartial = 8 * kBatchMaxRhs;  // partial sums of a chunk: two sets per wave
 
 struct BatchState {
   // per right-hand side q: |r_n|^2, the tolerances, and of the step before a, b, P and |r|^2
   double R[kBatchMaxRhs], bnorm2[kBatchMaxRhs], eps2[kBatchMaxRhs], sw_eps2[kBatchMaxRhs];
   double a[kBatchMaxRhs], b[kBatchMaxRhs];             // this step's
   double a1[kBatchMaxRhs], P1[kBatchMaxRhs], g1[kBatchMaxRhs];
-  double ru_g[kBatchMaxRhs], ru_c[kBatchMaxRhs];       // a reliable update's old |r|^2, Re r^H s
+  double ru_g[kBatchMaxRhs];   // a reliable update's old |r|^2
+  double c[kBatchMaxRhs];      // Re r_n^H s_{n-1}
+  double dev[kBatchMaxRhs];    // largest deviation of P from its short form
   int iter[kBatchMaxRhs], halt[kBatchMaxRhs], status[kBatchMaxRhs];
   int step[kBatchMaxRhs];      // this iteration takes a step
   int ru[kBatchMaxRhs];        // r was replaced since the last step
@@ -613,7 +624,9 @@ struct BatchState {
   double s[kBatchMaxShifts];
   int orig[kBatchMaxShifts];
   double sigma0;
-  int ns, nrhs, phase32, switch_pending, done;
+  int ns, nrhs, phase32, done;
+  int wait;                    // until the next BF: 1 switch to complex64, 2 take the direction up
+  int dir;                     // 1: the system carries its directions (in s) and its x_0
   int fresh;                   // 1: x_k and p_k were never written
   int slot;                    // steps since the phase began: r lies in ring slot slot % ring
   int max_iter, n_reliable, iters_fp64;
@@ -654,8 +667,8 @@ struct BatchArgs {
   int grid;
   int lanes;
   int rr;                 // right-hand sides per system, padded (1, 2 or 4)
-  int* active_systems;    // unfinished systems in FP64 [0] and in complex64 [1]
-  int phases;             // phases an iteration steps: 1 FP64, 2 complex64 (3: both)
+  int* active_systems;    // unfinished systems in FP64 [0], in complex64 [1], with directions [2]
+  int phases;             // what an iteration steps: 1 FP64, 2 complex64, 4 systems with directions
 };
 
 hipError_t launch_batch_init(const BatchArgs& a, hipStream_t s);

@@ -248,10 +248,6 @@ struct RealPlan {
   int64_t xo[kMaxShifts], po[kMaxShifts];
 };
 
-// The deviation of P from its short form beyond which the direction is taken up: ordinary grids
-// stay below 1e-13 (multishift.hip and its limits' comment).
-constexpr double kRealDev = 1e-9;
-
 __device__ __forceinline__ double r_b(const RealArgs& a, const RealRot& rs, double g) {
   return rs.iter == 0 ? 0.0 : (a.resume ? a.st->ru_g : g) / rs.g;
 }
@@ -280,7 +276,7 @@ __device__ void r_plan(const RealArgs& a, double g, double d, double c, RealPlan
   }
   // |r|^2 first: an infinite |b|^2 would pass for its own limit
   const bool done = isfinite(g) && (g <= eps2 || n >= st->max_iter);
-  const bool ok = done || (isfinite(g) && P > 0.0 && isfinite(P) && off <= kRealDev * P);
+  const bool ok = done || (isfinite(g) && P > 0.0 && isfinite(P) && off <= kDevLimit64 * P);
   const bool take = !ok && isfinite(g) && !a.dir && n > 0;  // the direction is to be taken up
   const bool live = !done && ok;
   const double step = live ? g / P : 0.0;
