@@ -576,6 +576,10 @@ __device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st,
       below = Rn <= sw2;
     }
   }
+  // the iterations of the right-hand sides that stepped: the same number
+  int most = it;
+  most = max(most, __shfl_xor(most, 16, kWave));
+  most = max(most, __shfl_xor(most, 32, kWave));
   const bool all_halted = __ballot(!halted_after) == 0;
   const bool all_below = __ballot(!halted_after && !below) == 0;
   if (lk == 0) {
@@ -586,7 +590,7 @@ __device__ __forceinline__ void bs2_system(const BatchSys& S, BatchState* st,
       if (dir) atomicSub(&active_systems[2], 1);
     } else if (!phase32 && all_below) {
       st->wait = !dir && dev > kDevSwitch ? 3 : 1;
-      st->iters_fp64 = it;
+      st->iters_fp64 = most;
     }
   }
 }
