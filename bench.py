@@ -39,20 +39,25 @@ WORKLOAD_NAMES = {
 # (FETCH_SIZE and WRITE_SIZE, KiB per dispatch, scaled by the calibration against a copy
 # kernel of known size); it is reported only while the kernel sources are unchanged since.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-KERNEL_NAMES = {("mixed", "head"): "k1_sell<float>",
+# The label of the first operator half's kernel with its share of the applications of the
+# composed steps (k_flush, a launch of its own every update_steps iterations): two kernels'
+# time and bytes.  Kernels go by their template arguments without the last one or two, the
+# operator's kind and the direction's flag.
+K1_APPLY = "K1 + applications"
+KERNEL_NAMES = {("mixed", K1_APPLY): "k1_sell<float>",
                 ("mixed", "K2"): "k2_sell<float>",
-                ("fp64", "head"): "k1_sell<double>",
+                ("fp64", K1_APPLY): "k1_sell<double>",
                 ("fp64", "K2"): "k2_sell<double>"}
 # the same kernels on the matrix-free staggered operator (M and M^H from the links, two rows
 # per SU(3) link; a lattice site per lane, marching along t where the lattice has enough
 # blocks of 64 sites for it, as at 32^3x64; lattices of up to 65536 sites run a form of
 # these with a direction per wave, reported under the first name): the first name that
 # the counter summary holds for the workload
-KERNEL_NAMES_MF = {("mixed", "head"): ("k1_site<float, 2, false, true>",
-                                       "k1_site<float, 2, false, false>"),
+KERNEL_NAMES_MF = {("mixed", K1_APPLY): ("k1_site<float, 2, false, true>",
+                                         "k1_site<float, 2, false, false>"),
                    ("mixed", "K2"): ("k2_site<float, 2, true>", "k2_site<float, 2, false>"),
-                   ("fp64", "head"): ("k1_site<double, 2, true, true>",
-                                      "k1_site<double, 2, true, false>"),
+                   ("fp64", K1_APPLY): ("k1_site<double, 2, true, true>",
+                                        "k1_site<double, 2, true, false>"),
                    ("fp64", "K2"): ("k2_site<double, 2, true>", "k2_site<double, 2, false>")}
 PHASE_NAMES = {"fp64": "FP64", "mixed": "complex64"}
 
@@ -360,8 +365,8 @@ def main():
             kms = np.sum([inf[key + "_ms"] for inf in infos], axis=0)
             kby = np.sum([inf[key + "_bytes"] for inf in infos], axis=0)
             # slot 2 (the application of the composed steps, apart) is empty where the library
-            # counts it with the first half ("head")
-            names = ["head", "K2"] if kms[2] == 0 else ["K1", "K2", "K3"]
+            # counts it with the first half
+            names = [K1_APPLY, "K2"] if kms[2] == 0 else ["K1", "K2", "K3"]
             for k, nm in enumerate(names):
                 # algorithmic bytes of the sampled launches (the library counts the shifts
                 # active at each sampled iteration) over their measured durations; the
@@ -427,6 +432,8 @@ def main():
                     "frac": round(ach / PEAK_HBM_GBS, 4),
                     "traffic": None if traffic is None else round(traffic),
                     "kernel": dom, "kernel_name": kname,
+                    "kernel_includes": ("k_flush, one launch in update_steps"
+                                        if kernels[dom]["kernel"] == K1_APPLY else None),
                     "alg_bytes": kernels[dom]["alg_bytes"],
                     "kernel_avg_us": kernels[dom]["avg_us"],
                     "kernel_ms_per_step": kernels[dom]["ms_per_step"]}

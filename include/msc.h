@@ -92,7 +92,9 @@ typedef struct {
                                 max(2, update_steps) of every timing iterations
                                 (both phases of a mixed solve, reported apart; at
                                 most 256 samples, at most 128 of them in the FP64
-                                phase of a mixed solve), 0 = off                  (0)    */
+                                phase of a mixed solve), 0 = off.  Operators made from
+                                links of up to 256 sites run other kernels, about half
+                                as fast, while it is on                           (0)    */
     int32_t max_grid;        /* cap on workgroups per iteration kernel (<= 2048),
                                 0 = automatic                                       (0)    */
     int32_t format;          /* msc_format: matrix copy the iteration SpMVs read     (0)    */
@@ -186,12 +188,14 @@ msc_status msc_op_update_values(msc_op op, const double* d_vals, msc_stream stre
  *   eta_0 = 1, eta_mu(x) = (-1)^(x0 + ... + x_{mu-1}).
  * The library keeps eta/2 U in complex128 and complex64 (the links are copied; the
  * caller may free them) and also builds the equivalent scalar CSR of M (25 sorted
- * entries per row) with every copy msc_op_create_csr makes, which the verification, the
- * FP64 residuals of the refinement, the gradient of the values and msc_op_apply in
- * complex64 and on small lattices use.  The iterations (multishift with its reliable
- * updates, refinement, batched solve) and msc_op_apply in FP64 on larger lattices apply
- * M and M^H from the links (msc_params.format AUTO; STENCIL where it is accepted).  MSC_EINVAL on an extent below 3, an oversized
- * lattice, a non-finite mass or a null pointer.
+ * entries per row) with every copy msc_op_create_csr makes, which the verification of a
+ * single solve, the FP64 residuals of the refinement and of msc_solve_multi_rhs, the
+ * gradient of the values and msc_op_apply in complex64 and on small lattices use.  The
+ * iterations (multishift with its reliable updates, refinement, batched solve) and
+ * msc_op_apply in FP64 on larger lattices apply M and M^H from the links
+ * (msc_params.format AUTO; STENCIL where it is accepted), and a batched solve measures its
+ * residuals with them, all nine values of each.  MSC_EINVAL on an extent below 3, an
+ * oversized lattice, a non-finite mass or a null pointer.
  */
 msc_status msc_op_create_staggered(msc_op* out, const int32_t* dims, double mass,
                                    const double* d_links, msc_stream stream);
@@ -213,7 +217,9 @@ msc_status msc_op_query(msc_op op, int64_t* n, int64_t* nnz, int32_t* ns, int32_
  * matrix has 16-bit column offsets and, for MSC_A_MHM, bit 1 when the copy of M^H has
  * them; bit 2 when an operator from msc_op_create_staggered found every link in SU(3)
  * (|U U^H - I| and |det U - 1| <= 1e-12) and its iteration reads the links' first two
- * rows, rebuilding the third (a third less link traffic).  Either pointer may be NULL. */
+ * rows, rebuilding the third (a third less link traffic); in FP64 the batched CG and the
+ * batched solve do so only where the links are in SU(3) to 4e-15.  Products and residuals
+ * (msc_op_apply, true_rel_res) read all nine values.  Either pointer may be NULL. */
 msc_status msc_op_storage(msc_op op, int32_t* sell, int32_t* narrow);
 
 /*
@@ -248,6 +254,11 @@ msc_status msc_op_apply_noalloc(msc_op op, int32_t prec, const double* d_in, dou
  * every shift meets tol (with verify on: in FP64 true residual), MSC_ENOTCONV when
  * not (x still holds the final iterates and info is filled), MSC_EBREAKDOWN on a
  * breakdown.  info may be NULL.
+ *
+ * The sequence runs without its direction p while the recurrences that replace it hold;
+ * where A has eigenvalues far above the rest, so that rounding makes them leave their form
+ * (or a verified shift misses tol), it takes p up and goes on with it, one vector more an
+ * iteration.  Batched solves and msc_solve_real do the same.
  */
 msc_status msc_solve(msc_op op, const double* d_b, double* d_x, const msc_params* params,
                      msc_info* info, msc_stream stream);
@@ -295,7 +306,8 @@ msc_status msc_solve_bicgstab(msc_op op, const double* d_b, double* d_x,
  *   d_x : device double[ns*n], shift-major, caller's shift order
  * params->prec: MSC_PREC_FP64 (double storage and arithmetic) or MSC_PREC_MIXED (float
  * vectors and matrix, FP64 reductions and shift scalars; meant for moderate tolerances
- * such as the paper's 1e-5: no reliable update or refinement).  x_k is kept in FP64.
+ * such as the paper's 1e-5: no reliable update or refinement; it carries the direction
+ * from the start).  x_k is kept in FP64.
  * Returns MSC_OK when the driving residual reached tol and (with verify) every shift's
  * FP64 true residual is below tol, MSC_ENOTCONV otherwise, MSC_EBREAKDOWN on a breakdown.
  * info: iters, true_rel_res, freeze_iter, alg_bytes; timing fields are zero.

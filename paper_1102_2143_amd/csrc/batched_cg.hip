@@ -14,7 +14,7 @@
 // L2 then serves the matrix to all but the first.  A system that has converged costs
 // nothing from the next iteration on.  Ten systems at 16^4 in FP64, an iteration's halves:
 // 155 and 162 us with 16 interleaved systems on the CSR (10 padded to 16, all of them to
-// the end); 49 and 53 us on the sliced copy, 30 and 35 us on the links on average here.
+// the end); 38 and 44 us on the sliced copy, 31 and 38 us on the links on average here.
 //
 // An outer defect-correction cycle recomputes f_j - (A + sigma_j) x_j in FP64 (the
 // multi-vector kernels below), the inner CG runs in the working precision from e = 0,

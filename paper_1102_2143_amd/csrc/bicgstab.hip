@@ -23,7 +23,7 @@
 // Complex scalars are FP64 throughout; the shadow vector is b.
 //
 // Bound by memory and, on grids that fit the caches, by latency.  64 x 48 x 50 points, 8
-// shifts, a solve of 42 steps: 3.60 ms with four kernels on the CSR, 1.95 ms here.
+// shifts, a solve of 42 steps: 3.60 ms with four kernels on the CSR, 1.71 ms here.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -449,8 +449,9 @@ msc_status run_multishift(msc_op op, const double* d_b, double* d_x, const msc_p
   MsArgs a64 = make_args(op, lanes, d_b, d_x);
   if (prm.max_grid > 0) a64.grid = std::min(prm.max_grid, kMaxGrid);
   if (prm.format == MSC_FORMAT_CSR) a64.sell = 0;
-  // the iteration's two operator halves from the links: the default for staggered
-  // operators (verification and refinement keep the stored copies)
+  // the iteration's two operator halves from the links: the default for staggered operators.
+  // Its verification and the FP64 residuals of a refinement read the stored copies; the
+  // refinement's inner CG and the reliable updates read the links.
   a64.stencil = op->stencil && a64.sell &&
                 (prm.format == MSC_FORMAT_AUTO || prm.format == MSC_FORMAT_STENCIL)
                     ? (op->two_rows ? 2 : 3) : 0;
@@ -836,7 +837,7 @@ msc_status batch_residual(msc_op op, int prec, int lanes, int m, const double* s
 // Defect correction over m <= kBssMax systems sharing the operator:
 //   repeat: r_j = f_j - (A + sig_j) x_j in FP64; stop when |r_j| <= tol_abs_j;
 //           CG on (A + sig_j) e_j = r_j in the working precision from e = 0 until
-//           |r_in| <= max(delta |r_j|, tol_abs_j / 2); x_j += e_j in FP64.
+//           |r_in| <= max(delta |r_j|, kRefineTarget tol_abs_j); x_j += e_j in FP64.
 // On return res_abs[j] = |f_j - (A + sig_j) x_j| of the final iterates.
 // The inner CG of a refinement cycle stops at this fraction of the outer tolerance (the
 // next FP64 residual decides whether another cycle runs).

@@ -251,7 +251,6 @@ struct msc_op_s {
   double2* yadj = nullptr;       // adjoint solutions, ns * n complex128
   size_t yadj_count = 0;
   double* adj_small = nullptr;   // 256 doubles: Gram sums and shift factors
-  int lanes64 = 0, lanes32 = 0;  // chosen lanes per row (0 = not yet tuned)
   msc::SweepOrder order{0, 0, 0, 0};  // lattice structure of the rows (zeros: none found)
   msc::SweepOrder order_sites{0, 0, 0, 0};    // the same in blocks of 64 sites (links'
   msc::SweepOrder order_sites64{0, 0, 0, 0};  // kernels; complex64 and FP64 tile spans)
@@ -389,10 +388,11 @@ struct ApplyArgs {
 };
 hipError_t launch_apply(const ApplyArgs& a, hipStream_t s);
 
-// No-allocation apply: temporaries in a file-scope device array of this many bytes per GPU
-// (FP64: n <= 2^21 rows for A = M^H M, 2^22 for A given; complex64: n <= 2^22).
+// No-allocation apply: its temporary in a file-scope device array of this many bytes per GPU.
+// It is held to n <= 2^21 rows (FP64, A = M^H M) or 2^22 (FP64 with A given; complex64), half of
+// what the one temporary would allow except for A given in FP64.
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
-// Bytes of that array one apply of n rows needs.
+// Bytes of that array that one apply of n rows counts for.
 size_t apply_scratch_bytes(int kind, int prec, int64_t n);
 // The array's address on `device`, which must be the current device; looked up with
 // hipGetSymbolAddress on the first call per device and kept.

@@ -82,14 +82,14 @@ template <> __device__ __forceinline__ Sell<double2> pick_shm<double>(const MsAr
 #define MSC_SELL_KP64 6
 #endif
 
-// Pairs per round trip of the sliced ELLPACK row product (register budget: complex64
-// keeps a 24-entry staggered row in flight at once, complex128 half of it).
 // The residual ring: launch l of the sequence reads its r_n from slot l % kRing (a.launch: a
 // kernel argument, so the first gathers wait for no state) and writes r_{n+1} into the next.
 template <class R> __device__ __forceinline__ cplx<R>* rslot(const MsArgs& a, int l) {
   return static_cast<cplx<R>*>(a.ring) + int64_t(l % kRing) * a.n;
 }
 
+// Pairs per round trip of the sliced ELLPACK row product (register budget: complex64
+// keeps a 24-entry staggered row in flight at once, complex128 half of it).
 template <class R> constexpr int sell_kp();
 template <> constexpr int sell_kp<float>() { return MSC_SELL_KP32; }
 template <> constexpr int sell_kp<double>() { return MSC_SELL_KP64; }
@@ -589,18 +589,14 @@ __device__ __forceinline__ bool k2_step(const MsArgs& a, const Early& e, const S
 }
 
 // The march positions [beg, end) of this wave: its XCD's share of [0, n) (workgroups are
-// dealt to the XCDs in turn), split evenly and contiguously over the XCD's waves.
+// dealt to the XCDs in turn), split evenly and contiguously over the XCD's waves.  g, the
+// workgroups that share them, is a multiple of kXcds (grid_rows, resident_grid).
 __device__ __forceinline__ void march_range(int64_t n, int wpb, int64_t& beg, int64_t& end,
                                             int g = gridDim.x) {
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
-  int64_t lo = 0, hi = n, nw = int64_t(g) * wpb, w = int64_t(blockIdx.x) * wpb + wv;
-  if (g % kXcds == 0) {
-    const int x = int(blockIdx.x % kXcds);
-    lo = n * x / kXcds;
-    hi = n * (x + 1) / kXcds;
-    nw = int64_t(g / kXcds) * wpb;
-    w = int64_t(blockIdx.x / kXcds) * wpb + wv;
-  }
+  const int x = int(blockIdx.x % kXcds);
+  const int64_t lo = n * x / kXcds, hi = n * (x + 1) / kXcds;
+  const int64_t nw = int64_t(g / kXcds) * wpb, w = int64_t(blockIdx.x / kXcds) * wpb + wv;
   beg = lo + (hi - lo) * w / nw;
   end = lo + (hi - lo) * (w + 1) / nw;
 }
@@ -954,9 +950,10 @@ template <class R> __global__ __launch_bounds__(kBlock) void k_herm_w(MsArgs a, 
 // is then its last one moved one slice along t: the site's t link (the next one's backward
 // t link), its values and its forward t neighbour's (the next one's own) stay in registers
 // (TCarry); a run that enters a new column loads them.
-// 32^3 x 64, K1 and K2 of an iteration: FP64 240 and 265 us, complex64 119 and 141 (with rows
+// 32^3 x 64, K1 and K2 of an iteration: FP64 222 and 268 us, complex64 119 and 140 (with rows
 // of three colours together and no hints 322 and 342, 184 and 175, of which the head's r,
-// p and t and the applications, now apart, are a part).
+// p and t and the applications, now apart, are a part); without the sum c_n that P's form is
+// held against, K2 took 266 and 141.
 constexpr int kSiteBlock = kWave;  // sites per wave pass
 
 // The march's block at position q.
@@ -2167,7 +2164,7 @@ int grid_rows(int64_t n, int rows_per_pass, int cap = kMaxGrid) {
 // rounded down to a multiple of the XCD count: the grid of a launch whose waves sweep a
 // lattice order in step (a larger grid would leave the later workgroups' positions to a
 // second round).  Cached per device and kernel.
-int resident_grid(const void* kern, int cap, size_t lds = 0) {
+int resident_grid(const void* kern, int cap) {
   static std::mutex mu;
   static std::map<std::pair<int, const void*>, int> cache;
   int dev = 0;
@@ -2178,7 +2175,7 @@ int resident_grid(const void* kern, int cap, size_t lds = 0) {
   if (it == cache.end()) {
     int per_cu = 0, cus = 0;
     int g = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBlock, lds) == hipSuccess &&
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBlock, 0) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
       g = per_cu * cus / kXcds * kXcds;
     it = cache.emplace(key, g).first;
@@ -2585,7 +2582,7 @@ hipError_t launch_apply(const ApplyArgs& a, hipStream_t s) {
 }
 
 // ---- operator application without allocation ------------------------------------------
-// The two temporaries of the no-allocation apply live in a file-scope device array: each
+// The temporary of the no-allocation apply lives in a file-scope device array: each
 // GPU the library runs on holds its own copy, until the process ends.  In host code the
 // name `scratch` is only a host-side stand-in, so it is never passed to a kernel: the
 // array's address on each device comes from hipGetSymbolAddress, looked up once per
@@ -2599,8 +2596,9 @@ void* scratch_addr[kMaxDevices] = {};
 }  // namespace
 
 size_t apply_scratch_bytes(int kind, int prec, int64_t n) {
-  // mixed: the complex64 input and one complex64 product (both kinds);
-  // FP64: one complex128 product, two for A = M^H M; each temporary 256-byte aligned
+  // The product uses one temporary, a vector of the working precision; the count leaves room
+  // for two (one for a given A in FP64).  It is the documented limit of the entry point, and
+  // what lies beyond it is refused.
   const size_t elem = prec == MSC_PREC_MIXED ? sizeof(float2) : sizeof(double2);
   const int count = (prec == MSC_PREC_MIXED || kind == MSC_A_MHM) ? 2 : 1;
   const size_t one = (elem * size_t(n) + 255) / 256 * 256;
