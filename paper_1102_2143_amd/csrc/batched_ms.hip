@@ -27,8 +27,9 @@
 // of 4^4 to 12^4 and 16 grids of 32^3, four right-hand sides and ten shifts each, took
 // 122 + 140 us an iteration in complex64; without the tickets 83 + 104; a kernel per
 // precision 66 + 78; descriptors and state through the scalar cache (164 and 98 registers)
-// 53 + 70, FP64 83 + 111 (the vectors and links alone at 5.5 TB/s: 35 + 54 and 70 + 108).
-// The solve in mixed precision: 172 -> 85 ms; as stored matrices 175 -> 122.
+// 53 + 70, FP64 83 + 111 (the vectors and links alone at 5.5 TB/s: 35 + 54 and 70 + 108); with
+// c_n summed besides, 53 + 74 and 84 + 115.
+// The solve in mixed precision: 172 -> 87 ms; as stored matrices 175 -> 122.
 #include <type_traits>
 
 #include "dev_common.h"

@@ -950,10 +950,9 @@ template <class R> __global__ __launch_bounds__(kBlock) void k_herm_w(MsArgs a, 
 // is then its last one moved one slice along t: the site's t link (the next one's backward
 // t link), its values and its forward t neighbour's (the next one's own) stay in registers
 // (TCarry); a run that enters a new column loads them.
-// 32^3 x 64, K1 and K2 of an iteration: FP64 222 and 268 us, complex64 119 and 140 (with rows
+// 32^3 x 64, K1 and K2 of an iteration: FP64 221 and 266 us, complex64 120 and 138 (with rows
 // of three colours together and no hints 322 and 342, 184 and 175, of which the head's r,
-// p and t and the applications, now apart, are a part); without the sum c_n that P's form is
-// held against, K2 took 266 and 141.
+// p and t and the applications, now apart, are a part).
 constexpr int kSiteBlock = kWave;  // sites per wave pass
 
 // The march's block at position q.
@@ -1108,7 +1107,8 @@ __global__ __launch_bounds__(kBlock, 2) void k2_site(MsArgs a) {
 // workgroup (prepare_impl): there an iteration is a chain of latencies.
 // An iteration in FP64, one lane per site and here: 4^4 16.8 and 12.2 us, 12^4 23.4 and 15.1,
 // 16^4 30.2 and 26.9, 18^4 37.9 and 43.0 (since the sums go by DPP: 8^4 11.8 -> 11.3, 12x10x14x18
-// 15.6 -> 14.9; 4^4 now has a form of its own below).
+// 15.6 -> 14.9; with K1 summing g_n and c_n for K2 a whole solve of 311 steps there 5.05 -> 4.97
+// ms; 4^4 now has a form of its own below).
 template <class R> using DirParts = cplx<R>[4][3][kWave];
 
 // (m + sign D) v, and v itself (own), at this thread's row of block `blk` (thread t < 192: colour t / 64 of site t %
@@ -1212,12 +1212,12 @@ __global__ __launch_bounds__(kBlock) void k2_split(MsArgs a) {
 // Four lanes a site, a direction each: a lane keeps its link and forms both products with
 // it; r and u lie in LDS, so an iteration's halves and sums are four barriers apart instead
 // of two kernels.  c_n is summed at the end of a launch (in every step it costs registers that
-// are not there, and the direction from the start a barrier: 2.53 and 2.10 ms for the solve at
-// 4^4 that takes 1.98), so P's form is looked at once in up to eight steps; where it is not
+// are not there, and the direction from the start a barrier: 2.53 and 2.10 ms for a solve at
+// 4^4 that takes 2.04, and 1.97 without c_n), so P's form is looked at once in up to eight steps; where it is not
 // positive in between, the direction is taken up there, by the pair of kernels.  The shifts' scalars of all a.span steps follow at the end, a shift per
 // lane; the state goes on as from a.span launches of the pair.  For lattices whose sites one
 // workgroup holds (256): an iteration in FP64 and mixed at 4^4 11.2 and 11.8 us with the
-// pair, 6.7 and 7.3 here, of which 1.6 are the launches and the applications; two sites a
+// pair, 7.0 and 7.6 here, of which 1.6 are the launches and the applications; two sites a
 // lane, 4^3 x 6, took 27.8 (the links do not fit the registers) for 11.5.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallSites = kSmallBlock / 4;
