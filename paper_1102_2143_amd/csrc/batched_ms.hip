@@ -771,7 +771,7 @@ template <int L, int NV, class OUT>
 __device__ __forceinline__ void product64(const BatchSys& S, const int4& ch, bool second, int nv,
                                           const double2* __restrict__ in, int64_t step, OUT out) {
   const bool mh = second && S.kind == MSC_A_MHM;
-  if (S.vlinks) {
+  if (S.links) {
     // a wave per 64 sites and vector
     const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kWave));
     const uint32_t s0 = uint32_t(ch.y) / 3u, s1 = uint32_t(ch.z) / 3u;
@@ -786,10 +786,7 @@ __device__ __forceinline__ void product64(const BatchSys& S, const int4& ch, boo
 #pragma unroll
       for (int c = 0; c < 3; ++c) own[c] = x[3 * int64_t(ss) + c];
       auto at = [&](uint32_t t, int c) { return x[3 * int64_t(t) + c]; };
-      if (S.vlinks == 2)
-        stencil_site<double, 2>(S.v64, ss, own, mh ? -1 : 1, at, o);
-      else
-        stencil_site<double, 3>(S.v64, ss, own, mh ? -1 : 1, at, o);
+      stencil_site<double, 3>(S.v64, ss, own, mh ? -1 : 1, at, o);
       if (live) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) out(3 * int64_t(s) + c, v, o[c]);

@@ -1264,7 +1264,6 @@ struct BatchRun {
         S.links32 = two32 ? 2 : 3;
         S.w64 = two64 ? op->wc64 : op->w64;
         S.w32 = two32 ? op->wc32 : op->w32;
-        S.vlinks = 3;
         S.v64 = op->w64;
       }
       S.b = reinterpret_cast<const double2*>(d_b[s]);

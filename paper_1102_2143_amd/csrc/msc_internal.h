@@ -642,8 +642,8 @@ struct BatchSys {
   Sell<double2> s64, sh64;
   Sell<float2> s32, sh32;
   int links, links32;     // link rows read in place of a stored copy, FP64 and complex64 (2 or 3), or 0
-  int vlinks;             // the same for the FP64 products of updates and verification
-  Stencil<double2> w64, v64;
+  Stencil<double2> w64;
+  Stencil<double2> v64;   // all nine values: the FP64 products of updates and verification
   Stencil<float2> w32;
   const double2* b;       // nrhs * n (rhs-major)
   double2* x;             // nrhs * ns * n (rhs-major, shift-major, caller order)
